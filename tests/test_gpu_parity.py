@@ -1755,3 +1755,32 @@ def test_several_query_tokens_on_the_scores_kernel_routes(setting, g, hq, bits, 
             le = float(np.abs(lse[b:b + 1].cpu().numpy() - lse_ref).max())
             print(f"[parity] path {path} sequence {b}: out err {e:.3e} lse err {le:.3e}", flush=True)
             assert e <= ATT_TOL and le <= max(LSE_TOL, 2e-6 * float(np.abs(lse_ref).max()))
+
+
+@pytest.mark.parametrize("T,k", [(1, 1), (64, 64), (65, 3), (1023, 5), (1025, 64), (4097, 4), (8193, 6), (9000, 64)])
+def test_sink_selection_and_retention_sizes(T, k):
+    """Selection and retention of sinks at the edges of their kernels' blocks (64, 1024, 4096 and 8192 tokens): ties on
+    purpose (scores out of a handful of values, the largest one on the last tokens too), picks held in registers and
+    read again from memory; retained rows equal the given ones bit for bit, in order of position."""
+    rng = np.random.default_rng(T + k)
+    B = 2
+    x = rng.integers(0, 6, size=(B, T, 8)).astype(np.float16)
+    x[:, -1] = -9.0
+    idx, mask = R.select_sinks(P.gpu(x), k)
+    idx, mask_h = idx.cpu().numpy(), mask.cpu().numpy()
+    for b in range(B):
+        ref = np.asarray(O.select_sinks(x[b], k))
+        assert (idx[b] == np.sort(ref)).all() and (np.nonzero(mask_h[b])[0] == idx[b]).all() and mask_h[b].max() == 1
+    cfg = R.RkvConfig(batch=B, n_q_heads=2, n_kv_heads=2, max_tokens=T, max_sinks=k, rot_heads=2)
+    cache = R.RkvCache(cfg)
+    kk = torch.randn(B, T, 2, 128, device="cuda").half()
+    vv = torch.randn(B, T, 2, 128, device="cuda").half()
+    cache.quantize_append(kk, vv, mask)
+    s = cache.export_sinks()
+    assert s["count"].tolist() == [k] * B and (s["pos"].cpu().numpy() == idx).all()
+    for b in range(B):
+        at = torch.from_numpy(idx[b]).long().cuda()
+        assert torch.equal(s["k"][b], kk[b, at].reshape(k, -1)) and torch.equal(s["v"][b], vv[b, at].reshape(k, -1))
+    cache.reset()
+    s = cache.export_sinks()
+    assert s["count"].tolist() == [0] * B and (s["pos"] == -1).all() and cache.length == 0
