@@ -577,15 +577,14 @@ RKV_EXPORT int rkv_decode_step(rkv_cache* cache, const void* dev_k, const void* 
                                float* dev_out, float* dev_lse, void* dev_scratch, void* stream) {
   if (!cache || !dev_k || !dev_v || !dev_q || !dev_out || !dev_scratch) return RKV_EINVAL;
   if ((int64_t)cache->v.len + 1 > cache->cfg.max_tokens) return RKV_ECAPACITY;
-  const bool fused = rkv_append_mfma_supported(cache) && rkv_append_mfma_variant(cache) != RKV_KERNEL_MFMA_ROW &&
-                     rkv_mfma_supported(cache) && cache->decode_path != 1;
+  const bool fused = rkv_append_mfma_supported(cache) && rkv_mfma_supported(cache) && cache->decode_path != 1;
   if (!fused) {   // the same two calls, one after the other
     const int rc = rkv_quantize_append(cache, dev_k, dev_v, 1, nullptr, stream);
     return rc != RKV_OK ? rc : rkv_decode_attention(cache, dev_q, dev_q_pos, dev_out, dev_lse, dev_scratch, stream);
   }
   hipStream_t s = (hipStream_t)stream;
   // (the sub-group variant of the decode kernel takes one query head per workgroup)
-  const int share = rkv_mfma_variant(cache) == RKV_KERNEL_MFMA_SUB ? 1 : rkv_mfma_share(cache->v.Hq / cache->v.Hkv);
+  const int share = (rkv_mfma_variant(cache) == RKV_KERNEL_MFMA_SUB || cache->v.qg < 128) ? 1 : rkv_mfma_share(cache->v.Hq / cache->v.Hkv);
   int rc = rkv_launch_step_mfma(cache, (const __half*)dev_k, (const __half*)dev_v, (const __half*)dev_q, dev_q_pos,
                                 (float*)dev_scratch, share, s);
   if (rc == RKV_OK && cache->ragged) rc = rkv_launch_lens(cache, -1, 1, s);

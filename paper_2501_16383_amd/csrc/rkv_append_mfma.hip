@@ -590,24 +590,33 @@ __global__ void __launch_bounds__(256, (HB || SUB) ? 4 : 6) k_append_values(RkvV
 // come back from the last-level cache - and quantizes every element with its own block's
 // parameters.  Codes stay where they are, by rotated channel.  The quantization block of each of a
 // lane's channels comes from a per-cache table of bytes (xgid8, written by rkv_set_perm).
-// dynamic LDS: [NG][16 tokens] float minima, the same of maxima, [NG][16] float4 parameters (block-major: the 16
+// dynamic LDS: [NG][16 tokens] float minima, the same of maxima, [NG][16] float4 parameters, [NRG][4 waves][4][G] table entries (block-major: the 16
 // tokens of a row of lanes, which share their channels and hence their blocks, touch 16 different LDS banks).
-template <int G, int HB = 0>
-__global__ void __launch_bounds__(256, 3) k_append_row_keys(RkvView v, const __half* __restrict__ kin, int n_new, int slab0) {
+// NP: wave sets (of four waves each) of the workgroup, which take NP rotation groups side by side.  A bulk append fills the
+// chip with its tiles, one set each (three workgroups per compute unit); an append of few tokens - a decode
+// step touches one tile per sequence - leaves it nearly empty and waits for one group after the
+// other, so there four sets share a tile: 8 sequences of one token, 32 heads: 22 us against 40 us.
+template <int G, int HB = 0, int NP = 1>
+__global__ void __launch_bounds__(256 * NP, NP == 1 ? 3 : 1) k_append_row_keys(RkvView v, const __half* __restrict__ kin, int n_new, int slab0) {
   constexpr int n = 128 * G;
   constexpr bool HI = HB == 2, H1 = HB == 1;
   constexpr float QMAX = HI ? 15.0f : (H1 ? 7.0f : 3.0f), INV_QMAX = HI ? 0.06666667f : (H1 ? 0.14285715f : 0.33333334f);
   constexpr int ROW16 = 16 * G, STRIDE16 = ROW16 + 1;
-  __shared__ __attribute__((aligned(16))) uint32_t lds[16 * STRIDE16 * 4];
+  __shared__ __attribute__((aligned(16))) uint32_t lds_all[NP][16 * STRIDE16 * 4];
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn_row[];
   const int NG = v.NG, NGP = NG | 1;           // the row's quantization blocks (of 128, 64 or 32 positions); the allocation counts NGP
   float* s_mn = reinterpret_cast<float*>(dyn_row);
   float* s_mx = s_mn + 16 * NGP;
   float4* s_par = reinterpret_cast<float4*>(dyn_row + (size_t)2 * 16 * NGP * 4);      // (128 NGP bytes in: 16-byte aligned)
-  __shared__ uint32_t img[2 * 128 * G];        // the tile image of one rotation group, in two halves (see k_append_mfma)
-  __shared__ uint32_t imgh[HB ? 2 * 128 * G : 1];   // the upper plane's: two halves (4-bit codes) or four quarter-size pieces (3-bit)
-  const int tid = threadIdx.x, lane = tid & 63;
+  uint2* s_gid = reinterpret_cast<uint2*>(dyn_row + (size_t)384 * NGP);
+  __shared__ uint32_t img_all[NP][2 * 128 * G];     // the tile image of one rotation group, in two halves (see k_append_mfma)
+  __shared__ uint32_t imgh_all[NP][HB ? 2 * 128 * G : 1];   // the upper plane's: two halves (4-bit codes) or four quarter-size pieces (3-bit)
+  const int all = threadIdx.x, tid = all & 255, lane = tid & 63;   // thread of the workgroup, of its wave set
+  const int set = NP == 1 ? 0 : __builtin_amdgcn_readfirstlane(all >> 8);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint32_t* lds = lds_all[set];
+  uint32_t* img = img_all[set];
+  uint32_t* imgh = imgh_all[set];
   const int b = blockIdx.y, ti = blockIdx.x & 1;
   const int len_b = rkv_len(v, b), n_b = v.nnew ? v.nnew[b] : n_new;
   const int slab = (v.lens ? (len_b >> 5) : slab0) + (blockIdx.x >> 1);
@@ -618,6 +627,7 @@ __global__ void __launch_bounds__(256, 3) k_append_row_keys(RkvView v, const __h
   const int tau_first = max(0, t_lo - ts), tau_last = min(31, t_hi - 1 - ts);
   const int d = wave & 1, pph = wave >> 1;                 // this wave: products pp = 2 pph + {0, 1} of dword half d
   const int col = lane & 15, q = lane >> 4;                // result: token `col` of the tile, rows 4q..4q+3
+  const bool live = 16 * ti + col >= tau_first && 16 * ti + col <= tau_last;   // a token of this call
   const float rs = rsqrtf((float)n);
   // A operands (see k_append_mfma): lane (row m, k-group kg) holds H_128[channel][32 ks + 8 kg + i]
   const int m = lane & 15, kg = lane >> 4, r = m & 3, qa = m >> 2;
@@ -689,38 +699,46 @@ __global__ void __launch_bounds__(256, 3) k_append_row_keys(RkvView v, const __h
         }
       }
   };
-  // quantization blocks (of the row) of the lane's eight channels of head h, one byte each (element 4 ppl + rr)
-  auto blocks_of = [&](int rg, int h) __attribute__((always_inline)) { return v.xgid8[(((size_t)rg * 4 + wave) * 4 + q) * G + h]; };
+  // quantization blocks (of the row) of the lane's eight channels of head h, one byte each (element 4 ppl + rr).
+  // The table is copied to LDS once: fetched from memory where it is used, an entry is waited for together
+  // with the next group's rows, which are requested before it (loads return in order).
+  for (int i = all; i < v.NRG * 16 * G; i += 256 * NP) s_gid[i] = v.xgid8[i];
+  auto blocks_of = [&](int rg, int h) __attribute__((always_inline)) { return s_gid[(rg * 16 + wave * 4 + q) * G + h]; };
 
-  for (int i = tid; i < 16 * NGP; i += 256) {
+  for (int i = all; i < 16 * NGP; i += 256 * NP) {
     s_mn[i] = 3.0e38f;
     s_mx[i] = -3.0e38f;
   }
-  // ---- first pass: extrema
-  RKV_ROW_REQUEST(0);
-  for (int rg = 0; rg < v.NRG; ++rg) {
+  // ---- first pass: extrema (a set without a group left in the last round takes the last group again: its minima and
+  // maxima change nothing)
+  const int last = v.NRG - 1;
+  RKV_ROW_REQUEST(min(set, last));
+  for (int r0 = 0; r0 < v.NRG; r0 += NP) {
+    const int rg = NP == 1 ? r0 : min(r0 + set, last);
     RKV_ROW_DEPOSIT();
     __syncthreads();
-    if (rg + 1 < v.NRG) RKV_ROW_REQUEST(rg + 1);
+    if (r0 + NP < v.NRG) RKV_ROW_REQUEST(min(r0 + NP + set, last));
     v4f acc[G][2];
     rotate(acc);
+    if (live) {                                            // (nothing to gather from rows that stand in for tokens outside this call)
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const uint2 gb = blocks_of(rg, h);
+      for (int h = 0; h < G; ++h) {
+        const uint2 gb = blocks_of(rg, h);
 #pragma unroll
-      for (int ppl = 0; ppl < 2; ++ppl)
+        for (int ppl = 0; ppl < 2; ++ppl)
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          const int blk = (int)(((ppl ? gb.y : gb.x) >> (8 * rr)) & 0xffu) * 16 + col;
-          lds_fmin(&s_mn[blk], acc[h][ppl][rr]);
-          lds_fmax(&s_mx[blk], acc[h][ppl][rr]);
-        }
+          for (int rr = 0; rr < 4; ++rr) {
+            const int blk = (int)(((ppl ? gb.y : gb.x) >> (8 * rr)) & 0xffu) * 16 + col;
+            lds_fmin(&s_mn[blk], acc[h][ppl][rr]);
+            lds_fmax(&s_mx[blk], acc[h][ppl][rr]);
+          }
+      }
     }
     __syncthreads();                                       // the rows are read: the next group's may come
   }
   // ---- Eq. 8-9 per (token, block)
-  RKV_ROW_REQUEST(0);
-  for (int e = tid; e < 16 * NG; e += 256) {
+  RKV_ROW_REQUEST(min(set, last));
+  for (int e = all; e < 16 * NG; e += 256 * NP) {
     const int tk = e & 15, bk = e >> 4;
     float sc, zero_b, inv, base_b, add_b;
     quant_params_nodiv(s_mn[e] * rs, s_mx[e] * rs, sc, zero_b, inv, v.meta8, INV_QMAX);
@@ -730,10 +748,11 @@ __global__ void __launch_bounds__(256, 3) k_append_row_keys(RkvView v, const __h
     if (tau >= tau_first && tau <= tau_last) rkv_store_meta(v, v.km, rkv_meta_index(v, b, ts + tau, bk), sc, zero_b);
   }
   // ---- second pass: Eq. 6 with each element's own block's parameters
-  for (int rg = 0; rg < v.NRG; ++rg) {
+  for (int r0 = 0; r0 < v.NRG; r0 += NP) {
+    const int rg = NP == 1 ? r0 : min(r0 + set, last);
     RKV_ROW_DEPOSIT();
     __syncthreads();                                       // (also: the parameters are complete)
-    if (rg + 1 < v.NRG) RKV_ROW_REQUEST(rg + 1);
+    if (r0 + NP < v.NRG) RKV_ROW_REQUEST(min(r0 + NP + set, last));
     v4f acc[G][2];
     rotate(acc);
     uint32_t words[G];
@@ -771,7 +790,7 @@ __global__ void __launch_bounds__(256, 3) k_append_row_keys(RkvView v, const __h
       const int off = tid + 256 * k;
       if (off < 128 * G) {
         const int t = ts + ti * 16 + rkv_k_tile_token(G, off);
-        if (t >= t_lo && t < t_hi) {
+        if (t >= t_lo && t < t_hi && (NP == 1 || r0 + set <= last)) {
           rkv_st_stream(&v.kc[rkv_k_tilebase(v, b, rg, 2 * slab + ti) + off], img[off] | img[128 * G + off]);
           if constexpr (HI) rkv_st_stream(&v.kh[rkv_k_tilebase(v, b, rg, 2 * slab + ti) + off], imgh[off] | imgh[128 * G + off]);
           if constexpr (H1) {
@@ -807,6 +826,20 @@ __global__ void __launch_bounds__(256, 4) k_step_mfma(RkvView v, const __half* _
   rkv_prep_q_one(v, q, q_pos, 1, qr, share, 1, h, blockIdx.z, threadIdx.x & 127);
 }
 
+// The same for a reorder over the whole row, whose keys have a kernel of their own: the first workgroup of a
+// (rotation group, sequence) appends the step's values, the rest prepare its query heads.
+template <int G, int HB = 0, int SUB = 0>
+__global__ void __launch_bounds__(256, 4) k_step_values(RkvView v, const __half* __restrict__ vin, int slab0, const __half* __restrict__ q,
+                                                     const int* __restrict__ q_pos, float* __restrict__ qr, int share) {
+  if (blockIdx.x == 0) {
+    append_mfma_body<G, HB, false, SUB>(v, nullptr, vin, 1, slab0, 2, blockIdx.y, blockIdx.z);
+    return;
+  }
+  const int rep = v.Hq / v.Hkv;
+  const int h = blockIdx.y * G * rep + 2 * ((int)blockIdx.x - 1) + (threadIdx.x >> 7);
+  rkv_prep_q_one(v, q, q_pos, 1, qr, share, 1, h, blockIdx.z, threadIdx.x & 127);
+}
+
 // a reorder over the whole row: k_append_row_keys + k_append_values
 static bool append_row(const rkv_cache* c) {
   const RkvView& v = c->v;
@@ -829,6 +862,32 @@ bool rkv_append_mfma_supported(const rkv_cache* c) {
   return (v.g == 2 || v.g == 4) && v.v_rotate == 0;
 }
 
+template <int G, int HB>
+static int launch_row_keys(const rkv_cache* c, const __half* k, int n_new, int max_slabs, int slab0, hipStream_t s) {
+  const RkvView& v = c->v;
+  const size_t dyn = (size_t)384 * (v.NG | 1) + (size_t)v.NRG * 128 * G;
+  // Four wave sets per tile as long as there is at most one such workgroup per compute unit and the tables fit
+  // beside their images.  One sequence, 32 heads, keys and values together: 2048 tokens 42 us against 53,
+  // 4096 tokens (one workgroup each) 52 against 60, 8192 tokens 92 against 73: from there on the
+  // narrow workgroups, three of which are resident at a time, are the better ones.
+  const size_t wide_static = 4 * (16 * (16 * G + 1) * 16 + (HB ? 2 : 1) * 2 * 128 * G * 4) + 64;
+  if (2 * max_slabs * v.B <= c->n_cu && v.NRG > 1 && dyn + wide_static <= RKV_LDS_BYTES) {
+    RKV_HIP_CHECK(hipFuncSetAttribute((const void*)k_append_row_keys<G, HB, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn));
+    hipLaunchKernelGGL((k_append_row_keys<G, HB, 4>), dim3(2 * max_slabs, v.B), dim3(1024), dyn, s, v, k, n_new, slab0);
+    return RKV_OK;
+  }
+  if (dyn > 48 * 1024)
+    RKV_HIP_CHECK(hipFuncSetAttribute((const void*)k_append_row_keys<G, HB, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn));
+  hipLaunchKernelGGL((k_append_row_keys<G, HB, 1>), dim3(2 * max_slabs, v.B), dim3(256), dyn, s, v, k, n_new, slab0);
+  return RKV_OK;
+}
+static int launch_row_keys_of(const rkv_cache* c, const __half* k, int n_new, int max_slabs, int slab0, hipStream_t s) {
+  const RkvView& v = c->v;
+#define RKV_ROW_G(H_) (v.g == 4 ? launch_row_keys<4, H_>(c, k, n_new, max_slabs, slab0, s) : launch_row_keys<2, H_>(c, k, n_new, max_slabs, slab0, s))
+  return v.hb == 2 ? RKV_ROW_G(2) : v.hb == 1 ? RKV_ROW_G(1) : RKV_ROW_G(0);
+#undef RKV_ROW_G
+}
+
 // max_slabs: most 32-token slabs any sequence's new tokens touch, or 0 to work it out for n_new
 // tokens per sequence
 int rkv_launch_append_mfma(rkv_cache* c, const __half* k, const __half* vv, int n_new, int max_slabs, hipStream_t s) {
@@ -846,13 +905,11 @@ int rkv_launch_append_mfma(rkv_cache* c, const __half* k, const __half* vv, int 
   dim3 grid(3 * max_slabs, v.NRG, v.B);
   if (c->ev_start) RKV_HIP_CHECK(hipEventRecord(c->ev_start, s));
   if (append_row(c)) {
-    const size_t dyn = (size_t)384 * (v.NG | 1);
+    const int rc = launch_row_keys_of(c, k, n_new, max_slabs, slab0, s);
+    if (rc != RKV_OK) return rc;
 #define RKV_AP_VAL(G_, H_, S_) hipLaunchKernelGGL((k_append_values<G_, H_, S_>), dim3(max_slabs, v.NRG, v.B), dim3(256), 0, s, v, vv, n_new, slab0)
 #define RKV_AP_ROW(G_, H_)                                                                                                        \
   do {                                                                                                                            \
-    if (dyn > 48 * 1024)                                                                                                          \
-      RKV_HIP_CHECK(hipFuncSetAttribute((const void*)k_append_row_keys<G_, H_>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn)); \
-    hipLaunchKernelGGL((k_append_row_keys<G_, H_>), dim3(2 * max_slabs, v.B), dim3(256), dyn, s, v, k, n_new, slab0);             \
     if (v.qg == 64) RKV_AP_VAL(G_, H_, 2); else if (v.qg == 32) RKV_AP_VAL(G_, H_, 4); else RKV_AP_VAL(G_, H_, 0);                \
   } while (0)
     if (v.g == 4) {
@@ -885,9 +942,22 @@ int rkv_launch_append_mfma(rkv_cache* c, const __half* k, const __half* vv, int 
 int rkv_launch_step_mfma(rkv_cache* c, const __half* k, const __half* vv, const __half* q, const int* q_pos, float* qr, int share,
                          hipStream_t s) {
   const RkvView& v = c->v;
-  if (!rkv_append_mfma_supported(c) || append_row(c)) return RKV_EINVAL;
+  if (!rkv_append_mfma_supported(c)) return RKV_EINVAL;
   int max_slabs = 1;                                        // one token touches one slab of its sequence
   const int n_append = 3 * max_slabs, rep = v.Hq / v.Hkv;
+  if (append_row(c)) {
+    const int rc = launch_row_keys_of(c, k, 1, max_slabs, v.len >> 5, s);
+    if (rc != RKV_OK) return rc;
+    dim3 grid(1 + v.g * rep / 2, v.NRG, v.B);
+#define RKV_SV(G_, H_, S_) hipLaunchKernelGGL((k_step_values<G_, H_, S_>), grid, dim3(256), 0, s, v, vv, v.len >> 5, q, q_pos, qr, share)
+#define RKV_SV_S(G_, H_) do { if (v.qg == 64) RKV_SV(G_, H_, 2); else if (v.qg == 32) RKV_SV(G_, H_, 4); else RKV_SV(G_, H_, 0); } while (0)
+#define RKV_SV_G(H_) do { if (v.g == 4) RKV_SV_S(4, H_); else RKV_SV_S(2, H_); } while (0)
+    if (v.hb == 2) RKV_SV_G(2); else if (v.hb == 1) RKV_SV_G(1); else RKV_SV_G(0);
+#undef RKV_SV_G
+#undef RKV_SV_S
+#undef RKV_SV
+    return rkv_check_launch();
+  }
   dim3 grid(n_append + v.g * rep / 2, v.NRG, v.B);
 #define RKV_ST(G_, H_, X_, S_) \
   hipLaunchKernelGGL((k_step_mfma<G_, H_, X_, S_>), grid, dim3(256), 0, s, v, k, vv, v.len >> 5, n_append, q, q_pos, qr, share)

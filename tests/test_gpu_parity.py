@@ -1784,3 +1784,28 @@ def test_sink_selection_and_retention_sizes(T, k):
     cache.reset()
     s = cache.export_sinks()
     assert s["count"].tolist() == [0] * B and (s["pos"] == -1).all() and cache.length == 0
+
+
+@pytest.mark.parametrize("hkv,g,bits,group", [(12, 4, 2, 128), (40, 4, 3, 128), (6, 2, 4, 128), (10, 2, 2, 32), (32, 4, 2, 64)])
+def test_whole_row_reorder_few_tokens_equal_bulk(hkv, g, bits, group):
+    """Appends of few tokens share a tile among four wave sets, one bulk append takes one set per tile: codes
+    and metadata are the same (numbers of rotation groups that four divides and does not; pieces that end inside a tile
+    and inside a slab)."""
+    T = 4200                                                 # 132 slabs: more tiles than compute units
+    cfg = R.RkvConfig(batch=1, n_q_heads=hkv, n_kv_heads=hkv, max_tokens=T, max_sinks=0, rot_heads=g, bits=bits, quant_group=group,
+                      perm_span=hkv * 128)
+    gen = torch.Generator(device="cuda").manual_seed(hkv)
+    k = torch.randn(1, T, hkv, 128, device="cuda", generator=gen).half()
+    v = torch.randn(1, T, hkv, 128, device="cuda", generator=gen).half()
+    perm = torch.from_numpy(np.random.default_rng(hkv).permutation(hkv * 128).astype(np.int32)).cuda()
+    bulk, pieces = R.RkvCache(cfg), R.RkvCache(cfg)
+    for c in (bulk, pieces):
+        c.set_perm(perm)
+    bulk.quantize_append(k, v)
+    at = 0
+    for n in (1, 2, 15, 16, 33, 1000, 2047, T):
+        n = min(n, T - at)
+        pieces.quantize_append(k[:, at:at + n].contiguous(), v[:, at:at + n].contiguous())
+        at += n
+    a, b = bulk.export_codes(), pieces.export_codes()
+    assert at == T and all(torch.equal(a[name], b[name]) for name in a)
