@@ -30,11 +30,10 @@
 // that share a KV head: unpacking, rotation and RoPE of the keys are done once for them, the
 // softmax and value phases once per query head.  Everything else takes the general kernel.
 #include "rkv_internal.h"
+#include "rkv_mfma_ops.h"
 #include <cstdlib>
 #include <hip/hip_ext.h>
 
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v4f __attribute__((ext_vector_type(4)));
 typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 
@@ -54,13 +53,6 @@ static_assert(MF_CH == RKV_MFMA_CHUNK, "the work-space size of a call is worked 
 #define MF_OCC 3           // workgroups per compute unit the register budget is set for
 #endif
 
-__device__ __forceinline__ v4f mfma_fp4(const v8i& a, const v8i& b, const v4f& c) {
-  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 4, 0, 0, 0, 0);
-}
-__device__ __forceinline__ v4f mfma_fp8_fp4(const v8i& a, const v8i& b, const v4f& c) {
-  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 4, 0, 0, 0, 0);
-}
-
 __device__ __forceinline__ v4h as_v4h(uint32_t a, uint32_t b) {
   union { uint32_t u[2]; v4h h; } c;
   c.u[0] = a;
@@ -75,38 +67,6 @@ __device__ __forceinline__ uint32_t pk_f16(float a, float b) {
 __device__ __forceinline__ v4f mfma_4x4x4(const v4h& a, const v4h& b, const v4f& c) {
   return __builtin_amdgcn_mfma_f32_4x4x4f16(a, b, c, 0, 0, 0);
 }
-
-// two dwords of 2-bit codes -> four dwords of FP4 nibbles (value = code / 2)
-__device__ __forceinline__ v8i unpack_fp4(uint32_t d0, uint32_t d1) {
-  v8i r;
-  r[0] = (int)(d0 & 0x33333333u);
-  r[1] = (int)((d0 >> 2) & 0x33333333u);
-  r[2] = (int)(d1 & 0x33333333u);
-  r[3] = (int)((d1 >> 2) & 0x33333333u);
-  r[4] = r[5] = r[6] = r[7] = 0;
-  return r;
-}
-
-// one dword of third bits (3-bit codes; bit 4j + k belongs to nibble j of operand dword k) -> four
-// dwords of FP4 nibbles (value = bit / 2)
-__device__ __forceinline__ v8i unpack_fp4_bits(uint32_t h) {
-  v8i r;
-  r[0] = (int)(h & 0x11111111u);
-  r[1] = (int)((h >> 1) & 0x11111111u);
-  r[2] = (int)((h >> 2) & 0x11111111u);
-  r[3] = (int)((h >> 3) & 0x11111111u);
-  r[4] = r[5] = r[6] = r[7] = 0;
-  return r;
-}
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-#define DPP_ROW_MIRROR 0x140
-#define DPP_ROW_HALF_MIRROR 0x141
-#define DPP_QUAD_MIRROR 0x1B      // quad_perm [3,2,1,0]
-#define DPP_QUAD_SWAP 0xB1        // quad_perm [1,0,3,2]
 
 // Sum NV values over the 16 lanes of a row; lane n ends with the total of value n (NV = 16) or of
 // value n & 7 (NV = 8).
@@ -191,21 +151,6 @@ __device__ __forceinline__ float row_transpose_reduce(float (&v)[NV], int n) {
   const bool hi = (n & 1) != 0;
   const float keep = hi ? k2[1] : k2[0], send = hi ? k2[0] : k2[1];
   return keep + dpp_f<DPP_QUAD_SWAP>(send);
-}
-
-// All-lanes reduction over the 64 lanes of a wave: 4 DPP steps inside each row of 16, then the
-// four row results through scalar registers.
-template <bool IS_MAX>
-__device__ __forceinline__ float wave_allreduce(float x) {
-  auto op = [](float a, float b) { return IS_MAX ? fmaxf(a, b) : a + b; };
-  x = op(x, dpp_f<DPP_QUAD_SWAP>(x));
-  x = op(x, dpp_f<0x4E>(x));                 // quad_perm [2,3,0,1]
-  x = op(x, dpp_f<DPP_ROW_HALF_MIRROR>(x));
-  x = op(x, dpp_f<DPP_ROW_MIRROR>(x));
-  const int xi = __float_as_int(x);
-  const float r0 = __int_as_float(__builtin_amdgcn_readlane(xi, 0)), r1 = __int_as_float(__builtin_amdgcn_readlane(xi, 16));
-  const float r2 = __int_as_float(__builtin_amdgcn_readlane(xi, 32)), r3 = __int_as_float(__builtin_amdgcn_readlane(xi, 48));
-  return op(op(r0, r1), op(r2, r3));
 }
 
 // MULTI: several query tokens per sequence.  v.Hq then counts virtual heads (nq per real head, see
@@ -1086,7 +1031,11 @@ static RkvDecodeFn pick_kernel(const rkv_cache* c, bool multi, int share, bool a
 // query heads of a KV head served by one workgroup: two where the ratio is even (four per
 // workgroup measured slower: 158 against 151 us on the GQA configuration - the variant needs
 // more registers than three workgroups per compute unit leave)
-int rkv_mfma_share(int heads_per_kv_head) { return heads_per_kv_head % 2 == 0 ? 2 : 1; }
+int rkv_mfma_share(const rkv_cache* c, bool multi, int heads_per_kv_head) {
+  if (rkv_shared_decode(c, multi)) return 0;                // all query heads of a KV head together: a query layout of its own
+  if (c->v.qg < 128) return 1;                              // groups of 64 / 32: one query head per workgroup
+  return heads_per_kv_head % 2 == 0 ? 2 : 1;
+}
 
 // q_prepared: the queries are already in the scratch block (rkv_launch_step_mfma put them there)
 int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int nq, float* out, float* lse, void* scratch,
@@ -1105,10 +1054,23 @@ int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int 
   const bool xb = mfma_cross_block(c) || sg;
   const bool row = rkv_scores_path(c);
   if (row && multi && !rkv_scores_multi_ok(c, nq)) return RKV_EINVAL;   // (the scores kernel serves 8 rows per KV head)
-  const int share = sg ? 1 : rkv_mfma_share(rep);           // (groups of 64 / 32: one query head per workgroup)
+  const int share = rkv_mfma_share(c, multi, rep);
   if (!q_prepared) rkv_launch_prep_q(v, q, q_pos, c->cur_k ? 1 : 0, qr, share, nq, s);
   float* qt = qr + (size_t)v.B * v.Hq * RKV_D;              // lane-ordered copy written by k_prep_q
   const int nch = (v.len + MF_CH - 1) / MF_CH;
+  if (share == 0) {
+    const bool timed = c->ev_start && c->ev_stop;
+    if (nch > 0) {
+      const int rc = rkv_launch_decode_shared(c, v, qr, part, nch, multi ? q_pos : nullptr, nq, timed ? c->ev_start : nullptr,
+                                              timed ? c->ev_stop : nullptr, s);
+      if (rc != RKV_OK) return rc;
+    } else if (timed) {
+      RKV_HIP_CHECK(hipEventRecord(c->ev_start, s));
+      RKV_HIP_CHECK(hipEventRecord(c->ev_stop, s));
+    }
+    rkv_launch_merge(v, qr, part, nch, MF_CH, c->cur_k, c->cur_v, multi ? q_pos : nullptr, nq, out, lse, s);
+    return rkv_check_launch();
+  }
   const int ns = rep / share;
   // reciprocals for the kernel's index arithmetic: ceil(2^32 / d) gives exact quotients n / d for n * d < 2^32
   auto recip = [](int d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };

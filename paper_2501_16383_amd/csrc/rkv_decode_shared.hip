@@ -1,0 +1,569 @@
+// Read half, matrix-core kernel for several query heads per KV head (grouped queries, several query
+// tokens per step): plain reorder (inside blocks of 128), rot_heads 2 or 4, codes of 2 to 4 bits in
+// groups of 128, either metadata format, both RoPE pairings.
+//
+// One workgroup = (sequence, rotation group, chunk of 256 tokens, up to 16 CT / G query heads of each of the
+// G KV heads), 4 waves.  Rotation, RoPE and unpacking of a key cost vector instructions per (token,
+// KV head); they are done once for all the query heads, and the product with the queries is a
+// matrix product whose columns are the (query head, KV head) pairs:
+//   phase K  wave w: tokens 64w..64w+63 in tiles of 16.  The operands of the Hadamard product are
+//            exchanged against k_decode_mfma's, H_128 tile [16 channels x 128] times codes [128 x 16 tokens]:
+//            lane (n, q) then holds channels 16p + 4q + 0..3 and their RoPE partners of token n, which is
+//            the layout the next product (v_mfma_f32_16x16x32_f16: [16 tokens x 32 channels] times
+//            [32 channels x 16 columns]) takes its left operand in: nothing crosses lanes.
+//            The scales and the butterfly over the blocks (H_g) are linear, so they come after the
+//            contraction over the channels:
+//              score(t, a, h) = sum_blk H_g[a][blk] scale_blk(t) * <RoPE_t(H_128 c_blk(t)), q~(a, h)>:
+//            the rotated codes meet the queries of ALL KV heads of the group, sixteen columns per product.
+//            Precision: H_128 c is exact, RoPE runs in fp32; both operands are then split into two
+//            fp16 numbers each (high + low: 2^-23) and the product is high * high + high * low + low * high
+//            (what is left out is below 2^-23 of the terms), accumulated in fp32.  Codes are centred on
+//            their middle value (the product's C operand starts at minus its share of channel 0), the
+//            zero-points with them, so that channel 0 is no larger than the others.
+//   phase S  wave: softmax statistics and weight digits of four query heads of one KV head; the digits
+//            (six base-16 digits of a 24-bit integer, in FP8, see k_decode_mfma) stay in the wave's own LDS.
+//   phase V  the same wave: rows = 4 query heads x 4 digits, contraction over 128 tokens of ONE KV head:
+//            no part of the operand is zero (k_decode_mfma's is block-diagonal over the heads), the codes
+//            are fetched once for all query heads.
+// Bound by the vector pipe in phase K (16 instructions of RoPE and 16 of the split for eight channels
+// of a token and block) up to 16 CT = 32 columns, beyond that by the matrix pipe.
+#include "rkv_internal.h"
+#include "rkv_mfma_ops.h"
+#include <hip/hip_ext.h>
+
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+
+#define SH_CH RKV_MFMA_CHUNK
+static_assert(SH_CH == 256, "four waves of four tiles of 16 tokens");
+
+// four dwords of FP4 nibbles (the other four registers of the operand are not read)
+__device__ __forceinline__ v8i as_fp4(const uint4& u) {
+  v8i r;
+  r[0] = (int)u.x; r[1] = (int)u.y; r[2] = (int)u.z; r[3] = (int)u.w;
+  r[4] = r[5] = r[6] = r[7] = 0;
+  return r;
+}
+// low or high half of a packed fp16 pair
+__device__ __forceinline__ float half_of(uint32_t w, int hi) {
+  return (float)__builtin_bit_cast(_Float16, (uint16_t)(hi ? w >> 16 : w & 0xffffu));
+}
+// x -> fp16 high and low parts, x = high + low to 2^-23
+__device__ __forceinline__ void split2(float x0, float x1, v2h& hi, v2h& lo) {
+  hi = __builtin_convertvector((v2f){x0, x1}, v2h);
+  lo = __builtin_convertvector((v2f){x0 - (float)hi[0], x1 - (float)hi[1]}, v2h);
+}
+// LDS writes of this wave before, its reads behind (other waves do not touch the region)
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// CT: column tiles (16 columns each).  HB: bits per code above the low two (planes as in k_decode_mfma).
+// q_lim: null, or the last position each of the nq query tokens may attend (v.Hq then counts virtual heads).
+template <int G, int CT, int HB>
+__global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_shared(RkvView v, const float* __restrict__ qr,
+                                                                                     float* __restrict__ part, int nch,
+                                                                                     const int* __restrict__ q_lim, int nq, int ns,
+                                                                                     uint32_t inv_ns, uint32_t inv_nrg) {
+  constexpr bool HI = HB != 0;
+  constexpr int NC = 16 * CT, RS = NC / G;           // columns; query heads per KV head
+  constexpr int SC_STRIDE = SH_CH + 4;               // (rows of sixteen columns fall on different LDS banks)
+  constexpr int QSTRIDE = NC + 1;                    // 16-byte pieces per row of the query operand
+  constexpr int GP = G / 2;                          // packed fp16 pairs per token
+  constexpr int DROW = 144, DSET1 = 16 * DROW, DWAVE = 24 * DROW;   // weight digits of a wave: 16 rows of set 0, 8 of set 1, 128 tokens each
+  constexpr float MID = HB == 0 ? 1.5f : HB == 1 ? 3.5f : 7.5f;     // middle code
+  struct KeyPart {
+    uint4 H[8][64];
+    uint4 q[32][QSTRIDE];                            // [(p, high / low, lane group)][column]
+    uint32_t ks[SH_CH * GP], kz[SH_CH * GP];         // scales and zero-points of the chunk's tokens
+    float2 cs0[SH_CH];                               // RoPE angle of channel pair 0
+    float2 step[64];                                 // RoPE rotation by 16 positions
+  };
+  union Shared {
+    KeyPart k;
+    uint8_t dig[4][DWAVE];
+  };
+  __shared__ __attribute__((aligned(16))) Shared sh;
+  __shared__ __attribute__((aligned(16))) float s_sc[NC][SC_STRIDE];
+  __shared__ __attribute__((aligned(16))) uint32_t s_vm[G][SH_CH];   // values: (scale, zero-point) pairs
+  __shared__ int s_sink[64];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = lane & 15, q = lane >> 4;
+  __builtin_amdgcn_s_setprio(3);                     // (short phases ahead of the other workgroups' key phases, as in k_decode_mfma)
+
+  // Workgroup -> (sequence, rotation group, chunk, query-head group): as in k_decode_mfma
+  const int rep = v.Hq / v.Hkv;
+  int rg = blockIdx.y;
+  int rrg, chunk, b;
+  if (v.lens) {
+    const int tot8 = gridDim.x / ns;
+    rrg = blockIdx.x / tot8;
+    const int w = blockIdx.x - rrg * tot8;
+    if (w >= v.cstart[v.B]) return;
+    int lo = 0, hi = v.B;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (v.cstart[mid] <= w) lo = mid;
+      else hi = mid;
+    }
+    b = lo;
+    chunk = w - v.cstart[b];
+  } else {
+    const int xcd = blockIdx.x & 7, rem = blockIdx.x >> 3;
+    chunk = inv_ns ? (int)__umulhi((uint32_t)rem, inv_ns) : rem;
+    rrg = rem - chunk * ns;
+    const int br = blockIdx.y * 8 + xcd;
+    if (br >= v.B * v.NRG) return;
+    b = inv_nrg ? (int)__umulhi((uint32_t)br, inv_nrg) : br;
+    rg = br - b * v.NRG;
+  }
+  const int len = rkv_len(v, b);
+  if (chunk * SH_CH >= len) return;
+  const int t0 = chunk * SH_CH;
+  const int rsv = min(RS, rep - rrg * RS);           // query heads per KV head that exist
+  // virtual head of column col = rr * G + a
+  auto head_of = [&](int col) { return (rg * G + col % G) * rep + rrg * RS + col / G; };
+
+  // ---- requests, back to back
+  const size_t nqh = (size_t)v.B * v.Hq;
+  const uint4* qimg = reinterpret_cast<const uint4*>(qr + nqh * RKV_D) + (size_t)b * v.Hq * 32;
+  const float* qscale = qr + 2 * nqh * RKV_D + (size_t)b * v.Hq;
+  const uint4 ld_h0 = reinterpret_cast<const uint4*>(v.hop)[tid], ld_h1 = reinterpret_cast<const uint4*>(v.hop)[tid + 256];
+  uint4 ld_q[2 * CT];
+#pragma unroll
+  for (int i = 0; i < 2 * CT; ++i) {                 // column 8 i + tid / 32, piece tid % 32
+    const int col = 8 * i + (tid >> 5);
+    ld_q[i] = col / G < rsv ? qimg[(size_t)head_of(col) * 32 + (tid & 31)] : make_uint4(0, 0, 0, 0);
+  }
+  const float2 ld_step = v.rope[16 * 64 + (tid & 63)], ld_cs0 = v.rope[(size_t)(t0 + tid) * 64];
+  const int cnt = v.max_sinks > 0 ? v.sink_cnt[b] : 0;
+  const int ld_spos = (v.max_sinks > 0 && (tid & 63) < v.max_sinks) ? v.sink_pos[b * v.max_sinks + (tid & 63)] : -1;
+  uint32_t ksp[2] = {0, 0}, kzp[2] = {0, 0}, vmw[4] = {0, 0, 0, 0};
+  if (v.meta8) {
+    // G scale bytes, then G zero-point bytes (z + 128) per token
+    const size_t mi = ((size_t)(b * v.NRG + rg) * v.Tpad + t0 + tid) * (2 * G);
+    auto fetch8 = [&](const uint32_t* m, float (&s)[4], float (&z)[4]) {
+      const uint8_t* p8 = reinterpret_cast<const uint8_t*>(m) + mi;
+      uint32_t sw, zw;
+      if constexpr (G == 4) {
+        const uint2 u = rkv_ld_stream(reinterpret_cast<const uint2*>(p8));
+        sw = u.x; zw = u.y;
+      } else {
+        sw = *reinterpret_cast<const uint32_t*>(p8);
+        zw = sw >> 16;
+      }
+      s[0] = __builtin_amdgcn_cvt_f32_fp8((int)sw, 0);
+      s[1] = __builtin_amdgcn_cvt_f32_fp8((int)sw, 1);
+      s[2] = __builtin_amdgcn_cvt_f32_fp8((int)sw, 2);
+      s[3] = __builtin_amdgcn_cvt_f32_fp8((int)sw, 3);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) z[i] = (float)((zw >> (8 * i)) & 0xffu) - 128.0f;
+    };
+    float s[4], z[4];
+    fetch8(v.km, s, z);
+#pragma unroll
+    for (int i = 0; i < GP; ++i) {
+      ksp[i] = rkv_pack_meta(s[2 * i], s[2 * i + 1]);
+      kzp[i] = rkv_pack_meta(z[2 * i], z[2 * i + 1]);
+    }
+    fetch8(v.vm, s, z);
+#pragma unroll
+    for (int i = 0; i < G; ++i) vmw[i] = rkv_pack_meta(s[i], z[i]);
+  } else {
+    const size_t mi = ((size_t)(b * v.NRG + rg) * v.Tpad + t0 + tid) * G;
+    uint32_t km[4] = {0, 0, 0, 0};
+    if constexpr (G == 4) {
+      const uint4 u = rkv_ld_stream(reinterpret_cast<const uint4*>(v.km + mi));
+      km[0] = u.x; km[1] = u.y; km[2] = u.z; km[3] = u.w;
+      const uint4 w = rkv_ld_stream(reinterpret_cast<const uint4*>(v.vm + mi));
+      vmw[0] = w.x; vmw[1] = w.y; vmw[2] = w.z; vmw[3] = w.w;
+    } else {
+      const uint2 u = rkv_ld_stream(reinterpret_cast<const uint2*>(v.km + mi));
+      km[0] = u.x; km[1] = u.y;
+      const uint2 w = rkv_ld_stream(reinterpret_cast<const uint2*>(v.vm + mi));
+      vmw[0] = w.x; vmw[1] = w.y;
+    }
+#pragma unroll
+    for (int i = 0; i < GP; ++i) {
+      ksp[i] = __builtin_amdgcn_perm(km[2 * i + 1], km[2 * i], 0x05040100u);
+      kzp[i] = __builtin_amdgcn_perm(km[2 * i + 1], km[2 * i], 0x07060302u);
+    }
+  }
+  // per column of this lane: scale of the score, the query's channel pair 0 for the zero-points, last position attended
+  float c_scale[CT], c_w0[CT], c_w1[CT];
+  int c_lim[CT];
+  const float lane_scale = 2.0f * rsqrtf((float)v.n);   // FP4 nibbles hold code / 2; 1 / sqrt(n) normalises the rotation
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    const int col = 16 * ct + n;
+    const bool ok = col / G < rsv;
+    const int hv = ok ? head_of(col) : head_of(n % G);  // (any head that exists)
+    const float* qn = qr + ((size_t)b * v.Hq + hv) * RKV_D;
+    c_scale[ct] = qscale[hv] * lane_scale;
+    c_w0[ct] = 64.0f * lane_scale * qn[0];
+    c_w1[ct] = 64.0f * lane_scale * qn[v.rope_style ? 1 : 64];
+    c_lim[ct] = len - 1;
+    if (q_lim) c_lim[ct] = min(c_lim[ct], q_lim[b * nq + (ok ? (rrg * RS + col / G) / (rep / nq) : 0)]);
+  }
+  const int tw = t0 + wave * 64;
+  float cc[4][4], ss[4][4];                          // RoPE angles of token n (of the tile), pairs 16 p + 4 q + r
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const float4* rp = reinterpret_cast<const float4*>(v.rope + (size_t)(tw + n) * 64 + 16 * p + 4 * q);
+    const float4 x = rp[0], y = rp[1];
+    cc[p][0] = x.x; ss[p][0] = x.y; cc[p][1] = x.z; ss[p][1] = x.w;
+    cc[p][2] = y.x; ss[p][2] = y.y; cc[p][3] = y.z; ss[p][3] = y.w;
+  }
+  const uint4* ktiles = reinterpret_cast<const uint4*>(v.kc + rkv_k_tilebase(v, b, rg, tw >> 4));
+  const uint32_t* khtiles = HI ? v.kh + (rkv_k_tilebase(v, b, rg, tw >> 4) >> (HB == 1 ? 1 : 0)) : nullptr;
+  uint4 cw[GP], cwh[HI ? GP : 1];
+  auto load_tile = [&](int ti) {
+#pragma unroll
+    for (int pr = 0; pr < GP; ++pr) {
+      const size_t li = (size_t)ti * (32 * G) + pr * 64 + lane;
+      cw[pr] = rkv_ld_stream(ktiles + li);
+      if constexpr (HB == 2) {
+        cwh[pr] = rkv_ld_stream(reinterpret_cast<const uint4*>(khtiles) + li);
+      } else if constexpr (HB == 1) {
+        const uint2 u = rkv_ld_stream(reinterpret_cast<const uint2*>(khtiles) + li);
+        cwh[pr] = make_uint4(u.x, u.y, 0, 0);
+      }
+    }
+  };
+  load_tile(0);
+
+  // ---- what came back goes to LDS
+  (&sh.k.H[0][0])[tid] = ld_h0;
+  (&sh.k.H[0][0])[tid + 256] = ld_h1;
+#pragma unroll
+  for (int i = 0; i < 2 * CT; ++i) sh.k.q[tid & 31][8 * i + (tid >> 5)] = ld_q[i];
+  sh.k.cs0[tid] = ld_cs0;
+  if (tid < 64) {
+    sh.k.step[tid] = ld_step;
+    s_sink[tid] = tid < cnt ? ld_spos : -1;
+  }
+#pragma unroll
+  for (int i = 0; i < GP; ++i) {
+    sh.k.ks[tid * GP + i] = ksp[i];
+    sh.k.kz[tid * GP + i] = kzp[i];
+  }
+#pragma unroll
+  for (int i = 0; i < G; ++i) s_vm[i][tid] = vmw[i];
+  __syncthreads();
+  __builtin_amdgcn_s_setprio(0);
+
+  // ------------------------------------------------------------------ phase K
+  uint32_t sink_tiles = 0;                           // the wave's tiles that hold a retained sink token
+  for (int i = 0; i < cnt; ++i) {
+    const int d = s_sink[i] - tw;
+    if (d >= 0 && d < 64) sink_tiles |= 1u << (d >> 4);
+  }
+  sink_tiles = __builtin_amdgcn_readfirstlane(sink_tiles);
+  const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+  const v4f centre4 = {q == 0 ? -64.0f * MID : 0.f, 0.f, 0.f, 0.f};   // channel 0 of H_128 of the constant MID / 2
+
+#pragma unroll 1
+  for (int ti = 0; ti < 4; ++ti) {
+    const int tt = tw + ti * 16;
+    if (tt >= len) break;                            // wave-uniform
+    v8i A[G], Ah[HI ? G : 1];
+#pragma unroll
+    for (int pr = 0; pr < GP; ++pr) {
+      A[2 * pr] = unpack_fp4(cw[pr].x, cw[pr].y);
+      A[2 * pr + 1] = unpack_fp4(cw[pr].z, cw[pr].w);
+      if constexpr (HB == 2) {
+        Ah[2 * pr] = unpack_fp4(cwh[pr].x, cwh[pr].y);
+        Ah[2 * pr + 1] = unpack_fp4(cwh[pr].z, cwh[pr].w);
+      } else if constexpr (HB == 1) {
+        Ah[2 * pr] = unpack_fp4_bits(cwh[pr].x);
+        Ah[2 * pr + 1] = unpack_fp4_bits(cwh[pr].y);
+      }
+    }
+    if (ti + 1 < 4) load_tile(ti + 1);               // prefetch (inside the padded allocation)
+    v4f d[G][CT];
+#pragma unroll
+    for (int blk = 0; blk < G; ++blk)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) d[blk][ct] = zero4;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      v8i Hl = as_fp4(sh.k.H[p][lane]), Hh = as_fp4(sh.k.H[p + 4][lane]);
+      v8h bh[CT], bl[CT];
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        bh[ct] = __builtin_bit_cast(v8h, sh.k.q[8 * p + q][16 * ct + n]);
+        bl[ct] = __builtin_bit_cast(v8h, sh.k.q[8 * p + 4 + q][16 * ct + n]);
+      }
+      v4f lo[G], hi[G];
+#pragma unroll
+      for (int blk = 0; blk < G; ++blk) {
+        lo[blk] = mfma_fp4(Hl, A[blk], p == 0 ? centre4 : zero4);
+        hi[blk] = mfma_fp4(Hh, A[blk], zero4);
+      }
+      if constexpr (HI) {                            // FP4 +-1 with bit 2 set is +-4
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          Hl[i] |= 0x44444444;
+          Hh[i] |= 0x44444444;
+        }
+#pragma unroll
+        for (int blk = 0; blk < G; ++blk) {
+          lo[blk] = mfma_fp4(Hl, Ah[blk], lo[blk]);
+          hi[blk] = mfma_fp4(Hh, Ah[blk], hi[blk]);
+        }
+      }
+#pragma unroll
+      for (int blk = 0; blk < G; ++blk) {
+        float x[8];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          x[r] = lo[blk][r] * cc[p][r] - hi[blk][r] * ss[p][r];
+          x[4 + r] = lo[blk][r] * ss[p][r] + hi[blk][r] * cc[p][r];
+        }
+        union { v2h h2[4]; v8h h8; } ah, al;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) split2(x[2 * i], x[2 * i + 1], ah.h2[i], al.h2[i]);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          d[blk][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al.h8, bh[ct], d[blk][ct], 0, 0, 0);
+          d[blk][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah.h8, bl[ct], d[blk][ct], 0, 0, 0);
+          d[blk][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah.h8, bh[ct], d[blk][ct], 0, 0, 0);
+        }
+      }
+      // on to the next tile's token
+      const float4* st = reinterpret_cast<const float4*>(&sh.k.step[16 * p + 4 * q]);
+      const float4 s01 = st[0], s23 = st[1];
+      const float sc4[4] = {s01.x, s01.z, s23.x, s23.z}, sn4[4] = {s01.y, s01.w, s23.y, s23.w};
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float c = cc[p][r], s = ss[p][r];
+        cc[p][r] = c * sc4[r] - s * sn4[r];
+        ss[p][r] = s * sc4[r] + c * sn4[r];
+      }
+    }
+    // scales, butterfly and zero-points of tokens 4q + r; this lane's columns all belong to KV head a = n % G
+    const int tl = wave * 64 + ti * 16 + 4 * q;
+    float sc[4][CT];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float s_[G], Z = 0.f;
+#pragma unroll
+      for (int blk = 0; blk < G; ++blk) {
+        const uint32_t sw = sh.k.ks[(tl + r) * GP + (blk >> 1)], zw = sh.k.kz[(tl + r) * GP + (blk >> 1)];
+        const float s = half_of(sw, blk & 1);
+        s_[blk] = (__popc(n & (G - 1) & blk) & 1) ? -s : s;
+        Z = fmaf(s_[blk], half_of(zw, blk & 1) - MID, Z);
+      }
+      const float2 cs0 = sh.k.cs0[tl + r];
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        float t = 0.f;
+#pragma unroll
+        for (int blk = 0; blk < G; ++blk) t = fmaf(s_[blk], d[blk][ct][r], t);
+        const float w = fmaf(cs0.x, c_w0[ct], cs0.y * c_w1[ct]);
+        sc[r][ct] = fmaf(t, c_scale[ct], -Z * w);
+      }
+    }
+    uint32_t masked = 0;
+    if (sink_tiles & (1u << ti))
+      for (int i = 0; i < cnt; ++i) {
+        const int dd = s_sink[i] - (tt + 4 * q);
+        if (dd >= 0 && dd < 4) masked |= 1u << dd;
+      }
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      float4 o;
+      float* op = &o.x;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) op[r] = (((masked >> r) & 1u) || tt + 4 * q + r > c_lim[ct]) ? -INFINITY : sc[r][ct];
+      *reinterpret_cast<float4*>(&s_sc[16 * ct + n][tl]) = o;
+    }
+  }
+  __builtin_amdgcn_s_setprio(3);
+
+  // ------------------------------------------------------------------ phases S and V
+  // wave -> KV head a, channel tiles: all eight (G = 4), or one half of them (G = 2)
+  constexpr int NB = G == 4 ? 4 : 2;                 // blocks of 32 channels per wave
+  const int a = wave & (G - 1), wb = G == 4 ? 0 : (wave >> 1) * 2;
+  const int nslab = min(SH_CH / 32, (len - t0 + 31) >> 5);
+  const uint4* vslab = reinterpret_cast<const uint4*>(v.vc + rkv_v_slabbase(v, b, rg, t0 >> 5));
+  const uint32_t* vhslab = HI ? v.vh + (rkv_v_slabbase(v, b, rg, t0 >> 5) >> (HB == 1 ? 1 : 0)) : nullptr;
+  uint4 vcodes[2][NB], vhcodes[HI ? 2 : 1][HI ? NB : 1];
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int w = 0; w < NB; ++w) {
+      // lane group q holds slab 4 s + q: 32 of the 128 tokens of a contraction
+      const size_t li = (size_t)(4 * s + q) * (64 * G) + ((wb + w) * G + a) * 16 + n;
+      const bool in = 4 * s + q < nslab;
+      vcodes[s][w] = make_uint4(0, 0, 0, 0);
+      if (in) vcodes[s][w] = rkv_ld_stream(vslab + li);
+      if constexpr (HI) {
+        vhcodes[s][w] = make_uint4(0, 0, 0, 0);
+        if (in) {
+          if constexpr (HB == 2) {
+            vhcodes[s][w] = rkv_ld_stream(reinterpret_cast<const uint4*>(vhslab) + li);
+          } else {
+            const uint2 u = rkv_ld_stream(reinterpret_cast<const uint2*>(vhslab) + li);
+            vhcodes[s][w] = make_uint4(u.x, u.y, 0, 0);
+          }
+        }
+      }
+    }
+  __syncthreads();                                   // all scores are there; the key phase's part of LDS is free
+
+  uint8_t* const dig = sh.dig[wave];
+  const int left = len - t0 - 4 * lane;              // of the lane's tokens 4 lane .. + 3: how many exist
+  float vs[4], vz[4];
+  {
+    const uint4 m4 = *reinterpret_cast<const uint4*>(&s_vm[a][4 * lane]);
+    rkv_unpack_meta(m4.x, vs[0], vz[0]);
+    rkv_unpack_meta(m4.y, vs[1], vz[1]);
+    rkv_unpack_meta(m4.z, vs[2], vz[2]);
+    rkv_unpack_meta(m4.w, vs[3], vz[3]);
+  }
+  const int groups = (rsv + 3) >> 2;
+#pragma unroll 1
+  for (int g = 0; g < groups; ++g) {
+    float hm[4], hl[4], hzs[4], hdown[4];
+    uint32_t dg[4][6];
+#pragma unroll
+    for (int qq = 0; qq < 4; ++qq) {
+      hm[qq] = -INFINITY;
+      hl[qq] = hzs[qq] = hdown[qq] = 0.f;
+#pragma unroll
+      for (int k = 0; k < 6; ++k) dg[qq][k] = 0;
+      const int rr = 4 * g + qq;
+      if (rr < rsv) {                                // wave-uniform
+        const float4 s4 = *reinterpret_cast<const float4*>(&s_sc[rr * G + a][4 * lane]);
+        const float sv[4] = {left > 0 ? s4.x : -INFINITY, left > 1 ? s4.y : -INFINITY, left > 2 ? s4.z : -INFINITY, left > 3 ? s4.w : -INFINITY};
+        const float m = wave_allreduce<true>(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])));
+        float pe[4], w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          pe[i] = sv[i] > -INFINITY ? __expf(sv[i] - m) : 0.f;
+          w[i] = pe[i] > 0.f ? pe[i] * vs[i] : 0.f;
+        }
+        const float l = wave_allreduce<false>((pe[0] + pe[1]) + (pe[2] + pe[3]));
+        const float wmax = wave_allreduce<true>(fmaxf(fmaxf(w[0], w[1]), fmaxf(w[2], w[3])));
+        // 24-bit fixed point: the largest weight lands in [2^23, 2^24); six base-16 digits, exact in E4M3
+        int ex = 0;
+        if (wmax > 0.f) frexpf(wmax, &ex);
+        const float up = ldexpf(1.0f, 24 - ex), down = ldexpf(1.0f, ex - 24);
+        uint32_t W[4];
+        float zs = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          W[i] = (uint32_t)rintf(w[i] * up);
+          if (W[i]) zs = fmaf((float)W[i], vz[i], zs);
+        }
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {                // most significant first (the first may be 16)
+          float f[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) f[i] = (float)(k == 0 ? W[i] >> 20 : (W[i] >> (20 - 4 * k)) & 15u);
+          int pk = __builtin_amdgcn_cvt_pk_fp8_f32(f[0], f[1], 0, false);
+          dg[qq][k] = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(f[2], f[3], pk, true);
+        }
+        hm[qq] = m;
+        hl[qq] = l;
+        hzs[qq] = wave_allreduce<false>(zs) * down;
+        hdown[qq] = down;
+      }
+    }
+    v4f acc[2 * NB][2];                              // [channel tile][digit set]
+#pragma unroll
+    for (int i = 0; i < 2 * NB; ++i) acc[i][0] = acc[i][1] = zero4;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      if (4 * s < nslab) {                           // workgroup-uniform
+        wave_lds_fence();                            // (the digits of the tokens before have been read)
+        if ((lane >> 5) == s) {
+          uint8_t* dst = dig + ((4 * lane) & 127);
+#pragma unroll
+          for (int qq = 0; qq < 4; ++qq)
+#pragma unroll
+            for (int k = 0; k < 6; ++k)
+              *reinterpret_cast<uint32_t*>(dst + (k < 4 ? (4 * qq + k) * DROW : DSET1 + (2 * qq + k - 4) * DROW)) = dg[qq][k];
+        }
+        wave_lds_fence();
+        // FP8 operand: lane group q holds tokens 16 q .. + 15 and 64 + 16 q .. + 15 of the 128.  Rows of set 1
+        // whose digit does not exist repeat another one; their results are not used
+        v8i D[2];
+#pragma unroll
+        for (int set = 0; set < 2; ++set) {
+          const uint8_t* row = dig + (set == 0 ? n * DROW : DSET1 + (2 * (n >> 2) + (n & 1)) * DROW) + 16 * q;
+          const uint4 d0 = *reinterpret_cast<const uint4*>(row), d1 = *reinterpret_cast<const uint4*>(row + 64);
+          D[set][0] = (int)d0.x; D[set][1] = (int)d0.y; D[set][2] = (int)d0.z; D[set][3] = (int)d0.w;
+          D[set][4] = (int)d1.x; D[set][5] = (int)d1.y; D[set][6] = (int)d1.z; D[set][7] = (int)d1.w;
+        }
+#pragma unroll
+        for (int w = 0; w < NB; ++w)
+#pragma unroll
+          for (int c2 = 0; c2 < 2; ++c2) {
+            const v8i B = c2 ? unpack_fp4(vcodes[s][w].z, vcodes[s][w].w) : unpack_fp4(vcodes[s][w].x, vcodes[s][w].y);
+            v8i Bh = B;
+            if constexpr (HB == 2) Bh = c2 ? unpack_fp4(vhcodes[s][w].z, vhcodes[s][w].w) : unpack_fp4(vhcodes[s][w].x, vhcodes[s][w].y);
+            if constexpr (HB == 1) Bh = unpack_fp4_bits(c2 ? vhcodes[s][w].y : vhcodes[s][w].x);
+#pragma unroll
+            for (int set = 0; set < 2; ++set) {
+              v4f& o = acc[2 * w + c2][set];
+              if constexpr (HI) o += 4.0f * mfma_fp8_fp4(D[set], Bh, zero4);   // the upper plane counts fourfold
+              o = mfma_fp8_fp4(D[set], B, o);
+            }
+          }
+      }
+    }
+    // lane group q: query head 4 g + q, channels 16 * tile + n; registers: digits
+    const int rr = 4 * g + q;
+    auto pick = [&](const float (&x)[4]) { return q == 0 ? x[0] : q == 1 ? x[1] : q == 2 ? x[2] : x[3]; };
+    const float wsc = 2.0f * pick(hdown), zs = pick(hzs), m = pick(hm), l = pick(hl);
+    if (rr < rsv) {
+      float* dst = part + (((size_t)b * v.Hq + head_of(rr * G + a)) * nch + chunk) * RKV_PART_STRIDE;
+#pragma unroll
+      for (int i = 0; i < 2 * NB; ++i) {
+        const v4f h = acc[i][0], lo = acc[i][1];
+        const float sum = ((((h[0] * 16.0f + h[1]) * 16.0f + h[2]) * 16.0f + h[3]) * 16.0f + lo[0]) * 16.0f + lo[1];
+        dst[4 + 16 * (2 * wb + i) + n] = sum * wsc - zs;
+      }
+      if (wb == 0 && n == 0) {
+        dst[0] = m;
+        dst[1] = l;
+      }
+    }
+  }
+}
+
+// More than one query head per KV head, or several query tokens per step, on a cache whose scores do
+// not come from the scores kernel.  (One query head per KV head fills 4 of the 16 columns: there
+// k_decode_mfma, which takes the dot product on the vector pipe, has fewer instructions per key.)
+bool rkv_shared_decode(const rkv_cache* c, bool multi) {
+  return c->decode_path != 3 && !rkv_scores_path(c) && (multi || c->v.Hq > c->v.Hkv);
+}
+
+// v, nq: the (virtual) view of rkv_launch_decode_mfma
+int rkv_launch_decode_shared(const rkv_cache* c, const RkvView& v, const float* qr, float* part, int nch, const int* q_lim, int nq,
+                             hipEvent_t ev_start, hipEvent_t ev_stop, hipStream_t s) {
+  const int rep = v.Hq / v.Hkv;
+  const int ct = rep * v.g <= 16 ? 1 : 2, rs = 16 * ct / v.g, ns = (rep + rs - 1) / rs;
+  auto recip = [](int d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };
+  dim3 grid(8 * nch * ns, (v.B * v.NRG + 7) / 8, 1);
+  if (c->ragged) {
+    int total = 0;
+    for (int b = 0; b < v.B; ++b) total += (c->hlens[b] + SH_CH - 1) / SH_CH;
+    grid = dim3(((total + 7) & ~7) * ns, v.NRG, 1);
+  }
+  if (grid.y > 65535) return RKV_EINVAL;
+#define RKV_SH(G_, C_) (v.hb == 2 ? k_decode_shared<G_, C_, 2> : v.hb == 1 ? k_decode_shared<G_, C_, 1> : k_decode_shared<G_, C_, 0>)
+  auto fn = v.g == 4 ? (ct == 1 ? RKV_SH(4, 1) : RKV_SH(4, 2)) : (ct == 1 ? RKV_SH(2, 1) : RKV_SH(2, 2));
+#undef RKV_SH
+  if (ev_start && ev_stop)
+    hipExtLaunchKernelGGL(fn, grid, dim3(256), 0, s, ev_start, ev_stop, 0, v, qr, part, nch, q_lim, nq, ns, recip(ns), recip(v.NRG));
+  else
+    hipLaunchKernelGGL(fn, grid, dim3(256), 0, s, v, qr, part, nch, q_lim, nq, ns, recip(ns), recip(v.NRG));
+  return RKV_OK;
+}

@@ -3,6 +3,20 @@
 #pragma once
 #include "rkv_internal.h"
 
+// one channel of the query, rotated to position pos and scaled.  Angles from the table (computed in
+// double, stored as float) when the position lies inside it - the usual case -, else computed here
+__device__ __forceinline__ float rkv_prep_q_rotate(const RkvView& v, float x, float partner, float sgn, int pos, int j) {
+  double sn, cs;
+  if (pos >= 0 && pos < v.Tpad) {
+    const float2 t = v.rope[(size_t)pos * 64 + j];
+    cs = t.x;
+    sn = t.y;
+  } else {
+    sincos((double)pos * pow((double)v.theta, -(double)j / 64.0), &sn, &cs);
+  }
+  return (float)(((double)x * cs + (double)sgn * (double)partner * sn) * 0.08838834764831845);
+}
+
 // One output channel c (0..127) of (virtual) query head h of sequence b.
 // q~[b][h][c] = RoPE(q, q_pos)[c] / sqrt(128), angles in double (q_pos may lie beyond the table).
 __device__ __forceinline__ void rkv_prep_q_one(const RkvView& v, const __half* __restrict__ q, const int* __restrict__ q_pos,
@@ -25,6 +39,29 @@ __device__ __forceinline__ void rkv_prep_q_one(const RkvView& v, const __half* _
     sgn = (c & 1) ? 1.f : -1.f;
   }
   const float x = __half2float(q[src + c]), p = __half2float(q[src + partner]);
+  const int nn = v.rope_style ? (c >> 1) & 15 : c & 15, pp = v.rope_style ? (c >> 5) & 3 : (c >> 4) & 3, half = v.rope_style ? c & 1 : c >> 6;
+  if (share == 0) {
+    // The kernel that serves all query heads of a KV head at once (k_decode_shared) takes the query
+    // as fp16 matrix operands, split into a high and a low part (a float to 2^-23): for each head
+    //   [p][high, low][lane group nn / 4][half][nn % 4]   fp16,
+    // scaled by a power of two that puts the head's largest component at 2^8 .. 2^11 (what is 2^-11
+    // of it still has all bits of its low part), and the scale's inverse behind all heads' operands.
+    float mx = fmaxf(fabsf(__half2float(q[src + (c & 63)])), fabsf(__half2float(q[src + (c & 63) + 64])));
+#pragma unroll
+    for (int i = 32; i > 0; i >>= 1) mx = fmaxf(mx, __shfl_xor(mx, i));
+    int ex = 0;
+    if (mx > 0.f && mx < INFINITY) frexpf(mx, &ex);
+    const float val = rkv_prep_q_rotate(v, x, p, sgn, pos, j);
+    qr[base + c] = val;
+    __half* img = reinterpret_cast<__half*>(qr + (size_t)v.B * v.Hq * RKV_D);
+    const size_t o = (((((size_t)b * v.Hq + h) * 4 + pp) * 2) * 4 + (nn >> 2)) * 8 + 4 * half + (nn & 3);
+    const float y = ldexpf(val, 14 - ex);
+    const __half hi = __float2half_rn(y);
+    img[o] = hi;
+    img[o + 4 * 8] = __float2half_rn(y - __half2float(hi));
+    if (c == 0) qr[2 * (size_t)v.B * v.Hq * RKV_D + (size_t)b * v.Hq + h] = ldexpf(1.0f, ex - 14);
+    return;
+  }
   // The matrix-core kernel keeps RoPE angles for the first of a lane's four consecutive tokens only
   // and rotates all four keys by them; the difference is put on the query side, which is exact:
   // <R(t + r) k, R(pos) q> = <R(t) k, R(pos - r) q>.  So it gets the query at positions pos - r,
@@ -37,23 +74,11 @@ __device__ __forceinline__ void rkv_prep_q_one(const RkvView& v, const __half* _
   const int g = v.g, rep = v.Hq / v.Hkv;
   const int kvh = h / rep, rr = h - kvh * rep, rg = kvh / g, a = kvh - rg * g;
   float* qt = qr + (size_t)v.B * v.Hq * RKV_D;
-  const int nn = v.rope_style ? (c >> 1) & 15 : c & 15, pp = v.rope_style ? (c >> 5) & 3 : (c >> 4) & 3, half = v.rope_style ? c & 1 : c >> 6;
   const int rrg = rr / share, rri = rr - rrg * share;
   const float lane_scale = 2.0f * rsqrtf((float)v.n);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    // angles: from the table (computed in double, stored as float) when the position lies inside
-    // it - the usual case -, else computed here
-    const int pr = pos - r;
-    double sn, cs;
-    if (pr >= 0 && pr < v.Tpad) {
-      const float2 t = v.rope[(size_t)pr * 64 + j];
-      cs = t.x;
-      sn = t.y;
-    } else {
-      sincos((double)pr * pow((double)v.theta, -(double)j / 64.0), &sn, &cs);
-    }
-    const float val = (float)(((double)x * cs + (double)sgn * (double)p * sn) * 0.08838834764831845);
+    const float val = rkv_prep_q_rotate(v, x, p, sgn, pos - r, j);
     if (r == 0) qr[base + c] = val;
     const int f = (a * share + rri) * 2 + half, nh2 = g * share / 2;
     size_t o = ((size_t)b * v.NRG + rg) * (rep / share) + rrg;
