@@ -45,14 +45,30 @@ __device__ __forceinline__ v8i as_fp4(const uint4& u) {
   r[4] = r[5] = r[6] = r[7] = 0;
   return r;
 }
-// low or high half of a packed fp16 pair
-__device__ __forceinline__ float half_of(uint32_t w, int hi) {
-  return (float)__builtin_bit_cast(_Float16, (uint16_t)(hi ? w >> 16 : w & 0xffffu));
-}
-// x -> fp16 high and low parts, x = high + low to 2^-23
-__device__ __forceinline__ void split2(float x0, float x1, v2h& hi, v2h& lo) {
-  hi = __builtin_convertvector((v2f){x0, x1}, v2h);
-  lo = __builtin_convertvector((v2f){x0 - (float)hi[0], x1 - (float)hi[1]}, v2h);
+__device__ __forceinline__ float flip(float x, uint32_t sign) { return __uint_as_float(__float_as_uint(x) ^ sign); }
+// Eight floats -> fp16 high and low parts, x = high + low to 2^-23.  x - high is exact: one multiply-add of mixed
+// precision each (high * -1 + x), which rounds into its half of the register; the compiler makes a
+// conversion, a subtraction and a conversion of it (24 instead of 12 instructions for the eight).
+// The compiler does not see that vector instructions wrote the result: the wait at the end is
+// what a matrix instruction needs that reads it next.
+struct Split8 { v8h hi, lo; };
+__device__ __forceinline__ Split8 split8(const float (&x)[8]) {
+  union { v2h h2[4]; uint32_t u[4]; v8h h8; } hi, lo;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) hi.h2[i] = __builtin_convertvector((v2f){x[2 * i], x[2 * i + 1]}, v2h);
+  asm("v_fma_mixlo_f16 %0, %4, -1.0, %8 op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixlo_f16 %1, %5, -1.0, %10 op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixlo_f16 %2, %6, -1.0, %12 op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixlo_f16 %3, %7, -1.0, %14 op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixhi_f16 %0, %4, -1.0, %9 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixhi_f16 %1, %5, -1.0, %11 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixhi_f16 %2, %6, -1.0, %13 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mixhi_f16 %3, %7, -1.0, %15 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
+      "s_nop 1"
+      : "=&v"(lo.u[0]), "=&v"(lo.u[1]), "=&v"(lo.u[2]), "=&v"(lo.u[3])
+      : "v"(hi.u[0]), "v"(hi.u[1]), "v"(hi.u[2]), "v"(hi.u[3]), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]),
+        "v"(x[6]), "v"(x[7]));
+  return {hi.h8, lo.h8};
 }
 // LDS writes of this wave before, its reads behind (other waves do not touch the region)
 __device__ __forceinline__ void wave_lds_fence() {
@@ -78,7 +94,8 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
   struct KeyPart {
     uint4 H[8][64];
     uint4 q[32][QSTRIDE];                            // [(p, high / low, lane group)][column]
-    uint32_t ks[SH_CH * GP], kz[SH_CH * GP];         // scales and zero-points of the chunk's tokens
+    float ks[G][SH_CH];                              // scales of the chunk's tokens
+    float kz[G][SH_CH];                              // their zero-points' share: sum_blk H_g[a][blk] scale_blk (zero_blk - MID)
     float2 cs0[SH_CH];                               // RoPE angle of channel pair 0
     float2 step[64];                                 // RoPE rotation by 16 positions
   };
@@ -142,7 +159,8 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
   const float2 ld_step = v.rope[16 * 64 + (tid & 63)], ld_cs0 = v.rope[(size_t)(t0 + tid) * 64];
   const int cnt = v.max_sinks > 0 ? v.sink_cnt[b] : 0;
   const int ld_spos = (v.max_sinks > 0 && (tid & 63) < v.max_sinks) ? v.sink_pos[b * v.max_sinks + (tid & 63)] : -1;
-  uint32_t ksp[2] = {0, 0}, kzp[2] = {0, 0}, vmw[4] = {0, 0, 0, 0};
+  float ks_[4], kz_[4];
+  uint32_t vmw[4] = {0, 0, 0, 0};
   if (v.meta8) {
     // G scale bytes, then G zero-point bytes (z + 128) per token
     const size_t mi = ((size_t)(b * v.NRG + rg) * v.Tpad + t0 + tid) * (2 * G);
@@ -164,12 +182,7 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
       for (int i = 0; i < 4; ++i) z[i] = (float)((zw >> (8 * i)) & 0xffu) - 128.0f;
     };
     float s[4], z[4];
-    fetch8(v.km, s, z);
-#pragma unroll
-    for (int i = 0; i < GP; ++i) {
-      ksp[i] = rkv_pack_meta(s[2 * i], s[2 * i + 1]);
-      kzp[i] = rkv_pack_meta(z[2 * i], z[2 * i + 1]);
-    }
+    fetch8(v.km, ks_, kz_);
     fetch8(v.vm, s, z);
 #pragma unroll
     for (int i = 0; i < G; ++i) vmw[i] = rkv_pack_meta(s[i], z[i]);
@@ -188,10 +201,7 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
       vmw[0] = w.x; vmw[1] = w.y;
     }
 #pragma unroll
-    for (int i = 0; i < GP; ++i) {
-      ksp[i] = __builtin_amdgcn_perm(km[2 * i + 1], km[2 * i], 0x05040100u);
-      kzp[i] = __builtin_amdgcn_perm(km[2 * i + 1], km[2 * i], 0x07060302u);
-    }
+    for (int i = 0; i < 4; ++i) rkv_unpack_meta(km[i], ks_[i], kz_[i]);
   }
   // per column of this lane: scale of the score, the query's channel pair 0 for the zero-points, last position attended
   float c_scale[CT], c_w0[CT], c_w1[CT];
@@ -247,9 +257,12 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
     s_sink[tid] = tid < cnt ? ld_spos : -1;
   }
 #pragma unroll
-  for (int i = 0; i < GP; ++i) {
-    sh.k.ks[tid * GP + i] = ksp[i];
-    sh.k.kz[tid * GP + i] = kzp[i];
+  for (int a = 0; a < G; ++a) {
+    float Z = 0.f;
+#pragma unroll
+    for (int i = 0; i < G; ++i) Z = fmaf((__popc(a & i) & 1) ? -ks_[i] : ks_[i], kz_[i] - MID, Z);
+    sh.k.ks[a][tid] = ks_[a];
+    sh.k.kz[a][tid] = Z;
   }
 #pragma unroll
   for (int i = 0; i < G; ++i) s_vm[i][tid] = vmw[i];
@@ -324,14 +337,12 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
           x[r] = lo[blk][r] * cc[p][r] - hi[blk][r] * ss[p][r];
           x[4 + r] = lo[blk][r] * ss[p][r] + hi[blk][r] * cc[p][r];
         }
-        union { v2h h2[4]; v8h h8; } ah, al;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) split2(x[2 * i], x[2 * i + 1], ah.h2[i], al.h2[i]);
+        const Split8 k = split8(x);
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
-          d[blk][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al.h8, bh[ct], d[blk][ct], 0, 0, 0);
-          d[blk][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah.h8, bl[ct], d[blk][ct], 0, 0, 0);
-          d[blk][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah.h8, bh[ct], d[blk][ct], 0, 0, 0);
+          d[blk][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(k.lo, bh[ct], d[blk][ct], 0, 0, 0);
+          d[blk][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(k.hi, bl[ct], d[blk][ct], 0, 0, 0);
+          d[blk][ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(k.hi, bh[ct], d[blk][ct], 0, 0, 0);
         }
       }
       // on to the next tile's token
@@ -347,27 +358,25 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
     }
     // scales, butterfly and zero-points of tokens 4q + r; this lane's columns all belong to KV head a = n % G
     const int tl = wave * 64 + ti * 16 + 4 * q;
-    float sc[4][CT];
+    float s_[G][4], sc[4][CT];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      float s_[G], Z = 0.f;
+    for (int blk = 0; blk < G; ++blk) {
+      const float4 f = *reinterpret_cast<const float4*>(&sh.k.ks[blk][tl]);
+      const uint32_t sg = (uint32_t)(__popc(n & (G - 1) & blk) & 1) << 31;
+      s_[blk][0] = flip(f.x, sg); s_[blk][1] = flip(f.y, sg); s_[blk][2] = flip(f.z, sg); s_[blk][3] = flip(f.w, sg);
+    }
+    const float4 Z4 = *reinterpret_cast<const float4*>(&sh.k.kz[n & (G - 1)][tl]);
+    const float4 e01 = *reinterpret_cast<const float4*>(&sh.k.cs0[tl]), e23 = *reinterpret_cast<const float4*>(&sh.k.cs0[tl + 2]);
+    const float Z[4] = {Z4.x, Z4.y, Z4.z, Z4.w}, c0[4] = {e01.x, e01.z, e23.x, e23.z}, s0[4] = {e01.y, e01.w, e23.y, e23.w};
 #pragma unroll
-      for (int blk = 0; blk < G; ++blk) {
-        const uint32_t sw = sh.k.ks[(tl + r) * GP + (blk >> 1)], zw = sh.k.kz[(tl + r) * GP + (blk >> 1)];
-        const float s = half_of(sw, blk & 1);
-        s_[blk] = (__popc(n & (G - 1) & blk) & 1) ? -s : s;
-        Z = fmaf(s_[blk], half_of(zw, blk & 1) - MID, Z);
-      }
-      const float2 cs0 = sh.k.cs0[tl + r];
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) {
         float t = 0.f;
 #pragma unroll
-        for (int blk = 0; blk < G; ++blk) t = fmaf(s_[blk], d[blk][ct][r], t);
-        const float w = fmaf(cs0.x, c_w0[ct], cs0.y * c_w1[ct]);
-        sc[r][ct] = fmaf(t, c_scale[ct], -Z * w);
+        for (int blk = 0; blk < G; ++blk) t = blk == 0 ? s_[0][r] * d[0][ct][r] : fmaf(s_[blk][r], d[blk][ct][r], t);
+        sc[r][ct] = fmaf(t, c_scale[ct], -Z[r] * fmaf(c0[r], c_w0[ct], s0[r] * c_w1[ct]));
       }
-    }
     uint32_t masked = 0;
     if (sink_tiles & (1u << ti))
       for (int i = 0; i < cnt; ++i) {
@@ -450,7 +459,7 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
         }
         const float l = wave_allreduce<false>((pe[0] + pe[1]) + (pe[2] + pe[3]));
         const float wmax = wave_allreduce<true>(fmaxf(fmaxf(w[0], w[1]), fmaxf(w[2], w[3])));
-        // 24-bit fixed point: the largest weight lands in [2^23, 2^24); six base-16 digits, exact in E4M3
+        // 24-bit fixed point: the largest weight lands in [2^23, 2^24); six base-16 digits
         int ex = 0;
         if (wmax > 0.f) frexpf(wmax, &ex);
         const float up = ldexpf(1.0f, 24 - ex), down = ldexpf(1.0f, ex - 24);
@@ -461,14 +470,16 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
           W[i] = (uint32_t)rintf(w[i] * up);
           if (W[i]) zs = fmaf((float)W[i], vz[i], zs);
         }
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {                // most significant first (the first may be 16)
-          float f[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) f[i] = (float)(k == 0 ? W[i] >> 20 : (W[i] >> (20 - 4 * k)) & 15u);
-          int pk = __builtin_amdgcn_cvt_pk_fp8_f32(f[0], f[1], 0, false);
-          dg[qq][k] = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(f[2], f[3], pk, true);
-        }
+        // (the largest weight is a 24-bit integer as it stands, so no digit exceeds 15.)  A byte 0..15 read as
+        // E4M3 is that integer times 2^-9 - subnormals and the first binade are one straight line -: the bytes of
+        // four tokens' weights are brought together and parted into their nibbles, nothing is converted
+        const uint32_t p01 = __builtin_amdgcn_perm(W[1], W[0], 0x05010400u), p23 = __builtin_amdgcn_perm(W[3], W[2], 0x05010400u);
+        const uint32_t b2 = __builtin_amdgcn_perm(__builtin_amdgcn_perm(W[3], W[2], 0x0c0c0602u),
+                                                  __builtin_amdgcn_perm(W[1], W[0], 0x0c0c0602u), 0x05040100u);
+        const uint32_t b0 = __builtin_amdgcn_perm(p23, p01, 0x05040100u), b1 = __builtin_amdgcn_perm(p23, p01, 0x07060302u);
+        dg[qq][0] = (b2 >> 4) & 0x0f0f0f0fu; dg[qq][1] = b2 & 0x0f0f0f0fu;
+        dg[qq][2] = (b1 >> 4) & 0x0f0f0f0fu; dg[qq][3] = b1 & 0x0f0f0f0fu;
+        dg[qq][4] = (b0 >> 4) & 0x0f0f0f0fu; dg[qq][5] = b0 & 0x0f0f0f0fu;
         hm[qq] = m;
         hl[qq] = l;
         hzs[qq] = wave_allreduce<false>(zs) * down;
@@ -521,7 +532,7 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
     // lane group q: query head 4 g + q, channels 16 * tile + n; registers: digits
     const int rr = 4 * g + q;
     auto pick = [&](const float (&x)[4]) { return q == 0 ? x[0] : q == 1 ? x[1] : q == 2 ? x[2] : x[3]; };
-    const float wsc = 2.0f * pick(hdown), zs = pick(hzs), m = pick(hm), l = pick(hl);
+    const float wsc = 1024.0f * pick(hdown), zs = pick(hzs), m = pick(hm), l = pick(hl);
     if (rr < rsv) {
       float* dst = part + (((size_t)b * v.Hq + head_of(rr * G + a)) * nch + chunk) * RKV_PART_STRIDE;
 #pragma unroll
