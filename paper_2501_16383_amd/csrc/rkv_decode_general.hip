@@ -6,6 +6,7 @@
 //   k_merge         combines the partials with the fp16 sink rows (Sec. 4.3) -> out, lse
 #include "rkv_internal.h"
 #include "rkv_prep_q.h"
+#include "rkv_mfma_ops.h"
 
 #define GEN_CHUNK RKV_GEN_CHUNK
 
@@ -213,9 +214,10 @@ __global__ void __launch_bounds__(256) k_decode_gen(RkvView v, const float* __re
 
 // One workgroup per (query head, sequence); thread = output channel.  All global loads whose
 // addresses do not depend on loaded data are issued up front (two dependent round trips in all).
-// NGRP groups of 128 threads share the chunks (long contexts: with 128 chunks a single group spends
-// its time waiting for one batch of partial sums after the other); group 0 also does everything
-// that is not per chunk, and adds up the groups' sums at the end.
+// NGRP groups of 128 threads share the chunks, so that a group's partial sums are one batch of loads
+// (sixteen chunks) up to 128 chunks in all; group 0 also does everything that is not per chunk, and adds
+// up the groups' sums at the end.  The kernel is a chain of latencies: sums over lanes take the
+// vector pipe's lane moves, and a chunk's weight is worked out in one lane and broadcast from there.
 #define MERGE_MAX_CH 512
 template <int NGRP>
 __global__ void __launch_bounds__(128 * NGRP) k_merge(RkvView v, const float* __restrict__ qr, const float* __restrict__ part,
@@ -285,7 +287,7 @@ __global__ void __launch_bounds__(128 * NGRP) k_merge(RkvView v, const float* __
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      for (int o = 32; o > 0; o >>= 1) d[i] += __shfl_xor(d[i], o);
+      d[i] = wave_allreduce<false>(d[i]);
       if (lane == 0 && s0 + i < cnt) s_part[wave][s0 + i] = v.sink_pos[b * v.max_sinks + s0 + i] <= lim ? d[i] : -INFINITY;
     }
   };
@@ -302,7 +304,7 @@ __global__ void __launch_bounds__(128 * NGRP) k_merge(RkvView v, const float* __
     sincos((double)len_b * pow((double)v.theta, -(double)j / 64.0), &sn, &cs);
     const float x = __half2float(kr[c]), p = __half2float(kr[partner]);
     float d = qc * (x * (float)cs + sgn * p * (float)sn);
-    for (int o = 32; o > 0; o >>= 1) d += __shfl_xor(d, o);
+    d = wave_allreduce<false>(d);
     if (lane == 0) s_cur[wave] = d;
   }
   __syncthreads();
@@ -311,31 +313,29 @@ __global__ void __launch_bounds__(128 * NGRP) k_merge(RkvView v, const float* __
   __syncthreads();
 
   float M = -INFINITY;
-  for (int k = 0; k < nch; ++k) M = fmaxf(M, s_w[k]);
+  for (int k = lane; k < nch; k += 64) M = fmaxf(M, s_w[k]);
+  M = wave_allreduce<true>(M);
   for (int s = 0; s < cnt; ++s) M = fmaxf(M, s_score[s]);
   M = fmaxf(M, cur_score);
   float L = 0.f, acc = 0.f;
+  for (int kb = k_lo; kb < k_hi; kb += 64) {                 // (one turn up to 64 chunks per group)
+    // lane i: chunk kb + i
+    const int in = min(k_hi - kb, 64);
+    const float mk = lane < in ? s_w[kb + lane] : -INFINITY;
+    const float w = mk > -INFINITY ? __expf(mk - M) : 0.f;
+    L += wave_allreduce<false>(lane < in ? w * s_l[kb + lane] : 0.f);
+    const int wi = __float_as_int(w);
+    if (kb > k_lo) {
 #pragma unroll
-  for (int k = 0; k < PRE; ++k) {
-    if (k_lo + k < k_hi) {
-      const float mk = s_w[k_lo + k];
-      const float w = mk > -INFINITY ? __expf(mk - M) : 0.f;
-      L += w * s_l[k_lo + k];
-      acc += w * pv[k];                                      // partial sums are always finite
+      for (int i = 0; i < PRE; ++i) pv[i] = i < in ? P[(size_t)(kb + i) * RKV_PART_STRIDE + 4 + c] : 0.f;
     }
-  }
-  for (int k0 = k_lo + PRE; k0 < k_hi; k0 += 8) {            // longer contexts: eight loads in flight at a time
-    float pw[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) pw[i] = k0 + i < k_hi ? P[(size_t)(k0 + i) * RKV_PART_STRIDE + 4 + c] : 0.f;
+    for (int i = 0; i < PRE; ++i) acc += __int_as_float(__builtin_amdgcn_readlane(wi, i)) * pv[i];   // partial sums are always finite
+    for (int k0 = PRE; k0 < in; k0 += PRE) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (k0 + i < k_hi) {
-        const float mk = s_w[k0 + i];
-        const float w = mk > -INFINITY ? __expf(mk - M) : 0.f;
-        L += w * s_l[k0 + i];
-        acc += w * pw[i];
-      }
+      for (int i = 0; i < PRE; ++i) pv[i] = k0 + i < in ? P[(size_t)(kb + k0 + i) * RKV_PART_STRIDE + 4 + c] : 0.f;
+#pragma unroll
+      for (int i = 0; i < PRE; ++i) acc += __int_as_float(__builtin_amdgcn_readlane(wi, k0 + i)) * pv[i];
     }
   }
   if constexpr (NGRP > 1) {                                  // group 0 takes the other groups' sums
@@ -392,10 +392,13 @@ void rkv_launch_prep_q(const RkvView& v, const __half* q, const int* q_pos, int 
 }
 void rkv_launch_merge(const RkvView& v, const float* qr, const float* part, int nch, int chunk_tokens, const __half* k_cur,
                       const __half* v_cur, const int* q_lim, int nq, float* out, float* lse, hipStream_t s) {
-  // long contexts: share the chunks among four groups of threads (128 chunks: 9 instead of 17 us;
-  // at 32 chunks the wider workgroups cost more than they save)
-  if (nch > 32) hipLaunchKernelGGL(k_merge<4>, dim3(v.Hq, v.B), dim3(512), 0, s, v, qr, part, nch, chunk_tokens, k_cur, v_cur, q_lim, nq, out, lse);
-  else hipLaunchKernelGGL(k_merge<1>, dim3(v.Hq, v.B), dim3(128), 0, s, v, qr, part, nch, chunk_tokens, k_cur, v_cur, q_lim, nq, out, lse);
+  // groups so that sixteen chunks are one group's, as far as a workgroup's threads go
+#define RKV_MERGE(N_) hipLaunchKernelGGL(k_merge<N_>, dim3(v.Hq, v.B), dim3(128 * N_), 0, s, v, qr, part, nch, chunk_tokens, k_cur, v_cur, q_lim, nq, out, lse)
+  if (nch > 64) RKV_MERGE(8);
+  else if (nch > 32) RKV_MERGE(4);
+  else if (nch > 16) RKV_MERGE(2);
+  else RKV_MERGE(1);
+#undef RKV_MERGE
 }
 
 // the split-K partial results of a launch over Tpad token slots (chunks of 128 tokens at the finest)
