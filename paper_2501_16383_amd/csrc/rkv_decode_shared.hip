@@ -279,7 +279,7 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
   const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
   const v4f centre4 = {q == 0 ? -64.0f * MID : 0.f, 0.f, 0.f, 0.f};   // channel 0 of H_128 of the constant MID / 2
 
-#pragma unroll 1
+#pragma unroll
   for (int ti = 0; ti < 4; ++ti) {
     const int tt = tw + ti * 16;
     if (tt >= len) break;                            // wave-uniform
