@@ -177,23 +177,24 @@ __device__ __forceinline__ float row_transpose_reduce(float (&v)[NV], int n) {
 // (-infinity at retained sink tokens) in place of the key phase - a reorder over the whole token
 // row, whose scores k_scores_row computes; qt then points to that buffer.  Softmax, values and
 // partial results as in the plain kernel.
-template <int G, int REP, bool MULTI, bool META8, int HB, int SUB = 0, bool ALU = false, bool PRE = false>
+template <int G, int REP, bool MULTI, bool META8, int HB, int SUB = 0, bool ALU = false, bool PRE = false, int TILES = MF_TILES>
 __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_decode_mfma(RkvView v, const float* __restrict__ qt,
                                                                        float* __restrict__ part, int nch,
                                                                        const int* __restrict__ q_lim, int nq, int ns, uint32_t inv_ns, uint32_t inv_nrg) {
   constexpr bool HI = HB != 0;
+  constexpr int CH = 64 * TILES;                 // tokens per workgroup (4 waves)
   constexpr int NH = G * REP;                    // query heads served by this workgroup: REP per KV head
   constexpr int RP = (MF_ACC / (G * REP) < 4) ? MF_ACC / (G * REP) : 4;   // tokens (of a lane's four) per pass of the key phase: MF_ACC score accumulators at most
-  __shared__ float s_sc[NH][MF_CH];
+  __shared__ float s_sc[NH][CH];
   // Weight digits of phase S for the matrix products of phase V.  The operand [16 rows = 4 heads x
   // 4 digits][128 = 4 heads x 32 tokens] is block-diagonal over the heads, so only the 32 token
   // bytes of each row are kept, [slab][digit set][row][token], followed by one 16-byte piece of
   // zeros that the lanes holding the operand's empty parts read instead.
   constexpr int SA_ZERO = 16 * 32, SA_SET = SA_ZERO + 16;
   constexpr int NS = SUB ? SUB : 1;              // sub-blocks of a value head (groups of 64 / 32): weights per sub-block
-  constexpr size_t SA_BYTES = (size_t)NS * (MF_CH / 32) * 2 * SA_SET;
+  constexpr size_t SA_BYTES = (size_t)NS * (CH / 32) * 2 * SA_SET;
   __shared__ __attribute__((aligned(16))) uint8_t s_A_raw[SA_BYTES];
-  uint8_t (*const s_A)[MF_CH / 32][2][SA_SET] = reinterpret_cast<uint8_t (*)[MF_CH / 32][2][SA_SET]>(s_A_raw);
+  uint8_t (*const s_A)[CH / 32][2][SA_SET] = reinterpret_cast<uint8_t (*)[CH / 32][2][SA_SET]>(s_A_raw);
   __shared__ float s_m[4], s_l[4], s_zs[NS][4], s_wsc[NS][4];
   __shared__ int s_sink[64];
   __shared__ uint4 s_H[8][64];                   // Hadamard operand tiles
@@ -218,9 +219,10 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
   constexpr bool LM = SUB == 0;
   constexpr int MWL = META8 ? G / 2 : G;             // metadata dwords per token and rotation group as stored
   constexpr int GP = G / 2;                          // packed pairs per token
-  __shared__ __attribute__((aligned(16))) uint32_t s_ks[LM ? MF_CH * GP : 1], s_vm[LM ? MF_CH * G : 1];
+  __shared__ __attribute__((aligned(16))) uint32_t s_ks[LM ? CH * GP : 1], s_vm[LM ? CH * G : 1];
   static_assert(SUB == 0 || PRE, "groups of 64 / 32 run on precomputed scores");
   static_assert(!ALU || (!META8 && HB == 0 && !MULTI), "the arithmetic-only measurement exists for the plain 2-bit variants");
+  static_assert(!PRE || CH == 256, "precomputed scores: a thread per token of the chunk");
   static_assert(!PRE || !ALU, "precomputed scores: no arithmetic-only measurement");
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -257,7 +259,8 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
   if (v.lens) {
     const int tot8 = gridDim.x / ns;
     rrg = blockIdx.x / tot8;
-    const int w = blockIdx.x - rrg * tot8;
+    constexpr int SPLIT = MF_CH / CH;            // (the table counts chunks of MF_CH tokens)
+    const int w_ = blockIdx.x - rrg * tot8, w = w_ / SPLIT;
     if (w >= v.cstart[v.B]) return;
     int lo = 0, hi = v.B;                        // the last sequence whose first chunk is <= w and that has chunks
     while (hi - lo > 1) {
@@ -266,7 +269,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
       else hi = mid;
     }
     b = lo;
-    chunk = w - v.cstart[b];
+    chunk = (w - v.cstart[b]) * SPLIT + w_ % SPLIT;
   } else {
     // One grid dimension.  Workgroups go to the chip's eight compute dies (each with an L2 of its
     // own) in turn, so id % 8 names the die: a die takes every eighth (sequence, rotation group)
@@ -283,8 +286,8 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
     rg = br - b * v.NRG;
   }
   const int len = rkv_len(v, b);
-  if (chunk * MF_CH >= len) return;
-  const int t0 = chunk * MF_CH;
+  if (chunk * CH >= len) return;
+  const int t0 = chunk * CH;
 
   // Everything the workgroup needs before its first tile is requested here, back to back, and put
   // in LDS further down, once - a request that is waited for before the next one goes out costs a
@@ -330,9 +333,11 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
         d[0] = *g;
       }
     };
-    fetch(v.km + mi, ld_mk);
-    fetch(v.vm + mi, ld_mv);
-    ld_cs0 = v.rope[(size_t)(t0 + tid) * 64];
+    if (CH == 256 || tid < CH) {
+      fetch(v.km + mi, ld_mk);
+      fetch(v.vm + mi, ld_mv);
+      ld_cs0 = v.rope[(size_t)(t0 + tid) * 64];
+    }
     // entry (r = 0, p = 0, n = 0) of the prepared queries: floats f % 4 of piece f / 4, f = 2 * head + half
 #pragma unroll
     for (int i = 0; i < NH / 2; ++i) ld_q0[i] = reinterpret_cast<const float4*>(q_src)[i * 16];
@@ -401,7 +406,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
     } else {
     // ------------------------------------------------------------------ phase K
     {
-      const int tw = t0 + wave * (16 * MF_TILES);
+      const int tw = t0 + wave * (16 * TILES);
       float cs_c[4], cs_s[4];
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
@@ -482,12 +487,12 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
       }
       if constexpr (!LM) {                                   // every wave clears its own 64 score slots
     #pragma unroll
-        for (int a = 0; a < NH; ++a) s_sc[a][wave * 64 + lane] = -INFINITY;
+        for (int a = 0; a < NH; ++a) s_sc[a][wave * (16 * TILES) + lane] = -INFINITY;
       }
       if constexpr (MULTI) {
         if (tid < NH) s_lim[tid] = min(ld_lim, len - 1);
       }
-      if constexpr (LM) {                              // thread = token of the chunk (inside the padded allocation)
+      if (LM && (CH == 256 || tid < CH)) {             // thread = token of the chunk (inside the padded allocation)
         // a token's metadata as stored -> packed fp16 pairs (s01, s23) and (z01, z23)
         auto pairs = [&](const uint32_t* src, uint32_t (&sp)[2], uint32_t (&zp)[2]) {
           sp[1] = zp[1] = 0;
@@ -566,12 +571,12 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
       uint32_t sink_tiles = 0;
       for (int i = 0; i < cnt; ++i) {
         const int d = s_sink[i] - tw;
-        if (d >= 0 && d < 16 * MF_TILES) sink_tiles |= 1u << (d >> 4);
+        if (d >= 0 && d < 16 * TILES) sink_tiles |= 1u << (d >> 4);
       }
       sink_tiles = __builtin_amdgcn_readfirstlane(sink_tiles);
 
 #pragma unroll
-      for (int ti = 0; ti < MF_TILES; ++ti) {
+      for (int ti = 0; ti < TILES; ++ti) {
         const int tt = tw + ti * 16;
         if (tt >= len) break;                              // wave-uniform
         v8i A[G];
@@ -596,7 +601,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
         // scale rows of the 4x4 products: (+-s_0, +-s_1, +-s_2, +-s_3) of token 4q + r, signs of H_g row n & 3
         v4h sA[4];
         if constexpr (LM) {
-          const uint32_t* sp = &s_ks[(wave * (16 * MF_TILES) + ti * 16 + 4 * q) * GP];
+          const uint32_t* sp = &s_ks[(wave * (16 * TILES) + ti * 16 + 4 * q) * GP];
           uint32_t sw[4][2];
           if constexpr (G == 4) {
 #pragma unroll
@@ -612,7 +617,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
 #pragma unroll
           for (int r = 0; r < 4; ++r) sA[r] = as_v4h((sw[r][0] ^ sm01) & keep_row, G == 4 ? (sw[r][1] ^ sm23) & keep_row : 0u);
         }
-        if (ti + 1 < MF_TILES) load_tile(ti + 1);          // prefetch (inside the padded allocation)
+        if (ti + 1 < TILES) load_tile(ti + 1);          // prefetch (inside the padded allocation)
 
         // The key phase runs in passes over RP of the lane's four tokens, so that the score
         // accumulators (RP tokens x G heads x REP query heads) stay within 16 registers - more of
@@ -747,9 +752,9 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
     // V metadata of the four tokens this lane turns into weights in phase S (head = wave); requested
     // here and not before the key phase, where four more live registers would mean spills - and
     // with them a scratch allocation, which keeps some shader engines from holding three workgroups
-    uint32_t vmeta[NS][MF_CH / 64];
+    uint32_t vmeta[NS][CH / 64];
 #pragma unroll
-    for (int i = 0; i < MF_CH / 64; ++i) {
+    for (int i = 0; i < CH / 64; ++i) {
       const size_t mi = ((size_t)(b * v.NRG + rg) * v.Tpad + t0 + lane + 64 * i) * (G * NS);
       if constexpr (LM) {
         // (read from LDS in the softmax phase)
@@ -781,15 +786,15 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
     const uint4* vslab = reinterpret_cast<const uint4*>(v.vc + rkv_v_slabbase(v, b, rg, t0 >> 5));
     const uint32_t* vhslab = HI ? v.vh + (rkv_v_slabbase(v, b, rg, t0 >> 5) >> (HB == 1 ? 1 : 0)) : nullptr;
     const int lidx = wave * (16 * G) + (has_head ? lane : 0);
-    const int nslab = min(MF_CH / 32, (len - t0 + 31) >> 5);
+    const int nslab = min(CH / 32, (len - t0 + 31) >> 5);
     // the softmax and value phases run once per query head of a KV head; the V codes are requested
     // again each time (from L2 after the first), which is cheaper than holding them across the loop
 #pragma unroll 1
     for (int rri = 0; rri < REP; ++rri) {
     // all V codes of the chunk (one 16-byte load per lane and slab): in flight while the softmax phase runs
-    uint4 vcodes[MF_CH / 32], vhcodes[HI ? MF_CH / 32 : 1];
+    uint4 vcodes[CH / 32], vhcodes[HI ? CH / 32 : 1];
 #pragma unroll
-    for (int sl = 0; sl < MF_CH / 32; ++sl) {
+    for (int sl = 0; sl < CH / 32; ++sl) {
       // (lanes without a head feed zeros to the products; slabs beyond the chunk's end are never used)
       if constexpr (G < 4) vcodes[sl] = make_uint4(0, 0, 0, 0);
       if constexpr (ALU) {
@@ -813,17 +818,17 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
     // ------------------------------------------------------------------ phase S
     if (wave < G) {
       const int a = wave;
-      float sv[MF_CH / 64], w[MF_CH / 64], zv[MF_CH / 64];
+      float sv[CH / 64], w[CH / 64], zv[CH / 64];
       float m = -INFINITY;
 #pragma unroll
-      for (int i = 0; i < MF_CH / 64; ++i) {
+      for (int i = 0; i < CH / 64; ++i) {
         sv[i] = s_sc[a * REP + rri][lane + 64 * i];
         m = fmaxf(m, sv[i]);
       }
       m = wave_allreduce<true>(m);
-      float pe[MF_CH / 64], l = 0.f;
+      float pe[CH / 64], l = 0.f;
 #pragma unroll
-      for (int i = 0; i < MF_CH / 64; ++i) {
+      for (int i = 0; i < CH / 64; ++i) {
         pe[i] = sv[i] > -INFINITY ? __expf(sv[i] - m) : 0.f;
         l += pe[i];
       }
@@ -832,7 +837,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
       for (int sb = 0; sb < NS; ++sb) {                     // once, or once per sub-block of the head (its own scales and zero-points)
       float wmax = 0.f;
 #pragma unroll
-      for (int i = 0; i < MF_CH / 64; ++i) {
+      for (int i = 0; i < CH / 64; ++i) {
         float s_, z_;
         if constexpr (LM) {                                 // token lane + 64 i, head a
           rkv_unpack_meta(s_vm[(lane + 64 * i) * G + a], s_, z_);
@@ -853,7 +858,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
       const float up = ldexpf(1.0f, 24 - ex), down = ldexpf(1.0f, ex - 24);
       float zs = 0.f;
 #pragma unroll
-      for (int i = 0; i < MF_CH / 64; ++i) {
+      for (int i = 0; i < CH / 64; ++i) {
         const int tl = lane + 64 * i, slab = tl >> 5, tau = tl & 31;
         const uint32_t W = (uint32_t)rintf(w[i] * up);
         zs += (float)W * zv[i];
@@ -896,7 +901,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
 #pragma unroll
       for (int i = 0; i < 2; ++i) acc[i][0] = acc[i][1] = acch[i][0] = acch[i][1] = (v4f){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int sl = 0; sl < MF_CH / 32; ++sl) {
+      for (int sl = 0; sl < CH / 32; ++sl) {
         if (sl < nslab) {                                   // workgroup-uniform
           v8i A[2];
 #pragma unroll
@@ -977,7 +982,7 @@ typedef void (*RkvDecodeFn)(RkvView, const float*, float*, int, const int*, int,
 
 // The variant of the kernel a cache takes.  multi: several query tokens per sequence; share: query
 // heads of a KV head per workgroup (1 or 2); alu: the arithmetic-only measurement.
-static RkvDecodeFn pick_kernel(const rkv_cache* c, bool multi, int share, bool alu) {
+static RkvDecodeFn pick_kernel(const rkv_cache* c, bool multi, int share, bool alu, int chunk) {
   const RkvView& v = c->v;
   // precomputed scores (groups of 64 / 32; a reorder over the whole row): softmax and value phases only
 #define RKV_MF_PRE_M(G_, R_, S_, H_, M_) (v.meta8 ? k_decode_mfma<G_, R_, M_, true, H_, S_, false, true> : k_decode_mfma<G_, R_, M_, false, H_, S_, false, true>)
@@ -1004,24 +1009,32 @@ static RkvDecodeFn pick_kernel(const rkv_cache* c, bool multi, int share, bool a
   return share == 1 ? k_decode_mfma<4, 1, false, false, 0> : k_decode_mfma<4, 2, false, false, 0>;
 #else
   if (alu) return v.g == 4 ? k_decode_mfma<4, 1, false, false, 0, 0, true> : k_decode_mfma<2, 1, false, false, 0, 0, true>;
-#define RKV_MF_PICK(G_, R_, M_)                                                                            \
-  do {                                                                                                     \
-    if (v.hb == 2) return v.meta8 ? k_decode_mfma<G_, R_, M_, true, 2> : k_decode_mfma<G_, R_, M_, false, 2>; \
-    if (v.hb == 1) return v.meta8 ? k_decode_mfma<G_, R_, M_, true, 1> : k_decode_mfma<G_, R_, M_, false, 1>; \
-    return v.meta8 ? k_decode_mfma<G_, R_, M_, true, 0> : k_decode_mfma<G_, R_, M_, false, 0>;               \
-  } while (0)
-  if (multi) {
-    if (v.g == 4 && share == 1) RKV_MF_PICK(4, 1, true);
-    else if (v.g == 4) RKV_MF_PICK(4, 2, true);
-    else if (share == 1) RKV_MF_PICK(2, 1, true);
-    else RKV_MF_PICK(2, 2, true);
-  }
-  if (v.g == 4 && share == 1) RKV_MF_PICK(4, 1, false);
-  else if (v.g == 4) RKV_MF_PICK(4, 2, false);
-  else if (share == 1) RKV_MF_PICK(2, 1, false);
-  else RKV_MF_PICK(2, 2, false);
+#define RKV_MF_PICK_H(G_, H_, T_) (v.meta8 ? k_decode_mfma<G_, 1, false, true, H_, 0, false, false, T_> : k_decode_mfma<G_, 1, false, false, H_, 0, false, false, T_>)
+#define RKV_MF_PICK(G_, T_) (v.hb == 2 ? RKV_MF_PICK_H(G_, 2, T_) : v.hb == 1 ? RKV_MF_PICK_H(G_, 1, T_) : RKV_MF_PICK_H(G_, 0, T_))
+  if (chunk == MF_CH) return v.g == 4 ? RKV_MF_PICK(4, MF_TILES) : RKV_MF_PICK(2, MF_TILES);
+  return v.g == 4 ? RKV_MF_PICK(4, MF_TILES / 2) : RKV_MF_PICK(2, MF_TILES / 2);
+#undef RKV_MF_PICK_H
 #undef RKV_MF_PICK
 #endif
+}
+
+// Chunks of 128 tokens where chunks of 256 are at most three for two compute units: every workgroup is then
+// resident at once either way (three fit a compute unit) and the call takes as long as one workgroup lives - half
+// the tiles in turn, at the price of setting up twice as many.  One sequence x 4096 tokens, 32 heads (128 chunks
+// of 256): 22.3 -> 19.5 us a step; 512 tokens: 18.2 -> 16.2 us.  Where the chip is full the set-up is what counts: 32768 tokens
+// (1024 chunks) 40.7 -> 42.2 us, 16 x 4096 tokens with 40 heads (2560) 76.4 -> 80.0 us.  (The second bound
+// keeps the partial results within what rkv_decode_attention_static has room for.)
+int rkv_mfma_chunk(const rkv_cache* c, int nq) {
+  const RkvView& v = c->v;
+  if (rkv_scores_path(c) || c->decode_path == 3) return MF_CH;
+  const int nch = (v.len + MF_CH - 1) / MF_CH;
+  size_t total = 0;
+  if (c->ragged)
+    for (int b = 0; b < v.B; ++b) total += (c->hlens[b] + MF_CH - 1) / MF_CH;
+  else
+    total = (size_t)v.B * nch;
+  const size_t bytes = rkv_query_scratch_bytes(v.B, (size_t)v.Hq * nq) + (size_t)v.B * v.Hq * nq * 2 * nch * RKV_PART_STRIDE * 4;
+  return 2 * total * v.NRG <= 3 * (size_t)c->n_cu && bytes <= RKV_STATIC_SCRATCH_BYTES / 2 ? MF_CH / 2 : MF_CH;
 }
 
 // nq == 0: the usual step, one query token that attends the whole cache (and, if set, the current
@@ -1057,18 +1070,19 @@ int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int 
   const int share = rkv_mfma_share(c, multi, rep);
   if (!q_prepared) rkv_launch_prep_q(v, q, q_pos, c->cur_k ? 1 : 0, qr, share, nq, s);
   float* qt = qr + (size_t)v.B * v.Hq * RKV_D;              // lane-ordered copy written by k_prep_q
-  const int nch = (v.len + MF_CH - 1) / MF_CH;
+  const int chunk = rkv_mfma_chunk(c, nq), split = MF_CH / chunk;
+  const int nch = (v.len + chunk - 1) / chunk;
   if (share == 0) {
     const bool timed = c->ev_start && c->ev_stop;
     if (nch > 0) {
-      const int rc = rkv_launch_decode_shared(c, v, qr, part, nch, multi ? q_pos : nullptr, nq, timed ? c->ev_start : nullptr,
+      const int rc = rkv_launch_decode_shared(c, v, qr, part, nch, chunk, multi ? q_pos : nullptr, nq, timed ? c->ev_start : nullptr,
                                               timed ? c->ev_stop : nullptr, s);
       if (rc != RKV_OK) return rc;
     } else if (timed) {
       RKV_HIP_CHECK(hipEventRecord(c->ev_start, s));
       RKV_HIP_CHECK(hipEventRecord(c->ev_stop, s));
     }
-    rkv_launch_merge(v, qr, part, nch, MF_CH, c->cur_k, c->cur_v, multi ? q_pos : nullptr, nq, out, lse, s);
+    rkv_launch_merge(v, qr, part, nch, chunk, c->cur_k, c->cur_v, multi ? q_pos : nullptr, nq, out, lse, s);
     return rkv_check_launch();
   }
   const int ns = rep / share;
@@ -1078,7 +1092,7 @@ int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int 
   if (c->ragged) {                                          // all sequences' chunks in one dimension
     int total = 0;
     for (int b = 0; b < v.B; ++b) total += (c->hlens[b] + MF_CH - 1) / MF_CH;
-    grid = dim3(((total + 7) & ~7) * ns, v.NRG, 1);
+    grid = dim3(((total * split + 7) & ~7) * ns, v.NRG, 1);
   }
   if (grid.y > 65535) return RKV_EINVAL;
   if (c->decode_path == 3 && (multi || xb || v.hb || v.meta8 || share != 1)) return RKV_EINVAL;   // arithmetic-only measurement: plain variants
@@ -1095,7 +1109,7 @@ int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int 
     const int rc = rkv_launch_scores_row(c, v, qr, sc, s);
     if (rc != RKV_OK) return rc;
     if (nch > 0)
-      hipLaunchKernelGGL(pick_kernel(c, multi, share, false), grid, dim3(256), 0, s, v, (const float*)sc, part, nch,
+      hipLaunchKernelGGL(pick_kernel(c, multi, share, false, MF_CH), grid, dim3(256), 0, s, v, (const float*)sc, part, nch,
                          multi ? q_pos : (const int*)nullptr, nq, ns, recip(ns), recip(v.NRG));
     if (timed) RKV_HIP_CHECK(hipEventRecord(c->ev_stop, s));
     rkv_launch_merge(v, qr, part, nch, MF_CH, c->cur_k, c->cur_v, multi ? q_pos : nullptr, nq, out, lse, s);
@@ -1103,15 +1117,15 @@ int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int 
   }
   if (nch > 0) {                                            // (an empty cache has only the current token)
     if (timed)
-      hipExtLaunchKernelGGL(pick_kernel(c, multi, share, c->decode_path == 3), grid, dim3(256), 0, s, c->ev_start, c->ev_stop, 0, v,
+      hipExtLaunchKernelGGL(pick_kernel(c, multi, share, c->decode_path == 3, chunk), grid, dim3(256), 0, s, c->ev_start, c->ev_stop, 0, v,
                             qt, part, nch, multi ? q_pos : nullptr, nq, ns, recip(ns), recip(v.NRG));
     else
-      hipLaunchKernelGGL(pick_kernel(c, multi, share, c->decode_path == 3), grid, dim3(256), 0, s, v, qt, part, nch,
+      hipLaunchKernelGGL(pick_kernel(c, multi, share, c->decode_path == 3, chunk), grid, dim3(256), 0, s, v, qt, part, nch,
                          multi ? q_pos : nullptr, nq, ns, recip(ns), recip(v.NRG));
   } else if (timed) {
     RKV_HIP_CHECK(hipEventRecord(c->ev_start, s));
     RKV_HIP_CHECK(hipEventRecord(c->ev_stop, s));
   }
-  rkv_launch_merge(v, qr, part, nch, MF_CH, c->cur_k, c->cur_v, multi ? q_pos : nullptr, nq, out, lse, s);
+  rkv_launch_merge(v, qr, part, nch, chunk, c->cur_k, c->cur_v, multi ? q_pos : nullptr, nq, out, lse, s);
   return rkv_check_launch();
 }

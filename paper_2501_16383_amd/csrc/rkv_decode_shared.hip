@@ -2,11 +2,11 @@
 // tokens per step): plain reorder (inside blocks of 128), rot_heads 2 or 4, codes of 2 to 4 bits in
 // groups of 128, either metadata format, both RoPE pairings.
 //
-// One workgroup = (sequence, rotation group, chunk of 256 tokens, up to 16 CT / G query heads of each of the
+// One workgroup = (sequence, rotation group, chunk of 256 or 128 tokens, up to 32 / G query heads of each of the
 // G KV heads), 4 waves.  Rotation, RoPE and unpacking of a key cost vector instructions per (token,
 // KV head); they are done once for all the query heads, and the product with the queries is a
 // matrix product whose columns are the (query head, KV head) pairs:
-//   phase K  wave w: tokens 64w..64w+63 in tiles of 16.  The operands of the Hadamard product are
+//   phase K  wave w: four (two) tiles of 16 tokens.  The operands of the Hadamard product are
 //            exchanged against k_decode_mfma's, H_128 tile [16 channels x 128] times codes [128 x 16 tokens]:
 //            lane (n, q) then holds channels 16p + 4q + 0..3 and their RoPE partners of token n, which is
 //            the layout the next product (v_mfma_f32_16x16x32_f16: [16 tokens x 32 channels] times
@@ -35,8 +35,6 @@ typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 
-#define SH_CH RKV_MFMA_CHUNK
-static_assert(SH_CH == 256, "four waves of four tiles of 16 tokens");
 
 // four dwords of FP4 nibbles (the other four registers of the operand are not read)
 __device__ __forceinline__ v8i as_fp4(const uint4& u) {
@@ -77,16 +75,17 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// CT: column tiles (16 columns each).  HB: bits per code above the low two (planes as in k_decode_mfma).
+// CT: column tiles (16 columns each), of which rs query heads per KV head are used.  TILES: tiles per wave.  HB: bits per code above the low two (planes as in k_decode_mfma).
 // q_lim: null, or the last position each of the nq query tokens may attend (v.Hq then counts virtual heads).
-template <int G, int CT, int HB>
+template <int G, int CT, int HB, int TILES>
 __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_shared(RkvView v, const float* __restrict__ qr,
                                                                                      float* __restrict__ part, int nch,
-                                                                                     const int* __restrict__ q_lim, int nq, int ns,
+                                                                                     const int* __restrict__ q_lim, int nq, int ns, int rs,
                                                                                      uint32_t inv_ns, uint32_t inv_nrg) {
   constexpr bool HI = HB != 0;
-  constexpr int NC = 16 * CT, RS = NC / G;           // columns; query heads per KV head
-  constexpr int SC_STRIDE = SH_CH + 4;               // (rows of sixteen columns fall on different LDS banks)
+  constexpr int CH = 64 * TILES;                     // tokens
+  constexpr int NC = 16 * CT;                        // columns
+  constexpr int SC_STRIDE = CH + 4;               // (rows of sixteen columns fall on different LDS banks)
   constexpr int QSTRIDE = NC + 1;                    // 16-byte pieces per row of the query operand
   constexpr int GP = G / 2;                          // packed fp16 pairs per token
   constexpr int DROW = 144, DSET1 = 16 * DROW, DWAVE = 24 * DROW;   // weight digits of a wave: 16 rows of set 0, 8 of set 1, 128 tokens each
@@ -94,9 +93,9 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
   struct KeyPart {
     uint4 H[8][64];
     uint4 q[32][QSTRIDE];                            // [(p, high / low, lane group)][column]
-    float ks[G][SH_CH];                              // scales of the chunk's tokens
-    float kz[G][SH_CH];                              // their zero-points' share: sum_blk H_g[a][blk] scale_blk (zero_blk - MID)
-    float2 cs0[SH_CH];                               // RoPE angle of channel pair 0
+    float ks[G][CH];                              // scales of the chunk's tokens
+    float kz[G][CH];                              // their zero-points' share: sum_blk H_g[a][blk] scale_blk (zero_blk - MID)
+    float2 cs0[CH];                               // RoPE angle of channel pair 0
     float2 step[64];                                 // RoPE rotation by 16 positions
   };
   union Shared {
@@ -105,7 +104,7 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
   };
   __shared__ __attribute__((aligned(16))) Shared sh;
   __shared__ __attribute__((aligned(16))) float s_sc[NC][SC_STRIDE];
-  __shared__ __attribute__((aligned(16))) uint32_t s_vm[G][SH_CH];   // values: (scale, zero-point) pairs
+  __shared__ __attribute__((aligned(16))) uint32_t s_vm[G][CH];   // values: (scale, zero-point) pairs
   __shared__ int s_sink[64];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -119,7 +118,8 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
   if (v.lens) {
     const int tot8 = gridDim.x / ns;
     rrg = blockIdx.x / tot8;
-    const int w = blockIdx.x - rrg * tot8;
+    constexpr int SPLIT = RKV_MFMA_CHUNK / CH;       // (the table counts chunks of 256 tokens)
+    const int w_ = blockIdx.x - rrg * tot8, w = w_ / SPLIT;
     if (w >= v.cstart[v.B]) return;
     int lo = 0, hi = v.B;
     while (hi - lo > 1) {
@@ -128,7 +128,7 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
       else hi = mid;
     }
     b = lo;
-    chunk = w - v.cstart[b];
+    chunk = (w - v.cstart[b]) * SPLIT + w_ % SPLIT;
   } else {
     const int xcd = blockIdx.x & 7, rem = blockIdx.x >> 3;
     chunk = inv_ns ? (int)__umulhi((uint32_t)rem, inv_ns) : rem;
@@ -139,11 +139,11 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
     rg = br - b * v.NRG;
   }
   const int len = rkv_len(v, b);
-  if (chunk * SH_CH >= len) return;
-  const int t0 = chunk * SH_CH;
-  const int rsv = min(RS, rep - rrg * RS);           // query heads per KV head that exist
+  if (chunk * CH >= len) return;
+  const int t0 = chunk * CH;
+  const int rsv = min(rs, rep - rrg * rs);           // query heads per KV head that exist
   // virtual head of column col = rr * G + a
-  auto head_of = [&](int col) { return (rg * G + col % G) * rep + rrg * RS + col / G; };
+  auto head_of = [&](int col) { return (rg * G + col % G) * rep + rrg * rs + col / G; };
 
   // ---- requests, back to back
   const size_t nqh = (size_t)v.B * v.Hq;
@@ -156,14 +156,14 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
     const int col = 8 * i + (tid >> 5);
     ld_q[i] = col / G < rsv ? qimg[(size_t)head_of(col) * 32 + (tid & 31)] : make_uint4(0, 0, 0, 0);
   }
-  const float2 ld_step = v.rope[16 * 64 + (tid & 63)], ld_cs0 = v.rope[(size_t)(t0 + tid) * 64];
+  const float2 ld_step = v.rope[16 * 64 + (tid & 63)], ld_cs0 = v.rope[(size_t)(t0 + min(tid, CH - 1)) * 64];
   const int cnt = v.max_sinks > 0 ? v.sink_cnt[b] : 0;
   const int ld_spos = (v.max_sinks > 0 && (tid & 63) < v.max_sinks) ? v.sink_pos[b * v.max_sinks + (tid & 63)] : -1;
   float ks_[4], kz_[4];
   uint32_t vmw[4] = {0, 0, 0, 0};
   if (v.meta8) {
     // G scale bytes, then G zero-point bytes (z + 128) per token
-    const size_t mi = ((size_t)(b * v.NRG + rg) * v.Tpad + t0 + tid) * (2 * G);
+    const size_t mi = ((size_t)(b * v.NRG + rg) * v.Tpad + t0 + min(tid, CH - 1)) * (2 * G);
     auto fetch8 = [&](const uint32_t* m, float (&s)[4], float (&z)[4]) {
       const uint8_t* p8 = reinterpret_cast<const uint8_t*>(m) + mi;
       uint32_t sw, zw;
@@ -187,7 +187,7 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
 #pragma unroll
     for (int i = 0; i < G; ++i) vmw[i] = rkv_pack_meta(s[i], z[i]);
   } else {
-    const size_t mi = ((size_t)(b * v.NRG + rg) * v.Tpad + t0 + tid) * G;
+    const size_t mi = ((size_t)(b * v.NRG + rg) * v.Tpad + t0 + min(tid, CH - 1)) * G;
     uint32_t km[4] = {0, 0, 0, 0};
     if constexpr (G == 4) {
       const uint4 u = rkv_ld_stream(reinterpret_cast<const uint4*>(v.km + mi));
@@ -217,9 +217,9 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
     c_w0[ct] = 64.0f * lane_scale * qn[0];
     c_w1[ct] = 64.0f * lane_scale * qn[v.rope_style ? 1 : 64];
     c_lim[ct] = len - 1;
-    if (q_lim) c_lim[ct] = min(c_lim[ct], q_lim[b * nq + (ok ? (rrg * RS + col / G) / (rep / nq) : 0)]);
+    if (q_lim) c_lim[ct] = min(c_lim[ct], q_lim[b * nq + (ok ? (rrg * rs + col / G) / (rep / nq) : 0)]);
   }
-  const int tw = t0 + wave * 64;
+  const int tw = t0 + wave * (16 * TILES);
   float cc[4][4], ss[4][4];                          // RoPE angles of token n (of the tile), pairs 16 p + 4 q + r
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
@@ -251,21 +251,23 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
   (&sh.k.H[0][0])[tid + 256] = ld_h1;
 #pragma unroll
   for (int i = 0; i < 2 * CT; ++i) sh.k.q[tid & 31][8 * i + (tid >> 5)] = ld_q[i];
-  sh.k.cs0[tid] = ld_cs0;
   if (tid < 64) {
     sh.k.step[tid] = ld_step;
     s_sink[tid] = tid < cnt ? ld_spos : -1;
   }
+  if (tid < CH) {                                    // thread = token of the chunk
+    sh.k.cs0[tid] = ld_cs0;
 #pragma unroll
-  for (int a = 0; a < G; ++a) {
-    float Z = 0.f;
+    for (int a = 0; a < G; ++a) {
+      float Z = 0.f;
 #pragma unroll
-    for (int i = 0; i < G; ++i) Z = fmaf((__popc(a & i) & 1) ? -ks_[i] : ks_[i], kz_[i] - MID, Z);
-    sh.k.ks[a][tid] = ks_[a];
-    sh.k.kz[a][tid] = Z;
+      for (int i = 0; i < G; ++i) Z = fmaf((__popc(a & i) & 1) ? -ks_[i] : ks_[i], kz_[i] - MID, Z);
+      sh.k.ks[a][tid] = ks_[a];
+      sh.k.kz[a][tid] = Z;
+    }
+#pragma unroll
+    for (int i = 0; i < G; ++i) s_vm[i][tid] = vmw[i];
   }
-#pragma unroll
-  for (int i = 0; i < G; ++i) s_vm[i][tid] = vmw[i];
   __syncthreads();
   __builtin_amdgcn_s_setprio(0);
 
@@ -273,14 +275,14 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
   uint32_t sink_tiles = 0;                           // the wave's tiles that hold a retained sink token
   for (int i = 0; i < cnt; ++i) {
     const int d = s_sink[i] - tw;
-    if (d >= 0 && d < 64) sink_tiles |= 1u << (d >> 4);
+    if (d >= 0 && d < 16 * TILES) sink_tiles |= 1u << (d >> 4);
   }
   sink_tiles = __builtin_amdgcn_readfirstlane(sink_tiles);
   const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
   const v4f centre4 = {q == 0 ? -64.0f * MID : 0.f, 0.f, 0.f, 0.f};   // channel 0 of H_128 of the constant MID / 2
 
 #pragma unroll
-  for (int ti = 0; ti < 4; ++ti) {
+  for (int ti = 0; ti < TILES; ++ti) {
     const int tt = tw + ti * 16;
     if (tt >= len) break;                            // wave-uniform
     v8i A[G], Ah[HI ? G : 1];
@@ -296,7 +298,7 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
         Ah[2 * pr + 1] = unpack_fp4_bits(cwh[pr].y);
       }
     }
-    if (ti + 1 < 4) load_tile(ti + 1);               // prefetch (inside the padded allocation)
+    if (ti + 1 < TILES) load_tile(ti + 1);               // prefetch (inside the padded allocation)
     v4f d[G][CT];
 #pragma unroll
     for (int blk = 0; blk < G; ++blk)
@@ -357,7 +359,7 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
       }
     }
     // scales, butterfly and zero-points of tokens 4q + r; this lane's columns all belong to KV head a = n % G
-    const int tl = wave * 64 + ti * 16 + 4 * q;
+    const int tl = wave * (16 * TILES) + ti * 16 + 4 * q;
     float s_[G][4], sc[4][CT];
 #pragma unroll
     for (int blk = 0; blk < G; ++blk) {
@@ -397,13 +399,14 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
   // ------------------------------------------------------------------ phases S and V
   // wave -> KV head a, channel tiles: all eight (G = 4), or one half of them (G = 2)
   constexpr int NB = G == 4 ? 4 : 2;                 // blocks of 32 channels per wave
+  constexpr int NQ = CH / 128;                       // contractions of 128 tokens
   const int a = wave & (G - 1), wb = G == 4 ? 0 : (wave >> 1) * 2;
-  const int nslab = min(SH_CH / 32, (len - t0 + 31) >> 5);
+  const int nslab = min(CH / 32, (len - t0 + 31) >> 5);
   const uint4* vslab = reinterpret_cast<const uint4*>(v.vc + rkv_v_slabbase(v, b, rg, t0 >> 5));
   const uint32_t* vhslab = HI ? v.vh + (rkv_v_slabbase(v, b, rg, t0 >> 5) >> (HB == 1 ? 1 : 0)) : nullptr;
-  uint4 vcodes[2][NB], vhcodes[HI ? 2 : 1][HI ? NB : 1];
+  uint4 vcodes[NQ][NB], vhcodes[HI ? NQ : 1][HI ? NB : 1];
 #pragma unroll
-  for (int s = 0; s < 2; ++s)
+  for (int s = 0; s < NQ; ++s)
 #pragma unroll
     for (int w = 0; w < NB; ++w) {
       // lane group q holds slab 4 s + q: 32 of the 128 tokens of a contraction
@@ -426,10 +429,11 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
   __syncthreads();                                   // all scores are there; the key phase's part of LDS is free
 
   uint8_t* const dig = sh.dig[wave];
-  const int left = len - t0 - 4 * lane;              // of the lane's tokens 4 lane .. + 3: how many exist
+  const int tq = CH == 256 ? 4 * lane : min(4 * lane, CH - 4);   // the lane's tokens 4 lane .. + 3, inside the chunk
+  const int left = min(CH, len - t0) - 4 * lane;     // how many of them exist
   float vs[4], vz[4];
   {
-    const uint4 m4 = *reinterpret_cast<const uint4*>(&s_vm[a][4 * lane]);
+    const uint4 m4 = *reinterpret_cast<const uint4*>(&s_vm[a][tq]);
     rkv_unpack_meta(m4.x, vs[0], vz[0]);
     rkv_unpack_meta(m4.y, vs[1], vz[1]);
     rkv_unpack_meta(m4.z, vs[2], vz[2]);
@@ -448,7 +452,7 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
       for (int k = 0; k < 6; ++k) dg[qq][k] = 0;
       const int rr = 4 * g + qq;
       if (rr < rsv) {                                // wave-uniform
-        const float4 s4 = *reinterpret_cast<const float4*>(&s_sc[rr * G + a][4 * lane]);
+        const float4 s4 = *reinterpret_cast<const float4*>(&s_sc[rr * G + a][tq]);
         const float sv[4] = {left > 0 ? s4.x : -INFINITY, left > 1 ? s4.y : -INFINITY, left > 2 ? s4.z : -INFINITY, left > 3 ? s4.w : -INFINITY};
         const float m = wave_allreduce<true>(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])));
         float pe[4], w[4];
@@ -490,7 +494,7 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
 #pragma unroll
     for (int i = 0; i < 2 * NB; ++i) acc[i][0] = acc[i][1] = zero4;
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
+    for (int s = 0; s < NQ; ++s) {
       if (4 * s < nslab) {                           // workgroup-uniform
         wave_lds_fence();                            // (the digits of the tokens before have been read)
         if ((lane >> 5) == s) {
@@ -556,25 +560,35 @@ bool rkv_shared_decode(const rkv_cache* c, bool multi) {
   return c->decode_path != 3 && !rkv_scores_path(c) && (multi || c->v.Hq > c->v.Hkv);
 }
 
-// v, nq: the (virtual) view of rkv_launch_decode_mfma
-int rkv_launch_decode_shared(const rkv_cache* c, const RkvView& v, const float* qr, float* part, int nch, const int* q_lim, int nq,
+// v, nq: the (virtual) view of rkv_launch_decode_mfma; chunk: 256 or 128 tokens per workgroup
+int rkv_launch_decode_shared(const rkv_cache* c, const RkvView& v, const float* qr, float* part, int nch, int chunk, const int* q_lim, int nq,
                              hipEvent_t ev_start, hipEvent_t ev_stop, hipStream_t s) {
+  // Query heads per KV head and workgroup: as many as 32 columns take; fewer where the workgroups would leave
+  // compute units idle (keys are then rotated again by other workgroups, but each has fewer query heads to
+  // go through one after the other)
   const int rep = v.Hq / v.Hkv;
-  const int ct = rep * v.g <= 16 ? 1 : 2, rs = 16 * ct / v.g, ns = (rep + rs - 1) / rs;
+  size_t total = (size_t)v.B * ((v.len + RKV_MFMA_CHUNK - 1) / RKV_MFMA_CHUNK);
+  if (c->ragged) {
+    total = 0;
+    for (int b = 0; b < v.B; ++b) total += (c->hlens[b] + RKV_MFMA_CHUNK - 1) / RKV_MFMA_CHUNK;
+  }
+  const int split = RKV_MFMA_CHUNK / chunk;
+  int rs = rep < 32 / v.g ? rep : 32 / v.g;
+  auto groups = [&]() { return (rep + rs - 1) / rs; };
+  while (rs > 4 && total * split * v.NRG * groups() <= (size_t)c->n_cu) rs = rs > 8 ? 8 : 4;
+  const int ns = groups(), ct = rs * v.g <= 16 ? 1 : 2;
   auto recip = [](int d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };
   dim3 grid(8 * nch * ns, (v.B * v.NRG + 7) / 8, 1);
-  if (c->ragged) {
-    int total = 0;
-    for (int b = 0; b < v.B; ++b) total += (c->hlens[b] + SH_CH - 1) / SH_CH;
-    grid = dim3(((total + 7) & ~7) * ns, v.NRG, 1);
-  }
+  if (c->ragged) grid = dim3((((unsigned)total * split + 7) & ~7u) * ns, v.NRG, 1);
   if (grid.y > 65535) return RKV_EINVAL;
-#define RKV_SH(G_, C_) (v.hb == 2 ? k_decode_shared<G_, C_, 2> : v.hb == 1 ? k_decode_shared<G_, C_, 1> : k_decode_shared<G_, C_, 0>)
-  auto fn = v.g == 4 ? (ct == 1 ? RKV_SH(4, 1) : RKV_SH(4, 2)) : (ct == 1 ? RKV_SH(2, 1) : RKV_SH(2, 2));
+#define RKV_SH(G_, C_, T_) (v.hb == 2 ? k_decode_shared<G_, C_, 2, T_> : v.hb == 1 ? k_decode_shared<G_, C_, 1, T_> : k_decode_shared<G_, C_, 0, T_>)
+#define RKV_SH_C(G_, T_) (ct == 1 ? RKV_SH(G_, 1, T_) : RKV_SH(G_, 2, T_))
+  auto fn = split == 1 ? (v.g == 4 ? RKV_SH_C(4, 4) : RKV_SH_C(2, 4)) : (v.g == 4 ? RKV_SH_C(4, 2) : RKV_SH_C(2, 2));
+#undef RKV_SH_C
 #undef RKV_SH
   if (ev_start && ev_stop)
-    hipExtLaunchKernelGGL(fn, grid, dim3(256), 0, s, ev_start, ev_stop, 0, v, qr, part, nch, q_lim, nq, ns, recip(ns), recip(v.NRG));
+    hipExtLaunchKernelGGL(fn, grid, dim3(256), 0, s, ev_start, ev_stop, 0, v, qr, part, nch, q_lim, nq, ns, rs, recip(ns), recip(v.NRG));
   else
-    hipLaunchKernelGGL(fn, grid, dim3(256), 0, s, v, qr, part, nch, q_lim, nq, ns, recip(ns), recip(v.NRG));
+    hipLaunchKernelGGL(fn, grid, dim3(256), 0, s, v, qr, part, nch, q_lim, nq, ns, rs, recip(ns), recip(v.NRG));
   return RKV_OK;
 }

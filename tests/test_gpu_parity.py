@@ -824,6 +824,38 @@ def test_tiny_caches(T, sinks):
     full_check(w, cfg, T, sink_positions=sinks, paths=(1, 2))
 
 
+@pytest.mark.parametrize("T,g,hq,bits,fmt", [(127, 4, 4, 2, 0), (128, 2, 4, 2, 1), (129, 4, 4, 4, 0), (255, 2, 4, 3, 0), (257, 4, 4, 2, 1),
+                                             (385, 2, 4, 2, 0), (129, 4, 8, 3, 1), (127, 2, 8, 4, 0), (385, 4, 12, 2, 0)])
+def test_chunk_edges_of_small_grids(T, g, hq, bits, fmt):
+    """A call that does not fill the chip goes through the cache in chunks of 128 tokens: one short of a chunk,
+    exactly one, one over, two and three of them; one query head per KV head and several."""
+    w = small("cfg1", n_q_heads=hq, n_kv_heads=4)
+    cfg = R.RkvConfig(batch=2, n_q_heads=hq, n_kv_heads=4, max_tokens=T, max_sinks=2, rot_heads=g, bits=bits, meta_format=fmt)
+    full_check(w, cfg, T, paths=(2,), sink_positions=[0] if T & 1 else [])
+
+
+@pytest.mark.parametrize("hq,hkv,g,nq,style,batch,T", [
+    (4, 4, 4, 1, 0, 2, 293), (8, 4, 4, 2, 1, 2, 293), (16, 4, 4, 1, 0, 2, 293), (20, 4, 4, 1, 0, 2, 293), (12, 4, 4, 3, 1, 2, 293),
+    (32, 4, 2, 1, 0, 2, 293), (12, 4, 2, 3, 0, 2, 293), (20, 4, 2, 4, 0, 2, 293), (12, 4, 2, 7, 0, 2, 293), (8, 4, 4, 8, 0, 2, 293),
+    (20, 4, 4, 2, 0, 140, 21), (24, 8, 2, 6, 1, 104, 18), (16, 8, 2, 2, 0, 104, 18)])
+def test_query_heads_per_kv_head_fill_the_columns(hq, hkv, g, nq, style, batch, T):
+    """Several query heads per KV head (or query tokens) are the columns of one product: fewer than sixteen,
+    exactly sixteen and thirty-two, a few over each (a second workgroup with a remainder); with two sequences,
+    where few heads go to a workgroup and chunks are short, and with so many that both are at their largest."""
+    w = small("cfg1", n_q_heads=hq, n_kv_heads=hkv)
+    cfg = R.RkvConfig(batch=batch, n_q_heads=hq, n_kv_heads=hkv, max_tokens=300, max_sinks=2, rot_heads=g, rope_style=style)
+    cache, oc, _ = build_pair(w, cfg, T, sink_positions=[1] if hq < 20 else [])
+    oc_g = oracle_from_export(oc, P.export_numpy(cache))
+    q = np.stack([S.make_q(w, batch=batch, step=i) for i in range(nq)], axis=1)
+    q[:, :, -1] *= 1e-3                                        # (operands are scaled per head: one far smaller than the others)
+    q_pos = np.stack([np.arange(T - nq, T), np.linspace(3, T + 9, nq).astype(int)] * (batch // 2)).astype(np.int32)
+    out, lse = cache.decode_attention_multi(P.gpu(q), P.gpu(q_pos), want_lse=True)
+    torch.cuda.synchronize()
+    ref, lse_ref = O.decode_attention_multi(oc_g, q, q_pos)
+    assert P.attention_error(out.cpu().numpy().astype(np.float64), ref) <= ATT_TOL
+    assert float(np.abs(lse.cpu().numpy() - lse_ref).max()) <= LSE_TOL
+
+
 def test_cache_filled_to_capacity_and_many_sinks():
     """A capacity that is no multiple of any tile size, filled exactly; the maximum number of sink
     rows (64), spread over the sequence; one more token must be refused without changing the cache."""
@@ -1289,8 +1321,7 @@ def test_one_call_decode_step_equals_the_two_calls(hq, hkv, g, ragged, bits):
 
 @pytest.mark.parametrize("hq,hkv,g,fmt", [(24, 8, 4, 0), (32, 4, 4, 1), (8, 4, 2, 0), (12, 4, 2, 1)])
 def test_gqa_ratios_and_metadata_formats(hq, hkv, g, fmt):
-    """Query heads per KV head of 3 (one per workgroup), 8 (four workgroups of two per KV head) and
-    2, with rotation over 4 and over 2 heads, in both metadata formats; both decode kernels."""
+    """Query heads per KV head of 3, 8 and 2, with rotation over 4 and over 2 heads, in both metadata formats; both decode kernels."""
     w = small("cfg4", n_q_heads=hq, n_kv_heads=hkv)
     cfg = R.RkvConfig(batch=2, n_q_heads=hq, n_kv_heads=hkv, max_tokens=600, max_sinks=4, rot_heads=g, meta_format=fmt,
                       rope_theta=500000.0)
