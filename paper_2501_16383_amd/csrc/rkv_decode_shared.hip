@@ -439,7 +439,7 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
     rkv_unpack_meta(m4.z, vs[2], vz[2]);
     rkv_unpack_meta(m4.w, vs[3], vz[3]);
   }
-  const int groups = (rsv + 3) >> 2;
+  const int groups = NC / G <= 4 ? 1 : (rsv + 3) >> 2;   // (no loop, and no registers kept for one, where four heads are all there can be)
 #pragma unroll 1
   for (int g = 0; g < groups; ++g) {
     float hm[4], hl[4], hzs[4], hdown[4];
