@@ -17,8 +17,8 @@
 // internal accumulation is exact (with weights of mixed magnitude in one dot product it is not:
 // small terms are cut ~2^-14 below the largest); zero-points enter as one scalar per head.
 //
-// One workgroup = (sequence, rotation group, chunk of 256 tokens), 4 waves.
-//   phase K  wave w: tokens 64w..64w+63 in tiles of 16.  A = codes [16 tokens x 128], B = H_128 tile
+// One workgroup = (sequence, rotation group, chunk of 256 or 128 tokens), 4 waves.
+//   phase K  wave w: four or two tiles of 16 tokens.  A = codes [16 tokens x 128], B = H_128 tile
 //            [128 x 16 channels]; lane (n, q) of the result holds channel 16*tile + n of tokens
 //            4q..4q+3.  Scores are reduced over the 16 channel lanes with DPP and go to LDS.
 //   phase S  wave a: softmax statistics of head a over the chunk, weights -> FP8 digits in LDS.
@@ -26,9 +26,9 @@
 //            tokens)], block-diagonal over heads, B = codes [(4 heads x 32 tokens) x 16 channels].
 // Covers: reorder that keeps 128-blocks, rot_heads 2 or 4, codes of 2 to 4 bits in groups of 128;
 // both RoPE pairings (the Hadamard operand tiles are built so that tiles p and p + 4 yield the two
-// channels of a pair).  With GQA (or several query tokens per step) a workgroup serves two of the query heads
-// that share a KV head: unpacking, rotation and RoPE of the keys are done once for them, the
-// softmax and value phases once per query head.  Everything else takes the general kernel.
+// channels of a pair); one query head per KV head.  Several of them, or several query tokens per step, are
+// k_decode_shared's; here the variants on precomputed scores (PRE) take them.  Everything else takes the
+// general kernel.
 #include "rkv_internal.h"
 #include "rkv_mfma_ops.h"
 #include <cstdlib>
@@ -199,8 +199,6 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
   __shared__ int s_sink[64];
   __shared__ uint4 s_H[8][64];                   // Hadamard operand tiles
   __shared__ float2 s_step[64];                  // RoPE rotation by 16 positions, per channel pair
-  __shared__ float2 s_step1[REP > 1 ? 64 : 1];   // ... by one position (several query heads per KV head)
-  __shared__ int s_lim[MULTI ? NH : 1];          // last position each served query head may attend
   constexpr int QV = REP == 1 ? 4 : 1;            // query versions held (positions pos - r); with REP > 1 only r = 0
   __shared__ uint4 s_q[QV][4][NH / 2][16];        // [r][p][f / 4][n] x 4 floats f % 4, f = (KV head * REP + query head of it) * 2 + (lo, hi)
   // Metadata of the chunk's keys and values (plain variants): fetched once, at the start, token by
@@ -223,6 +221,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
   static_assert(SUB == 0 || PRE, "groups of 64 / 32 run on precomputed scores");
   static_assert(!ALU || (!META8 && HB == 0 && !MULTI), "the arithmetic-only measurement exists for the plain 2-bit variants");
   static_assert(!PRE || CH == 256, "precomputed scores: a thread per token of the chunk");
+  static_assert(PRE || (REP == 1 && !MULTI), "the key phase serves one query head per KV head");
   static_assert(!PRE || !ALU, "precomputed scores: no arithmetic-only measurement");
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -302,15 +301,10 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
   uint4 ld_q[QN];
 #pragma unroll
   for (int i = 0; i < QN; ++i) ld_q[i] = tid + 256 * i < Q16 ? q_src[tid + 256 * i] : make_uint4(0, 0, 0, 0);
-  //  - RoPE angles are kept for the first of a lane's four tokens only.  With one query head per KV
-  //    head they rotate all four keys and the query comes rotated back by 0..3 positions to make up
-  //    for it (k_prep_q); with several (REP > 1: the extra query copies would not fit the register
-  //    budget) the other three tokens follow by rotating one position at a time (table row 1).  The
-  //    next tile follows by rotating 16 positions (table row 16; used once per tile, read from LDS)
-  const float2 ld_step = v.rope[(REP == 1 ? 16 : 12) * 64 + (tid & 63)];
-  //    (the one-position rotation: table row 1, kept in LDS as well - eight registers less where they are scarce)
-  float2 ld_step1 = make_float2(0.f, 0.f);
-  if constexpr (REP > 1) ld_step1 = v.rope[64 + (tid & 63)];
+  //  - RoPE angles are kept for the first of a lane's four tokens only: they rotate all four keys and the query
+  //    comes rotated back by 0..3 positions to make up for it (k_prep_q).  The next tile follows by
+  //    rotating 16 positions (table row 16; used once per tile, read from LDS)
+  const float2 ld_step = v.rope[16 * 64 + (tid & 63)];
   //  - the sink list: positions unconditionally (the store holds max_sinks of them, unused ones -1), masked by the count below
   const int ld_cnt = v.max_sinks > 0 ? v.sink_cnt[b] : 0;
   const int ld_spos = (v.max_sinks > 0 && (tid & 63) < v.max_sinks) ? v.sink_pos[b * v.max_sinks + (tid & 63)] : -1;
@@ -343,11 +337,8 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
     for (int i = 0; i < NH / 2; ++i) ld_q0[i] = reinterpret_cast<const float4*>(q_src)[i * 16];
   }
   //  - the RoPE angles of this lane's first token and the first key tile: in the key phase below
-  int ld_lim = 0;
-  if constexpr (MULTI) {
-    // served head a * REP + rri is virtual head rrg * REP + rri of its KV head: query token (that / heads per token)
-    ld_lim = q_lim[b * nq + (rrg * REP + (tid < NH ? tid : 0) % REP) / (rep / nq)];
-  }
+  [[maybe_unused]] int per_query = 1;            // query heads of a KV head per query token
+  if constexpr (MULTI) per_query = rep / nq;
 
   const int cnt = ld_cnt;
   {
@@ -390,7 +381,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
           const int qh = (rg * G + a) * rep + rrg * REP + rri;
           bool seen = t0 + tid < len;
           // (several query tokens: virtual head rrg * REP + rri of its KV head belongs to query token (that / heads per token))
-          if constexpr (MULTI) seen = seen && t0 + tid <= q_lim[b * nq + (rrg * REP + rri) / (rep / nq)];
+          if constexpr (MULTI) seen = seen && t0 + tid <= q_lim[b * nq + (rrg * REP + rri) / per_query];
           pre[a * REP + rri] = seen ? qt[((size_t)b * v.Hq + qh) * v.Tpad + t0 + tid] : -INFINITY;
         }
       uint4* a4 = reinterpret_cast<uint4*>(s_A_raw);
@@ -417,11 +408,8 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
       const uint4* ktiles = reinterpret_cast<const uint4*>(v.kc + rkv_k_tilebase(v, b, rg, tw >> 4));
       // the plane above the low two bits: 16 bytes per lane and pair of blocks (HB = 2) or 8 (HB = 1)
       const uint32_t* khtiles = HI ? v.kh + (rkv_k_tilebase(v, b, rg, tw >> 4) >> (HB == 1 ? 1 : 0)) : nullptr;
-      const uint32_t* kmeta = v.km + ((size_t)(b * v.NRG + rg) * v.Tpad + tw) * (META8 ? G / 2 : G);
 
       uint4 cw[G / 2], cwh[HI ? G / 2 : 1];
-      constexpr int MW = META8 ? G / 2 : G;              // metadata dwords per token and rotation group
-      uint32_t mw[4][MW];
       auto load_tile = [&](int ti) {
         if constexpr (ALU) {                                 // made-up codes
           const uint32_t x = (uint32_t)lane * 2654435761u ^ (uint32_t)(nq + ti);
@@ -442,32 +430,6 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
             }
           }
         }
-        if constexpr (LM) {
-          // (plain variants: the chunk's metadata are in LDS)
-        } else if constexpr (META8) {
-          // the lane's four tokens are consecutive: 4 x 2G bytes in one piece
-          const uint4* mp = reinterpret_cast<const uint4*>(kmeta + (size_t)(ti * 16 + 4 * q) * MW);
-          const uint4 u0 = rkv_ld_stream(mp);
-          if constexpr (G == 4) {
-            const uint4 u1 = rkv_ld_stream(mp + 1);
-            mw[0][0] = u0.x; mw[0][1] = u0.y; mw[1][0] = u0.z; mw[1][1] = u0.w;
-            mw[2][0] = u1.x; mw[2][1] = u1.y; mw[3][0] = u1.z; mw[3][1] = u1.w;
-          } else {
-            mw[0][0] = u0.x; mw[1][0] = u0.y; mw[2][0] = u0.z; mw[3][0] = u0.w;
-          }
-        } else {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const uint32_t* mp = kmeta + (size_t)(ti * 16 + 4 * q + r) * G;
-            if constexpr (G == 4) {
-              const uint4 u = rkv_ld_stream(reinterpret_cast<const uint4*>(mp));
-              mw[r][0] = u.x; mw[r][1] = u.y; mw[r][2] = u.z; mw[r][3] = u.w;
-            } else {
-              const uint2 u = rkv_ld_stream(reinterpret_cast<const uint2*>(mp));
-              mw[r][0] = u.x; mw[r][1] = u.y;
-            }
-          }
-        }
       };
       load_tile(0);
       // (the requests are all out: what came back goes to LDS)
@@ -482,15 +444,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
       if (tid + 256 * i < Q16) (&s_q[0][0][0][0])[tid + 256 * i] = ld_q[i];
       if (tid < 64) {
         s_step[tid] = ld_step;
-        if constexpr (REP > 1) s_step1[tid] = ld_step1;
         s_sink[tid] = tid < cnt ? ld_spos : -1;              // complete after the barrier that precedes the key phase
-      }
-      if constexpr (!LM) {                                   // every wave clears its own 64 score slots
-    #pragma unroll
-        for (int a = 0; a < NH; ++a) s_sc[a][wave * (16 * TILES) + lane] = -INFINITY;
-      }
-      if constexpr (MULTI) {
-        if (tid < NH) s_lim[tid] = min(ld_lim, len - 1);
       }
       if (LM && (CH == 256 || tid < CH)) {             // thread = token of the chunk (inside the padded allocation)
         // a token's metadata as stored -> packed fp16 pairs (s01, s23) and (z01, z23)
@@ -659,7 +613,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
               }
             }
           }
-          float c = cs_c[p], s = cs_s[p];                      // angles of the pass's first token (REP == 1: of token 4q)
+          const float c = cs_c[p], s = cs_s[p];                // angles of token 4q
 #pragma unroll
           for (int rr = 0; rr < RP; ++rr) {
             const int r = r0 + rr;
@@ -699,21 +653,10 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
                 }
               }
             }
-            if constexpr (REP > 1) {                           // next token: one position further
-              const float2 s1 = s_step1[16 * p + n];
-              const float c1 = c * s1.x - s * s1.y;
-              s = s * s1.x + c * s1.y;
-              c = c1;
-            }
-          }
-          if constexpr (REP > 1) {                             // the state moves on with the passes
-            cs_c[p] = c;
-            cs_s[p] = s;
           }
         }
         if (r0 + RP >= 4) {
-          // after the last pass: on to the next tile's first token (16 positions from this tile's;
-          // with REP > 1 the passes have covered 4 of them)
+          // after the last pass: on to the next tile's first token, 16 positions from this tile's
 #pragma unroll
           for (int p = 0; p < 4; ++p) {
             const float c = cs_c[p], s = cs_s[p];
@@ -735,7 +678,6 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
           const int idx = NR * j + (n & (NR - 1));
           const int tok = tt + 4 * q + r0 + idx / (G * REP), hq = idx % (G * REP);
           bool masked = tok >= len;
-          if constexpr (MULTI) masked = tok > s_lim[hq];
           if (sink_tiles & (1u << ti))
             for (int i = 0; i < cnt; ++i) masked |= (s_sink[i] == tok);
           if constexpr (LM) {                              // onto the zero-points' share, put there when the metadata were staged
@@ -1004,9 +946,8 @@ static RkvDecodeFn pick_kernel(const rkv_cache* c, bool multi, int share, bool a
 #undef RKV_MF_PRE_M
 #ifdef RKV_DEV_FEW_VARIANTS
   // developer builds: only the plain 2-bit variants of four-head rotation groups (quick to compile)
-  if (multi || v.g != 4 || v.hb || v.meta8 || !c->blocks_aligned || v.qg != 128) abort();
-  if (alu) return k_decode_mfma<4, 1, false, false, 0, 0, true>;
-  return share == 1 ? k_decode_mfma<4, 1, false, false, 0> : k_decode_mfma<4, 2, false, false, 0>;
+  if (multi || v.g != 4 || v.hb || v.meta8 || !c->blocks_aligned || v.qg != 128 || chunk != MF_CH) abort();
+  return alu ? k_decode_mfma<4, 1, false, false, 0, 0, true> : k_decode_mfma<4, 1, false, false, 0>;
 #else
   if (alu) return v.g == 4 ? k_decode_mfma<4, 1, false, false, 0, 0, true> : k_decode_mfma<2, 1, false, false, 0, 0, true>;
 #define RKV_MF_PICK_H(G_, H_, T_) (v.meta8 ? k_decode_mfma<G_, 1, false, true, H_, 0, false, false, T_> : k_decode_mfma<G_, 1, false, false, H_, 0, false, false, T_>)
