@@ -978,19 +978,18 @@ int rkv_mfma_chunk(const rkv_cache* c, int nq) {
   return 2 * total * v.NRG <= 3 * (size_t)c->n_cu && bytes <= RKV_STATIC_SCRATCH_BYTES / 2 ? MF_CH / 2 : MF_CH;
 }
 
-// nq == 0: the usual step, one query token that attends the whole cache (and, if set, the current
-// token's exact row).  nq >= 1: nq query tokens per sequence, token i at position q_pos[b][i] and
-// blind to cached tokens behind it; q, out and lse are then [batch][nq][heads][...] and the scratch
-// buffer holds nq times the single-query size.
-// query heads of a KV head served by one workgroup: two where the ratio is even (four per
-// workgroup measured slower: 158 against 151 us on the GQA configuration - the variant needs
-// more registers than three workgroups per compute unit leave)
+// Query heads of a KV head served by one workgroup on precomputed scores: two where the ratio is even (they
+// read the same V codes).  0: k_decode_shared, which serves them all.
 int rkv_mfma_share(const rkv_cache* c, bool multi, int heads_per_kv_head) {
   if (rkv_shared_decode(c, multi)) return 0;                // all query heads of a KV head together: a query layout of its own
   if (c->v.qg < 128) return 1;                              // groups of 64 / 32: one query head per workgroup
   return heads_per_kv_head % 2 == 0 ? 2 : 1;
 }
 
+// nq == 0: the usual step, one query token that attends the whole cache (and, if set, the current
+// token's exact row).  nq >= 1: nq query tokens per sequence, token i at position q_pos[b][i] and
+// blind to cached tokens behind it; q, out and lse are then [batch][nq][heads][...] and the scratch
+// buffer holds nq times the single-query size.
 // q_prepared: the queries are already in the scratch block (rkv_launch_step_mfma put them there)
 int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int nq, float* out, float* lse, void* scratch,
                            bool q_prepared, hipStream_t s) {
