@@ -269,6 +269,13 @@ int rkv_decode_attention_multi(rkv_cache* cache, const void* dev_q, const int32_
  * 128, one query head per KV head), else RKV_EINVAL at the next decode. */
 int rkv_set_decode_path(rkv_cache* cache, int32_t path);
 
+/* Tokens of a sequence per workgroup of the matrix-core decode kernels (groups of 128, reorder
+ * inside blocks of 128): 0 = by the size of the call (default), 128 or 256 = always that many.  Every
+ * variant of the kernels is reached on a small cache this way, and both sizes can be timed on any;
+ * results agree to rounding.  The general kernel and the variants that take their scores from the
+ * scores kernel do not look at it.  RKV_EINVAL for any other number. */
+int rkv_set_decode_chunk(rkv_cache* cache, int32_t tokens);
+
 /* Which kernel the cache's configuration and installed reorder take (no device work): the decode
  * kernel of rkv_decode_attention / rkv_decode_step (n_queries = 0) or of
  * rkv_decode_attention_multi (n_queries >= 1), the append kernel of rkv_quantize_append.  A

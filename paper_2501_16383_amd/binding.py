@@ -23,7 +23,7 @@ EXPORTS = [
     "rkv_query_sizes", "rkv_cache_create", "rkv_cache_destroy", "rkv_cache_reset", "rkv_cache_length",
     "rkv_calibrate_perm", "rkv_fold_rotation", "rkv_set_perm", "rkv_select_sinks", "rkv_quantize_append", "rkv_decode_attention", "rkv_decode_attention_static", "rkv_decode_attention_with_current",
     "rkv_decode_attention_multi", "rkv_decode_step", "rkv_quantize_append_ragged", "rkv_cache_lengths", "rkv_cache_truncate",
-    "rkv_set_decode_path", "rkv_decode_kernel_of", "rkv_append_kernel_of", "rkv_set_profile_events", "rkv_dequantize", "rkv_export_codes", "rkv_import_codes", "rkv_export_sinks", "rkv_layout_locate",
+    "rkv_set_decode_path", "rkv_set_decode_chunk", "rkv_decode_kernel_of", "rkv_append_kernel_of", "rkv_set_profile_events", "rkv_dequantize", "rkv_export_codes", "rkv_import_codes", "rkv_export_sinks", "rkv_layout_locate",
     "rkv_strerror",
 ]
 
@@ -105,6 +105,7 @@ def load_library():
     lib.rkv_cache_lengths.argtypes = [vp, vp]
     lib.rkv_cache_truncate.argtypes = [vp, vp, vp]
     lib.rkv_set_decode_path.argtypes = [vp, i32]
+    lib.rkv_set_decode_chunk.argtypes = [vp, i32]
     lib.rkv_decode_kernel_of.argtypes = [vp, i32]
     lib.rkv_append_kernel_of.argtypes = [vp]
     lib.rkv_set_profile_events.argtypes = [vp, vp, vp]
@@ -247,6 +248,10 @@ class RkvCache:
 
     def set_decode_path(self, path: int):
         _check(self.lib.rkv_set_decode_path(self.handle, path), "rkv_set_decode_path")
+
+    def set_decode_chunk(self, tokens: int):
+        """rkv_set_decode_chunk: 128 or 256 tokens per workgroup of the matrix-core decode kernels, 0 by size."""
+        _check(self.lib.rkv_set_decode_chunk(self.handle, tokens), "rkv_set_decode_chunk")
 
     def decode_kernel(self, n_queries: int = 0) -> int:
         """rkv_decode_kernel_of: the KERNEL_* value of the decode kernel this cache takes."""

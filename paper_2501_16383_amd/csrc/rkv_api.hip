@@ -190,6 +190,7 @@ RKV_EXPORT int rkv_cache_create(const rkv_config* cfg, void* dev_mem, size_t byt
   c->off_tables = o.tables;
   c->blocks_aligned = 1;
   c->decode_path = 0;
+  c->decode_chunk = 0;
   c->ev_start = c->ev_stop = nullptr;
   c->cur_k = c->cur_v = nullptr;
   c->ragged = 0;
@@ -370,6 +371,12 @@ RKV_EXPORT int rkv_cache_truncate(rkv_cache* cache, const int32_t* host_new_leng
 RKV_EXPORT int rkv_set_decode_path(rkv_cache* cache, int32_t path) {
   if (!cache || path < 0 || path > 3) return RKV_EINVAL;
   cache->decode_path = path;
+  return RKV_OK;
+}
+
+RKV_EXPORT int rkv_set_decode_chunk(rkv_cache* cache, int32_t tokens) {
+  if (!cache || (tokens != 0 && tokens != RKV_MFMA_CHUNK && tokens != RKV_MFMA_CHUNK / 2)) return RKV_EINVAL;
+  cache->decode_chunk = tokens;
   return RKV_OK;
 }
 

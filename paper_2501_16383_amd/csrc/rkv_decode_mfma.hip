@@ -968,6 +968,7 @@ static RkvDecodeFn pick_kernel(const rkv_cache* c, bool multi, int share, bool a
 int rkv_mfma_chunk(const rkv_cache* c, int nq) {
   const RkvView& v = c->v;
   if (rkv_scores_path(c) || c->decode_path == 3) return MF_CH;
+  if (c->decode_chunk) return c->decode_chunk;
   const int nch = (v.len + MF_CH - 1) / MF_CH;
   size_t total = 0;
   if (c->ragged)

@@ -109,6 +109,7 @@ struct rkv_cache {
   int wide;               // 1 with codes wider than 2 bits or groups smaller than 128: general kernels only
   int in_groups;          // 1 if the reorder keeps every rotated channel inside its rotation group (and rot_heads is 2 or 4)
   int decode_path;
+  int decode_chunk;       // tokens per workgroup of the matrix-core decode kernels: 0 by rkv_mfma_chunk's rule, else 128 or 256 (rkv_set_decode_chunk)
   int n_cu;               // compute units of the device the cache lives on
   hipEvent_t ev_start, ev_stop;   // optional measurement hook around the main kernels
   const __half* cur_k;    // set for the duration of a decode call that attends the token being decoded

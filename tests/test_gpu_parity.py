@@ -78,16 +78,19 @@ def check_dequant(cache, oc_same_codes):
 
 def check_decode(cache, oc_same_codes, q, q_pos=None, tag="", lse_relative=False, lse_bar=None):
     qp = None if q_pos is None else P.gpu(np.asarray(q_pos, dtype=np.int32))
-    out, lse = cache.decode_attention(P.gpu(q), qp, want_lse=True)
-    torch.cuda.synchronize()
     ref, lse_ref = O.decode_attention(oc_same_codes, q, q_pos)
-    e = P.attention_error(out.cpu().numpy().astype(np.float64), ref)
-    le = np.abs(lse.cpu().numpy() - lse_ref)
-    if lse_relative:        # scores in the thousands (keys at the end of the fp16 range): fp32 carries them to ~1e-7 of their size
-        le = le / np.maximum(1.0, np.abs(lse_ref))
-    le = float(le.max())
-    print(f"[parity] decode {tag}: out err {e:.3e}  lse err {le:.3e}", flush=True)
-    assert e <= ATT_TOL and le <= (LSE_TOL if lse_bar is None else lse_bar(lse_ref))
+    # (by the rule on sizes, and with the chunks of 256 tokens that a grid which fills the chip takes)
+    for chunk in (256, 0):
+        cache.set_decode_chunk(chunk)
+        out, lse = cache.decode_attention(P.gpu(q), qp, want_lse=True)
+        torch.cuda.synchronize()
+        e = P.attention_error(out.cpu().numpy().astype(np.float64), ref)
+        le = np.abs(lse.cpu().numpy() - lse_ref)
+        if lse_relative:        # scores in the thousands (keys at the end of the fp16 range): fp32 carries them to ~1e-7 of their size
+            le = le / np.maximum(1.0, np.abs(lse_ref))
+        le = float(le.max())
+        print(f"[parity] decode {tag} chunk={chunk}: out err {e:.3e}  lse err {le:.3e}", flush=True)
+        assert e <= ATT_TOL and le <= (LSE_TOL if lse_bar is None else lse_bar(lse_ref))
     return e
 
 
@@ -1690,8 +1693,9 @@ def test_randomly_drawn_steps_lengths_and_query_counts(seed):
         q = S.make_q(w, batch=B, step=77)
         kc = np.concatenate([data[s_][0][:, total[s_]] for s_ in range(B)])
         vc = np.concatenate([data[s_][1][:, total[s_]] for s_ in range(B)])
-        for path in ((1, 0) if a.decode_kernel() == RB.KERNEL_GENERAL else (1, 2)):
+        for path, chunk in (((1, 0), (0, 0)) if a.decode_kernel() == RB.KERNEL_GENERAL else ((1, 0), (2, 256), (2, 0))):
             a.set_decode_path(path)
+            a.set_decode_chunk(chunk)
             out, lse = a.decode_attention(P.gpu(q), want_lse=True)
             out_cur = a.decode_attention(P.gpu(q), k_cur=P.gpu(kc), v_cur=P.gpu(vc))
             torch.cuda.synchronize()
@@ -1716,11 +1720,14 @@ def test_randomly_drawn_steps_lengths_and_query_counts(seed):
             qn = np.stack([S.make_q(w, batch=B, step=20 + j) for j in range(nq)], axis=1)
             q_pos = np.array([[total[s_] - nq + j for j in range(nq)] for s_ in range(B)], dtype=np.int32)
             out = a.decode_attention_multi(P.gpu(qn), P.gpu(q_pos))
+            a.set_decode_chunk(256)
+            out256 = a.decode_attention_multi(P.gpu(qn), P.gpu(q_pos))
             torch.cuda.synchronize()
             for s_ in range(B):
                 ref, _ = O.decode_attention_multi(ocg[s_], qn[s_:s_ + 1], q_pos[s_:s_ + 1])
-                e = P.attention_error(out[s_:s_ + 1].cpu().numpy().astype(np.float64), ref)
-                assert e <= ATT_TOL, f"{nq} query tokens, sequence {s_}: {e}"
+                for o in (out, out256):
+                    e = P.attention_error(o[s_:s_ + 1].cpu().numpy().astype(np.float64), ref)
+                    assert e <= ATT_TOL, f"{nq} query tokens, sequence {s_}: {e}"
 
 
 @pytest.mark.parametrize("setting,g,hq,bits,group,fmt,nq", [("whole row", 4, 8, 2, 128, 0, 4), ("whole row", 2, 16, 2, 128, 1, 3),
@@ -1840,3 +1847,101 @@ def test_whole_row_reorder_few_tokens_equal_bulk(hkv, g, bits, group):
         at += n
     a, b = bulk.export_codes(), pieces.export_codes()
     assert at == T and all(torch.equal(a[name], b[name]) for name in a)
+
+
+# Decode attention of keys with a few strong channels per head, noise otherwise, against the float64 oracle on the
+# same codes: 2-norm of the difference over that of the result, its largest element over the result's root mean square,
+# and the log-sum-exp's.  Bars: about four times the largest seen over 210 calls (4.6e-6, 3.0e-5, 1.7e-5).  ATT_TOL allows for
+# caches whose scores run into the thousands; here they stay below a hundred: operands without their low
+# parts (2^-12 off) would move scores by some 1e-3 and outputs with them, a hundred times the bar.
+TIGHT_REL, TIGHT_MAX, TIGHT_LSE = 1.8e-5, 1.2e-4, 7e-5
+
+
+def noise_cache(cfg, lens, seed, sink_positions=(), sample=None):
+    """A cache of lens[b] tokens in sequence b, and an oracle cache on its codes for each sampled sequence."""
+    rng = np.random.default_rng(seed)
+    B, T, shape = cfg.batch, max(lens), (cfg.batch, max(lens), cfg.n_kv_heads, 128)
+    gain = np.ones((cfg.n_kv_heads, 128), np.float32)
+    for h in range(cfg.n_kv_heads):
+        gain[h, rng.permutation(128)[:6]] = rng.uniform(10, 50, 6)
+    k = (rng.standard_normal(shape, dtype=np.float32) * gain).astype(np.float16)
+    v = rng.standard_normal(shape, dtype=np.float32).astype(np.float16)
+    mask = np.zeros((B, T), np.uint8)
+    mask[:, list(sink_positions)] = 1
+    cache = R.RkvCache(cfg)
+    m = P.gpu(mask) if sink_positions else None
+    if len(set(lens)) == 1:
+        cache.quantize_append(P.gpu(k), P.gpu(v), m)
+    else:
+        cache.quantize_append_ragged(P.gpu(k), P.gpu(v), lens, m)
+    g = P.export_numpy(cache)
+    ocs = {}
+    for b in (range(B) if sample is None else sample):
+        n = lens[b]
+        oc = O.cache_new(P.oracle_cfg(dataclasses.replace(cfg, batch=1)))
+        O.quantize_append(oc, k[b:b + 1, :n], v[b:b + 1, :n], mask[b:b + 1, :n])
+        ocs[b] = oracle_from_export(oc, {name: arr[b:b + 1, :n] for name, arr in g.items()})
+    return cache, ocs
+
+
+def check_tight(cache, ocs, lens, nq, seed, tag):
+    """nq query tokens per sequence (0: the usual step) at the ends of the sequences."""
+    cfg = cache.cfg
+    rng = np.random.default_rng(seed)
+    q = rng.standard_normal((cfg.batch, max(nq, 1), cfg.n_q_heads, 128), dtype=np.float32).astype(np.float16)
+    q[:, :, -1] *= np.float16(1e-3)                            # (a head far smaller than the others)
+    pos = np.array([[n - max(nq, 1) + i for i in range(max(nq, 1))] for n in lens], np.int32)
+    if nq:
+        out, lse = cache.decode_attention_multi(P.gpu(q), P.gpu(pos), want_lse=True)
+    else:
+        out, lse = cache.decode_attention(P.gpu(q[:, 0]), want_lse=True)
+        out, lse = out[:, None], lse[:, None]
+    out, lse = out.cpu().numpy().astype(np.float64), lse.cpu().numpy().astype(np.float64)
+    rel = mx = le = 0.0
+    for b, oc in ocs.items():
+        ref, lse_ref = O.decode_attention_multi(oc, q[b:b + 1], pos[b:b + 1])
+        d = out[b:b + 1] - ref
+        rel = max(rel, float(np.linalg.norm(d) / np.linalg.norm(ref)))
+        mx = max(mx, float(np.abs(d).max() / np.sqrt((ref ** 2).mean())))
+        le = max(le, float(np.abs(lse[b:b + 1] - lse_ref).max()))
+    print(f"[tight] {tag}: rel {rel:.2e} max {mx:.2e} lse {le:.2e}", flush=True)
+    assert rel <= TIGHT_REL and mx <= TIGHT_MAX and le <= TIGHT_LSE, (tag, rel, mx, le)
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("fmt", [0, 1])
+@pytest.mark.parametrize("g", [4, 2])
+@pytest.mark.parametrize("rep,nq", [(1, 0), (1, 1), (3, 0), (2, 2)])
+def test_both_chunk_sizes_of_the_decode_kernels(bits, fmt, g, rep, nq):
+    """A workgroup takes 256 tokens of a sequence on a full grid and 128 on a small one: both on the same small
+    caches, sequences of different lengths (one over a chunk, one short of it, and tokens in every tile of a chunk)
+    and of one length, retained rows in several tiles; one query head per KV head and several."""
+    for lens, sinks in (([511, 129, 257, 300], (3, 70, 128)), ([385, 385], ())):
+        cfg = R.RkvConfig(batch=len(lens), n_q_heads=4 * rep, n_kv_heads=4, max_tokens=520, max_sinks=4, rot_heads=g, bits=bits,
+                          meta_format=fmt, rope_style=bits & 1)
+        cache, ocs = noise_cache(cfg, lens, 10 * bits + fmt, sinks)
+        for chunk in (256, 128):
+            cache.set_decode_chunk(chunk)
+            check_tight(cache, ocs, lens, nq, 7, f"bits={bits} fmt={fmt} g={g} rep={rep} nq={nq} chunk={chunk} lens={lens}")
+
+
+@pytest.mark.parametrize("hq,g,nq,bits,fmt", [(20, 4, 0, 2, 0), (32, 4, 0, 3, 1), (24, 4, 0, 4, 0), (12, 4, 2, 2, 1), (28, 4, 0, 4, 1),
+                                              (8, 2, 8, 4, 1), (8, 2, 6, 3, 0), (20, 2, 4, 2, 0), (16, 4, 4, 3, 0)])
+def test_two_column_tiles_of_the_shared_decode_kernel(hq, g, nq, bits, fmt):
+    """More than sixteen (query head, KV head) pairs in a workgroup take two column tiles; that needs a grid that
+    fills the chip.  130 sequences of 261 tokens, three of them recomputed; both chunk sizes."""
+    lens = [261] * 130
+    cfg = R.RkvConfig(batch=130, n_q_heads=hq, n_kv_heads=4, max_tokens=261, max_sinks=2, rot_heads=g, bits=bits, meta_format=fmt)
+    cache, ocs = noise_cache(cfg, lens, hq + bits, (140,) if fmt else (), sample=(0, 64, 129))
+    for chunk in (256, 128):
+        cache.set_decode_chunk(chunk)
+        check_tight(cache, ocs, lens, nq, 8, f"hq={hq} g={g} nq={nq} bits={bits} fmt={fmt} chunk={chunk}")
+
+
+def test_chunk_size_hook_is_checked():
+    cache = R.RkvCache(R.RkvConfig(batch=1, n_q_heads=2, n_kv_heads=2, max_tokens=64, rot_heads=2))
+    for bad in (-1, 1, 64, 512):
+        with pytest.raises(R.RkvError):
+            cache.set_decode_chunk(bad)
+    for good in (128, 256, 0):
+        cache.set_decode_chunk(good)
