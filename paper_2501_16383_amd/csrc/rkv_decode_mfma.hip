@@ -26,7 +26,7 @@
 //            tokens)], block-diagonal over heads, B = codes [(4 heads x 32 tokens) x 16 channels].
 // Covers: reorder that keeps 128-blocks, rot_heads 2 or 4, codes of 2 to 4 bits in groups of 128;
 // both RoPE pairings (the Hadamard operand tiles are built so that tiles p and p + 4 yield the two
-// channels of a pair); one query head per KV head.  Several of them, or several query tokens per step, are
+// channels of a pair); one query head per KV head and one query token.  Several of either are
 // k_decode_shared's; here the variants on precomputed scores (PRE) take them.  Everything else takes the
 // general kernel.
 #include "rkv_internal.h"
@@ -153,8 +153,9 @@ __device__ __forceinline__ float row_transpose_reduce(float (&v)[NV], int n) {
   return keep + dpp_f<DPP_QUAD_SWAP>(send);
 }
 
-// MULTI: several query tokens per sequence.  v.Hq then counts virtual heads (nq per real head, see
+// MULTI (with PRE): several query tokens per sequence.  v.Hq then counts virtual heads (nq per real head, see
 // rkv_virtual_head) and virtual head hv only attends tokens at positions <= q_lim[b][query token of hv].
+// Without PRE q_lim, if set, is the position of the sequence's one query token.
 // META8: scales in FP8 E4M3 and zero-points in 8 bits (rkv_load_meta describes the layout); they
 // are widened to the fp16 operands of the small matrix products right after loading.
 // HB = 2: 4-bit codes, c = c_lo + 4 c_hi.  The plane of the upper two bits has the layout of the lower
@@ -284,9 +285,12 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
     b = inv_nrg ? (int)__umulhi((uint32_t)br, inv_nrg) : br;
     rg = br - b * v.NRG;
   }
-  const int len = rkv_len(v, b);
+  int len = rkv_len(v, b);
   if (chunk * CH >= len) return;
   const int t0 = chunk * CH;
+  // (on scores of its own: one query token per sequence, which may lie before the sequence's end; a chunk behind it has weights of zero)
+  if constexpr (!PRE)
+    if (q_lim) len = min(len, q_lim[b] + 1);
 
   // Everything the workgroup needs before its first tile is requested here, back to back, and put
   // in LDS further down, once - a request that is waited for before the next one goes out costs a
@@ -979,10 +983,10 @@ int rkv_mfma_chunk(const rkv_cache* c, int nq) {
   return 2 * total * v.NRG <= 3 * (size_t)c->n_cu && bytes <= RKV_STATIC_SCRATCH_BYTES / 2 ? MF_CH / 2 : MF_CH;
 }
 
-// Query heads of a KV head served by one workgroup on precomputed scores: two where the ratio is even (they
-// read the same V codes).  0: k_decode_shared, which serves them all.
-int rkv_mfma_share(const rkv_cache* c, bool multi, int heads_per_kv_head) {
-  if (rkv_shared_decode(c, multi)) return 0;                // all query heads of a KV head together: a query layout of its own
+// Query heads of a KV head (virtual ones: times the query tokens) served by one workgroup: two on precomputed scores where
+// their number is even (they read the same V codes), else one.  0: k_decode_shared, which serves them all.
+int rkv_mfma_share(const rkv_cache* c, int heads_per_kv_head) {
+  if (rkv_shared_decode(c, heads_per_kv_head)) return 0;    // all query heads of a KV head together: a query layout of its own
   if (c->v.qg < 128) return 1;                              // groups of 64 / 32: one query head per workgroup
   return heads_per_kv_head % 2 == 0 ? 2 : 1;
 }
@@ -1008,7 +1012,7 @@ int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int 
   const bool xb = mfma_cross_block(c) || sg;
   const bool row = rkv_scores_path(c);
   if (row && multi && !rkv_scores_multi_ok(c, nq)) return RKV_EINVAL;   // (the scores kernel serves 8 rows per KV head)
-  const int share = rkv_mfma_share(c, multi, rep);
+  const int share = rkv_mfma_share(c, rep);
   if (!q_prepared) rkv_launch_prep_q(v, q, q_pos, c->cur_k ? 1 : 0, qr, share, nq, s);
   float* qt = qr + (size_t)v.B * v.Hq * RKV_D;              // lane-ordered copy written by k_prep_q
   const int chunk = rkv_mfma_chunk(c, nq), split = MF_CH / chunk;

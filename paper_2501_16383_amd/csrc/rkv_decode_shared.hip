@@ -555,12 +555,14 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
   }
 }
 
-// More than one query head per KV head, or several query tokens per step, on a cache whose scores do
-// not come from the scores kernel.  (One query head per KV head fills 4 of the 16 columns: there
-// k_decode_mfma, which takes the dot product on the vector pipe, has about 650 vector instructions per tile of
-// 16 tokens and four heads where this kernel has 840, of one query head or of four.)
-bool rkv_shared_decode(const rkv_cache* c, bool multi) {
-  return c->decode_path != 3 && !rkv_scores_path(c) && (multi || c->v.Hq > c->v.Hkv);
+// More than one (query token, query head) pair per KV head, on a cache whose scores do not come from the scores
+// kernel.  (One pair fills 4 of the 16 columns: there k_decode_mfma, which takes the dot product on the vector pipe, has
+// about 650 vector instructions per tile of 16 tokens and four heads where this kernel has 840, of one query head or
+// of four.  8 sequences x 4096 tokens, 32 heads, one query token through rkv_decode_attention_multi: 38 us there,
+// 45.5 here.  From two pairs on this kernel is the faster one: 47.9 us against the 53.2 of a k_decode_mfma with two
+// query heads per workgroup.)
+bool rkv_shared_decode(const rkv_cache* c, int heads_per_kv_head) {
+  return c->decode_path != 3 && !rkv_scores_path(c) && heads_per_kv_head > 1;
 }
 
 // v, nq: the (virtual) view of rkv_launch_decode_mfma; chunk: 256 or 128 tokens per workgroup

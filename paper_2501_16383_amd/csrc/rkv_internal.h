@@ -298,9 +298,9 @@ int rkv_launch_decode_general(rkv_cache* c, const __half* q, const int* q_pos, i
 int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int nq, float* out, float* lse, void* scratch,
                            bool q_prepared, hipStream_t s);
 int rkv_mfma_chunk(const rkv_cache* c, int nq);             // tokens per workgroup of the matrix-core decode kernels
-int rkv_mfma_share(const rkv_cache* c, bool multi, int heads_per_kv_head);
+int rkv_mfma_share(const rkv_cache* c, int heads_per_kv_head);   // (virtual heads, with several query tokens)
 // several query heads per KV head, or several query tokens per step (rkv_decode_shared.hip)
-bool rkv_shared_decode(const rkv_cache* c, bool multi);
+bool rkv_shared_decode(const rkv_cache* c, int heads_per_kv_head);
 int rkv_launch_decode_shared(const rkv_cache* c, const RkvView& v, const float* qr, float* part, int nch, int chunk, const int* q_lim, int nq,
                              hipEvent_t ev_start, hipEvent_t ev_stop, hipStream_t s);
 // a reorder over the whole token row (rkv_decode_row.hip): its scores kernel and the buffer it fills

@@ -1938,6 +1938,33 @@ def test_two_column_tiles_of_the_shared_decode_kernel(hq, g, nq, bits, fmt):
         check_tight(cache, ocs, lens, nq, 8, f"hq={hq} g={g} nq={nq} bits={bits} fmt={fmt} chunk={chunk}")
 
 
+@pytest.mark.parametrize("g,bits,fmt,lens", [(4, 2, 0, [300, 300]), (2, 2, 1, [300, 130, 512]), (4, 4, 0, [513, 40]), (2, 3, 0, [257, 257])])
+def test_one_query_token_takes_the_kernel_of_the_usual_step(g, bits, fmt, lens):
+    """decode_attention_multi with one query token and one query head per KV head is the usual step: at the
+    last position the same bits; before it (inside a tile, at a chunk's edge, in the first chunk) the oracle's result."""
+    B = len(lens)
+    cfg = R.RkvConfig(batch=B, n_q_heads=4, n_kv_heads=4, max_tokens=520, max_sinks=4, rot_heads=g, bits=bits, meta_format=fmt)
+    cache, ocs = noise_cache(cfg, lens, 40 + bits, (3, 20))
+    q = np.random.default_rng(9).standard_normal((B, 4, 128), dtype=np.float32).astype(np.float16)
+    for chunk in (128, 256):
+        cache.set_decode_chunk(chunk)
+        step, lse = cache.decode_attention(P.gpu(q), want_lse=True)
+        for past in (0, 3):                                    # (a position past the cache only sets the angle)
+            pos = P.gpu(np.array([[n - 1 + past] for n in lens], np.int32))
+            step, lse = cache.decode_attention(P.gpu(q), pos[:, 0].contiguous(), want_lse=True)
+            one, lse1 = cache.decode_attention_multi(P.gpu(q[:, None]), pos, want_lse=True)
+            assert torch.equal(one[:, 0], step) and torch.equal(lse1[:, 0], lse)
+        for back in (2, 17, 39):
+            pos = np.array([[n - back] for n in lens], np.int32)
+            pos[0, 0] = {2: 127, 17: 128, 39: 12}[back]
+            out, lse = cache.decode_attention_multi(P.gpu(q[:, None]), P.gpu(pos), want_lse=True)
+            for b, oc in ocs.items():
+                ref, lse_ref = O.decode_attention_multi(oc, q[b:b + 1, None], pos[b:b + 1])
+                e = np.linalg.norm(out[b].cpu().numpy() - ref[0]) / np.linalg.norm(ref)
+                le = np.abs(lse[b].cpu().numpy() - lse_ref[0]).max()
+                assert e <= TIGHT_REL and le <= TIGHT_LSE, (chunk, b, pos[b], e, le)
+
+
 def test_chunk_size_hook_is_checked():
     cache = R.RkvCache(R.RkvConfig(batch=1, n_q_heads=2, n_kv_heads=2, max_tokens=64, rot_heads=2))
     for bad in (-1, 1, 64, 512):
