@@ -565,7 +565,7 @@ RKV_EXPORT int rkv_decode_attention_static(rkv_cache* cache, const void* dev_q, 
   // what this call's kernels write: the prepared queries, then one partial per (sequence, query
   // head, chunk of the cache's current length) - chunks of the kernel that will run
   const bool fast = rkv_mfma_supported(cache) && cache->decode_path != 1;
-  const size_t chunk = fast ? rkv_mfma_chunk(cache, 1) : RKV_GEN_CHUNK;
+  const size_t chunk = fast ? rkv_mfma_chunk(cache, 0) : RKV_GEN_CHUNK;
   const size_t nch = ((size_t)cache->v.len + chunk - 1) / chunk;
   size_t need = rkv_query_scratch_bytes(cache->v.B, cache->v.Hq) +
                 (size_t)cache->v.B * cache->v.Hq * nch * RKV_PART_STRIDE * 4 + 256;

@@ -963,24 +963,57 @@ static RkvDecodeFn pick_kernel(const rkv_cache* c, bool multi, int share, bool a
 #endif
 }
 
-// Chunks of 128 tokens where chunks of 256 are at most three for two compute units: every workgroup is then
-// resident at once either way (three fit a compute unit) and the call takes as long as one workgroup lives - half
-// the tiles in turn, at the price of setting up twice as many.  One sequence x 4096 tokens, 32 heads (128 chunks
-// of 256): 22.3 -> 19.5 us a step; 512 tokens: 18.2 -> 16.2 us.  Where the chip is full the set-up is what counts: 32768 tokens
-// (1024 chunks) 40.7 -> 42.2 us, 16 x 4096 tokens with 40 heads (2560) 76.4 -> 80.0 us.  (The second bound
-// keeps the partial results within what rkv_decode_attention_static has room for.)
+// Workgroups of `chunk` tokens of a call, per group of query heads, on the busiest of the eight dies, times eight: what
+// counts against the chip's compute units.  A die takes every eighth (sequence, rotation group) pair with all its
+// chunks, so that a single sequence with two rotation groups keeps two dies busy; with per-sequence
+// lengths the chunks of all sequences go to the dies in turn.
+size_t rkv_mfma_load(const rkv_cache* c, int chunk) {
+  const RkvView& v = c->v;
+  if (!c->ragged) return ((size_t)v.B * v.NRG + 7) / 8 * 8 * ((v.len + chunk - 1) / chunk);
+  size_t total = 0;
+  for (int b = 0; b < v.B; ++b) total += (c->hlens[b] + MF_CH - 1) / MF_CH;
+  return total * (MF_CH / chunk) * v.NRG;
+}
+
+// Tokens per workgroup.  Half chunks are half the tiles in turn, at the price of setting up twice as many
+// workgroups, and they leave a last round of half its size.  Up to half a workgroup per compute unit they make a call 1.2 times
+// as fast; up to one and a half (two rounds of whole chunks on some units become three half ones on all) 1.05 to
+// 1.1 times, except where a workgroup has two column tiles (two fit a compute unit, not three) or the query heads
+// have been given to several workgroups already (which half chunks would take back): there they lose.  Above that they
+// lose.  The exception are wider codes on k_decode_mfma with four heads in a rotation group: of whole chunks two fit
+// a compute unit, of half ones three.
+// us, whole / half chunks, at 0.5, 1, 1.5, 1.75, 3 and 10 workgroups per unit:
+//   k_decode_mfma, 2-bit codes             20.6 / 18.2, 20.9 / 19.3, 24.9 / 23.6, 24.8 / 26.9, 34.0 / 36.0, 71.4 / 79.1
+//   ... 3-bit                              22.8 / 19.2, 23.5 / 21.1, 28.1 / 25.9, 29.1 / 29.9, 43.1 / 41.2, 100.7 / 98.5
+//   ... 4-bit                              24.0 / 18.7, 25.2 / 21.7, 29.1 / 26.5, 30.2 / 30.8, 45.8 / 41.5, 110.8 / 104.6
+//   ... 4-bit, two heads per group         20.4 / 16.7, 20.7 / 19.1, 23.5 / 20.6, 23.4 / 24.0, 29.9 / 32.2
+//   k_decode_shared, 4 heads on each of 8  24.1 / 19.8, 25.2 / 24.9, 34.3 / 32.2, 35.0 / 37.3, 47.8 / 49.9
+//   ... 3-bit                              25.8 / 21.4, 27.3 / 27.3, 38.0 / 37.4, 39.0 / 43.8, 54.4 / 60.6
+//   ... two column tiles, 8 on each of 8   25.0 / 24.6, 33.1 / 34.4, 45.7 / 46.5, 48.0 / 54.1, 69.4 / 76.0
+// (The work space: partial results of half chunks are within what a caller brings.  The one built in for
+// rkv_decode_attention_static, a single query's, may hold those of whole chunks only; the usual step then takes these, with it or without.)
 int rkv_mfma_chunk(const rkv_cache* c, int nq) {
   const RkvView& v = c->v;
   if (rkv_scores_path(c) || c->decode_path == 3) return MF_CH;
   if (c->decode_chunk) return c->decode_chunk;
-  const int nch = (v.len + MF_CH - 1) / MF_CH;
-  size_t total = 0;
-  if (c->ragged)
-    for (int b = 0; b < v.B; ++b) total += (c->hlens[b] + MF_CH - 1) / MF_CH;
-  else
-    total = (size_t)v.B * nch;
-  const size_t bytes = rkv_query_scratch_bytes(v.B, (size_t)v.Hq * nq) + (size_t)v.B * v.Hq * nq * 2 * nch * RKV_PART_STRIDE * 4;
-  return 2 * total * v.NRG <= 3 * (size_t)c->n_cu && bytes <= RKV_STATIC_SCRATCH_BYTES / 2 ? MF_CH / 2 : MF_CH;
+  const int rep = v.Hq / v.Hkv * (nq > 0 ? nq : 1);
+  const bool shared = rkv_shared_decode(c, rep);
+  if (shared || !v.hb || v.g != 4) {
+    size_t load = rkv_mfma_load(c, MF_CH);
+    int halves = 3;                                         // of a workgroup per compute unit
+    if (shared) {
+      const int rs = rkv_shared_heads(c, rep, MF_CH), ns = (rep + rs - 1) / rs;
+      load *= ns;
+      if (ns > 1 || rs * v.g > 16) halves = 1;
+    }
+    if (2 * load > halves * (size_t)c->n_cu) return MF_CH;
+  }
+  if (nq > 0) return MF_CH / 2;
+  auto fits = [&](int chunk) {
+    const size_t nch = ((size_t)v.len + chunk - 1) / chunk;
+    return rkv_query_scratch_bytes(v.B, v.Hq) + (size_t)v.B * v.Hq * nch * RKV_PART_STRIDE * 4 + 256 <= RKV_STATIC_SCRATCH_BYTES;
+  };
+  return fits(MF_CH / 2) || !fits(MF_CH) ? MF_CH / 2 : MF_CH;
 }
 
 // Query heads of a KV head (virtual ones: times the query tokens) served by one workgroup: two on precomputed scores where
@@ -1015,7 +1048,7 @@ int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int 
   const int share = rkv_mfma_share(c, rep);
   if (!q_prepared) rkv_launch_prep_q(v, q, q_pos, c->cur_k ? 1 : 0, qr, share, nq, s);
   float* qt = qr + (size_t)v.B * v.Hq * RKV_D;              // lane-ordered copy written by k_prep_q
-  const int chunk = rkv_mfma_chunk(c, nq), split = MF_CH / chunk;
+  const int chunk = rkv_mfma_chunk(c, multi ? nq : 0), split = MF_CH / chunk;
   const int nch = (v.len + chunk - 1) / chunk;
   if (share == 0) {
     const bool timed = c->ev_start && c->ev_stop;

@@ -565,26 +565,30 @@ bool rkv_shared_decode(const rkv_cache* c, int heads_per_kv_head) {
   return c->decode_path != 3 && !rkv_scores_path(c) && heads_per_kv_head > 1;
 }
 
+// Query heads per KV head and workgroup: as many as 32 columns take; fewer, down to four, as long as the workgroups
+// that makes are at most one per compute unit (their keys are rotated again by each, but it has fewer query heads to go through one
+// after the other, and sixteen columns).  8 heads on each of 8, 1024 tokens: 32 sequences (128 workgroups of eight heads)
+// 25.0 us, of four; 48 sequences (192) 31.3 us, 33.7 if split into 384; 64 (256) 33.1 and 35.2.
+int rkv_shared_heads(const rkv_cache* c, int heads_per_kv_head, int chunk) {
+  const int most = 32 / c->v.g;
+  int rs = heads_per_kv_head < most ? heads_per_kv_head : most;
+  const size_t load = rkv_mfma_load(c, chunk);
+  while (rs > 4 && 2 * load * ((heads_per_kv_head + rs - 1) / rs) <= (size_t)c->n_cu) rs = rs > 8 ? 8 : 4;
+  return rs;
+}
+
 // v, nq: the (virtual) view of rkv_launch_decode_mfma; chunk: 256 or 128 tokens per workgroup
 int rkv_launch_decode_shared(const rkv_cache* c, const RkvView& v, const float* qr, float* part, int nch, int chunk, const int* q_lim, int nq,
                              hipEvent_t ev_start, hipEvent_t ev_stop, hipStream_t s) {
-  // Query heads per KV head and workgroup: as many as 32 columns take; fewer where the workgroups would leave
-  // compute units idle (keys are then rotated again by other workgroups, but each has fewer query heads to
-  // go through one after the other)
-  const int rep = v.Hq / v.Hkv;
-  size_t total = (size_t)v.B * ((v.len + RKV_MFMA_CHUNK - 1) / RKV_MFMA_CHUNK);
-  if (c->ragged) {
-    total = 0;
-    for (int b = 0; b < v.B; ++b) total += (c->hlens[b] + RKV_MFMA_CHUNK - 1) / RKV_MFMA_CHUNK;
-  }
-  const int split = RKV_MFMA_CHUNK / chunk;
-  int rs = rep < 32 / v.g ? rep : 32 / v.g;
-  auto groups = [&]() { return (rep + rs - 1) / rs; };
-  while (rs > 4 && total * split * v.NRG * groups() <= (size_t)c->n_cu) rs = rs > 8 ? 8 : 4;
-  const int ns = groups(), ct = rs * v.g <= 16 ? 1 : 2;
+  const int rep = v.Hq / v.Hkv, split = RKV_MFMA_CHUNK / chunk;
+  const int rs = rkv_shared_heads(c, rep, chunk), ns = (rep + rs - 1) / rs, ct = rs * v.g <= 16 ? 1 : 2;
   auto recip = [](int d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };
   dim3 grid(8 * nch * ns, (v.B * v.NRG + 7) / 8, 1);
-  if (c->ragged) grid = dim3((((unsigned)total * split + 7) & ~7u) * ns, v.NRG, 1);
+  if (c->ragged) {                                          // all sequences' chunks in one dimension
+    unsigned total = 0;
+    for (int b = 0; b < v.B; ++b) total += (c->hlens[b] + RKV_MFMA_CHUNK - 1) / RKV_MFMA_CHUNK;
+    grid = dim3(((total * split + 7) & ~7u) * ns, v.NRG, 1);
+  }
   if (grid.y > 65535) return RKV_EINVAL;
 #define RKV_SH(G_, C_, T_) (v.hb == 2 ? k_decode_shared<G_, C_, 2, T_> : v.hb == 1 ? k_decode_shared<G_, C_, 1, T_> : k_decode_shared<G_, C_, 0, T_>)
 #define RKV_SH_C(G_, T_) (ct == 1 ? RKV_SH(G_, 1, T_) : RKV_SH(G_, 2, T_))

@@ -297,7 +297,9 @@ int rkv_launch_decode_general(rkv_cache* c, const __half* q, const int* q_pos, i
                               hipStream_t s);
 int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int nq, float* out, float* lse, void* scratch,
                            bool q_prepared, hipStream_t s);
-int rkv_mfma_chunk(const rkv_cache* c, int nq);             // tokens per workgroup of the matrix-core decode kernels
+int rkv_mfma_chunk(const rkv_cache* c, int nq);             // tokens per workgroup of the matrix-core decode kernels (nq: query tokens, 0 for the usual step)
+size_t rkv_mfma_load(const rkv_cache* c, int chunk);
+int rkv_shared_heads(const rkv_cache* c, int heads_per_kv_head, int chunk);
 int rkv_mfma_share(const rkv_cache* c, int heads_per_kv_head);   // (virtual heads, with several query tokens)
 // several query heads per KV head, or several query tokens per step (rkv_decode_shared.hip)
 bool rkv_shared_decode(const rkv_cache* c, int heads_per_kv_head);

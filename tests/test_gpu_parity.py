@@ -1965,6 +1965,44 @@ def test_one_query_token_takes_the_kernel_of_the_usual_step(g, bits, fmt, lens):
                 assert e <= TIGHT_REL and le <= TIGHT_LSE, (chunk, b, pos[b], e, le)
 
 
+@pytest.mark.parametrize("B,T,hq,hkv,g,nq,lens,chunk,bits", [
+    # one sequence of two rotation groups: two of eight dies are busy, with 48 or 49 chunks on 32 units each
+    (1, 2048, 8, 8, 4, 0, None, 128, 2), (1, 12288, 32, 8, 4, 0, None, 128, 2), (1, 12289, 32, 8, 4, 0, None, 256, 2), (1, 12289, 8, 8, 4, 0, None, 256, 2),
+    (130, 261, 20, 4, 4, 0, None, 256, 2),                     # two column tiles: half a workgroup per unit at most
+    (20, 261, 20, 4, 4, 0, None, 128, 2), (64, 1024, 4, 4, 4, 0, None, 128, 2), (104, 1024, 4, 4, 4, 0, None, 256, 2),
+    (4, 1024, 32, 8, 4, 4, None, 128, 2), (16, 1024, 32, 8, 4, 4, None, 256, 2), (104, 1024, 4, 4, 2, 0, None, 256, 4),
+    (104, 1024, 4, 4, 4, 0, None, 128, 4), (104, 1024, 4, 4, 4, 1, None, 128, 3), (104, 1024, 8, 4, 4, 0, None, 256, 4),
+    # wider codes: half chunks, but whole ones where only their partial results fit the built-in work space
+    (96, 4100, 16, 16, 4, 0, [4100] + [40] * 95, 256, 4), (96, 4100, 16, 16, 4, 1, [4100] + [40] * 95, 128, 4),
+    (4, 600, 8, 8, 4, 0, [600, 300, 20, 1], 128, 2), (40, 1100, 8, 8, 4, 0, [1100 - i for i in range(40)], 256, 2)])
+def test_tokens_per_workgroup_follow_what_the_chip_holds(B, T, hq, hkv, g, nq, lens, chunk, bits):
+    """The rule between chunks of 128 and 256 tokens, by the results' bits: whole chunks as soon as the compute units
+    that get work have more than one and a half workgroups each (half a one, where those have two column tiles or
+    share the query heads), counted on the dies that get work at all."""
+    cfg = R.RkvConfig(batch=B, n_q_heads=hq, n_kv_heads=hkv, max_tokens=T, max_sinks=0, rot_heads=g, bits=bits)
+    cache = R.RkvCache(cfg)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    k = torch.randn(B, T, hkv, 128, device="cuda", generator=gen).half()
+    v = torch.randn(B, T, hkv, 128, device="cuda", generator=gen).half()
+    if lens:
+        cache.quantize_append_ragged(k, v, lens)
+    else:
+        cache.quantize_append(k, v)
+    q = torch.randn(B, max(nq, 1), hq, 128, device="cuda", generator=gen).half()
+    pos = torch.tensor([[n - max(nq, 1) + i for i in range(max(nq, 1))] for n in cache.lengths], dtype=torch.int32).clamp_(min=0).cuda()
+    outs = {}
+    for c in (0, 128, 256):
+        cache.set_decode_chunk(c)
+        outs[c] = cache.decode_attention_multi(q, pos) if nq else cache.decode_attention(q[:, 0].contiguous())
+    assert not torch.equal(outs[128], outs[256]) and torch.equal(outs[0], outs[chunk])
+    assert float((outs[128] - outs[256]).norm() / outs[256].norm()) <= TIGHT_REL
+    if nq == 0 and (chunk == 256 or bits == 4):                # the built-in work space: the same chunks where it is large enough
+        cache.set_decode_chunk(0)
+        out = torch.empty_like(outs[0])
+        cache.decode_attention_static(q[:, 0].contiguous(), out)
+        assert torch.equal(out, outs[0])
+
+
 def test_chunk_size_hook_is_checked():
     cache = R.RkvCache(R.RkvConfig(batch=1, n_q_heads=2, n_kv_heads=2, max_tokens=64, rot_heads=2))
     for bad in (-1, 1, 64, 512):
