@@ -715,15 +715,16 @@ def test_large_zero_points():
         check_decode(cache, oc_g, q, tag=f"large zero-points path={path}")
 
 
-@pytest.mark.parametrize("bits", [2, 3, 4])
-def test_degenerate_and_extreme_blocks(bits):
+@pytest.mark.parametrize("bits,hq", [(2, 8), (3, 8), (4, 8), (2, 16), (3, 32), (4, 24)])
+def test_degenerate_and_extreme_blocks(bits, hq):
     """Blocks the quantizer has special rules for, in keys and values alike (keys arrive rotated,
     so both are quantized exactly as given): all zeros, constants, a range that rounds to a zero
     scale, ranges of a few fp16 subnormals, values at the end of the fp16 range, and an offset so
     far from zero that the zero-point is clamped.  Metadata and codes against the oracle (exact
-    outside ties), then the read half on those codes on both kernels."""
-    w = small("cfg1", n_q_heads=8, n_kv_heads=8, n_sinks=0)
-    cfg = R.RkvConfig(batch=1, n_q_heads=8, n_kv_heads=8, max_tokens=64, max_sinks=0, rot_heads=4, keys_rotated=1, bits=bits)
+    outside ties), then the read half on those codes on both kernels (with several query heads per KV
+    head too, whose scores are products of fp16 pairs)."""
+    w = small("cfg1", n_q_heads=hq, n_kv_heads=8, n_sinks=0)
+    cfg = R.RkvConfig(batch=1, n_q_heads=hq, n_kv_heads=8, max_tokens=64, max_sinks=0, rot_heads=4, keys_rotated=1, bits=bits)
     T = 40
     rng = np.random.default_rng(123 + bits)
     x = rng.standard_normal((1, T, 8, 128)).astype(np.float16)
@@ -2001,6 +2002,29 @@ def test_tokens_per_workgroup_follow_what_the_chip_holds(B, T, hq, hkv, g, nq, l
         out = torch.empty_like(outs[0])
         cache.decode_attention_static(q[:, 0].contiguous(), out)
         assert torch.equal(out, outs[0])
+
+
+@pytest.mark.parametrize("hq,g,nq,sinks", [(16, 4, 0, ()), (16, 4, 0, (3,)), (8, 2, 2, ()), (32, 4, 2, (3, 200)), (4, 4, 0, ())])
+def test_a_query_that_is_not_finite_stays_in_its_own_rows(hq, g, nq, sinks):
+    """NaN and infinities in single components of some query heads: those rows come out as NaN (as on the general
+    kernel), every other row has the bits it has without them - they share matrix products with them."""
+    lens = [300, 300]
+    cfg = R.RkvConfig(batch=2, n_q_heads=hq, n_kv_heads=4, max_tokens=300, max_sinks=4, rot_heads=g)
+    cache, _ = noise_cache(cfg, lens, 5, sinks)
+    q = np.random.default_rng(6).standard_normal((2, max(nq, 1), hq, 128), dtype=np.float32).astype(np.float16)
+    bad = q.copy()
+    bad[0, 0, 0, 5], bad[0, -1, 1, 127], bad[1, 0, hq - 1, 64], bad[1, -1, 2, 0] = np.nan, np.inf, -np.inf, np.nan
+    hit = ~np.isfinite(bad).all(-1)
+    pos = P.gpu(np.tile(np.arange(300 - max(nq, 1), 300, dtype=np.int32), (2, 1)))
+    for path, chunk in ((2, 256), (2, 128), (1, 0)):
+        if path == 1 and hq // 4 * max(nq, 1) > 8:
+            continue
+        cache.set_decode_path(path)
+        cache.set_decode_chunk(chunk)
+        run = lambda x: (cache.decode_attention_multi(P.gpu(x), pos) if nq else cache.decode_attention(P.gpu(x[:, 0]))[:, None]).cpu().numpy()
+        good, out = run(q), run(bad)
+        assert np.isfinite(good).all() and np.isnan(out[hit]).all(), (path, chunk)
+        assert np.array_equal(out[~hit], good[~hit]), (path, chunk)
 
 
 def test_chunk_size_hook_is_checked():
