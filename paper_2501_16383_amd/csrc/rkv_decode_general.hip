@@ -318,24 +318,23 @@ __global__ void __launch_bounds__(128 * NGRP) k_merge(RkvView v, const float* __
   for (int s = 0; s < cnt; ++s) M = fmaxf(M, s_score[s]);
   M = fmaxf(M, cur_score);
   float L = 0.f, acc = 0.f;
-  for (int kb = k_lo; kb < k_hi; kb += 64) {                 // (one turn up to 64 chunks per group)
-    // lane i: chunk kb + i
-    const int in = min(k_hi - kb, 64);
-    const float mk = lane < in ? s_w[kb + lane] : -INFINITY;
+  {
+    // lane i: chunk k_lo + i (a group has sixteen chunks at most, of eight groups 64)
+    static_assert(MERGE_MAX_CH <= 8 * 64 && PRE == 16, "a chunk of a group per lane; rkv_launch_merge's groups");
+    const int in = k_hi - k_lo;
+    const float mk = lane < in ? s_w[k_lo + lane] : -INFINITY;
     const float w = mk > -INFINITY ? __expf(mk - M) : 0.f;
-    L += wave_allreduce<false>(lane < in ? w * s_l[kb + lane] : 0.f);
+    L = wave_allreduce<false>(lane < in ? w * s_l[k_lo + lane] : 0.f);
     const int wi = __float_as_int(w);
-    if (kb > k_lo) {
-#pragma unroll
-      for (int i = 0; i < PRE; ++i) pv[i] = i < in ? P[(size_t)(kb + i) * RKV_PART_STRIDE + 4 + c] : 0.f;
-    }
 #pragma unroll
     for (int i = 0; i < PRE; ++i) acc += __int_as_float(__builtin_amdgcn_readlane(wi, i)) * pv[i];   // partial sums are always finite
-    for (int k0 = PRE; k0 < in; k0 += PRE) {
+    if constexpr (NGRP == 8) {
+      for (int k0 = PRE; k0 < in; k0 += PRE) {
 #pragma unroll
-      for (int i = 0; i < PRE; ++i) pv[i] = k0 + i < in ? P[(size_t)(kb + k0 + i) * RKV_PART_STRIDE + 4 + c] : 0.f;
+        for (int i = 0; i < PRE; ++i) pv[i] = k0 + i < in ? P[(size_t)(k_lo + k0 + i) * RKV_PART_STRIDE + 4 + c] : 0.f;
 #pragma unroll
-      for (int i = 0; i < PRE; ++i) acc += __int_as_float(__builtin_amdgcn_readlane(wi, k0 + i)) * pv[i];
+        for (int i = 0; i < PRE; ++i) acc += __int_as_float(__builtin_amdgcn_readlane(wi, k0 + i)) * pv[i];
+      }
     }
   }
   if constexpr (NGRP > 1) {                                  // group 0 takes the other groups' sums

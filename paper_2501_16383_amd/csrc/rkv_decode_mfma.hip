@@ -31,7 +31,6 @@
 // general kernel.
 #include "rkv_internal.h"
 #include "rkv_mfma_ops.h"
-#include <cstdlib>
 #include <hip/hip_ext.h>
 
 typedef _Float16 v4h __attribute__((ext_vector_type(4)));
@@ -43,15 +42,8 @@ typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 #define MF_CH (64 * MF_TILES)   // tokens per workgroup (4 waves)
 static_assert(MF_CH == 256, "the per-sequence chunk table (k_lens) counts chunks of 256 tokens");
 static_assert(MF_CH == RKV_MFMA_CHUNK, "the work-space size of a call is worked out from RKV_MFMA_CHUNK");
-#ifndef MF_ACC
-#define MF_ACC 16         // score accumulators per lane and pass of the key phase
-#endif
-#ifndef MF_OCC_HI
-#define MF_OCC_HI 2        // the same for the variants that hold a second plane of codes of four heads (three would spill)
-#endif
-#ifndef MF_OCC
 #define MF_OCC 3           // workgroups per compute unit the register budget is set for
-#endif
+#define MF_OCC_HI 2        // the same for the variants that hold a second plane of codes of four heads (three would spill)
 
 __device__ __forceinline__ v4h as_v4h(uint32_t a, uint32_t b) {
   union { uint32_t u[2]; v4h h; } c;
@@ -113,31 +105,21 @@ __device__ __forceinline__ void row_transpose_reduce_16_to_4(const float (&v)[16
 }
 
 template <int NV>
-__device__ __forceinline__ float row_transpose_reduce(float (&v)[NV], int n) {
+__device__ __forceinline__ float row_transpose_reduce(const float (&v)[NV], int n) {
+  static_assert(NV == 16 || NV == 8, "");
   float k4[4];
   if constexpr (NV == 16) {
     row_transpose_reduce_16_to_4(v, k4);
   } else {
-  float k8[8];
-  if constexpr (NV == 16) {
-    const bool hi = (n & 8) != 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float keep = hi ? v[i + 8] : v[i], send = hi ? v[i] : v[i + 8];
-      k8[i] = keep + dpp_f<DPP_ROW_MIRROR>(send);
-    }
-  } else {
+    float k8[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) k8[i] = v[i] + dpp_f<DPP_ROW_MIRROR>(v[i]);
-  }
-  {
     const bool hi = (n & 4) != 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float keep = hi ? k8[i + 4] : k8[i], send = hi ? k8[i] : k8[i + 4];
       k4[i] = keep + dpp_f<DPP_ROW_HALF_MIRROR>(send);
     }
-  }
   }
   float k2[2];
   {
@@ -185,7 +167,6 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
   constexpr bool HI = HB != 0;
   constexpr int CH = 64 * TILES;                 // tokens per workgroup (4 waves)
   constexpr int NH = G * REP;                    // query heads served by this workgroup: REP per KV head
-  constexpr int RP = (MF_ACC / (G * REP) < 4) ? MF_ACC / (G * REP) : 4;   // tokens (of a lane's four) per pass of the key phase: MF_ACC score accumulators at most
   __shared__ float s_sc[NH][CH];
   // Weight digits of phase S for the matrix products of phase V.  The operand [16 rows = 4 heads x
   // 4 digits][128 = 4 heads x 32 tokens] is block-diagonal over the heads, so only the 32 token
@@ -200,13 +181,12 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
   __shared__ int s_sink[64];
   __shared__ uint4 s_H[8][64];                   // Hadamard operand tiles
   __shared__ float2 s_step[64];                  // RoPE rotation by 16 positions, per channel pair
-  constexpr int QV = REP == 1 ? 4 : 1;            // query versions held (positions pos - r); with REP > 1 only r = 0
-  __shared__ uint4 s_q[QV][4][NH / 2][16];        // [r][p][f / 4][n] x 4 floats f % 4, f = (KV head * REP + query head of it) * 2 + (lo, hi)
+  __shared__ uint4 s_q[4][4][G / 2][16];         // key phase: [r][p][f / 4][n] x 4 floats f % 4, f = 2 * KV head + (lo, hi); version r: at position pos - r
   // Metadata of the chunk's keys and values (plain variants): fetched once, at the start, token by
   // token, and kept in LDS - a tile's worth held in registers a whole tile ahead of its use costs
   // 16 registers, which is the difference between three and four workgroups per compute unit
   // They are stored there in the form their users take: per token the scales of the group's blocks
-  // as packed fp16 pairs (s_ks: the A operand of the small matrix products, up to signs), for the
+  // as packed fp16 pairs (s_ks, key phase: the A operand of the small matrix products, up to signs), for the
   // values (scale, zero-point) per head (s_vm) - whatever the storage format was.  The keys'
   // zero-points never reach the key phase: H_128 of a constant block is 128 z e_0, so they only
   // touch channel 0 of every head, k^[a][0] -= (2 / sqrt(n)) * 64 * Z_a(t) with
@@ -218,7 +198,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
   constexpr bool LM = SUB == 0;
   constexpr int MWL = META8 ? G / 2 : G;             // metadata dwords per token and rotation group as stored
   constexpr int GP = G / 2;                          // packed pairs per token
-  __shared__ __attribute__((aligned(16))) uint32_t s_ks[LM ? CH * GP : 1], s_vm[LM ? CH * G : 1];
+  __shared__ __attribute__((aligned(16))) uint32_t s_ks[CH * GP], s_vm[LM ? CH * G : 1];
   static_assert(SUB == 0 || PRE, "groups of 64 / 32 run on precomputed scores");
   static_assert(!ALU || (!META8 && HB == 0 && !MULTI), "the arithmetic-only measurement exists for the plain 2-bit variants");
   static_assert(!PRE || CH == 256, "precomputed scores: a thread per token of the chunk");
@@ -299,9 +279,9 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
   //  - Hadamard operand tiles (the key phase reads two of them per step)
   const uint4 ld_h0 = reinterpret_cast<const uint4*>(v.hop)[tid], ld_h1 = reinterpret_cast<const uint4*>(v.hop)[tid + 256];
   //  - queries of this rotation group, already RoPE'd, scaled and laid out as s_q by k_prep_q
-  constexpr int Q16 = QV * 16 * 4 * 2 * NH / 4;          // 16-byte pieces in all
+  constexpr int Q16 = 4 * 16 * 4 * 2 * G / 4;            // 16-byte pieces in all
   constexpr int QN = (Q16 + 255) / 256;                  // per thread
-  const uint4* q_src = reinterpret_cast<const uint4*>(qt + (((size_t)b * v.NRG + rg) * ns + rrg) * (4 * 16 * 4 * 2 * NH));
+  const uint4* q_src = reinterpret_cast<const uint4*>(qt + ((size_t)b * v.NRG + rg) * (4 * 16 * 4 * 2 * G));
   uint4 ld_q[QN];
 #pragma unroll
   for (int i = 0; i < QN; ++i) ld_q[i] = tid + 256 * i < Q16 ? q_src[tid + 256 * i] : make_uint4(0, 0, 0, 0);
@@ -316,8 +296,8 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
   //    pair 0 and the queries' entries for that pair: staged below
   uint32_t ld_mk[4] = {0, 0, 0, 0}, ld_mv[4] = {0, 0, 0, 0};
   float2 ld_cs0 = make_float2(0.f, 0.f);
-  float4 ld_q0[LM ? NH / 2 : 1];
-  if constexpr (LM) {
+  float4 ld_q0[G / 2];
+  if constexpr (!PRE) {
     const size_t mi = ((size_t)(b * v.NRG + rg) * v.Tpad + t0 + tid) * MWL;
     auto fetch = [&](const uint32_t* g, uint32_t (&d)[4]) {
       if constexpr (ALU) return;
@@ -338,7 +318,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
     }
     // entry (r = 0, p = 0, n = 0) of the prepared queries: floats f % 4 of piece f / 4, f = 2 * head + half
 #pragma unroll
-    for (int i = 0; i < NH / 2; ++i) ld_q0[i] = reinterpret_cast<const float4*>(q_src)[i * 16];
+    for (int i = 0; i < G / 2; ++i) ld_q0[i] = reinterpret_cast<const float4*>(q_src)[i * 16];
   }
   //  - the RoPE angles of this lane's first token and the first key tile: in the key phase below
   [[maybe_unused]] int per_query = 1;            // query heads of a KV head per query token
@@ -450,7 +430,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
         s_step[tid] = ld_step;
         s_sink[tid] = tid < cnt ? ld_spos : -1;              // complete after the barrier that precedes the key phase
       }
-      if (LM && (CH == 256 || tid < CH)) {             // thread = token of the chunk (inside the padded allocation)
+      if (CH == 256 || tid < CH) {                     // thread = token of the chunk (inside the padded allocation)
         // a token's metadata as stored -> packed fp16 pairs (s01, s23) and (z01, z23)
         auto pairs = [&](const uint32_t* src, uint32_t (&sp)[2], uint32_t (&zp)[2]) {
           sp[1] = zp[1] = 0;
@@ -500,13 +480,9 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
             float Z = 0.f;
     #pragma unroll
             for (int i = 0; i < G; ++i) Z = fmaf((__popc(a & i) & 1) ? -sf[i] : sf[i], zf[i], Z);
-    #pragma unroll
-            for (int rri = 0; rri < REP; ++rri) {
-              const int f = (a * REP + rri) * 2;                 // entry (r = 0, p = 0, n = 0) of the prepared query: floats f, f + 1
-              const float4 q4 = ld_q0[f >> 2];
-              const float ql = (f & 3) ? q4.z : q4.x, qh = (f & 3) ? q4.w : q4.y;
-              s_sc[a * REP + rri][tid] = t0 + tid < len ? -64.0f * Z * fmaf(cs0.x, ql, cs0.y * qh) : -INFINITY;
-            }
+                const float4 q4 = ld_q0[a >> 1];                     // entry (r = 0, p = 0, n = 0) of the prepared query: floats 2a, 2a + 1
+            const float ql = (a & 1) ? q4.z : q4.x, qh = (a & 1) ? q4.w : q4.y;
+            s_sc[a][tid] = t0 + tid < len ? -64.0f * Z * fmaf(cs0.x, ql, cs0.y * qh) : -INFINITY;
           }
         }
         if constexpr (META8 || ALU) {                      // values: (scale, zero-point) per head
@@ -558,7 +534,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
         }
         // scale rows of the 4x4 products: (+-s_0, +-s_1, +-s_2, +-s_3) of token 4q + r, signs of H_g row n & 3
         v4h sA[4];
-        if constexpr (LM) {
+        {
           const uint32_t* sp = &s_ks[(wave * (16 * TILES) + ti * 16 + 4 * q) * GP];
           uint32_t sw[4][2];
           if constexpr (G == 4) {
@@ -577,16 +553,13 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
         }
         if (ti + 1 < TILES) load_tile(ti + 1);          // prefetch (inside the padded allocation)
 
-        // The key phase runs in passes over RP of the lane's four tokens, so that the score
-        // accumulators (RP tokens x G heads x REP query heads) stay within 16 registers - more of
-        // them and the compiler's allocation leaves the 256-register budget.  A pass repeats the big
-        // matrix products (every one yields all four tokens), which costs less than repeating the
-        // small ones, the packing or RoPE.
+        // (One pass.  Without the loop the compiler waits for the value codes before the softmax phase's barrier
+        // instead of behind it: one sequence x 4096 tokens, half chunks, 9.4 -> 10.0 us.)
 #pragma unroll
-        for (int r0 = 0; r0 < 4; r0 += RP) {
-        float pt[RP * G * REP];                            // [token of the pass][KV head][query head of it]
+        for (int pass = 0; pass < 1; ++pass) {
+        float pt[4 * G];                                   // [token of the lane][KV head]
 #pragma unroll
-        for (int i = 0; i < RP * G * REP; ++i) pt[i] = 0.f;
+        for (int i = 0; i < 4 * G; ++i) pt[i] = 0.f;
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
           // H_128 of the raw codes for channels 16p + n (lo) and 16p + n + 64 (hi) - or the even and the odd
@@ -619,8 +592,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
           }
           const float c = cs_c[p], s = cs_s[p];                // angles of token 4q
 #pragma unroll
-          for (int rr = 0; rr < RP; ++rr) {
-            const int r = r0 + rr;
+          for (int r = 0; r < 4; ++r) {
             // k^[a] = sum_blk H_g[a][blk] * scale_blk * u_blk   (H_g butterfly over the blocks)
             // as 16 independent 4x4x4 products per instruction: block = (token 4q + r, 4 channel
             // lanes), A row a = signed fp16 scales, B = the four blocks' results (half-integers
@@ -634,98 +606,67 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
               klo = mfma_4x4x4(sA[r], as_v4h(pk_f16(lo[0][r], lo[1][r]), 0u), z4);
               khi = mfma_4x4x4(sA[r], as_v4h(pk_f16(hi[0][r], hi[1][r]), 0u), z4);
             }
-            // the query: with REP == 1 the copy rotated back by r positions, else the plain one
-            // (floats 2 * REP * a .. of the row belong to KV head a: [query head of it][lo, hi])
-            constexpr int QF = (2 * REP * G < 8) ? 2 * REP * G : 8;   // floats fetched at a time
+            // the query: the copy rotated back by r positions
+            float qv[2 * G];
 #pragma unroll
-            for (int f0 = 0; f0 < 2 * REP * G; f0 += QF) {
-              float qv[QF];
+            for (int i = 0; i < 2 * G; i += 4) {
+              const uint4 u = s_q[r][p][i / 4][n];
+              qv[i] = __uint_as_float(u.x); qv[i + 1] = __uint_as_float(u.y); qv[i + 2] = __uint_as_float(u.z); qv[i + 3] = __uint_as_float(u.w);
+            }
 #pragma unroll
-              for (int i = 0; i < QF; i += 4) {
-                const uint4 u = s_q[REP == 1 ? r : 0][p][(f0 + i) / 4][n];
-                qv[i] = __uint_as_float(u.x); qv[i + 1] = __uint_as_float(u.y); qv[i + 2] = __uint_as_float(u.z); qv[i + 3] = __uint_as_float(u.w);
-              }
-#pragma unroll
-              for (int fa = 0; fa < QF; fa += 2 * REP) {
-                const int a = (f0 + fa) / (2 * REP);
-                const float xl = klo[a] * c - khi[a] * s;
-                const float xh = klo[a] * s + khi[a] * c;
-#pragma unroll
-                for (int rri = 0; rri < REP; ++rri) {
-                  const int o = (rr * G + a) * REP + rri;
-                  pt[o] = fmaf(xh, qv[fa + 2 * rri + 1], fmaf(xl, qv[fa + 2 * rri], pt[o]));
-                }
-              }
+            for (int a = 0; a < G; ++a) {
+              const float xl = klo[a] * c - khi[a] * s;
+              const float xh = klo[a] * s + khi[a] * c;
+              pt[r * G + a] = fmaf(xh, qv[2 * a + 1], fmaf(xl, qv[2 * a], pt[r * G + a]));
             }
           }
         }
-        if (r0 + RP >= 4) {
-          // after the last pass: on to the next tile's first token, 16 positions from this tile's
+        // on to the next tile's first token, 16 positions from this tile's
 #pragma unroll
-          for (int p = 0; p < 4; ++p) {
-            const float c = cs_c[p], s = cs_s[p];
-            const float2 st = s_step[16 * p + n];
-            cs_c[p] = c * st.x - s * st.y;
-            cs_s[p] = s * st.x + c * st.y;
-          }
+        for (int p = 0; p < 4; ++p) {
+          const float c = cs_c[p], s = cs_s[p];
+          const float2 st = s_step[16 * p + n];
+          cs_c[p] = c * st.x - s * st.y;
+          cs_s[p] = s * st.x + c * st.y;
         }
-        // reduce over the 16 channel lanes: value idx = (rr * G + a) * REP + rri ends in lane idx
-        // (token 4q + r0 + rr, query head a * REP + rri)
-        constexpr int NV = RP * G * REP;
-        constexpr int NR = NV < 16 ? NV : 16;              // values per transposing reduction
-#pragma unroll
-        for (int j = 0; j < NV / NR; ++j) {
-          float grp[NR];
-#pragma unroll
-          for (int i = 0; i < NR; ++i) grp[i] = pt[NR * j + i];
-          const float tot = row_transpose_reduce<NR>(grp, n);
-          const int idx = NR * j + (n & (NR - 1));
-          const int tok = tt + 4 * q + r0 + idx / (G * REP), hq = idx % (G * REP);
-          bool masked = tok >= len;
-          if (sink_tiles & (1u << ti))
-            for (int i = 0; i < cnt; ++i) masked |= (s_sink[i] == tok);
-          if constexpr (LM) {                              // onto the zero-points' share, put there when the metadata were staged
-            if (n < NR) s_sc[hq][tok - t0] = masked ? -INFINITY : tot + s_sc[hq][tok - t0];
-          } else {
-            if (n < NR && !masked) s_sc[hq][tok - t0] = tot;
-          }
-        }
+        // reduce over the 16 channel lanes: value idx = r * G + a (token 4q + r, head a) ends in lane idx, and is added to the
+        // zero-points' share, put there when the metadata were staged
+        const float tot = row_transpose_reduce<4 * G>(pt, n);
+        const int idx = n & (4 * G - 1), tok = tt + 4 * q + idx / G, a = idx % G;
+        bool masked = tok >= len;
+        if (sink_tiles & (1u << ti))
+          for (int i = 0; i < cnt; ++i) masked |= (s_sink[i] == tok);
+        if (n < 4 * G) s_sc[a][tok - t0] = masked ? -INFINITY : tot + s_sc[a][tok - t0];
         }
       }
     }
     }
     __builtin_amdgcn_s_setprio(3);
-    // V metadata of the four tokens this lane turns into weights in phase S (head = wave); requested
-    // here and not before the key phase, where four more live registers would mean spills - and
-    // with them a scratch allocation, which keeps some shader engines from holding three workgroups
-    uint32_t vmeta[NS][CH / 64];
+    // Groups of 64 / 32: the V metadata of the four tokens this lane turns into weights in phase S (head = wave)
+    // - otherwise they are in LDS
+    [[maybe_unused]] uint32_t vmeta[NS][CH / 64];
+    if constexpr (SUB != 0) {
 #pragma unroll
-    for (int i = 0; i < CH / 64; ++i) {
-      const size_t mi = ((size_t)(b * v.NRG + rg) * v.Tpad + t0 + lane + 64 * i) * (G * NS);
-      if constexpr (LM) {
-        // (read from LDS in the softmax phase)
-      } else if constexpr (SUB != 0 && META8) {
-        // the head's NS scale bytes and NS zero-point bytes, one load each
-        const uint8_t* vm8 = reinterpret_cast<const uint8_t*>(v.vm) + 2 * mi + (wave < G ? wave : 0) * NS;
-        uint32_t sw, zw;
-        if constexpr (NS == 4) {
-          sw = *reinterpret_cast<const uint32_t*>(vm8);
-          zw = *reinterpret_cast<const uint32_t*>(vm8 + G * NS);
+      for (int i = 0; i < CH / 64; ++i) {
+        const size_t mi = ((size_t)(b * v.NRG + rg) * v.Tpad + t0 + lane + 64 * i) * (G * NS);
+        if constexpr (META8) {
+          // the head's NS scale bytes and NS zero-point bytes, one load each
+          const uint8_t* vm8 = reinterpret_cast<const uint8_t*>(v.vm) + 2 * mi + (wave < G ? wave : 0) * NS;
+          uint32_t sw, zw;
+          if constexpr (NS == 4) {
+            sw = *reinterpret_cast<const uint32_t*>(vm8);
+            zw = *reinterpret_cast<const uint32_t*>(vm8 + G * NS);
+          } else {
+            sw = *reinterpret_cast<const uint16_t*>(vm8);
+            zw = *reinterpret_cast<const uint16_t*>(vm8 + G * NS);
+          }
+#pragma unroll
+          for (int sb = 0; sb < NS; ++sb)
+            vmeta[sb][i] = wave < G ? __builtin_amdgcn_perm(zw, sw, 0x0c0c0000u | ((4u + sb) << 8) | sb) : 0x8000u;
         } else {
-          sw = *reinterpret_cast<const uint16_t*>(vm8);
-          zw = *reinterpret_cast<const uint16_t*>(vm8 + G * NS);
+#pragma unroll
+          for (int sb = 0; sb < NS; ++sb) vmeta[sb][i] = wave < G ? v.vm[mi + wave * NS + sb] : 0u;
         }
-#pragma unroll
-        for (int sb = 0; sb < NS; ++sb)
-          vmeta[sb][i] = wave < G ? __builtin_amdgcn_perm(zw, sw, 0x0c0c0000u | ((4u + sb) << 8) | sb) : 0x8000u;
-      } else if constexpr (SUB != 0) {
-#pragma unroll
-        for (int sb = 0; sb < NS; ++sb) vmeta[sb][i] = wave < G ? v.vm[mi + wave * NS + sb] : 0u;
-      } else if constexpr (META8) {
-        const uint8_t* vm8 = reinterpret_cast<const uint8_t*>(v.vm) + 2 * mi;
-        vmeta[0][i] = wave < G ? ((uint32_t)vm8[wave] | ((uint32_t)vm8[G + wave] << 8)) : 0x8000u;
-      } else {
-        vmeta[0][i] = wave < G ? v.vm[mi + wave] : 0u;
       }
     }
     const bool has_head = q < G;
@@ -948,11 +889,6 @@ static RkvDecodeFn pick_kernel(const rkv_cache* c, bool multi, int share, bool a
 #undef RKV_MF_PRE_SUB
 #undef RKV_MF_PRE
 #undef RKV_MF_PRE_M
-#ifdef RKV_DEV_FEW_VARIANTS
-  // developer builds: only the plain 2-bit variants of four-head rotation groups (quick to compile)
-  if (multi || v.g != 4 || v.hb || v.meta8 || !c->blocks_aligned || v.qg != 128 || chunk != MF_CH) abort();
-  return alu ? k_decode_mfma<4, 1, false, false, 0, 0, true> : k_decode_mfma<4, 1, false, false, 0>;
-#else
   if (alu) return v.g == 4 ? k_decode_mfma<4, 1, false, false, 0, 0, true> : k_decode_mfma<2, 1, false, false, 0, 0, true>;
 #define RKV_MF_PICK_H(G_, H_, T_) (v.meta8 ? k_decode_mfma<G_, 1, false, true, H_, 0, false, false, T_> : k_decode_mfma<G_, 1, false, false, H_, 0, false, false, T_>)
 #define RKV_MF_PICK(G_, T_) (v.hb == 2 ? RKV_MF_PICK_H(G_, 2, T_) : v.hb == 1 ? RKV_MF_PICK_H(G_, 1, T_) : RKV_MF_PICK_H(G_, 0, T_))
@@ -960,7 +896,6 @@ static RkvDecodeFn pick_kernel(const rkv_cache* c, bool multi, int share, bool a
   return v.g == 4 ? RKV_MF_PICK(4, MF_TILES / 2) : RKV_MF_PICK(2, MF_TILES / 2);
 #undef RKV_MF_PICK_H
 #undef RKV_MF_PICK
-#endif
 }
 
 // Workgroups of `chunk` tokens of a call, per group of query heads, on the busiest of the eight dies, times eight: what
