@@ -192,6 +192,9 @@ int rkv_quantize_append_ragged(rkv_cache* cache, const void* dev_k, const void* 
  *   dev_lse    [batch][n_q_heads] fp32 log-sum-exp of the scaled scores, or NULL
  *   dev_scratch >= scratch_bytes of rkv_query_sizes; calls sharing a scratch block must be
  *              ordered on one stream.
+ * A sequence's result depends on the rest of the batch by rounding: how many of its tokens a workgroup
+ * takes, and in what order partial results are summed, follows from the size of the whole call and the
+ * number of compute units.  The same call on the same cache gives the same bits.
  * RKV_ESTATE on an empty cache. */
 int rkv_decode_attention(rkv_cache* cache, const void* dev_q, const int32_t* dev_q_pos,
                          float* dev_out, float* dev_lse, void* dev_scratch, void* stream);
@@ -202,8 +205,9 @@ int rkv_decode_attention(rkv_cache* cache, const void* dev_q, const int32_t* dev
  * RKV_STATIC_SCRATCH_BYTES, one copy per GPU, held until the process ends) instead of dev_scratch;
  * the call allocates and frees nothing.  Same arguments otherwise, same kernels, same results bit
  * for bit.  RKV_ESCRATCH - and nothing enqueued - if this call needs more than the built-in space:
- * 2560 bytes per (sequence, query head) plus 528 bytes per (sequence, query head, chunk of 256
- * cached tokens; of 128 on the general kernel), e.g. 7 MB for batch 16 x 40 heads x 4096 tokens.
+ * 2560 bytes per (sequence, query head) plus 528 bytes per (sequence, query head, chunk of the longest
+ * sequence's cached tokens), e.g. 7 MB for batch 16 x 40 heads x 4096 tokens.  Chunks are 128 tokens on the
+ * general kernel, 256 or 128 on the matrix-core kernels - never 128 where only the partials of 256 fit.
  * With a reorder that crosses blocks of 128 (inside the rotation groups or over the whole row), or
  * groups of 64 / 32, on the matrix-core path the scores pass through the work space as well: the partials then count the chunks of max_tokens, and 4 bytes
  * per (sequence, query head, token slot of max_tokens rounded up to 256) come on top.
@@ -246,7 +250,7 @@ int rkv_decode_step(rkv_cache* cache, const void* dev_k, const void* dev_v, cons
  *   dev_out    [batch][n_queries][n_q_heads][head_dim] fp32
  *   dev_lse    [batch][n_queries][n_q_heads] fp32, or NULL
  *   dev_scratch >= n_queries * scratch_bytes of rkv_query_sizes
- * Runs on the plain matrix-core decode kernel where the configuration has it (reorder inside
+ * Runs on the plain matrix-core decode kernels where the configuration has them (reorder inside
  * blocks of 128, rot_heads 2 or 4, groups of 128).  The matrix-core variants that take their
  * scores from the scores kernel (groups of 64 / 32, reorders across blocks) serve at most 8
  * (query token, query head) pairs per KV head, and so does the general kernel, which takes what

@@ -593,9 +593,12 @@ __global__ void __launch_bounds__(256, (HB || SUB) ? 4 : 6) k_append_values(RkvV
 // dynamic LDS: [NG][16 tokens] float minima, the same of maxima, [NG][16] float4 parameters, [NRG][4 waves][4][G] table entries (block-major: the 16
 // tokens of a row of lanes, which share their channels and hence their blocks, touch 16 different LDS banks).
 // NP: wave sets (of four waves each) of the workgroup, which take NP rotation groups side by side.  A bulk append fills the
-// chip with its tiles, one set each (three workgroups per compute unit); an append of few tokens - a decode
+// chip with its tiles, one set each (three workgroups per compute unit; two where the row has 80 blocks and more:
+// 4 x 4096 tokens, 40 heads in groups of 64, keys and values: 138 us, 145 with the table in memory and three of
+// them); an append of few tokens - a decode
 // step touches one tile per sequence - leaves it nearly empty and waits for one group after the
 // other, so there four sets share a tile: 8 sequences of one token, 32 heads: 22 us against 40 us.
+// (Four sets of rotation groups of four heads are 1024 threads of 128 registers; 7 to 12 more are held in scratch memory.)
 template <int G, int HB = 0, int NP = 1>
 __global__ void __launch_bounds__(256 * NP, NP == 1 ? 3 : 1) k_append_row_keys(RkvView v, const __half* __restrict__ kin, int n_new, int slab0) {
   constexpr int n = 128 * G;
@@ -840,12 +843,15 @@ __global__ void __launch_bounds__(256, 4) k_step_values(RkvView v, const __half*
   rkv_prep_q_one(v, q, q_pos, 1, qr, share, 1, h, blockIdx.z, threadIdx.x & 127);
 }
 
+static size_t row_keys_dynamic_lds(const RkvView& v) { return (size_t)384 * (v.NG | 1) + (size_t)v.NRG * 128 * v.g; }
+
 // a reorder over the whole row: k_append_row_keys + k_append_values
 static bool append_row(const rkv_cache* c) {
   const RkvView& v = c->v;
-  // (a block's number is a byte in the kernel's table; its dynamic LDS beside 26 KB of static)
+  // (a block's number is a byte in the kernel's table; its dynamic LDS - tables per block and token, and the row's block
+  // numbers - beside 25 KB of static)
   return !c->blocks_aligned && !c->in_groups && (v.g == 2 || v.g == 4) && v.v_rotate == 0 &&
-         !c->cfg.keys_rotated && v.NG <= 255 && (size_t)384 * (v.NG | 1) <= 120 * 1024;
+         !c->cfg.keys_rotated && v.NG <= 255 && row_keys_dynamic_lds(v) <= 120 * 1024;
 }
 int rkv_append_mfma_variant(const rkv_cache* c) {
   return append_row(c) ? RKV_KERNEL_MFMA_ROW : c->v.qg != 128 ? RKV_KERNEL_MFMA_SUB : c->blocks_aligned ? RKV_KERNEL_MFMA : RKV_KERNEL_MFMA_CROSS;
@@ -865,11 +871,11 @@ bool rkv_append_mfma_supported(const rkv_cache* c) {
 template <int G, int HB>
 static int launch_row_keys(const rkv_cache* c, const __half* k, int n_new, int max_slabs, int slab0, hipStream_t s) {
   const RkvView& v = c->v;
-  const size_t dyn = (size_t)384 * (v.NG | 1) + (size_t)v.NRG * 128 * G;
+  const size_t dyn = row_keys_dynamic_lds(v);
   // Four wave sets per tile as long as there is at most one such workgroup per compute unit and the tables fit
   // beside their images.  One sequence, 32 heads, keys and values together: 2048 tokens 42 us against 53,
   // 4096 tokens (one workgroup each) 52 against 60, 8192 tokens 92 against 73: from there on the
-  // narrow workgroups, three of which are resident at a time, are the better ones.
+  // narrow workgroups, several of which are resident at a time, are the better ones.
   const size_t wide_static = 4 * (16 * (16 * G + 1) * 16 + (HB ? 2 : 1) * 2 * 128 * G * 4) + 64;
   if (2 * max_slabs * v.B <= c->n_cu && v.NRG > 1 && dyn + wide_static <= RKV_LDS_BYTES) {
     RKV_HIP_CHECK(hipFuncSetAttribute((const void*)k_append_row_keys<G, HB, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn));

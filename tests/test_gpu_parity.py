@@ -618,7 +618,7 @@ def test_full_size_config4_gqa_sampled(with_sinks):
     """(With the workload's four fp16 sink rows, as bench.py runs it, and without any, so that the
     compressed stream alone decides the outputs.)  Configuration 4 at full size (batch 32, 32 query / 8 KV heads, context 8192, RoPE base
     500000) in the launch configuration bench.py times: bulk append of 8191 tokens, then one
-    rkv_decode_step on the matrix-core path, where a workgroup serves two of the four query heads of
+    rkv_decode_step on the matrix-core path, where a workgroup serves the four query heads of
     each KV head.  Two (sequence, rotation group) slices - four KV heads, sixteen query heads each -
     are recomputed by the oracle."""
     w = S.WORKLOADS["cfg4"]
