@@ -223,9 +223,8 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
   const uint32_t sm01 = ((__popc(hrow & 1) & 1) ? 0x80000000u : 0u);
   const uint32_t sm23 = ((__popc(hrow & 2) & 1) ? 0x00008000u : 0u) | ((__popc(hrow & 3) & 1) ? 0x80000000u : 0u);
 
-  // Of the `rep` query heads that share a KV head (GQA) one workgroup serves REP, so that unpacking,
-  // rotation and RoPE of the keys are done once for them; if rep > REP the workgroups of the other
-  // query-head groups re-read the same chunk.
+  // On precomputed scores one workgroup serves REP of the `rep` query heads that share a KV head, which read the
+  // same V codes; the workgroups of the other query-head groups read the chunk's again.
   // With per-sequence lengths the grid has no sequence dimension: the chunks of all sequences are
   // numbered consecutively (cstart[b] = chunks of the sequences before b), rounded up to 8 in all,
   // so that no workgroup is launched for chunks a shorter sequence does not have.
