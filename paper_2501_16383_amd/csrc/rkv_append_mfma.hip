@@ -593,13 +593,12 @@ __global__ void __launch_bounds__(256, (HB || SUB) ? 4 : 6) k_append_values(RkvV
 // dynamic LDS: [NG][16 tokens] float minima, the same of maxima, [NG][16] float4 parameters, [NRG][4 waves][4][G] table entries (block-major: the 16
 // tokens of a row of lanes, which share their channels and hence their blocks, touch 16 different LDS banks).
 // NP: wave sets (of four waves each) of the workgroup, which take NP rotation groups side by side.  A bulk append fills the
-// chip with its tiles, one set each (three workgroups per compute unit; two where the row has 80 blocks and more:
-// 4 x 4096 tokens, 40 heads in groups of 64, keys and values: 138 us, 145 with the table in memory and three of
-// them); an append of few tokens - a decode
+// chip with its tiles, one set each (three workgroups per compute unit, or two); an append of few tokens - a decode
 // step touches one tile per sequence - leaves it nearly empty and waits for one group after the
 // other, so there four sets share a tile: 8 sequences of one token, 32 heads: 22 us against 40 us.
 // (Four sets of rotation groups of four heads are 1024 threads of 128 registers; 7 to 12 more are held in scratch memory.)
-template <int G, int HB = 0, int NP = 1>
+// TAB: the table of block numbers in LDS; without it (narrow workgroups only) entries are fetched from memory where they are used.
+template <int G, int HB = 0, int NP = 1, bool TAB = true>
 __global__ void __launch_bounds__(256 * NP, NP == 1 ? 3 : 1) k_append_row_keys(RkvView v, const __half* __restrict__ kin, int n_new, int slab0) {
   constexpr int n = 128 * G;
   constexpr bool HI = HB == 2, H1 = HB == 1;
@@ -703,10 +702,15 @@ __global__ void __launch_bounds__(256 * NP, NP == 1 ? 3 : 1) k_append_row_keys(R
       }
   };
   // quantization blocks (of the row) of the lane's eight channels of head h, one byte each (element 4 ppl + rr).
-  // The table is copied to LDS once: fetched from memory where it is used, an entry is waited for together
+  // The table is copied to LDS once (TAB): fetched from memory where it is used, an entry is waited for together
   // with the next group's rows, which are requested before it (loads return in order).
-  for (int i = all; i < v.NRG * 16 * G; i += 256 * NP) s_gid[i] = v.xgid8[i];
-  auto blocks_of = [&](int rg, int h) __attribute__((always_inline)) { return s_gid[(rg * 16 + wave * 4 + q) * G + h]; };
+  if constexpr (TAB)
+    for (int i = all; i < v.NRG * 16 * G; i += 256 * NP) s_gid[i] = v.xgid8[i];
+  auto blocks_of = [&](int rg, int h) __attribute__((always_inline)) {
+    const int i = (rg * 16 + wave * 4 + q) * G + h;
+    if constexpr (TAB) return s_gid[i];
+    else return v.xgid8[i];
+  };
 
   for (int i = all; i < 16 * NGP; i += 256 * NP) {
     s_mn[i] = 3.0e38f;
@@ -843,7 +847,9 @@ __global__ void __launch_bounds__(256, 4) k_step_values(RkvView v, const __half*
   rkv_prep_q_one(v, q, q_pos, 1, qr, share, 1, h, blockIdx.z, threadIdx.x & 127);
 }
 
-static size_t row_keys_dynamic_lds(const RkvView& v) { return (size_t)384 * (v.NG | 1) + (size_t)v.NRG * 128 * v.g; }
+static size_t row_keys_dynamic_lds(const RkvView& v, bool table = true) {
+  return (size_t)384 * (v.NG | 1) + (table ? (size_t)v.NRG * 128 * v.g : 0);
+}
 
 // a reorder over the whole row: k_append_row_keys + k_append_values
 static bool append_row(const rkv_cache* c) {
@@ -876,15 +882,29 @@ static int launch_row_keys(const rkv_cache* c, const __half* k, int n_new, int m
   // beside their images.  One sequence, 32 heads, keys and values together: 2048 tokens 42 us against 53,
   // 4096 tokens (one workgroup each) 52 against 60, 8192 tokens 92 against 73: from there on the
   // narrow workgroups, several of which are resident at a time, are the better ones.
-  const size_t wide_static = 4 * (16 * (16 * G + 1) * 16 + (HB ? 2 : 1) * 2 * 128 * G * 4) + 64;
+  const size_t set_static = 16 * (16 * G + 1) * 16 + (HB ? 2 : 1) * 2 * 128 * G * 4, wide_static = 4 * set_static + 64;
   if (2 * max_slabs * v.B <= c->n_cu && v.NRG > 1 && dyn + wide_static <= RKV_LDS_BYTES) {
     RKV_HIP_CHECK(hipFuncSetAttribute((const void*)k_append_row_keys<G, HB, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn));
     hipLaunchKernelGGL((k_append_row_keys<G, HB, 4>), dim3(2 * max_slabs, v.B), dim3(1024), dyn, s, v, k, n_new, slab0);
     return RKV_OK;
   }
-  if (dyn > 48 * 1024)
-    RKV_HIP_CHECK(hipFuncSetAttribute((const void*)k_append_row_keys<G, HB, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn));
-  hipLaunchKernelGGL((k_append_row_keys<G, HB, 1>), dim3(2 * max_slabs, v.B), dim3(256), dyn, s, v, k, n_new, slab0);
+  // The table of block numbers stays in memory where its place in LDS would be the third workgroup's (LDS is given out
+  // in pieces of 1280 bytes).  16 sequences x 4096 tokens, 40 heads in groups of 64, 2-bit codes, keys and values:
+  // 484 us with it in memory, 505 in LDS; 32 heads with 3- and 4-bit codes 427 and 452.  Where as many fit either way LDS
+  // is the better place: groups of 128 525 -> 515 us, 3-bit codes in groups of 64 568 -> 527, groups of 32 880 -> 740; with
+  // rotation over two heads also where it costs the third of three (26 heads in groups of 32: 377 us in memory, 364).
+  size_t lds = dyn;
+  auto fn = k_append_row_keys<G, HB, 1, true>;
+  if constexpr (G == 4) {
+    auto resident = [&](size_t dynamic) { return RKV_LDS_BYTES / 1280 / ((set_static + dynamic + 64 + 1279) / 1280); };
+    const size_t dyn0 = row_keys_dynamic_lds(v, false);
+    if (resident(dyn0) >= 3 && resident(dyn) < 3) {
+      fn = k_append_row_keys<G, HB, 1, false>;
+      lds = dyn0;
+    }
+  }
+  if (lds > 48 * 1024) RKV_HIP_CHECK(hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL(fn, dim3(2 * max_slabs, v.B), dim3(256), lds, s, v, k, n_new, slab0);
   return RKV_OK;
 }
 static int launch_row_keys_of(const rkv_cache* c, const __half* k, int n_new, int max_slabs, int slab0, hipStream_t s) {

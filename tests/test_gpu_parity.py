@@ -1825,7 +1825,8 @@ def test_sink_selection_and_retention_sizes(T, k):
     assert s["count"].tolist() == [0] * B and (s["pos"] == -1).all() and cache.length == 0
 
 
-@pytest.mark.parametrize("hkv,g,bits,group", [(12, 4, 2, 128), (40, 4, 3, 128), (6, 2, 4, 128), (10, 2, 2, 32), (32, 4, 2, 64)])
+@pytest.mark.parametrize("hkv,g,bits,group", [(12, 4, 2, 128), (40, 4, 3, 128), (6, 2, 4, 128), (10, 2, 2, 32), (32, 4, 2, 64),
+                                              (40, 4, 2, 64), (32, 4, 4, 64), (32, 4, 3, 64), (62, 2, 2, 128), (26, 2, 2, 32)])
 def test_whole_row_reorder_few_tokens_equal_bulk(hkv, g, bits, group):
     """Appends of few tokens share a tile among four wave sets, one bulk append takes one set per tile: codes
     and metadata are the same (numbers of rotation groups that four divides and does not; pieces that end inside a tile
