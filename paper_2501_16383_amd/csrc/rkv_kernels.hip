@@ -46,9 +46,11 @@ __global__ void k_fill_zero(uint4* p, size_t n16) {
   for (; i < n16; i += stride) p[i] = z;
 }
 
-// The identity reorder's tables
-__global__ void k_init_tables(RkvView v) {
+// The identity reorder's tables; zeros (x16 16-byte pieces, fewer than channels) in those of the append
+// kernel's variants, which not every configuration fills: a new cache has the same bytes whatever its memory held
+__global__ void k_init_tables(RkvView v, uint4* xt, int x16) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < x16) xt[i] = make_uint4(0, 0, 0, 0);
   if (i < v.E) {
     v.perm[i] = i;
     v.pinv[i] = i;
@@ -112,7 +114,10 @@ int rkv_launch_init(rkv_cache* c, bool tables, hipStream_t s) {
   const int S = v.max_sinks > 0 ? v.max_sinks : 1;
   hipLaunchKernelGGL(k_reset, dim3((unsigned)blocks), dim3(256), 0, s, (uint4*)c->base, n16, (size_t)((char*)v.sink_pos - c->base) / 16,
                      v.B * S);
-  if (tables) hipLaunchKernelGGL(k_init_tables, dim3((v.E + 255) / 256), dim3(256), 0, s, v);
+  if (tables) {
+    const size_t off = (size_t)((char*)v.xgsel - c->base);  // (both tables, to the end of the block)
+    hipLaunchKernelGGL(k_init_tables, dim3((v.E + 255) / 256), dim3(256), 0, s, v, (uint4*)v.xgsel, (int)((c->bytes - off) / 16));
+  }
   if (tables) hipLaunchKernelGGL(k_init_rope, dim3((v.Tpad * 64 + 255) / 256), dim3(256), 0, s, v);
   if (tables) hipLaunchKernelGGL(k_init_hop, dim3(8), dim3(256), 0, s, v.hop, v.rope_style);
   if (tables) c->blocks_aligned = 1;

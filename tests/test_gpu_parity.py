@@ -2028,6 +2028,25 @@ def test_a_query_that_is_not_finite_stays_in_its_own_rows(hq, g, nq, sinks):
         assert np.array_equal(out[~hit], good[~hit]), (path, chunk)
 
 
+@pytest.mark.parametrize("hkv,g,span,bits,group,sinks", [(4, 4, 128, 2, 128, 4), (1, 1, 128, 2, 128, 0), (2, 2, 256, 3, 64, 1), (5, 1, 640, 4, 32, 3), (128, 4, 128, 2, 128, 2)])
+def test_creation_writes_every_byte_of_the_cache(hkv, g, span, bits, group, sinks):
+    """The block a caller hands over has the same bytes after creation whatever it held before."""
+    import ctypes
+    cfg = R.RkvConfig(batch=1, n_q_heads=hkv, n_kv_heads=hkv, max_tokens=33, max_sinks=sinks, rot_heads=g, perm_span=span, bits=bits, quant_group=group)
+    lib, n = R.load_library(), R.query_sizes(cfg)[0]
+    images = []
+    for fill in (0, 0xAB):
+        mem = torch.full((n + 256,), fill, dtype=torch.uint8, device="cuda")
+        at = -mem.data_ptr() % 256
+        h, cc = ctypes.c_void_p(), cfg.to_c()
+        assert lib.rkv_cache_create(ctypes.byref(cc), mem.data_ptr() + at, n, torch.cuda.current_stream().cuda_stream, ctypes.byref(h)) == 0
+        torch.cuda.synchronize()
+        images.append(mem[at:at + n].clone())
+        assert bool((mem[:at] == fill).all()) and bool((mem[at + n:] == fill).all())
+        lib.rkv_cache_destroy(h)
+    assert torch.equal(images[0], images[1])
+
+
 def test_chunk_size_hook_is_checked():
     cache = R.RkvCache(R.RkvConfig(batch=1, n_q_heads=2, n_kv_heads=2, max_tokens=64, rot_heads=2))
     for bad in (-1, 1, 64, 512):
