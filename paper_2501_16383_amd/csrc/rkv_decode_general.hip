@@ -429,7 +429,7 @@ int rkv_launch_decode_general(rkv_cache* c, const __half* q, const int* q_pos, i
   const size_t qbytes = rkv_query_scratch_bytes(v.B, v.Hq);
   float* part = (float*)((char*)scratch + qbytes);
   const int nch = (v.len + GEN_CHUNK - 1) / GEN_CHUNK;
-  rkv_launch_prep_q(v, q, q_pos, c->cur_k ? 1 : 0, qr, 1, nqt, s);
+  rkv_launch_prep_q(v, q, q_pos, c->cur_k ? 1 : 0, qr, -1, nqt, s);
   const int rep = v.Hq / v.Hkv, nq = rep * v.g;
   const size_t lds = ((size_t)nq * RKV_D + (size_t)nq * GEN_CHUNK + 2 * (size_t)v.gm * GEN_CHUNK + 2 * nq) * 4;
   dim3 grid(nch, v.NRG, v.B);

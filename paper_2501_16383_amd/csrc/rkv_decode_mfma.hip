@@ -9,8 +9,10 @@
 // (H_n = H_g (x) H_128 for the grouped-head rotation of Sec. 4.2; Eq. 7 folded in).  The sum over
 // the blocks is a second, tiny matrix product on v_mfma_f32_4x4x4_16b_f16 (16 independent 4x4x4
 // products per instruction): rows = the token's fp16 scales signed by a row of H_g, columns = the
-// blocks' results, which are exact in fp16; the zero-point term is one more such product.  The
-// vector ALU does RoPE and the dot with the query (Eq. 5).  p.V runs on the same instruction with the codes as the FP4
+// blocks' results, which are exact in fp16.  Codes are centred on their middle value (the big product of channel 0 starts
+// at minus its share of it), the zero-points with them: channel 0 is then no larger than the others, which halves the error of
+// the scores (30 drawn calls of one query head per KV head: 0.56 times the distance from 64-bit attention).  The
+// vector ALU does RoPE - on the query, see the key phase - and the dot with the query (Eq. 5).  p.V runs on the same instruction with the codes as the FP4
 // operand and the softmax weights p_t * scale_t as the other: each weight is scaled by a power of
 // two per (head, chunk) to a 24-bit integer and split into six base-16 digits, which FP8 (E4M3)
 // holds exactly.  All products are then small half-integers of similar size, so the instruction's
@@ -21,9 +23,13 @@
 //   phase K  wave w: four or two tiles of 16 tokens.  A = codes [16 tokens x 128], B = H_128 tile
 //            [128 x 16 channels]; lane (n, q) of the result holds channel 16*tile + n of tokens
 //            4q..4q+3.  Scores are reduced over the 16 channel lanes with DPP and go to LDS.
-//   phase S  wave a: softmax statistics of head a over the chunk, weights -> FP8 digits in LDS.
-//   phase V  wave w: channels 32w..32w+31 of every head; A = weight digits [16 x (4 heads x 32
-//            tokens)], block-diagonal over heads, B = codes [(4 heads x 32 tokens) x 16 channels].
+//   phase S  wave: softmax statistics of head a = wave mod G over the chunk, weights -> FP8 digits in the wave's own LDS.
+//   phase V  the same wave: rows = the head's six digits, contraction over 128 tokens of the head, columns = 16
+//            channels: sixteen products per wave, and no workgroup barrier between S and V.  (With rows = 4 heads x 4
+//            digits of one 32-token slab, block-diagonal over the heads, there were 32 of 33 cycles each.)
+// What an instruction costs on this chip (cycles of a SIMD, four waves on it, measured): 16x16x128 FP4 product 16.6,
+// FP8 x FP4 33, 4x4x4 8.3, float multiply-add 2.4, conversion, permute or lane move 4.2; matrix and vector
+// instructions add up but for two of the latter per product.
 // Covers: reorder that keeps 128-blocks, rot_heads 2 or 4, codes of 2 to 4 bits in groups of 128;
 // both RoPE pairings (the Hadamard operand tiles are built so that tiles p and p + 4 yield the two
 // channels of a pair); one query head per KV head and one query token.  Several of either are
@@ -43,7 +49,7 @@ typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 static_assert(MF_CH == 256, "the per-sequence chunk table (k_lens) counts chunks of 256 tokens");
 static_assert(MF_CH == RKV_MFMA_CHUNK, "the work-space size of a call is worked out from RKV_MFMA_CHUNK");
 #define MF_OCC 3           // workgroups per compute unit the register budget is set for
-#define MF_OCC_HI 2        // the same for the variants that hold a second plane of codes of four heads (three would spill)
+#define MF_OCC_HI 2        // the same for the variants that hold a second plane of codes of four heads over whole chunks (three would spill)
 
 __device__ __forceinline__ v4h as_v4h(uint32_t a, uint32_t b) {
   union { uint32_t u[2]; v4h h; } c;
@@ -161,36 +167,33 @@ __device__ __forceinline__ float row_transpose_reduce(const float (&v)[NV], int 
 // row, whose scores k_scores_row computes; qt then points to that buffer.  Softmax, values and
 // partial results as in the plain kernel.
 template <int G, int REP, bool MULTI, bool META8, int HB, int SUB = 0, bool ALU = false, bool PRE = false, int TILES = MF_TILES>
-__global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_decode_mfma(RkvView v, const float* __restrict__ qt,
+__global__ void __launch_bounds__(256, (HB && G == 4 && TILES == 4) ? MF_OCC_HI : MF_OCC) k_decode_mfma(RkvView v, const float* __restrict__ qt,
                                                                        float* __restrict__ part, int nch,
                                                                        const int* __restrict__ q_lim, int nq, int ns, uint32_t inv_ns, uint32_t inv_nrg) {
   constexpr bool HI = HB != 0;
   constexpr int CH = 64 * TILES;                 // tokens per workgroup (4 waves)
   constexpr int NH = G * REP;                    // query heads served by this workgroup: REP per KV head
-  __shared__ float s_sc[NH][CH];
-  // Weight digits of phase S for the matrix products of phase V.  The operand [16 rows = 4 heads x
-  // 4 digits][128 = 4 heads x 32 tokens] is block-diagonal over the heads, so only the 32 token
-  // bytes of each row are kept, [slab][digit set][row][token], followed by one 16-byte piece of
-  // zeros that the lanes holding the operand's empty parts read instead.
-  constexpr int SA_ZERO = 16 * 32, SA_SET = SA_ZERO + 16;
+  constexpr float MID = HB == 0 ? 1.5f : HB == 1 ? 3.5f : 7.5f;     // middle code
+  __shared__ __attribute__((aligned(16))) float s_sc[NH][CH];
+  // Weight digits of phase S for the matrix products of phase V, a part of its own for each wave: [query head][sub-block][digit] rows
+  // of a byte per token (rows of a stride that spreads the operand's sixteen-byte pieces over the banks)
   constexpr int NS = SUB ? SUB : 1;              // sub-blocks of a value head (groups of 64 / 32): weights per sub-block
-  constexpr size_t SA_BYTES = (size_t)NS * (CH / 32) * 2 * SA_SET;
-  __shared__ __attribute__((aligned(16))) uint8_t s_A_raw[SA_BYTES];
-  uint8_t (*const s_A)[CH / 32][2][SA_SET] = reinterpret_cast<uint8_t (*)[CH / 32][2][SA_SET]>(s_A_raw);
-  __shared__ float s_m[4], s_l[4], s_zs[NS][4], s_wsc[NS][4];
+  constexpr int DROW = CH + 16;
+  __shared__ __attribute__((aligned(16))) uint8_t s_dig[4][REP * NS * 6 * DROW];
   __shared__ int s_sink[64];
   __shared__ uint4 s_H[8][64];                   // Hadamard operand tiles
   __shared__ float2 s_step[64];                  // RoPE rotation by 16 positions, per channel pair
-  __shared__ uint4 s_q[4][4][G / 2][16];         // key phase: [r][p][f / 4][n] x 4 floats f % 4, f = 2 * KV head + (lo, hi); version r: at position pos - r
+  __shared__ float s_c2[64];                     // 2 cos of one position's angle, per channel pair
+  __shared__ uint4 s_q[2][4][G / 2][16];         // key phase: [r - 1][p][f / 4][n] x 4 floats f % 4, f = 2 * KV head + (lo, hi); version r: at position pos - r
   // Metadata of the chunk's keys and values (plain variants): fetched once, at the start, token by
   // token, and kept in LDS - a tile's worth held in registers a whole tile ahead of its use costs
-  // 16 registers, which is the difference between three and four workgroups per compute unit
+  // 16 registers.
   // They are stored there in the form their users take: per token the scales of the group's blocks
   // as packed fp16 pairs (s_ks, key phase: the A operand of the small matrix products, up to signs), for the
   // values (scale, zero-point) per head (s_vm) - whatever the storage format was.  The keys'
   // zero-points never reach the key phase: H_128 of a constant block is 128 z e_0, so they only
   // touch channel 0 of every head, k^[a][0] -= (2 / sqrt(n)) * 64 * Z_a(t) with
-  // Z_a(t) = sum_blk H_g[a][blk] * scale_blk * zero_blk, and channel 0 is one half of RoPE pair 0,
+  // Z_a(t) = sum_blk H_g[a][blk] * scale_blk * (zero_blk - the middle code), and channel 0 is one half of RoPE pair 0,
   // whose angle at token t is t itself.  Their share of the score of (token t, query head h),
   //     - 64 * Z_a(t) * (cos(t) * q~[h][pair 0, first half] + sin(t) * q~[h][pair 0, second half]),
   // is worked out once per token when the metadata are staged and put where the key phase adds
@@ -198,7 +201,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
   constexpr bool LM = SUB == 0;
   constexpr int MWL = META8 ? G / 2 : G;             // metadata dwords per token and rotation group as stored
   constexpr int GP = G / 2;                          // packed pairs per token
-  __shared__ __attribute__((aligned(16))) uint32_t s_ks[CH * GP], s_vm[LM ? CH * G : 1];
+  __shared__ __attribute__((aligned(16))) uint32_t s_ks[CH * GP], s_vm[LM ? G : 1][LM ? CH : 4];
   static_assert(SUB == 0 || PRE, "groups of 64 / 32 run on precomputed scores");
   static_assert(!ALU || (!META8 && HB == 0 && !MULTI), "the arithmetic-only measurement exists for the plain 2-bit variants");
   static_assert(!PRE || CH == 256, "precomputed scores: a thread per token of the chunk");
@@ -278,9 +281,9 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
   //  - Hadamard operand tiles (the key phase reads two of them per step)
   const uint4 ld_h0 = reinterpret_cast<const uint4*>(v.hop)[tid], ld_h1 = reinterpret_cast<const uint4*>(v.hop)[tid + 256];
   //  - queries of this rotation group, already RoPE'd, scaled and laid out as s_q by k_prep_q
-  constexpr int Q16 = 4 * 16 * 4 * 2 * G / 4;            // 16-byte pieces in all
+  constexpr int Q16 = 2 * 16 * 4 * 2 * G / 4;            // 16-byte pieces in all
   constexpr int QN = (Q16 + 255) / 256;                  // per thread
-  const uint4* q_src = reinterpret_cast<const uint4*>(qt + ((size_t)b * v.NRG + rg) * (4 * 16 * 4 * 2 * G));
+  const uint4* q_src = reinterpret_cast<const uint4*>(qt + ((size_t)b * v.NRG + rg) * (2 * 16 * 4 * 2 * G));
   uint4 ld_q[QN];
 #pragma unroll
   for (int i = 0; i < QN; ++i) ld_q[i] = tid + 256 * i < Q16 ? q_src[tid + 256 * i] : make_uint4(0, 0, 0, 0);
@@ -288,6 +291,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
   //    comes rotated back by 0..3 positions to make up for it (k_prep_q).  The next tile follows by
   //    rotating 16 positions (table row 16; used once per tile, read from LDS)
   const float2 ld_step = v.rope[16 * 64 + (tid & 63)];
+  const float ld_c2 = 2.0f * v.rope[64 + (tid & 63)].x;
   //  - the sink list: positions unconditionally (the store holds max_sinks of them, unused ones -1), masked by the count below
   const int ld_cnt = v.max_sinks > 0 ? v.sink_cnt[b] : 0;
   const int ld_spos = (v.max_sinks > 0 && (tid & 63) < v.max_sinks) ? v.sink_pos[b * v.max_sinks + (tid & 63)] : -1;
@@ -295,7 +299,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
   //    pair 0 and the queries' entries for that pair: staged below
   uint32_t ld_mk[4] = {0, 0, 0, 0}, ld_mv[4] = {0, 0, 0, 0};
   float2 ld_cs0 = make_float2(0.f, 0.f);
-  float4 ld_q0[G / 2];
+  float ld_q0[G][2];
   if constexpr (!PRE) {
     const size_t mi = ((size_t)(b * v.NRG + rg) * v.Tpad + t0 + tid) * MWL;
     auto fetch = [&](const uint32_t* g, uint32_t (&d)[4]) {
@@ -315,9 +319,14 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
       fetch(v.vm + mi, ld_mv);
       ld_cs0 = v.rope[(size_t)(t0 + tid) * 64];
     }
-    // entry (r = 0, p = 0, n = 0) of the prepared queries: floats f % 4 of piece f / 4, f = 2 * head + half
+    // channel pair 0 of the queries at their own position (the plain copy, in front of the other), scaled like the other
+    const float* q_nat = qt - (size_t)v.B * v.Hq * RKV_D + ((size_t)b * v.Hq + rg * G) * RKV_D;
+    const float lane_scale = 2.0f * rsqrtf((float)v.n);
 #pragma unroll
-    for (int i = 0; i < G / 2; ++i) ld_q0[i] = reinterpret_cast<const float4*>(q_src)[i * 16];
+    for (int i = 0; i < G; ++i) {
+      ld_q0[i][0] = q_nat[i * RKV_D] * lane_scale;
+      ld_q0[i][1] = q_nat[i * RKV_D + (v.rope_style ? 1 : 64)] * lane_scale;
+    }
   }
   //  - the RoPE angles of this lane's first token and the first key tile: in the key phase below
   [[maybe_unused]] int per_query = 1;            // query heads of a KV head per query token
@@ -367,12 +376,10 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
           if constexpr (MULTI) seen = seen && t0 + tid <= q_lim[b * nq + (rrg * REP + rri) / per_query];
           pre[a * REP + rri] = seen ? qt[((size_t)b * v.Hq + qh) * v.Tpad + t0 + tid] : -INFINITY;
         }
-      uint4* a4 = reinterpret_cast<uint4*>(s_A_raw);
-      for (int i = tid; i < (int)(SA_BYTES / 16); i += 256) a4[i] = make_uint4(0, 0, 0, 0);
       if (tid < 64) s_sink[tid] = tid < cnt ? ld_spos : -1;
       if constexpr (LM) {
 #pragma unroll
-        for (int i = 0; i < G; ++i) s_vm[tid * G + i] = dv[i];
+        for (int i = 0; i < G; ++i) s_vm[i][tid] = dv[i];
       }
 #pragma unroll
       for (int a = 0; a < NH; ++a) s_sc[a][tid] = pre[a];
@@ -416,10 +423,6 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
       };
       load_tile(0);
       // (the requests are all out: what came back goes to LDS)
-      {
-        uint4* a4 = reinterpret_cast<uint4*>(s_A_raw);
-        for (int i = tid; i < (int)(SA_BYTES / 16); i += 256) a4[i] = make_uint4(0, 0, 0, 0);
-      }
       (&s_H[0][0])[tid] = ld_h0;
       (&s_H[0][0])[tid + 256] = ld_h1;
     #pragma unroll
@@ -427,6 +430,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
       if (tid + 256 * i < Q16) (&s_q[0][0][0][0])[tid + 256 * i] = ld_q[i];
       if (tid < 64) {
         s_step[tid] = ld_step;
+        s_c2[tid] = ld_c2;
         s_sink[tid] = tid < cnt ? ld_spos : -1;              // complete after the barrier that precedes the key phase
       }
       if (CH == 256 || tid < CH) {                     // thread = token of the chunk (inside the padded allocation)
@@ -478,23 +482,21 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
           for (int a = 0; a < G; ++a) {
             float Z = 0.f;
     #pragma unroll
-            for (int i = 0; i < G; ++i) Z = fmaf((__popc(a & i) & 1) ? -sf[i] : sf[i], zf[i], Z);
-                const float4 q4 = ld_q0[a >> 1];                     // entry (r = 0, p = 0, n = 0) of the prepared query: floats 2a, 2a + 1
-            const float ql = (a & 1) ? q4.z : q4.x, qh = (a & 1) ? q4.w : q4.y;
-            s_sc[a][tid] = t0 + tid < len ? -64.0f * Z * fmaf(cs0.x, ql, cs0.y * qh) : -INFINITY;
+            for (int i = 0; i < G; ++i) Z = fmaf((__popc(a & i) & 1) ? -sf[i] : sf[i], zf[i] - MID, Z);
+            s_sc[a][tid] = t0 + tid < len ? -64.0f * Z * fmaf(cs0.x, ld_q0[a][0], cs0.y * ld_q0[a][1]) : -INFINITY;
           }
         }
         if constexpr (META8 || ALU) {                      // values: (scale, zero-point) per head
           pairs(dv, sp, zp);
-          s_vm[tid * G] = __builtin_amdgcn_perm(zp[0], sp[0], 0x05040100u);
-          s_vm[tid * G + 1] = __builtin_amdgcn_perm(zp[0], sp[0], 0x07060302u);
+          s_vm[0][tid] = __builtin_amdgcn_perm(zp[0], sp[0], 0x05040100u);
+          s_vm[1][tid] = __builtin_amdgcn_perm(zp[0], sp[0], 0x07060302u);
           if constexpr (G == 4) {
-            s_vm[tid * G + 2] = __builtin_amdgcn_perm(zp[1], sp[1], 0x05040100u);
-            s_vm[tid * G + 3] = __builtin_amdgcn_perm(zp[1], sp[1], 0x07060302u);
+            s_vm[2][tid] = __builtin_amdgcn_perm(zp[1], sp[1], 0x05040100u);
+            s_vm[3][tid] = __builtin_amdgcn_perm(zp[1], sp[1], 0x07060302u);
           }
         } else {
     #pragma unroll
-          for (int i = 0; i < G; ++i) s_vm[tid * G + i] = dv[i];
+          for (int i = 0; i < G; ++i) s_vm[i][tid] = dv[i];
         }
       }
       __syncthreads();        // LDS copies of the Hadamard operand and the query are complete; first tile already in flight
@@ -556,67 +558,65 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
         // instead of behind it: one sequence x 4096 tokens, half chunks, 9.4 -> 10.0 us.)
 #pragma unroll
         for (int pass = 0; pass < 1; ++pass) {
+        const float centre = n == 0 ? -64.0f * MID : 0.f;  // channel 0 of H_128 of the constant MID / 2
+        const v4f centre4 = {centre, centre, centre, centre};
         float pt[4 * G];                                   // [token of the lane][KV head]
 #pragma unroll
         for (int i = 0; i < 4 * G; ++i) pt[i] = 0.f;
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-          // H_128 of the raw codes for channels 16p + n (lo) and 16p + n + 64 (hi) - or the even and the odd
-          // channel of pair 16p + n -: half-integers, exact
-          v4f lo[G], hi[G];
-          {
-            v8i Hlo, Hhi;
-            const uint4 h0 = s_H[p][lane], h1 = s_H[p + 4][lane];
-            Hlo[0] = (int)h0.x; Hlo[1] = (int)h0.y; Hlo[2] = (int)h0.z; Hlo[3] = (int)h0.w; Hlo[4] = Hlo[5] = Hlo[6] = Hlo[7] = 0;
-            Hhi[0] = (int)h1.x; Hhi[1] = (int)h1.y; Hhi[2] = (int)h1.z; Hhi[3] = (int)h1.w; Hhi[4] = Hhi[5] = Hhi[6] = Hhi[7] = 0;
-            const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+          // k^[a] = sum_blk H_g[a][blk] * scale_blk * u_blk for the channels 16p + n and 16p + n + 64 - or the even and the odd
+          // channel of pair 16p + n -, u = H_128 of the raw codes: half-integers, exact
+          const float c = cs_c[p], s = cs_s[p], cc = s_c2[16 * p + n];  // angles of token 4q
+          v4f k[2][4];
 #pragma unroll
-            for (int blk = 0; blk < G; ++blk) {
-              lo[blk] = mfma_fp4(A[blk], Hlo, zero4);
-              hi[blk] = mfma_fp4(A[blk], Hhi, zero4);
+          for (int half = 0; half < 2; ++half) {
+            v4f u[G];
+            {
+              v8i H;
+              const uint4 h0 = s_H[p + 4 * half][lane];
+              H[0] = (int)h0.x; H[1] = (int)h0.y; H[2] = (int)h0.z; H[3] = (int)h0.w; H[4] = H[5] = H[6] = H[7] = 0;
+              const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+              for (int blk = 0; blk < G; ++blk) u[blk] = mfma_fp4(A[blk], H, p == 0 && half == 0 ? centre4 : zero4);
+              if constexpr (HI) {
+                // FP4 1.0 (0x2) and -1.0 (0xA) with bit 2 set are 4.0 and -4.0
+#pragma unroll
+                for (int i = 0; i < 4; ++i) H[i] |= 0x44444444;
+#pragma unroll
+                for (int blk = 0; blk < G; ++blk) u[blk] = mfma_fp4(Ah[blk], H, u[blk]);
+              }
             }
-            if constexpr (HI) {
-              // FP4 1.0 (0x2) and -1.0 (0xA) with bit 2 set are 4.0 and -4.0
+            // The butterfly H_g over the blocks with their scales: 16 independent 4x4x4 products per instruction - block = (token
+            // 4q + r, 4 channel lanes), A row a = signed fp16 scales, B = the four blocks' results (exact in fp16), fp32 accumulate
 #pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                Hlo[i] |= 0x44444444;
-                Hhi[i] |= 0x44444444;
-              }
-#pragma unroll
-              for (int blk = 0; blk < G; ++blk) {
-                lo[blk] = mfma_fp4(Ah[blk], Hlo, lo[blk]);
-                hi[blk] = mfma_fp4(Ah[blk], Hhi, hi[blk]);
-              }
+            for (int r = 0; r < 4; ++r) {
+              const v4f z4 = {0.f, 0.f, 0.f, 0.f};
+              if constexpr (G == 4) k[half][r] = mfma_4x4x4(sA[r], as_v4h(pk_f16(u[0][r], u[1][r]), pk_f16(u[2][r], u[3][r])), z4);
+              else k[half][r] = mfma_4x4x4(sA[r], as_v4h(pk_f16(u[0][r], u[1][r]), 0u), z4);
             }
           }
-          const float c = cs_c[p], s = cs_s[p];                // angles of token 4q
+          // RoPE is put on the query: <R(4q + r) k, q~> = <k, x_r>, x_r the query rotated back to token 4q + r.  Tokens 4q + 1 and
+          // 4q + 2 from the query's two copies, their neighbours by x(t + 1) + x(t - 1) = 2 cos(1) x(t), one multiply-add per
+          // number: twelve operations for four tokens where rotating each key took sixteen (and eight for the dot products in
+          // either form).  16 sequences x 4096 tokens, 40 heads: 76.4 -> 71.4 us a step.
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            // k^[a] = sum_blk H_g[a][blk] * scale_blk * u_blk   (H_g butterfly over the blocks)
-            // as 16 independent 4x4x4 products per instruction: block = (token 4q + r, 4 channel
-            // lanes), A row a = signed fp16 scales, B = the four blocks' results (half-integers
-            // below 1024: exact in fp16), fp32 accumulate
-            const v4f z4 = {0.f, 0.f, 0.f, 0.f};
-            v4f klo, khi;
-            if constexpr (G == 4) {
-              klo = mfma_4x4x4(sA[r], as_v4h(pk_f16(lo[0][r], lo[1][r]), pk_f16(lo[2][r], lo[3][r])), z4);
-              khi = mfma_4x4x4(sA[r], as_v4h(pk_f16(hi[0][r], hi[1][r]), pk_f16(hi[2][r], hi[3][r])), z4);
-            } else {
-              klo = mfma_4x4x4(sA[r], as_v4h(pk_f16(lo[0][r], lo[1][r]), 0u), z4);
-              khi = mfma_4x4x4(sA[r], as_v4h(pk_f16(hi[0][r], hi[1][r]), 0u), z4);
-            }
-            // the query: the copy rotated back by r positions
-            float qv[2 * G];
+          for (int i = 0; i < 2 * G; i += 4) {
+            const uint4 w1 = s_q[0][p][i / 4][n], w2 = s_q[1][p][i / 4][n];
+            const float q1[4] = {__uint_as_float(w1.x), __uint_as_float(w1.y), __uint_as_float(w1.z), __uint_as_float(w1.w)};
+            const float q2[4] = {__uint_as_float(w2.x), __uint_as_float(w2.y), __uint_as_float(w2.z), __uint_as_float(w2.w)};
 #pragma unroll
-            for (int i = 0; i < 2 * G; i += 4) {
-              const uint4 u = s_q[r][p][i / 4][n];
-              qv[i] = __uint_as_float(u.x); qv[i + 1] = __uint_as_float(u.y); qv[i + 2] = __uint_as_float(u.z); qv[i + 3] = __uint_as_float(u.w);
-            }
+            for (int a2 = 0; a2 < 2; ++a2) {
+              const int a = i / 2 + a2;
 #pragma unroll
-            for (int a = 0; a < G; ++a) {
-              const float xl = klo[a] * c - khi[a] * s;
-              const float xh = klo[a] * s + khi[a] * c;
-              pt[r * G + a] = fmaf(xh, qv[2 * a + 1], fmaf(xl, qv[2 * a], pt[r * G + a]));
+              for (int half = 0; half < 2; ++half) {
+                const float x1 = half == 0 ? q1[2 * a2] * c + q1[2 * a2 + 1] * s : q1[2 * a2 + 1] * c - q1[2 * a2] * s;
+                const float x2 = half == 0 ? q2[2 * a2] * c + q2[2 * a2 + 1] * s : q2[2 * a2 + 1] * c - q2[2 * a2] * s;
+                pt[0 * G + a] = fmaf(k[half][0][a], fmaf(cc, x1, -x2), pt[0 * G + a]);
+                pt[1 * G + a] = fmaf(k[half][1][a], x1, pt[1 * G + a]);
+                pt[2 * G + a] = fmaf(k[half][2][a], x2, pt[2 * G + a]);
+                pt[3 * G + a] = fmaf(k[half][3][a], fmaf(cc, x2, -x1), pt[3 * G + a]);
+              }
             }
           }
         }
@@ -641,16 +641,21 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
     }
     }
     __builtin_amdgcn_s_setprio(3);
-    // Groups of 64 / 32: the V metadata of the four tokens this lane turns into weights in phase S (head = wave)
-    // - otherwise they are in LDS
-    [[maybe_unused]] uint32_t vmeta[NS][CH / 64];
+    // ------------------------------------------------------------------ phases S and V
+    // wave -> KV head a, channel tiles: all eight (G = 4), or one half of them (G = 2; the head's two waves make the same digits)
+    constexpr int NB = G == 4 ? 4 : 2;             // blocks of 32 channels per wave
+    constexpr int NQ = CH / 128;                   // contractions of 128 tokens
+    constexpr int NT = CH / 64;                    // tokens of a lane in phase S: consecutive ones
+    const int a = wave & (G - 1), wb = G == 4 ? 0 : (wave >> 1) * 2;
+    // Groups of 64 / 32: the V metadata of the lane's tokens - otherwise they are in LDS
+    [[maybe_unused]] uint32_t vmeta[NS][NT];
     if constexpr (SUB != 0) {
 #pragma unroll
-      for (int i = 0; i < CH / 64; ++i) {
-        const size_t mi = ((size_t)(b * v.NRG + rg) * v.Tpad + t0 + lane + 64 * i) * (G * NS);
+      for (int i = 0; i < NT; ++i) {
+        const size_t mi = ((size_t)(b * v.NRG + rg) * v.Tpad + t0 + NT * lane + i) * (G * NS);
         if constexpr (META8) {
           // the head's NS scale bytes and NS zero-point bytes, one load each
-          const uint8_t* vm8 = reinterpret_cast<const uint8_t*>(v.vm) + 2 * mi + (wave < G ? wave : 0) * NS;
+          const uint8_t* vm8 = reinterpret_cast<const uint8_t*>(v.vm) + 2 * mi + a * NS;
           uint32_t sw, zw;
           if constexpr (NS == 4) {
             sw = *reinterpret_cast<const uint32_t*>(vm8);
@@ -660,180 +665,197 @@ __global__ void __launch_bounds__(256, (HB && G == 4) ? MF_OCC_HI : MF_OCC) k_de
             zw = *reinterpret_cast<const uint16_t*>(vm8 + G * NS);
           }
 #pragma unroll
-          for (int sb = 0; sb < NS; ++sb)
-            vmeta[sb][i] = wave < G ? __builtin_amdgcn_perm(zw, sw, 0x0c0c0000u | ((4u + sb) << 8) | sb) : 0x8000u;
+          for (int sb = 0; sb < NS; ++sb) vmeta[sb][i] = __builtin_amdgcn_perm(zw, sw, 0x0c0c0000u | ((4u + sb) << 8) | sb);
         } else {
 #pragma unroll
-          for (int sb = 0; sb < NS; ++sb) vmeta[sb][i] = wave < G ? v.vm[mi + wave * NS + sb] : 0u;
+          for (int sb = 0; sb < NS; ++sb) vmeta[sb][i] = v.vm[mi + a * NS + sb];
         }
       }
     }
-    const bool has_head = q < G;
     const uint4* vslab = reinterpret_cast<const uint4*>(v.vc + rkv_v_slabbase(v, b, rg, t0 >> 5));
     const uint32_t* vhslab = HI ? v.vh + (rkv_v_slabbase(v, b, rg, t0 >> 5) >> (HB == 1 ? 1 : 0)) : nullptr;
-    const int lidx = wave * (16 * G) + (has_head ? lane : 0);
-    const int nslab = min(CH / 32, (len - t0 + 31) >> 5);
-    // the softmax and value phases run once per query head of a KV head; the V codes are requested
-    // again each time (from L2 after the first), which is cheaper than holding them across the loop
-#pragma unroll 1
-    for (int rri = 0; rri < REP; ++rri) {
-    // all V codes of the chunk (one 16-byte load per lane and slab): in flight while the softmax phase runs
-    uint4 vcodes[CH / 32], vhcodes[HI ? CH / 32 : 1];
+    const int nslab = max(1, min(CH / 32, (len - t0 + 31) >> 5));   // (a chunk behind the query's position: weights of zero)
+    // all V codes of the chunk's share of the wave: in flight while the softmax phase runs.  Lane group q holds slab 4 s + q, 32 of
+    // the 128 tokens of a contraction (behind the sequence's end: the last one again, their weights are zero)
+    uint4 vcodes[NQ][NB], vhcodes[HI ? NQ : 1][HI ? NB : 1];
 #pragma unroll
-    for (int sl = 0; sl < CH / 32; ++sl) {
-      // (lanes without a head feed zeros to the products; slabs beyond the chunk's end are never used)
-      if constexpr (G < 4) vcodes[sl] = make_uint4(0, 0, 0, 0);
-      if constexpr (ALU) {
-        const uint32_t x = (uint32_t)lidx * 2654435761u ^ (uint32_t)(nq + sl);
-        if (has_head && sl < nslab) vcodes[sl] = make_uint4(x, x * 3u, x * 5u, x * 7u);
-      } else if (has_head && sl < nslab) vcodes[sl] = rkv_ld_stream(vslab + (size_t)sl * (64 * G) + lidx);
-      if constexpr (HI) {
-        vhcodes[sl] = make_uint4(0, 0, 0, 0);
-        if (has_head && sl < nslab) {
-          if constexpr (HB == 2) {
-            vhcodes[sl] = rkv_ld_stream(reinterpret_cast<const uint4*>(vhslab) + (size_t)sl * (64 * G) + lidx);
-          } else {
-            const uint2 u = rkv_ld_stream(reinterpret_cast<const uint2*>(vhslab) + (size_t)sl * (64 * G) + lidx);
-            vhcodes[sl] = make_uint4(u.x, u.y, 0, 0);
-          }
+    for (int s = 0; s < NQ; ++s)
+#pragma unroll
+      for (int w = 0; w < NB; ++w) {
+        const uint32_t li = (uint32_t)(min(4 * s + q, nslab - 1) * (64 * G) + ((wb + w) * G + a) * 16 + n);
+        if constexpr (ALU) {
+          const uint32_t x = li * 2654435761u ^ (uint32_t)(nq + s);
+          vcodes[s][w] = make_uint4(x, x * 3u, x * 5u, x * 7u);
+        } else {
+          vcodes[s][w] = rkv_ld_stream(vslab + li);
+        }
+        if constexpr (HB == 2) {
+          vhcodes[s][w] = rkv_ld_stream(reinterpret_cast<const uint4*>(vhslab) + li);
+        } else if constexpr (HB == 1) {
+          const uint2 u = rkv_ld_stream(reinterpret_cast<const uint2*>(vhslab) + li);
+          vhcodes[s][w] = make_uint4(u.x, u.y, 0, 0);
         }
       }
-    }
-    __syncthreads();
+    __syncthreads();                               // all scores are there
 
-    // ------------------------------------------------------------------ phase S
-    if (wave < G) {
-      const int a = wave;
-      float sv[CH / 64], w[CH / 64], zv[CH / 64];
+    // ---- phase S: the head's statistics over the chunk, its weights as rows of digits in the wave's own part of LDS
+    uint8_t* const dig = s_dig[wave];
+    float hm[REP], hl[REP], hzs[REP][NS], hdown[REP][NS];
+#pragma unroll
+    for (int rri = 0; rri < REP; ++rri) {
+      float sv[NT], w[NT], zv[NT];
+      if constexpr (NT == 4) {
+        const float4 x = *reinterpret_cast<const float4*>(&s_sc[a * REP + rri][4 * lane]);
+        sv[0] = x.x; sv[1] = x.y; sv[2] = x.z; sv[3] = x.w;
+      } else {
+        const float2 x = *reinterpret_cast<const float2*>(&s_sc[a * REP + rri][2 * lane]);
+        sv[0] = x.x; sv[1] = x.y;
+      }
+      [[maybe_unused]] uint32_t vmw[NT];
+      if constexpr (LM) {
+#pragma unroll
+        for (int i = 0; i < NT; ++i) vmw[i] = s_vm[a][NT * lane + i];
+      }
       float m = -INFINITY;
 #pragma unroll
-      for (int i = 0; i < CH / 64; ++i) {
-        sv[i] = s_sc[a * REP + rri][lane + 64 * i];
-        m = fmaxf(m, sv[i]);
-      }
+      for (int i = 0; i < NT; ++i) m = fmaxf(m, sv[i]);
       m = wave_allreduce<true>(m);
-      float pe[CH / 64], l = 0.f;
+      float pe[NT], l = 0.f;
 #pragma unroll
-      for (int i = 0; i < CH / 64; ++i) {
+      for (int i = 0; i < NT; ++i) {
         pe[i] = sv[i] > -INFINITY ? __expf(sv[i] - m) : 0.f;
         l += pe[i];
       }
-      l = wave_allreduce<false>(l);
+      hm[rri] = m;
+      hl[rri] = wave_allreduce<false>(l);
 #pragma unroll
       for (int sb = 0; sb < NS; ++sb) {                     // once, or once per sub-block of the head (its own scales and zero-points)
-      float wmax = 0.f;
+        float wmax = 0.f;
 #pragma unroll
-      for (int i = 0; i < CH / 64; ++i) {
-        float s_, z_;
-        if constexpr (LM) {                                 // token lane + 64 i, head a
-          rkv_unpack_meta(s_vm[(lane + 64 * i) * G + a], s_, z_);
-        } else if constexpr (META8) {
-          s_ = __builtin_amdgcn_cvt_f32_fp8((int)vmeta[sb][i], 0);
-          z_ = (float)((vmeta[sb][i] >> 8) & 0xffu) - 128.0f;
+        for (int i = 0; i < NT; ++i) {
+          float s_, z_;
+          if constexpr (LM) {
+            rkv_unpack_meta(vmw[i], s_, z_);
+          } else if constexpr (META8) {
+            s_ = __builtin_amdgcn_cvt_f32_fp8((int)vmeta[sb][i], 0);
+            z_ = (float)((vmeta[sb][i] >> 8) & 0xffu) - 128.0f;
+          } else {
+            rkv_unpack_meta(vmeta[sb][i], s_, z_);
+          }
+          w[i] = pe[i] * s_;
+          zv[i] = z_;
+          wmax = fmaxf(wmax, w[i]);
+        }
+        wmax = wave_allreduce<true>(wmax);
+        // 24-bit fixed point: largest weight lands in [2^23, 2^24); six base-16 digits.  (It is a 24-bit integer as it
+        // stands, so no digit exceeds 15.)  A byte 0..15 read as E4M3 is that integer times 2^-9 - subnormals and the
+        // first binade are one straight line -: the bytes of the lane's weights are brought together and parted into
+        // their nibbles, nothing is converted
+        int ex = 0;
+        if (wmax > 0.f) frexpf(wmax, &ex);
+        const float up = ldexpf(1.0f, 24 - ex), down = ldexpf(1.0f, ex - 24);
+        float zs = 0.f;
+        uint32_t W[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+          W[i] = (uint32_t)rintf(w[i] * up);
+          zs += (float)W[i] * zv[i];
+        }
+        hzs[rri][sb] = wave_allreduce<false>(zs) * down;
+        hdown[rri][sb] = down;
+        const uint32_t p01 = __builtin_amdgcn_perm(W[1], W[0], 0x05010400u);       // bytes 0 of both, bytes 1 of both
+        uint32_t by[3];                                                            // byte j of all the lane's weights
+        by[2] = __builtin_amdgcn_perm(W[1], W[0], 0x0c0c0602u);
+        if constexpr (NT == 4) {
+          const uint32_t p23 = __builtin_amdgcn_perm(W[3], W[2], 0x05010400u);
+          by[2] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(W[3], W[2], 0x0c0c0602u), by[2], 0x05040100u);
+          by[0] = __builtin_amdgcn_perm(p23, p01, 0x05040100u);
+          by[1] = __builtin_amdgcn_perm(p23, p01, 0x07060302u);
         } else {
-          rkv_unpack_meta(vmeta[sb][i], s_, z_);
+          by[0] = p01 & 0xffffu;
+          by[1] = p01 >> 16;
         }
-        w[i] = pe[i] * s_;
-        zv[i] = z_;
-        wmax = fmaxf(wmax, w[i]);
-      }
-      wmax = wave_allreduce<true>(wmax);
-      // 24-bit fixed point: largest weight lands in [2^23, 2^24); six base-16 digits, exact in E4M3
-      int ex = 0;
-      if (wmax > 0.f) frexpf(wmax, &ex);
-      const float up = ldexpf(1.0f, 24 - ex), down = ldexpf(1.0f, ex - 24);
-      float zs = 0.f;
+        uint8_t* const dst = dig + (rri * NS + sb) * (6 * DROW) + NT * lane;
 #pragma unroll
-      for (int i = 0; i < CH / 64; ++i) {
-        const int tl = lane + 64 * i, slab = tl >> 5, tau = tl & 31;
-        const uint32_t W = (uint32_t)rintf(w[i] * up);
-        zs += (float)W * zv[i];
-        uint8_t* dst = &s_A[sb][slab][0][(4 * a) * 32 + tau];
-#pragma unroll
-        for (int k = 0; k < 6; k += 2) {
-          // digits 5-k and 4-k (most significant first): rows 0..3 of set 0, rows 0..1 of set 1
-          const float d_hi = (float)(k == 0 ? (W >> 20) : ((W >> (20 - 4 * k)) & 15u));
-          const float d_lo = (float)((W >> (16 - 4 * k)) & 15u);
-          const int pk = __builtin_amdgcn_cvt_pk_fp8_f32(d_hi, d_lo, 0, false);
-          const int row = k & 3, set = k >> 2;
-          dst[set * SA_SET + row * 32] = (uint8_t)(pk & 0xff);
-          dst[set * SA_SET + (row + 1) * 32] = (uint8_t)((pk >> 8) & 0xff);
+        for (int k = 0; k < 6; ++k) {                       // most significant first
+          const uint32_t dg = (k & 1) ? by[2 - k / 2] & 0x0f0f0f0fu : (by[2 - k / 2] >> 4) & 0x0f0f0f0fu;
+          if constexpr (NT == 4) *reinterpret_cast<uint32_t*>(dst + k * DROW) = dg;
+          else *reinterpret_cast<uint16_t*>(dst + k * DROW) = (uint16_t)dg;
         }
-      }
-      zs = wave_allreduce<false>(zs);
-      if (lane == 0) {
-        s_m[a] = m;
-        s_l[a] = l;
-        s_zs[sb][a] = zs * down;
-        s_wsc[sb][a] = down;
-      }
       }
     }
-    __syncthreads();
+    wave_lds_fence();
 
-    // ------------------------------------------------------------------ phase V
+    // ---- phase V: rows = 8 * query head + digit (the rows of digits that do not exist repeat one that does, their results are
+    // not used), contraction over 128 tokens, columns = 16 channels of the head
     {
-      // Operand lane (row n = 4 * head + digit, lane group q) covers contraction indices 32q..32q+31,
-      // which the V codes' layout assigns to head 2 * (second half of the 32) + (q >> 1), tokens
-      // 16 * (q & 1) .. + 15 of the slab: its first or second 16 bytes are that head's row, the
-      // rest of the operand is zero
-      const int vsub = SUB ? (wave * SUB) / 4 : 0;          // this wave's channels 32 wave .. + 31 lie in one sub-block of their head
-      const int arow = n >> 2;
-      const bool ause = (q >> 1) == (arow & 1);
-      const int adata = n * 32 + 16 * (q & 1);
-      const int aoff0 = (ause && (arow >> 1) == 0) ? adata : SA_ZERO;
-      const int aoff1 = (ause && (arow >> 1) == 1) ? adata : SA_ZERO;
-      v4f acc[2][2], acch[2][2];                            // [channel tile][digit set]; acch: the plane of the upper bits
+      const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+      v4f acc[2 * NB], acch[HI ? 2 * NB : 1];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) acc[i][0] = acc[i][1] = acch[i][0] = acch[i][1] = (v4f){0.f, 0.f, 0.f, 0.f};
+      for (int i = 0; i < 2 * NB; ++i) acc[i] = zero4;
+      if constexpr (HI) {
 #pragma unroll
-      for (int sl = 0; sl < CH / 32; ++sl) {
-        if (sl < nslab) {                                   // workgroup-uniform
-          v8i A[2];
+        for (int i = 0; i < 2 * NB; ++i) acch[i] = zero4;
+      }
+      const uint8_t* const row = dig + ((REP == 2 ? (n >> 3) * NS * 6 : 0) + min(n & 7, 5)) * DROW + 16 * q;
 #pragma unroll
-          for (int set = 0; set < 2; ++set) {
-            const uint4 a0 = *reinterpret_cast<const uint4*>(&s_A[vsub][sl][set][aoff0]);
-            const uint4 a1 = *reinterpret_cast<const uint4*>(&s_A[vsub][sl][set][aoff1]);
-            A[set][0] = (int)a0.x; A[set][1] = (int)a0.y; A[set][2] = (int)a0.z; A[set][3] = (int)a0.w;
-            A[set][4] = (int)a1.x; A[set][5] = (int)a1.y; A[set][6] = (int)a1.z; A[set][7] = (int)a1.w;
-          }
-          const v8i B0 = unpack_fp4(vcodes[sl].x, vcodes[sl].y), B1 = unpack_fp4(vcodes[sl].z, vcodes[sl].w);
+      for (int s = 0; s < NQ; ++s) {
+        if (4 * s < nslab) {                                // workgroup-uniform
+          v8i D;
 #pragma unroll
-          for (int set = 0; set < 2; ++set) {
-            acc[0][set] = mfma_fp8_fp4(A[set], B0, acc[0][set]);
-            acc[1][set] = mfma_fp8_fp4(A[set], B1, acc[1][set]);
-          }
-          if constexpr (HI) {
-            const v8i B0h = HB == 2 ? unpack_fp4(vhcodes[sl].x, vhcodes[sl].y) : unpack_fp4_bits(vhcodes[sl].x);
-            const v8i B1h = HB == 2 ? unpack_fp4(vhcodes[sl].z, vhcodes[sl].w) : unpack_fp4_bits(vhcodes[sl].y);
+          for (int w = 0; w < NB; ++w) {
+            if (w == 0 || (SUB == 4) || (SUB == 2 && NB == 4 && w == 2)) {
+              // FP8 operand: lane group q holds tokens 16 q .. + 15 and 64 + 16 q .. + 15 of the 128
+              const int sb = SUB == 4 ? wb + w : SUB == 2 ? (wb + w) >> 1 : 0;      // channels 32 (wb + w) .. + 31 lie in one sub-block
+              const uint4 d0 = *reinterpret_cast<const uint4*>(row + sb * 6 * DROW + 128 * s), d1 = *reinterpret_cast<const uint4*>(row + sb * 6 * DROW + 128 * s + 64);
+              D[0] = (int)d0.x; D[1] = (int)d0.y; D[2] = (int)d0.z; D[3] = (int)d0.w;
+              D[4] = (int)d1.x; D[5] = (int)d1.y; D[6] = (int)d1.z; D[7] = (int)d1.w;
+            }
 #pragma unroll
-            for (int set = 0; set < 2; ++set) {
-              acch[0][set] = mfma_fp8_fp4(A[set], B0h, acch[0][set]);
-              acch[1][set] = mfma_fp8_fp4(A[set], B1h, acch[1][set]);
+            for (int ct = 0; ct < 2; ++ct) {
+              const uint4 u = vcodes[s][w];
+              acc[2 * w + ct] = mfma_fp8_fp4(D, ct ? unpack_fp4(u.z, u.w) : unpack_fp4(u.x, u.y), acc[2 * w + ct]);
+              if constexpr (HI) {
+                const uint4 uh = vhcodes[s][w];
+                const v8i Bh = HB == 2 ? (ct ? unpack_fp4(uh.z, uh.w) : unpack_fp4(uh.x, uh.y)) : unpack_fp4_bits(ct ? uh.y : uh.x);
+                acch[2 * w + ct] = mfma_fp8_fp4(D, Bh, acch[2 * w + ct]);
+              }
             }
           }
         }
       }
-      if (has_head) {
-        const int qh = (rg * G + q) * rep + rrg * REP + rri;   // query head served for KV head rg*G + q
-        float* dst = part + (((size_t)b * v.Hq + qh) * nch + chunk) * RKV_PART_STRIDE;
-        const float wsc = 2.0f * s_wsc[vsub][q];            // FP4 nibble = code/2
+      // Lane groups 0 and 1 hold the upper four and the lower two digits of the first query head's results (2 and 3: of the
+      // second's).  They exchange half of the channel tiles each and put together the other half
+      const bool up4 = (q & 1) == 0;
+      float part_[2 * NB];
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-          v4f hi = acc[ct][0], lo = acc[ct][1];
-          if constexpr (HI) {
-            hi += acch[ct][0] * 4.0f;
-            lo += acch[ct][1] * 4.0f;
-          }
-          const float sum = ((((hi[0] * 16.0f + hi[1]) * 16.0f + hi[2]) * 16.0f + hi[3]) * 16.0f + lo[0]) * 16.0f + lo[1];
-          dst[4 + 16 * (2 * wave + ct) + n] = sum * wsc - s_zs[vsub][q];
-        }
-        if (wave == 0 && n == 0) {
-          dst[0] = s_m[q];
-          dst[1] = s_l[q];
+      for (int i = 0; i < 2 * NB; ++i) {
+        v4f h = acc[i];
+        if constexpr (HI) h += acch[i] * 4.0f;              // the upper plane counts fourfold
+        const float two = h[0] * 16.0f + h[1];
+        part_[i] = up4 ? ((two * 16.0f + h[2]) * 16.0f + h[3]) * 256.0f : two;
+      }
+      const int rr = q >> 1;
+      float* const dst = part + (((size_t)b * v.Hq + (rg * G + a) * rep + rrg * REP + (REP == 2 ? rr : 0)) * nch + chunk) * RKV_PART_STRIDE;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const float sum = (up4 ? part_[i] : part_[NB + i]) + __shfl_xor(up4 ? part_[NB + i] : part_[i], 16);
+        if (rr < REP) {
+          const int tile = 2 * wb + (up4 ? i : NB + i);     // 16 channels each
+          const int sb = SUB ? tile * SUB / 8 : 0;
+          float wsc = hdown[0][0], z = hzs[0][0];
+#pragma unroll
+          for (int r2 = 0; r2 < REP; ++r2)
+#pragma unroll
+            for (int s2 = 0; s2 < NS; ++s2)
+              if ((r2 || s2) && rr == r2 && sb == s2) { wsc = hdown[r2][s2]; z = hzs[r2][s2]; }
+          dst[4 + 16 * tile + n] = sum * (1024.0f * wsc) - z;  // (FP4 nibble = code / 2, digit byte = digit * 2^-9)
         }
       }
-    }
+      if (rr < REP && up4 && n == 0 && wb == 0) {
+        dst[0] = REP == 2 && rr ? hm[REP - 1] : hm[0];
+        dst[1] = REP == 2 && rr ? hl[REP - 1] : hl[0];
+      }
     }
   }
 }
@@ -958,6 +980,12 @@ int rkv_mfma_share(const rkv_cache* c, int heads_per_kv_head) {
   return heads_per_kv_head % 2 == 0 ? 2 : 1;
 }
 
+// The form of the prepared queries (rkv_prep_q_one): 0 k_decode_shared's, 1 k_decode_mfma's, -1 the plain copy alone.
+int rkv_prep_form(const rkv_cache* c, int heads_per_kv_head) {
+  const int share = rkv_mfma_share(c, heads_per_kv_head);
+  return share == 0 ? 0 : heads_per_kv_head == 1 && !rkv_scores_path(c) ? 1 : -1;
+}
+
 // nq == 0: the usual step, one query token that attends the whole cache (and, if set, the current
 // token's exact row).  nq >= 1: nq query tokens per sequence, token i at position q_pos[b][i] and
 // blind to cached tokens behind it; q, out and lse are then [batch][nq][heads][...] and the scratch
@@ -980,7 +1008,7 @@ int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int 
   const bool row = rkv_scores_path(c);
   if (row && multi && !rkv_scores_multi_ok(c, nq)) return RKV_EINVAL;   // (the scores kernel serves 8 rows per KV head)
   const int share = rkv_mfma_share(c, rep);
-  if (!q_prepared) rkv_launch_prep_q(v, q, q_pos, c->cur_k ? 1 : 0, qr, share, nq, s);
+  if (!q_prepared) rkv_launch_prep_q(v, q, q_pos, c->cur_k ? 1 : 0, qr, rkv_prep_form(c, rep), nq, s);
   float* qt = qr + (size_t)v.B * v.Hq * RKV_D;              // lane-ordered copy written by k_prep_q
   const int chunk = rkv_mfma_chunk(c, multi ? nq : 0), split = MF_CH / chunk;
   const int nch = (v.len + chunk - 1) / chunk;

@@ -75,13 +75,6 @@ __device__ __forceinline__ Split8 split8(const float (&x)[8]) {
         "v"(x[6]), "v"(x[7]));
   return {hi.h8, lo.h8};
 }
-// LDS writes of this wave before, its reads behind (other waves do not touch the region)
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // CT: column tiles (16 columns each), of which rs query heads per KV head are used.  TILES: tiles per wave.  HB: bits per code above the low two (planes as in k_decode_mfma).
 // q_lim: null, or the last position each of the nq query tokens may attend (v.Hq then counts virtual heads).
 template <int G, int CT, int HB, int TILES>

@@ -275,8 +275,8 @@ __device__ inline RkvVHead rkv_virtual_head(const RkvView& v, int hv, int nq) {
   return r;
 }
 
-// bytes at the start of the decode scratch block that hold the prepared queries: the natural
-// layout once, the matrix-core kernel's lane-ordered layout four times (see k_prep_q)
+// bytes at the start of the decode scratch block that hold the prepared queries: the natural layout once, the
+// matrix-core kernels' operands (rkv_prep_q_one), and room for two copies more (what callers bring has not changed)
 inline size_t rkv_query_scratch_bytes(size_t batch, size_t n_q_heads) {
   return (batch * n_q_heads * RKV_D * 4 * 5 + 255) & ~(size_t)255;
 }
@@ -301,6 +301,7 @@ int rkv_mfma_chunk(const rkv_cache* c, int nq);             // tokens per workgr
 size_t rkv_mfma_load(const rkv_cache* c, int chunk);
 int rkv_shared_heads(const rkv_cache* c, int heads_per_kv_head, int chunk);
 int rkv_mfma_share(const rkv_cache* c, int heads_per_kv_head);   // (virtual heads, with several query tokens)
+int rkv_prep_form(const rkv_cache* c, int heads_per_kv_head);
 // several query heads per KV head, or several query tokens per step (rkv_decode_shared.hip)
 bool rkv_shared_decode(const rkv_cache* c, int heads_per_kv_head);
 int rkv_launch_decode_shared(const rkv_cache* c, const RkvView& v, const float* qr, float* part, int nch, int chunk, const int* q_lim, int nq,

@@ -58,3 +58,10 @@ __device__ __forceinline__ float wave_allreduce(float x) {
   const float r2 = __int_as_float(__builtin_amdgcn_readlane(xi, 32)), r3 = __int_as_float(__builtin_amdgcn_readlane(xi, 48));
   return op(op(r0, r1), op(r2, r3));
 }
+
+// LDS writes of this wave before, its reads behind (other waves do not touch the region)
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}

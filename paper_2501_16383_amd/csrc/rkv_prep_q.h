@@ -19,6 +19,7 @@ __device__ __forceinline__ float rkv_prep_q_rotate(const RkvView& v, float x, fl
 
 // One output channel c (0..127) of (virtual) query head h of sequence b.
 // q~[b][h][c] = RoPE(q, q_pos)[c] / sqrt(128), angles in double (q_pos may lie beyond the table).
+// share: 0 for k_decode_shared's operands besides, 1 for k_decode_mfma's (Hq == Hkv), -1 for neither.
 __device__ __forceinline__ void rkv_prep_q_one(const RkvView& v, const __half* __restrict__ q, const int* __restrict__ q_pos,
                                                int cur, float* __restrict__ qr, int share, int nq, int h, int b, int c) {
   // v.Hq counts virtual heads when nq > 1 (several query tokens, each at its own position)
@@ -62,28 +63,22 @@ __device__ __forceinline__ void rkv_prep_q_one(const RkvView& v, const __half* _
     if (c == 0) qr[2 * (size_t)v.B * v.Hq * RKV_D + (size_t)b * v.Hq + h] = ldexpf(1.0f, ex - 14);
     return;
   }
-  // The matrix-core kernel keeps RoPE angles for the first of a lane's four consecutive tokens only
-  // and rotates all four keys by them; the difference is put on the query side, which is exact:
-  // <R(t + r) k, R(pos) q> = <R(t) k, R(pos - r) q>.  So it gets the query at positions pos - r,
-  // r = 0..3, in its own layout:
-  //   [b][rot group][rr / share][r][p 0..3][f / 4][n 0..15][f % 4],  f = (KV head a * share + rr % share) * 2 + half
-  // (rr = which of the query heads sharing KV head a; one workgroup serves `share` of them; the 16
-  // channel lanes n read consecutive 16-byte pieces, which LDS serves without bank conflicts) with
+  qr[base + c] = rkv_prep_q_rotate(v, x, p, sgn, pos, j);
+  if (share != 1) return;                                   // (scores from the scores kernel, the general kernel: the plain copy only)
+  // k_decode_mfma keeps RoPE angles for the first of a lane's four consecutive tokens only, and rotates the query back to
+  // tokens 1 and 2 of the four: it gets it at positions pos - r, r = 1 and 2 (<R(t + r) k, R(pos) q> = <R(t) k, R(pos - r) q>, exactly),
+  // in its own layout: [b][rot group][r - 1][p 0..3][f / 4][n 0..15][f % 4],  f = KV head a * 2 + half
+  // (the 16 channel lanes n read consecutive 16-byte pieces, which LDS serves without bank conflicts) with
   // entry (n, p, half) = channel 16p + n + 64*half (interleaved pairs: 2 (16p + n) + half), pre-multiplied by 2/sqrt(rotation size)
   // (FP4 nibbles hold code/2; 1/sqrt(n) is the normalisation of Eq. 10).
-  const int g = v.g, rep = v.Hq / v.Hkv;
-  const int kvh = h / rep, rr = h - kvh * rep, rg = kvh / g, a = kvh - rg * g;
+  const int rg = h / v.g, a = h - rg * v.g;                 // (one query head per KV head)
   float* qt = qr + (size_t)v.B * v.Hq * RKV_D;
-  const int rrg = rr / share, rri = rr - rrg * share;
   const float lane_scale = 2.0f * rsqrtf((float)v.n);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const float val = rkv_prep_q_rotate(v, x, p, sgn, pos - r, j);
-    if (r == 0) qr[base + c] = val;
-    const int f = (a * share + rri) * 2 + half, nh2 = g * share / 2;
-    size_t o = ((size_t)b * v.NRG + rg) * (rep / share) + rrg;
-    o = (o * 4 + r) * 4 + pp;
-    o = (o * nh2 + (f >> 2)) * 16 + nn;
-    qt[o * 4 + (f & 3)] = val * lane_scale;
+  for (int r = 1; r < 3; ++r) {
+    const int f = 2 * a + half;
+    size_t o = (((size_t)b * v.NRG + rg) * 2 + r - 1) * 4 + pp;
+    o = (o * (v.g / 2) + (f >> 2)) * 16 + nn;
+    qt[o * 4 + (f & 3)] = rkv_prep_q_rotate(v, x, p, sgn, pos - r, j) * lane_scale;
   }
 }
