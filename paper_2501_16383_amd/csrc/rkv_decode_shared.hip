@@ -52,29 +52,24 @@ __device__ __forceinline__ v8i as_fp4(const uint4& u) {
 }
 __device__ __forceinline__ float flip(float x, uint32_t sign) { return __uint_as_float(__float_as_uint(x) ^ sign); }
 // Eight floats -> fp16 high and low parts, x = high + low to 2^-23.  x - high is exact: one multiply-add of mixed
-// precision each (high * -1 + x), which rounds into its half of the register; the compiler makes a
-// conversion, a subtraction and a conversion of it (24 instead of 12 instructions for the eight).
-// The compiler does not see that vector instructions wrote the result: the wait at the end is
-// what a matrix instruction needs that reads it next.
+// precision each (high * -1 + x) into a float, two of which are rounded by one conversion.  What an instruction costs here (cycles
+// of a SIMD, four waves on it, measured): a float multiply-add 2.4, a conversion of two floats or a mixed multiply-add into
+// a float 4.2, one into half a register 8.2 - the form with those was 1.5 instructions an element instead of 2, and 82 cycles for
+// eight elements instead of 67.
 struct Split8 { v8h hi, lo; };
 __device__ __forceinline__ Split8 split8(const float (&x)[8]) {
   union { v2h h2[4]; uint32_t u[4]; v8h h8; } hi, lo;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) hi.h2[i] = __builtin_convertvector((v2f){x[2 * i], x[2 * i + 1]}, v2h);
-  asm("v_fma_mixlo_f16 %0, %4, -1.0, %8 op_sel_hi:[1,0,0]\n\t"
-      "v_fma_mixlo_f16 %1, %5, -1.0, %10 op_sel_hi:[1,0,0]\n\t"
-      "v_fma_mixlo_f16 %2, %6, -1.0, %12 op_sel_hi:[1,0,0]\n\t"
-      "v_fma_mixlo_f16 %3, %7, -1.0, %14 op_sel_hi:[1,0,0]\n\t"
-      "v_fma_mixhi_f16 %0, %4, -1.0, %9 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
-      "v_fma_mixhi_f16 %1, %5, -1.0, %11 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
-      "v_fma_mixhi_f16 %2, %6, -1.0, %13 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
-      "v_fma_mixhi_f16 %3, %7, -1.0, %15 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
-      "s_nop 1"
-      : "=&v"(lo.u[0]), "=&v"(lo.u[1]), "=&v"(lo.u[2]), "=&v"(lo.u[3])
-      : "v"(hi.u[0]), "v"(hi.u[1]), "v"(hi.u[2]), "v"(hi.u[3]), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]),
-        "v"(x[6]), "v"(x[7]));
+  for (int i = 0; i < 4; ++i) {
+    float l0, l1;
+    hi.h2[i] = __builtin_convertvector((v2f){x[2 * i], x[2 * i + 1]}, v2h);
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(l0) : "v"(hi.u[i]), "v"(x[2 * i]));
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(l1) : "v"(hi.u[i]), "v"(x[2 * i + 1]));
+    lo.h2[i] = __builtin_convertvector((v2f){l0, l1}, v2h);
+  }
   return {hi.h8, lo.h8};
 }
+
 // CT: column tiles (16 columns each), of which rs query heads per KV head are used.  TILES: tiles per wave.  HB: bits per code above the low two (planes as in k_decode_mfma).
 // q_lim: null, or the last position each of the nq query tokens may attend (v.Hq then counts virtual heads).
 template <int G, int CT, int HB, int TILES>
@@ -409,21 +404,15 @@ __global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_sh
   for (int s = 0; s < NQ; ++s)
 #pragma unroll
     for (int w = 0; w < NB; ++w) {
-      // lane group q holds slab 4 s + q: 32 of the 128 tokens of a contraction
-      const size_t li = (size_t)(4 * s + q) * (64 * G) + ((wb + w) * G + a) * 16 + n;
-      const bool in = 4 * s + q < nslab;
-      vcodes[s][w] = make_uint4(0, 0, 0, 0);
-      if (in) vcodes[s][w] = rkv_ld_stream(vslab + li);
-      if constexpr (HI) {
-        vhcodes[s][w] = make_uint4(0, 0, 0, 0);
-        if (in) {
-          if constexpr (HB == 2) {
-            vhcodes[s][w] = rkv_ld_stream(reinterpret_cast<const uint4*>(vhslab) + li);
-          } else {
-            const uint2 u = rkv_ld_stream(reinterpret_cast<const uint2*>(vhslab) + li);
-            vhcodes[s][w] = make_uint4(u.x, u.y, 0, 0);
-          }
-        }
+      // lane group q holds slab 4 s + q: 32 of the 128 tokens of a contraction (behind the sequence's end: the last one
+      // again, their weights are zero)
+      const uint32_t li = (uint32_t)(min(4 * s + q, nslab - 1) * (64 * G) + ((wb + w) * G + a) * 16 + n);
+      vcodes[s][w] = rkv_ld_stream(vslab + li);
+      if constexpr (HB == 2) {
+        vhcodes[s][w] = rkv_ld_stream(reinterpret_cast<const uint4*>(vhslab) + li);
+      } else if constexpr (HB == 1) {
+        const uint2 u = rkv_ld_stream(reinterpret_cast<const uint2*>(vhslab) + li);
+        vhcodes[s][w] = make_uint4(u.x, u.y, 0, 0);
       }
     }
   __syncthreads();                                   // all scores are there; the key phase's part of LDS is free
