@@ -194,6 +194,7 @@ RKV_EXPORT int rkv_cache_create(const rkv_config* cfg, void* dev_mem, size_t byt
   c->ev_start = c->ev_stop = nullptr;
   c->cur_k = c->cur_v = nullptr;
   c->ragged = 0;
+  c->sinks_below = 0;
   c->hlens = new (std::nothrow) int32_t[cfg->batch]();
   c->stage = nullptr;
   c->stage_next = 0;
@@ -293,7 +294,16 @@ RKV_EXPORT int rkv_cache_create(const rkv_config* cfg, void* dev_mem, size_t byt
   return RKV_OK;
 }
 
-// Per-sequence counts that a call takes from host memory go to the device through a slot of the
+// Per-sequence counts that a call takes from host memory: with the kernels' arguments where they fit, else staged
+static bool counts_by_value(const rkv_cache* c, const int32_t* host_vals, RkvCounts& counts) {
+  if (c->v.B > RKV_ARG_COUNTS) return false;
+  counts.on = 1;
+  for (int b = 0; b < c->v.B; ++b) counts.n[b] = host_vals[b];
+  for (int b = c->v.B; b < RKV_ARG_COUNTS; ++b) counts.n[b] = 0;
+  return true;
+}
+
+// Staged counts go to the device through a slot of the
 // cache's own pinned ring, so that the caller's array is done with when the call returns whatever
 // the runtime does with pageable memory.  A slot is reused only after the copy that last read it
 // has completed (its event).
@@ -326,6 +336,7 @@ RKV_EXPORT int rkv_cache_reset(rkv_cache* cache, void* stream) {
   cache->v.lens = nullptr;
   cache->v.cstart = nullptr;
   cache->ragged = 0;
+  cache->sinks_below = 0;
   for (int b = 0; b < cache->v.B; ++b) cache->hlens[b] = 0;
   return rkv_launch_init(cache, false, (hipStream_t)stream);
 }
@@ -350,14 +361,20 @@ RKV_EXPORT int rkv_cache_truncate(rkv_cache* cache, const int32_t* host_new_leng
   }
   if (lo != hi && !cache->ragged && !rkv_append_mfma_supported(cache)) return RKV_EINVAL;   // would need per-sequence lengths
   hipStream_t s = (hipStream_t)stream;
-  {
-    const int rc = stage_counts(cache, host_new_lengths, s);
+  // With one length for all, before and after, the device has nothing to learn unless a retained sink row goes (its
+  // copy of the lengths is set when the sequences come to differ)
+  if (cache->ragged || lo != hi || hi < cache->sinks_below) {
+    RkvCounts counts;
+    if (!counts_by_value(cache, host_new_lengths, counts)) {
+      const int rc = stage_counts(cache, host_new_lengths, s);
+      if (rc != RKV_OK) return rc;
+      cache->v.nnew = cache->dev_nnew;
+    }
+    const int rc = rkv_launch_lens(cache, -2, 0, counts, s);
+    cache->v.nnew = nullptr;
     if (rc != RKV_OK) return rc;
   }
-  cache->v.nnew = cache->dev_nnew;
-  const int rc = rkv_launch_lens(cache, -2, 0, s);
-  cache->v.nnew = nullptr;
-  if (rc != RKV_OK) return rc;
+  if (hi < cache->sinks_below) cache->sinks_below = hi;
   for (int b = 0; b < B; ++b) cache->hlens[b] = host_new_lengths[b];
   cache->v.len = hi;
   if (lo != hi && !cache->ragged) {
@@ -478,7 +495,8 @@ RKV_EXPORT int rkv_quantize_append(rkv_cache* cache, const void* dev_k, const vo
   if ((int64_t)cache->v.len + n_new > cache->cfg.max_tokens) return RKV_ECAPACITY;   // v.len: the longest sequence
   if (cache->ragged && !rkv_append_mfma_supported(cache)) return RKV_EINVAL;
   int rc = rkv_launch_append(cache, (const __half*)dev_k, (const __half*)dev_v, n_new, dev_sink_mask, (hipStream_t)stream);
-  if (rc == RKV_OK && cache->ragged) rc = rkv_launch_lens(cache, -1, n_new, (hipStream_t)stream);
+  if (dev_sink_mask) cache->sinks_below = cache->v.len + n_new;   // (also after an error: retention may be under way)
+  if (rc == RKV_OK && cache->ragged) rc = rkv_launch_lens(cache, -1, n_new, RkvCounts(), (hipStream_t)stream);
   if (rc == RKV_OK) {
     cache->v.len += n_new;
     for (int b = 0; b < cache->v.B; ++b) cache->hlens[b] += n_new;
@@ -509,22 +527,44 @@ RKV_EXPORT int rkv_quantize_append_ragged(rkv_cache* cache, const void* dev_k, c
   if (lo == hi && hi == n_new_max) return rkv_quantize_append(cache, dev_k, dev_v, n_new_max, dev_sink_mask, stream);
   if (!rkv_append_mfma_supported(cache)) return RKV_EINVAL;
   hipStream_t s = (hipStream_t)stream;
+  const uint8_t* mask = cache->v.max_sinks > 0 ? dev_sink_mask : nullptr;
+  if (mask) cache->sinks_below = cache->sinks_below > new_max ? cache->sinks_below : new_max;
+  RkvCounts counts;
   int rc = RKV_OK;
-  if (!cache->ragged) {
-    rc = rkv_launch_lens(cache, cache->v.len, 0, s);          // device lengths start from the common length
+  if (counts_by_value(cache, host_n_new, counts)) {
+    // (the first lengths of the sequences' own are written by the append's launch; later ones follow it: its workgroups read them)
+    const bool first = !cache->ragged;
+    if (first && !rkv_append_extra(cache)) {
+      rc = rkv_launch_lens(cache, cache->v.len, 0, RkvCounts(), s);
+      if (rc != RKV_OK) return rc;
+      cache->ragged = 1;
+      cache->v.lens = cache->dev_lens;
+      cache->v.cstart = cache->dev_cstart;
+    }
+    rc = rkv_launch_append_mfma(cache, (const __half*)dev_k, (const __half*)dev_v, n_new_max, max_slabs, mask, counts, s);
     if (rc != RKV_OK) return rc;
-    cache->ragged = 1;
-    cache->v.lens = cache->dev_lens;
-    cache->v.cstart = cache->dev_cstart;
+    if (first && !cache->ragged) {
+      cache->ragged = 1;
+      cache->v.lens = cache->dev_lens;
+      cache->v.cstart = cache->dev_cstart;
+    } else {
+      rc = rkv_launch_lens(cache, -1, 0, counts, s);            // lengths += the counts
+    }
+  } else {
+    if (!cache->ragged) {
+      rc = rkv_launch_lens(cache, cache->v.len, 0, counts, s);   // (more sequences than counts fit) device lengths start from the common length
+      if (rc != RKV_OK) return rc;
+      cache->ragged = 1;
+      cache->v.lens = cache->dev_lens;
+      cache->v.cstart = cache->dev_cstart;
+    }
+    rc = stage_counts(cache, host_n_new, s);
+    if (rc != RKV_OK) return rc;
+    cache->v.nnew = cache->dev_nnew;
+    rc = rkv_launch_append_mfma(cache, (const __half*)dev_k, (const __half*)dev_v, n_new_max, max_slabs, mask, counts, s);
+    if (rc == RKV_OK) rc = rkv_launch_lens(cache, -1, 0, counts, s);   // lengths += the staged counts
+    cache->v.nnew = nullptr;
   }
-  rc = stage_counts(cache, host_n_new, s);
-  if (rc != RKV_OK) return rc;
-  cache->v.nnew = cache->dev_nnew;
-  if (dev_sink_mask && cache->v.max_sinks > 0)
-    rc = rkv_launch_sinks(cache, (const __half*)dev_k, (const __half*)dev_v, dev_sink_mask, n_new_max, s);
-  if (rc == RKV_OK) rc = rkv_launch_append_mfma(cache, (const __half*)dev_k, (const __half*)dev_v, n_new_max, max_slabs, s);
-  if (rc == RKV_OK) rc = rkv_launch_lens(cache, -1, 0, s);      // lengths += the staged counts
-  cache->v.nnew = nullptr;
   if (rc == RKV_OK) {
     for (int b = 0; b < B; ++b) cache->hlens[b] += host_n_new[b];
     cache->v.len = new_max;
@@ -593,7 +633,7 @@ RKV_EXPORT int rkv_decode_step(rkv_cache* cache, const void* dev_k, const void* 
   const int share = rkv_prep_form(cache, cache->v.Hq / cache->v.Hkv);
   int rc = rkv_launch_step_mfma(cache, (const __half*)dev_k, (const __half*)dev_v, (const __half*)dev_q, dev_q_pos,
                                 (float*)dev_scratch, share, s);
-  if (rc == RKV_OK && cache->ragged) rc = rkv_launch_lens(cache, -1, 1, s);
+  if (rc == RKV_OK && cache->ragged) rc = rkv_launch_lens(cache, -1, 1, RkvCounts(), s);
   if (rc != RKV_OK) return rc;
   cache->v.len += 1;
   for (int b = 0; b < cache->v.B; ++b) cache->hlens[b] += 1;

@@ -23,6 +23,7 @@
 #include "rkv_internal.h"
 #include "rkv_quant.h"
 #include "rkv_prep_q.h"
+#include "rkv_sinks.h"
 
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -124,7 +125,7 @@ __device__ __forceinline__ void fused_round_consts(float zero, float& base, floa
 // channels of a head, so the lane-exchange reduction simply stops earlier.
 template <int G, int HB, bool XW = false, int SUB = 0>
 __device__ __forceinline__ void append_mfma_body(const RkvView& v, const __half* __restrict__ kin, const __half* __restrict__ vin,
-                                                 int n_new, int slab0, int bx, int rg, int b) {
+                                                 int n_new, int n_b, int slab0, int bx, int rg, int b) {
   constexpr int PL = 2 * G;                    // value channels per lane
   constexpr int LPB = 128 / PL;                // lanes per 128-block in the value role
   constexpr int n = 128 * G;
@@ -157,9 +158,8 @@ __device__ __forceinline__ void append_mfma_body(const RkvView& v, const __half*
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // in a scalar register: everything that depends only on it stays scalar
   const int role = bx % 3;                     // 0, 1: the keys of K tile 0 / 1 of a slab; 2: the slab's values
-  // n_new: rows per sequence in kin and vin; sequence b holds len_b tokens and appends the first
-  // n_b rows (all of them, at the common length, unless the view carries per-sequence arrays)
-  const int len_b = rkv_len(v, b), n_b = v.nnew ? v.nnew[b] : n_new;
+  // n_new: rows per sequence in kin and vin; sequence b holds len_b tokens and appends the first n_b rows
+  const int len_b = rkv_len(v, b);
   const int slab = (v.lens ? (len_b >> 5) : slab0) + bx / 3;
   const int t_lo = len_b, t_hi = len_b + n_b;
   const int ts = slab * 32;
@@ -567,16 +567,71 @@ __device__ __forceinline__ void append_mfma_body(const RkvView& v, const __half*
   }
 }
 
-template <int G, int HB, bool XW = false, int SUB = 0>
-__global__ void __launch_bounds__(256, (HB || XW || SUB) ? 4 : 6) k_append_mfma(RkvView v, const __half* __restrict__ kin, const __half* __restrict__ vin,
-                                                                      int n_new, int slab0) {
-  append_mfma_body<G, HB, XW, SUB>(v, kin, vin, n_new, slab0, blockIdx.x, blockIdx.y, blockIdx.z);
+// What an append has to do besides, in workgroups of its launch: the first column of the grid (x = 0) then counts
+// sequences, (z, y) in the order in which workgroups start.  Retention of the flagged tokens' rows, and the device's
+// lengths where the sequences have one in common so far and this call gives each its own (nobody reads them in this launch:
+// the view has no per-sequence lengths yet).  4 x 4096 tokens, 40 heads: 119 -> 109 us with selection and reset in front; 8
+// prompts of 37 to 1531 tokens, 8 heads: 54 -> 42 us (retention and two updates of the lengths were launches of 3.8 to 9.9 us).
+#define RKV_EXTRA_COLS 8               // columns in front of k_append_mfma's own, of which the first is used: the others keep their places among the eight dies
+struct RkvAppendExtra {
+  const uint8_t* mask;                 // flags of sink tokens [batch][n_new], or null
+  int* lens;                           // lengths, chunk table and staged counts to write, or null
+  int* cstart;
+  int* staged;
+  RkvCounts counts;
+};
+__device__ __forceinline__ void append_extra(const RkvView& v, const __half* kin, const __half* vin, int n_new, const RkvAppendExtra& x) {
+  __shared__ RkvSinkLds lds;
+  const int idx = blockIdx.z * v.NRG + blockIdx.y;
+  if (x.lens && idx == min(v.B, v.B * v.NRG - 1) && threadIdx.x < 64) {
+    // lane = sequence (at most RKV_ARG_COUNTS of them): lengths, and the running count of their chunks
+    static_assert(RKV_ARG_COUNTS == 64, "a sequence per lane");
+    const int b = threadIdx.x, n_b = b < v.B ? x.counts.n[b] : 0, len = b < v.B ? v.len + n_b : 0;
+    int run = (len + 255) >> 8;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int below = __shfl_up(run, o);
+      if (b >= o) run += below;
+    }
+    if (b < v.B) {
+      x.lens[b] = len;
+      x.staged[b] = n_b;
+      x.cstart[b + 1] = run;
+      if (b == 0) x.cstart[0] = 0;
+    }
+  }
+  if (x.mask && idx < v.B) rkv_sinks_of<256>(v, kin, vin, x.mask, n_new, rkv_count(v, x.counts, idx, n_new), idx, lds);
+}
+
+// EXTRA: with the work above (a variant of its own: an append that has none keeps the scalar registers it takes)
+template <int G, int HB, bool XW = false, int SUB = 0, bool EXTRA = false>
+__global__ void __launch_bounds__(256, (XW || SUB || HB == 1) ? 4 : G == 2 ? 8 : 6) k_append_mfma(RkvView v, const __half* __restrict__ kin, const __half* __restrict__ vin,
+                                                                      int n_new, int slab0, RkvAppendExtra extra) {
+  int bx = blockIdx.x;
+  if constexpr (EXTRA) {
+    if (bx < RKV_EXTRA_COLS) {
+      if (bx == 0) append_extra(v, kin, vin, n_new, extra);
+      return;
+    }
+    bx -= RKV_EXTRA_COLS;
+  }
+  append_mfma_body<G, HB, XW, SUB>(v, kin, vin, n_new, rkv_count(v, extra.counts, blockIdx.z, n_new), slab0, bx, blockIdx.y, blockIdx.z);
 }
 
 // the value role alone (grid x = slabs): the keys of a reorder over the whole row have a kernel of their own
-template <int G, int HB = 0, int SUB = 0>
-__global__ void __launch_bounds__(256, (HB || SUB) ? 4 : 6) k_append_values(RkvView v, const __half* __restrict__ vin, int n_new, int slab0) {
-  append_mfma_body<G, HB, false, SUB>(v, nullptr, vin, n_new, slab0, 3 * blockIdx.x + 2, blockIdx.y, blockIdx.z);
+template <int G, int HB = 0, int SUB = 0, bool EXTRA = false>
+__global__ void __launch_bounds__(256, (HB || SUB) ? 4 : 6) k_append_values(RkvView v, const __half* __restrict__ kin, const __half* __restrict__ vin,
+                                                                  int n_new, int slab0, RkvAppendExtra extra) {
+  int bx = blockIdx.x;
+  if constexpr (EXTRA) {
+    if (bx == 0) {
+      append_extra(v, kin, vin, n_new, extra);
+      return;
+    }
+    --bx;
+  }
+  append_mfma_body<G, HB, false, SUB>(v, nullptr, vin, n_new, rkv_count(v, extra.counts, blockIdx.z, n_new), slab0, 3 * bx + 2, blockIdx.y,
+                                      blockIdx.z);
 }
 
 // Keys under a reorder over the whole token row (perm_span = n_kv_heads * 128, Alg. 1 as printed;
@@ -599,7 +654,7 @@ __global__ void __launch_bounds__(256, (HB || SUB) ? 4 : 6) k_append_values(RkvV
 // (Four sets of rotation groups of four heads are 1024 threads of 128 registers; 7 to 12 more are held in scratch memory.)
 // TAB: the table of block numbers in LDS; without it (narrow workgroups only) entries are fetched from memory where they are used.
 template <int G, int HB = 0, int NP = 1, bool TAB = true>
-__global__ void __launch_bounds__(256 * NP, NP == 1 ? 3 : 1) k_append_row_keys(RkvView v, const __half* __restrict__ kin, int n_new, int slab0) {
+__global__ void __launch_bounds__(256 * NP, NP == 1 ? 3 : 1) k_append_row_keys(RkvView v, const __half* __restrict__ kin, int n_new, int slab0, RkvCounts counts) {
   constexpr int n = 128 * G;
   constexpr bool HI = HB == 2, H1 = HB == 1;
   constexpr float QMAX = HI ? 15.0f : (H1 ? 7.0f : 3.0f), INV_QMAX = HI ? 0.06666667f : (H1 ? 0.14285715f : 0.33333334f);
@@ -620,7 +675,7 @@ __global__ void __launch_bounds__(256 * NP, NP == 1 ? 3 : 1) k_append_row_keys(R
   uint32_t* img = img_all[set];
   uint32_t* imgh = imgh_all[set];
   const int b = blockIdx.y, ti = blockIdx.x & 1;
-  const int len_b = rkv_len(v, b), n_b = v.nnew ? v.nnew[b] : n_new;
+  const int len_b = rkv_len(v, b), n_b = rkv_count(v, counts, b, n_new);
   const int slab = (v.lens ? (len_b >> 5) : slab0) + (blockIdx.x >> 1);
   const int t_lo = len_b, t_hi = len_b + n_b;
   const int ts = slab * 32;
@@ -825,7 +880,7 @@ __global__ void __launch_bounds__(256, 4) k_step_mfma(RkvView v, const __half* _
                                                    int slab0, int n_append_blocks, const __half* __restrict__ q,
                                                    const int* __restrict__ q_pos, float* __restrict__ qr, int share) {
   if ((int)blockIdx.x < n_append_blocks) {
-    append_mfma_body<G, HB, XW, SUB>(v, kin, vin, 1, slab0, blockIdx.x, blockIdx.y, blockIdx.z);
+    append_mfma_body<G, HB, XW, SUB>(v, kin, vin, 1, 1, slab0, blockIdx.x, blockIdx.y, blockIdx.z);
     return;
   }
   const int rep = v.Hq / v.Hkv;
@@ -839,7 +894,7 @@ template <int G, int HB = 0, int SUB = 0>
 __global__ void __launch_bounds__(256, 4) k_step_values(RkvView v, const __half* __restrict__ vin, int slab0, const __half* __restrict__ q,
                                                      const int* __restrict__ q_pos, float* __restrict__ qr, int share) {
   if (blockIdx.x == 0) {
-    append_mfma_body<G, HB, false, SUB>(v, nullptr, vin, 1, slab0, 2, blockIdx.y, blockIdx.z);
+    append_mfma_body<G, HB, false, SUB>(v, nullptr, vin, 1, 1, slab0, 2, blockIdx.y, blockIdx.z);
     return;
   }
   const int rep = v.Hq / v.Hkv;
@@ -863,6 +918,11 @@ int rkv_append_mfma_variant(const rkv_cache* c) {
   return append_row(c) ? RKV_KERNEL_MFMA_ROW : c->v.qg != 128 ? RKV_KERNEL_MFMA_SUB : c->blocks_aligned ? RKV_KERNEL_MFMA : RKV_KERNEL_MFMA_CROSS;
 }
 
+// Whether the append's launch retains sink rows and sets the first lengths itself.  Not where the quantization
+// blocks differ from the rotated ones inside a rotation group: those kernels would lose a workgroup per compute unit to the
+// registers and the LDS it takes.
+bool rkv_append_extra(const rkv_cache* c) { return c->v.qg == 128 && (c->blocks_aligned || append_row(c)); }
+
 bool rkv_append_mfma_supported(const rkv_cache* c) {
   const RkvView& v = c->v;
   if (append_row(c)) return true;
@@ -875,7 +935,7 @@ bool rkv_append_mfma_supported(const rkv_cache* c) {
 }
 
 template <int G, int HB>
-static int launch_row_keys(const rkv_cache* c, const __half* k, int n_new, int max_slabs, int slab0, hipStream_t s) {
+static int launch_row_keys(const rkv_cache* c, const __half* k, int n_new, int max_slabs, int slab0, const RkvCounts& counts, hipStream_t s) {
   const RkvView& v = c->v;
   const size_t dyn = row_keys_dynamic_lds(v);
   // Four wave sets per tile as long as there is at most one such workgroup per compute unit and the tables fit
@@ -885,7 +945,7 @@ static int launch_row_keys(const rkv_cache* c, const __half* k, int n_new, int m
   const size_t set_static = 16 * (16 * G + 1) * 16 + (HB ? 2 : 1) * 2 * 128 * G * 4, wide_static = 4 * set_static + 64;
   if (2 * max_slabs * v.B <= c->n_cu && v.NRG > 1 && dyn + wide_static <= RKV_LDS_BYTES) {
     RKV_HIP_CHECK(hipFuncSetAttribute((const void*)k_append_row_keys<G, HB, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn));
-    hipLaunchKernelGGL((k_append_row_keys<G, HB, 4>), dim3(2 * max_slabs, v.B), dim3(1024), dyn, s, v, k, n_new, slab0);
+    hipLaunchKernelGGL((k_append_row_keys<G, HB, 4>), dim3(2 * max_slabs, v.B), dim3(1024), dyn, s, v, k, n_new, slab0, counts);
     return RKV_OK;
   }
   // The table of block numbers stays in memory where its place in LDS would be the third workgroup's (LDS is given out
@@ -904,19 +964,21 @@ static int launch_row_keys(const rkv_cache* c, const __half* k, int n_new, int m
     }
   }
   if (lds > 48 * 1024) RKV_HIP_CHECK(hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL(fn, dim3(2 * max_slabs, v.B), dim3(256), lds, s, v, k, n_new, slab0);
+  hipLaunchKernelGGL(fn, dim3(2 * max_slabs, v.B), dim3(256), lds, s, v, k, n_new, slab0, counts);
   return RKV_OK;
 }
-static int launch_row_keys_of(const rkv_cache* c, const __half* k, int n_new, int max_slabs, int slab0, hipStream_t s) {
+static int launch_row_keys_of(const rkv_cache* c, const __half* k, int n_new, int max_slabs, int slab0, const RkvCounts& counts, hipStream_t s) {
   const RkvView& v = c->v;
-#define RKV_ROW_G(H_) (v.g == 4 ? launch_row_keys<4, H_>(c, k, n_new, max_slabs, slab0, s) : launch_row_keys<2, H_>(c, k, n_new, max_slabs, slab0, s))
+#define RKV_ROW_G(H_) (v.g == 4 ? launch_row_keys<4, H_>(c, k, n_new, max_slabs, slab0, counts, s) : launch_row_keys<2, H_>(c, k, n_new, max_slabs, slab0, counts, s))
   return v.hb == 2 ? RKV_ROW_G(2) : v.hb == 1 ? RKV_ROW_G(1) : RKV_ROW_G(0);
 #undef RKV_ROW_G
 }
 
 // max_slabs: most 32-token slabs any sequence's new tokens touch, or 0 to work it out for n_new
-// tokens per sequence
-int rkv_launch_append_mfma(rkv_cache* c, const __half* k, const __half* vv, int n_new, int max_slabs, hipStream_t s) {
+// tokens per sequence; mask: flags of sink tokens, whose rows are retained, or null; counts: per-sequence token counts, which
+// where the sequences had one length so far also give the device its lengths (if rkv_append_extra)
+int rkv_launch_append_mfma(rkv_cache* c, const __half* k, const __half* vv, int n_new, int max_slabs, const uint8_t* mask, const RkvCounts& counts,
+                           hipStream_t s) {
   const RkvView& v = c->v;
   if (!rkv_append_mfma_supported(c)) return RKV_EINVAL;
   const int slab0 = v.len >> 5, slab1 = (v.len + n_new - 1) >> 5;
@@ -928,12 +990,23 @@ int rkv_launch_append_mfma(rkv_cache* c, const __half* k, const __half* vv, int 
         max_slabs = sl > max_slabs ? sl : max_slabs;
       }
   }
-  dim3 grid(3 * max_slabs, v.NRG, v.B);
+  RkvAppendExtra extra{};
+  extra.counts = counts;
+  if (rkv_append_extra(c)) extra.mask = mask;
+  else if (mask) rkv_launch_sinks(c, k, vv, mask, n_new, counts, s);
+  if (counts.on && !c->ragged) {
+    extra.lens = c->dev_lens;
+    extra.cstart = c->dev_cstart;
+    extra.staged = c->dev_nnew;
+  }
+  const bool xc = extra.mask || extra.lens;
+  dim3 grid(3 * max_slabs + (xc ? RKV_EXTRA_COLS : 0), v.NRG, v.B);
   if (c->ev_start) RKV_HIP_CHECK(hipEventRecord(c->ev_start, s));
   if (append_row(c)) {
-    const int rc = launch_row_keys_of(c, k, n_new, max_slabs, slab0, s);
+    const int rc = launch_row_keys_of(c, k, n_new, max_slabs, slab0, counts, s);
     if (rc != RKV_OK) return rc;
-#define RKV_AP_VAL(G_, H_, S_) hipLaunchKernelGGL((k_append_values<G_, H_, S_>), dim3(max_slabs, v.NRG, v.B), dim3(256), 0, s, v, vv, n_new, slab0)
+#define RKV_AP_VAL_X(G_, H_, S_, E_) hipLaunchKernelGGL((k_append_values<G_, H_, S_, E_>), dim3(max_slabs + (E_ ? 1 : 0), v.NRG, v.B), dim3(256), 0, s, v, k, vv, n_new, slab0, extra)
+#define RKV_AP_VAL(G_, H_, S_) do { if (S_ == 0 && xc) RKV_AP_VAL_X(G_, H_, 0, true); else RKV_AP_VAL_X(G_, H_, S_, false); } while (0)
 #define RKV_AP_ROW(G_, H_)                                                                                                        \
   do {                                                                                                                            \
     if (v.qg == 64) RKV_AP_VAL(G_, H_, 2); else if (v.qg == 32) RKV_AP_VAL(G_, H_, 4); else RKV_AP_VAL(G_, H_, 0);                \
@@ -945,9 +1018,10 @@ int rkv_launch_append_mfma(rkv_cache* c, const __half* k, const __half* vv, int 
     }
 #undef RKV_AP_ROW
 #undef RKV_AP_VAL
+#undef RKV_AP_VAL_X
   } else {
     // (G, bits above the low two, cross-block flag, sub-blocks per head)
-#define RKV_AP(G_, H_, X_, S_) hipLaunchKernelGGL((k_append_mfma<G_, H_, X_, S_>), grid, dim3(256), 0, s, v, k, vv, n_new, slab0)
+#define RKV_AP(G_, H_, X_, S_) hipLaunchKernelGGL((k_append_mfma<G_, H_, X_, S_>), grid, dim3(256), 0, s, v, k, vv, n_new, slab0, extra)
 #define RKV_AP_G(H_, X_, S_) do { if (v.g == 4) RKV_AP(4, H_, X_, S_); else RKV_AP(2, H_, X_, S_); } while (0)
 #define RKV_AP_H(X_, S_) do { if (v.hb == 2) RKV_AP_G(2, X_, S_); else if (v.hb == 1) RKV_AP_G(1, X_, S_); else RKV_AP_G(0, X_, S_); } while (0)
     if (v.qg == 64 && c->blocks_aligned) RKV_AP_H(false, 2);
@@ -955,7 +1029,14 @@ int rkv_launch_append_mfma(rkv_cache* c, const __half* k, const __half* vv, int 
     else if (v.qg == 64) RKV_AP_H(true, 2);
     else if (v.qg == 32) RKV_AP_H(true, 4);
     else if (!c->blocks_aligned) RKV_AP_H(true, 0);
-    else RKV_AP_H(false, 0);
+    else if (!xc) RKV_AP_H(false, 0);
+    else {
+#define RKV_AP_E(G_, H_) hipLaunchKernelGGL((k_append_mfma<G_, H_, false, 0, true>), grid, dim3(256), 0, s, v, k, vv, n_new, slab0, extra)
+#define RKV_AP_EH(G_) do { if (v.hb == 2) RKV_AP_E(G_, 2); else if (v.hb == 1) RKV_AP_E(G_, 1); else RKV_AP_E(G_, 0); } while (0)
+      if (v.g == 4) RKV_AP_EH(4); else RKV_AP_EH(2);
+#undef RKV_AP_EH
+#undef RKV_AP_E
+    }
 #undef RKV_AP_H
 #undef RKV_AP_G
 #undef RKV_AP
@@ -972,7 +1053,7 @@ int rkv_launch_step_mfma(rkv_cache* c, const __half* k, const __half* vv, const 
   int max_slabs = 1;                                        // one token touches one slab of its sequence
   const int n_append = 3 * max_slabs, rep = v.Hq / v.Hkv;
   if (append_row(c)) {
-    const int rc = launch_row_keys_of(c, k, 1, max_slabs, v.len >> 5, s);
+    const int rc = launch_row_keys_of(c, k, 1, max_slabs, v.len >> 5, RkvCounts(), s);
     if (rc != RKV_OK) return rc;
     dim3 grid(1 + v.g * rep / 2, v.NRG, v.B);
 #define RKV_SV(G_, H_, S_) hipLaunchKernelGGL((k_step_values<G_, H_, S_>), grid, dim3(256), 0, s, v, vv, v.len >> 5, q, q_pos, qr, share)

@@ -88,6 +88,19 @@ struct RkvView {
   float theta;
 };
 
+// Per-sequence token counts of an append or a truncation.  Up to RKV_ARG_COUNTS sequences they are part of the kernel's
+// arguments: a copy to the device ahead of it is an operation of its own on the stream, and the host has to keep its source.
+#define RKV_ARG_COUNTS 64
+struct RkvCounts {
+  int on = 0;                          // 1: n[b] counts; 0: RkvView::nnew, if set
+  int n[RKV_ARG_COUNTS] = {};
+};
+__device__ inline int rkv_count(const RkvView& v, const RkvCounts& c, int b, int otherwise) {
+  const int n = c.n[b % RKV_ARG_COUNTS];                    // (asked for together with the rest of the arguments)
+  if (v.nnew) otherwise = v.nnew[b];
+  return c.on ? n : otherwise;
+}
+
 // length of sequence b
 __device__ inline int rkv_len(const RkvView& v, int b) { return v.lens ? v.lens[b] : v.len; }
 
@@ -95,13 +108,14 @@ struct rkv_cache {
   rkv_config cfg;
   RkvView v;           // v.len: the length of the longest sequence
   int32_t* hlens;      // host mirror of the per-sequence lengths [batch]
-  int32_t* stage;      // pinned host ring [RKV_STAGE_SLOTS][batch]: per-sequence counts on their way to dev_nnew
+  int32_t* stage;      // pinned host ring [RKV_STAGE_SLOTS][batch]: per-sequence counts of more than RKV_ARG_COUNTS sequences on their way to dev_nnew
   hipEvent_t stage_ev[RKV_STAGE_SLOTS];   // recorded after the copy that reads a slot
   int stage_used[RKV_STAGE_SLOTS], stage_next;
   int* dev_lens;       // device copy (kept current once `ragged` is set) and staging for per-sequence token counts
   int* dev_nnew;
   int* dev_cstart;     // [batch + 1], see RkvView::cstart
   int ragged;          // 1 once sequences differ in length
+  int sinks_below;     // every retained sink token lies before this position
   size_t bytes;
   char* base;
   size_t off_tables;      // everything before this offset is cleared by reset
@@ -286,9 +300,10 @@ int rkv_launch_init(rkv_cache* c, bool tables, hipStream_t s);
 int rkv_launch_set_perm_tables(rkv_cache* c, hipStream_t s);
 int rkv_launch_append(rkv_cache* c, const __half* k, const __half* v, int n_new, const uint8_t* mask, hipStream_t s);
 bool rkv_append_mfma_supported(const rkv_cache* c);
-int rkv_launch_append_mfma(rkv_cache* c, const __half* k, const __half* v, int n_new, int max_slabs, hipStream_t s);
-int rkv_launch_sinks(rkv_cache* c, const __half* k, const __half* v, const uint8_t* mask, int n_new, hipStream_t s);
-int rkv_launch_lens(rkv_cache* c, int set_to, int add, hipStream_t s);
+int rkv_launch_append_mfma(rkv_cache* c, const __half* k, const __half* v, int n_new, int max_slabs, const uint8_t* mask, const RkvCounts& counts, hipStream_t s);
+bool rkv_append_extra(const rkv_cache* c);
+void rkv_launch_sinks(const rkv_cache* c, const __half* k, const __half* v, const uint8_t* mask, int n_new, const RkvCounts& counts, hipStream_t s);
+int rkv_launch_lens(rkv_cache* c, int set_to, int add, const RkvCounts& counts, hipStream_t s);
 int rkv_launch_dequant(rkv_cache* c, float* k_hat, float* v_hat, hipStream_t s);
 int rkv_launch_export(rkv_cache* c, uint8_t* kc, float* ks, float* kz, uint8_t* vc, float* vs, float* vz, hipStream_t s);
 int rkv_launch_import(rkv_cache* c, int T, const uint8_t* kc, const float* ks, const float* kz, const uint8_t* vc,

@@ -2,6 +2,7 @@
 // cache used by tests (dequantize, export, import).
 #include "rkv_internal.h"
 #include "rkv_quant.h"
+#include "rkv_sinks.h"
 
 // ---------------------------------------------------------------------------------------------
 // small device helpers
@@ -128,116 +129,15 @@ int rkv_launch_init(rkv_cache* c, bool tables, hipStream_t s) {
 // sinks: keep the original fp16 rows of flagged tokens (Sec. 4.3), first come first kept
 // ---------------------------------------------------------------------------------------------
 
-// One workgroup per sequence.  Latency bounds it: the flags of 4096 tokens are 4 KB and the rows kept a few
-// tens of KB.  Flags are read in coalesced passes (thread = token, all of a block's loads in flight together) and turned into
-// wave ballots; the first wave places the flagged tokens with a prefix sum over the ballots of a block,
-// and the rows are copied piece by piece over all retained rows at once, so that a copy is one round
-// trip.  4 sequences of 4096 tokens, 4 rows of 5120 channels each: 10.3 us, against 23.4 us with 256 threads
-// that each counted their own stretch of tokens, a serial prefix sum and a round trip per row.
+// (the paths whose append kernel does not do it beside its own work: rkv_sinks.h)
 #define SINK_THREADS 1024
-#define SINK_PASSES 4                      // passes of SINK_THREADS tokens per block: 64 ballots, one per lane of the first wave
 __global__ void __launch_bounds__(SINK_THREADS) k_sinks(RkvView v, const __half* __restrict__ k, const __half* __restrict__ vv,
-                                                        const uint8_t* __restrict__ mask, int n_new) {
-  static_assert(SINK_PASSES * SINK_THREADS == 64 * 64, "one ballot of a block per lane of the first wave");
-  __shared__ unsigned long long s_ball[64];
-  __shared__ int s_tok[64];
-  __shared__ int s_new;
-  __shared__ float s_row[512];
-  // n_new: rows per sequence in k, vv and mask; sequence b uses the first n_b of them
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int n_b = v.nnew ? v.nnew[b] : n_new;
-  const int cnt0 = v.sink_cnt[b];
-  const int room = v.max_sinks - cnt0;
-  const uint8_t* mb = mask + (size_t)b * n_new;
-  int run = 0;                                              // flagged tokens of the blocks before this one
-  for (int base = 0; base < n_b && run < room; base += 64 * 64) {
-    uint8_t f[SINK_PASSES];
-#pragma unroll
-    for (int p = 0; p < SINK_PASSES; ++p) {
-      const int t = base + p * SINK_THREADS + tid;
-      f[p] = t < n_b ? mb[t] : (uint8_t)0;
-    }
-#pragma unroll
-    for (int p = 0; p < SINK_PASSES; ++p) {
-      const unsigned long long bal = __ballot(f[p] != 0);
-      if (lane == 0) s_ball[p * (SINK_THREADS / 64) + wave] = bal;
-    }
-    __syncthreads();
-    if (wave == 0) {
-      unsigned long long bal = s_ball[lane];                // tokens base + 64 lane .. + 63
-      int upto = __popcll(bal);
-      const int own = upto;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int below = __shfl_up(upto, o);
-        if (lane >= o) upto += below;
-      }
-      int slot = run + upto - own;
-      while (bal && slot < room) {                          // (room <= 64: at most as many slots as s_tok holds)
-        s_tok[slot++] = base + 64 * lane + (int)__ffsll((unsigned long long)bal) - 1;
-        bal &= bal - 1;
-      }
-      if (lane == 63) s_new = run + upto;
-    }
-    __syncthreads();
-    run = s_new;
-  }
-  const int nn = min(run, max(room, 0));
-  // whole rows, 16 bytes per thread, all retained rows together and every load of a round issued before
-  // its stores (rows are 256-byte multiples and 16-byte aligned: E is a multiple of 128 halves)
-  {
-    const uint4* k4 = reinterpret_cast<const uint4*>(k) + (size_t)b * n_new * (v.E / 8);
-    const uint4* v4 = reinterpret_cast<const uint4*>(vv) + (size_t)b * n_new * (v.E / 8);
-    uint4* dk4 = reinterpret_cast<uint4*>(v.sink_k) + ((size_t)b * v.max_sinks + cnt0) * (v.E / 8);
-    uint4* dv4 = reinterpret_cast<uint4*>(v.sink_v) + ((size_t)b * v.max_sinks + cnt0) * (v.E / 8);
-    const int n16 = v.E / 8;
-    for (int e0 = 0; e0 < nn * n16; e0 += 4 * SINK_THREADS) {
-      uint4 a[4], c[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int e = e0 + u * SINK_THREADS + tid;
-        if (e < nn * n16) {
-          const int i = e / n16;
-          const size_t src = (size_t)s_tok[i] * n16 + (e - i * n16);
-          if (!v.keys_rotated) a[u] = k4[src];
-          c[u] = v4[src];
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int e = e0 + u * SINK_THREADS + tid;
-        if (e < nn * n16) {
-          if (!v.keys_rotated) dk4[e] = a[u];
-          dv4[e] = c[u];
-        }
-      }
-    }
-  }
-  if (tid < nn) v.sink_pos[b * v.max_sinks + cnt0 + tid] = rkv_len(v, b) + s_tok[tid];
-  if (tid == 0) v.sink_cnt[b] = cnt0 + nn;
-  if (!v.keys_rotated) return;
-  for (int i = 0; i < nn; ++i) {
-    const size_t src = ((size_t)b * n_new + s_tok[i]) * v.E, dst = ((size_t)b * v.max_sinks + cnt0 + i) * v.E;
-    // the keys arrived rotated and reordered: undo the reorder, rotate again (H is its own
-    // inverse), round to fp16 - group by group, butterflies in LDS (n <= 512 in this mode)
-    for (int rg = 0; rg < v.NRG; ++rg) {
-      const int gb = rg * v.n;
-      for (int c = tid; c < v.n; c += SINK_THREADS) s_row[c] = __half2float(k[src + v.pinv[gb + c]]);
-      __syncthreads();
-      for (int h = 1; h < v.n; h <<= 1) {
-        for (int j = tid; j < v.n / 2; j += SINK_THREADS) {
-          const int lo = ((j / h) * 2 * h) + (j % h), hi = lo + h;
-          const float a = s_row[lo], c2 = s_row[hi];
-          s_row[lo] = a + c2;
-          s_row[hi] = a - c2;
-        }
-        __syncthreads();
-      }
-      const float rs = rsqrtf((float)v.n);
-      for (int c = tid; c < v.n; c += SINK_THREADS) v.sink_k[dst + gb + c] = __float2half_rn(s_row[c] * rs);
-      __syncthreads();
-    }
-  }
+                                                        const uint8_t* __restrict__ mask, int n_new, RkvCounts counts) {
+  __shared__ RkvSinkLds lds;
+  rkv_sinks_of<SINK_THREADS>(v, k, vv, mask, n_new, rkv_count(v, counts, blockIdx.x, n_new), blockIdx.x, lds);
+}
+void rkv_launch_sinks(const rkv_cache* c, const __half* k, const __half* vv, const uint8_t* mask, int n_new, const RkvCounts& counts, hipStream_t s) {
+  hipLaunchKernelGGL(k_sinks, dim3(c->v.B), dim3(SINK_THREADS), 0, s, c->v, k, vv, mask, n_new, counts);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -583,25 +483,22 @@ __global__ void __launch_bounds__(256) k_append_fast(RkvView v, const __half* __
   }
 }
 
-int rkv_launch_sinks(rkv_cache* c, const __half* k, const __half* vv, const uint8_t* mask, int n_new, hipStream_t s) {
-  const RkvView& v = c->v;
-  hipLaunchKernelGGL(k_sinks, dim3(v.B), dim3(SINK_THREADS), 0, s, v, k, vv, mask, n_new);
-  return rkv_check_launch();
-}
-
 // Per-sequence lengths on the device: set_to >= 0 sets every length to it; set_to == -2 takes them
 // from the staged per-sequence array (a truncation: retained sink rows at or behind the new end
 // are dropped too - they were added in order of position); otherwise each length grows by `add`
 // plus, while an append with per-sequence counts is in progress, by its count.
 // Also rebuilds cstart (running count of 256-token chunks, see RkvView) - one workgroup; thread i
 // owns a contiguous slice of the sequences.
-__global__ void __launch_bounds__(256) k_lens(RkvView v, int* lens, int* cstart, int set_to, int add) {
+// Counts come by value or from the staged array; what came by value is left there.
+__global__ void __launch_bounds__(256) k_lens(RkvView v, int* lens, int* cstart, int* staged, int set_to, int add, RkvCounts counts) {
   __shared__ int s_sum[256];
   const int tid = threadIdx.x;
   const int per = (v.B + 255) / 256, b0 = min(tid * per, v.B), b1 = min(b0 + per, v.B);
   int chunks = 0;
   for (int b = b0; b < b1; ++b) {
-    const int len = set_to >= 0 ? set_to : (set_to == -2 ? v.nnew[b] : lens[b] + add + (v.nnew ? v.nnew[b] : 0));
+    const int n_b = rkv_count(v, counts, b, 0);
+    const int len = set_to >= 0 ? set_to : (set_to == -2 ? n_b : lens[b] + add + n_b);
+    if (counts.on) staged[b] = n_b;
     lens[b] = len;
     if (set_to == -2 && v.max_sinks > 0) {
       int c = v.sink_cnt[b];
@@ -629,16 +526,16 @@ __global__ void __launch_bounds__(256) k_lens(RkvView v, int* lens, int* cstart,
   }
 }
 
-int rkv_launch_lens(rkv_cache* c, int set_to, int add, hipStream_t s) {
+int rkv_launch_lens(rkv_cache* c, int set_to, int add, const RkvCounts& counts, hipStream_t s) {
   const RkvView& v = c->v;
-  hipLaunchKernelGGL(k_lens, dim3(1), dim3(256), 0, s, v, c->dev_lens, c->dev_cstart, set_to, add);
+  hipLaunchKernelGGL(k_lens, dim3(1), dim3(256), 0, s, v, c->dev_lens, c->dev_cstart, c->dev_nnew, set_to, add, counts);
   return rkv_check_launch();
 }
 
 int rkv_launch_append(rkv_cache* c, const __half* k, const __half* vv, int n_new, const uint8_t* mask, hipStream_t s) {
   const RkvView& v = c->v;
-  if (mask && v.max_sinks > 0) hipLaunchKernelGGL(k_sinks, dim3(v.B), dim3(SINK_THREADS), 0, s, v, k, vv, mask, n_new);
-  if (rkv_append_mfma_supported(c)) return rkv_launch_append_mfma(c, k, vv, n_new, 0, s);
+  if (rkv_append_mfma_supported(c)) return rkv_launch_append_mfma(c, k, vv, n_new, 0, v.max_sinks > 0 ? mask : nullptr, RkvCounts(), s);
+  if (mask && v.max_sinks > 0) rkv_launch_sinks(c, k, vv, mask, n_new, RkvCounts(), s);
   if (c->blocks_aligned && !c->wide && (v.g == 2 || v.g == 4)) {
     const int slab0 = v.len >> 5, slab1 = (v.len + n_new - 1) >> 5;
     dim3 grid(slab1 - slab0 + 1, v.NRG, v.B);

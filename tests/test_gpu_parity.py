@@ -2054,3 +2054,83 @@ def test_chunk_size_hook_is_checked():
             cache.set_decode_chunk(bad)
     for good in (128, 256, 0):
         cache.set_decode_chunk(good)
+
+
+@pytest.mark.parametrize("B,hkv,g,kw", [(1, 2, 2, {}), (3, 2, 2, {}), (9, 8, 4, {"bits": 4}), (64, 2, 2, {}), (65, 2, 2, {}),
+                                        (5, 4, 4, {"quant_group": 32}), (5, 8, 4, {"perm_span": 1024}), (65, 4, 4, {"perm_span": 512, "quant_group": 64})])
+def test_ragged_append_with_sinks_equals_single_sequences(B, hkv, g, kw):
+    """What an append does besides the codes - retention of flagged rows, the device's lengths and its chunk table - in
+    workgroups of its launch or in launches of their own, with counts as arguments (up to 64 sequences) or staged:
+    each sequence has the codes, sinks and outputs of a cache of its own.  Sequences without tokens, the first and a
+    later append with counts, a reset between."""
+    T = 300
+    cfg = R.RkvConfig(batch=B, n_q_heads=hkv, n_kv_heads=hkv, max_tokens=T, max_sinks=3, rot_heads=g, **kw)
+    one_cfg = dataclasses.replace(cfg, batch=1)
+    rng = np.random.default_rng(B + hkv)
+    perm = None
+    if cfg.perm_span > 128:
+        perm = np.concatenate([s0 + rng.permutation(cfg.perm_span) for s0 in range(0, hkv * 128, cfg.perm_span)]).astype(np.int32)
+    cache = R.RkvCache(cfg)
+    if perm is not None:
+        cache.set_perm(P.gpu(perm))
+    for rnd in range(2):
+        parts = []
+        for n_max in (260, 33):
+            counts = [int(x) for x in rng.integers(1, n_max, size=B)]
+            counts[0] = n_max
+            if B > 2:
+                counts[1] = 0 if n_max == 33 else 1            # (a sequence needs a token before it is attended)
+            k = torch.from_numpy(rng.standard_normal((B, n_max, hkv, 128), dtype=np.float32)).cuda().half()
+            v = torch.from_numpy(rng.standard_normal((B, n_max, hkv, 128), dtype=np.float32)).cuda().half()
+            mask = torch.from_numpy((rng.random((B, n_max)) < 0.02).astype(np.uint8)).cuda()
+            mask[:, 0] = 1
+            parts.append((counts, k, v, mask))
+            cache.quantize_append_ragged(k, v, counts, mask)
+        lens = [a + b for a, b in zip(parts[0][0], parts[1][0])]
+        assert cache.lengths == lens
+        q = torch.from_numpy(rng.standard_normal((B, hkv, 128), dtype=np.float32)).cuda().half()
+        out = cache.decode_attention(q)
+        codes, sinks = cache.export_codes(), cache.export_sinks()
+        for b in sorted({0, 1 % B, B // 2, B - 1}):
+            one = R.RkvCache(one_cfg)
+            if perm is not None:
+                one.set_perm(P.gpu(perm))
+            for counts, k, v, mask in parts:
+                n = counts[b]
+                if n:
+                    one.quantize_append(k[b:b + 1, :n].contiguous(), v[b:b + 1, :n].contiguous(), mask[b:b + 1, :n].contiguous())
+            ref, rs = one.export_codes(), one.export_sinks()
+            for name in ref:
+                assert torch.equal(codes[name][b, :lens[b]], ref[name][0, :lens[b]]), (rnd, b, name)
+            c = int(rs["count"][0])
+            assert int(sinks["count"][b]) == c
+            for name in ("pos", "k", "v"):
+                assert torch.equal(sinks[name][b, :c], rs[name][0, :c]), (rnd, b, name)
+            o = one.decode_attention(q[b:b + 1])
+            assert float((out[b] - o[0]).abs().max()) <= 1e-4 * float(o.abs().max()), (rnd, b)
+        cache.reset()
+
+
+@pytest.mark.parametrize("new_len", [40, 21, 20, 3, 0])
+def test_truncate_of_equal_lengths_drops_sinks_behind_the_end(new_len):
+    """A cut of equal lengths is the host's affair unless a retained sink lies behind it; sinks at 2 and 20."""
+    B, hkv = 2, 4
+    cfg = R.RkvConfig(batch=B, n_q_heads=hkv, n_kv_heads=hkv, max_tokens=64, max_sinks=4, rot_heads=4)
+    gen = torch.Generator(device="cuda").manual_seed(new_len)
+    k, v = (torch.randn(B, 60, hkv, 128, device="cuda", generator=gen).half() for _ in range(2))
+    mask = torch.zeros(B, 60, dtype=torch.uint8, device="cuda")
+    mask[:, [2, 20]] = 1
+    a, b = R.RkvCache(cfg), R.RkvCache(cfg)
+    a.quantize_append(k[:, :30].contiguous(), v[:, :30].contiguous(), mask[:, :30].contiguous())
+    a.quantize_append(k[:, 30:50].contiguous(), v[:, 30:50].contiguous())
+    a.truncate(new_len)
+    if new_len:
+        b.quantize_append(k[:, :new_len].contiguous(), v[:, :new_len].contiguous(), mask[:, :new_len].contiguous())
+    for c in (a, b):
+        c.quantize_append(k[:, 50:60].contiguous(), v[:, 50:60].contiguous(), mask[:, :10].contiguous())   # (a sink at new_len + 2)
+    q = torch.randn(B, hkv, 128, device="cuda", generator=gen).half()
+    assert a.length == b.length == new_len + 10 and torch.equal(a.decode_attention(q), b.decode_attention(q))
+    sa, sb = a.export_sinks(), b.export_sinks()
+    assert torch.equal(sa["count"], sb["count"])
+    for i in range(B):
+        assert torch.equal(sa["pos"][i, :int(sa["count"][i])], sb["pos"][i, :int(sa["count"][i])])
