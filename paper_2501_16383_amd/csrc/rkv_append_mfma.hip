@@ -870,6 +870,138 @@ __global__ void __launch_bounds__(256 * NP, NP == 1 ? 3 : 1) k_append_row_keys(R
 #undef RKV_ROW_DEPOSIT
 }
 
+// The same for an append of few tokens: one workgroup per token.  A matrix product of the kernel above has sixteen tokens of
+// one head in its columns, fifteen of them stand-ins when one token is appended; here the columns are sixteen heads of the
+// token, and the whole row takes 64 products (4096 channels) in place of 2 x 1024.  An output of a product depends on its own
+// row and column alone and the channels are summed in the same order, so the codes are the same bit for bit.  What is left is
+// a chain of latencies (row, extrema through LDS atomics, parameters, codes), three barriers long.  8 sequences x one token, 32
+// heads: 21.9 -> 6.0 us with the values and the query preparation in the same launch, which took 5.4 us of their own.
+// Wave (hg, pw): heads 16 hg + column, channels 32 pw .. + 31 of them: tiles p = 2 pw and 2 pw + 1; lane (column, q) of a
+// result holds channels 16 p + 4 q + r, which are the four codes at bits 16 (q & 1) + 4 r + 2 (q >> 1) of dword (head, p) of the token.
+// LDS: [NG] minima, [NG] maxima, [NG] parameters.
+#define RKV_ROW_FEW_HEADS 64           // a wave per sixteen heads and 32 channels: 1024 threads
+struct RkvRowFewLds {
+  float mn[256], mx[256];
+  float4 par[256];
+};
+template <int G, int HB>
+__device__ __forceinline__ void append_row_few(const RkvView& v, const __half* __restrict__ kin, int n_new, int i, int b, RkvRowFewLds& lds) {
+  constexpr bool HI = HB == 2, H1 = HB == 1;
+  constexpr float QMAX = HI ? 15.0f : (H1 ? 7.0f : 3.0f), INV_QMAX = HI ? 0.06666667f : (H1 ? 0.14285715f : 0.33333334f);
+  const int tid = threadIdx.x, lane = tid & 63, threads = blockDim.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), hg = wave >> 2, pw = wave & 3;
+  const int col = lane & 15, q = lane >> 4;
+  const int head = 16 * hg + col, hd = min(head, v.Hkv - 1);          // (columns without a head repeat the last one)
+  const int t = rkv_len(v, b) + i;
+  const __half* row = kin + ((size_t)b * n_new + i) * v.E + (size_t)hd * RKV_D;
+  uint4 x[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) x[ks] = rkv_ld_stream(reinterpret_cast<const uint4*>(row + 32 * ks + 8 * q));
+  int4 blk[2];                                                        // quantization blocks of the lane's channels
+#pragma unroll
+  for (int pp = 0; pp < 2; ++pp) blk[pp] = *reinterpret_cast<const int4*>(v.gid + hd * RKV_D + 16 * (2 * pw + pp) + 4 * q);
+  for (int e = tid; e < v.NG; e += threads) {
+    lds.mn[e] = 3.0e38f;
+    lds.mx[e] = -3.0e38f;
+  }
+  // A operand: lane (row m, k-group kg) holds H_128[16 p + m][32 ks + 8 kg + j], j = 0..7: the parity of (channel & k)
+  const int m = col, kg = q;
+  uint32_t sg[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    sg[j] = (0x3C003C00u ^ parity_mask(m & (2 * j) & 7, 0x00008000u)) ^ parity_mask(m & (2 * j + 1) & 7, 0x80000000u);
+  v4f acc[2];
+#pragma unroll
+  for (int pp = 0; pp < 2; ++pp) {
+    const int p = 2 * pw + pp;
+    const uint32_t mk = parity_mask(((m >> 3) & 1 & kg) ^ ((p & 1) & (kg >> 1)), 0x80008000u);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const uint32_t mm = mk ^ parity_mask((p >> 1) & ks, 0x80008000u);
+      const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+      acc[pp] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_v8h(sg[0] ^ mm, sg[1] ^ mm, sg[2] ^ mm, sg[3] ^ mm),
+                                                       as_v8h(x[ks].x, x[ks].y, x[ks].z, x[ks].w), ks == 0 ? zero4 : acc[pp], 0, 0, 0);
+    }
+  }
+  // H_g over the heads: neighbouring columns
+#pragma unroll
+  for (int pp = 0; pp < 2; ++pp)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float a = acc[pp][r];
+      const float b1 = __uint_as_float(dpp_u<0xB1>(__float_as_uint(a)));             // quad_perm [1,0,3,2]
+      a = (col & 1) ? b1 - a : a + b1;
+      if constexpr (G == 4) {
+        const float b2 = __uint_as_float(dpp_u<0x4E>(__float_as_uint(a)));           // quad_perm [2,3,0,1]
+        a = (col & 2) ? b2 - a : a + b2;
+      }
+      acc[pp][r] = a;
+    }
+  __syncthreads();
+  if (head < v.Hkv) {
+#pragma unroll
+    for (int pp = 0; pp < 2; ++pp) {
+      const int bk[4] = {blk[pp].x, blk[pp].y, blk[pp].z, blk[pp].w};
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        lds_fmin(&lds.mn[bk[r]], acc[pp][r]);
+        lds_fmax(&lds.mx[bk[r]], acc[pp][r]);
+      }
+    }
+  }
+  __syncthreads();
+  const float rs = rsqrtf((float)v.n);
+  for (int e = tid; e < v.NG; e += threads) {
+    float sc, zero_b, inv, base_b, add_b;
+    quant_params_nodiv(lds.mn[e] * rs, lds.mx[e] * rs, sc, zero_b, inv, v.meta8, INV_QMAX);
+    fused_round_consts(zero_b, base_b, add_b);
+    lds.par[e] = make_float4(inv * rs, add_b, base_b, 0.f);
+    rkv_store_meta(v, v.km, rkv_meta_index(v, b, t, e), sc, zero_b);
+  }
+  __syncthreads();
+  const int rg = head / G, hb = head & (G - 1);
+  const size_t tile = rkv_k_tilebase(v, b, rg, t >> 4);
+  uint32_t third = 0;
+#pragma unroll
+  for (int pp = 0; pp < 2; ++pp) {
+    const int bk[4] = {blk[pp].x, blk[pp].y, blk[pp].z, blk[pp].w};
+    uint32_t word = 0, upper = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float4 pr = lds.par[bk[r]];
+      const float c = __builtin_amdgcn_fmed3f(fmaf(acc[pp][r], pr.x, pr.y), pr.z, pr.z + QMAX);
+      const uint32_t code = __float_as_uint(c) - __float_as_uint(pr.z);
+      word |= (code & 3u) << (16 * (q & 1) + 4 * r + 2 * (q >> 1));
+      if constexpr (HI) upper |= (code >> 2) << (16 * (q & 1) + 4 * r + 2 * (q >> 1));
+      // (bit position m = 8 (q & 1) + 2 r + (q >> 1) of dword pp of the pair: bit 4 (m >> 1) + 2 pp + (m & 1))
+      if constexpr (H1) third |= (code >> 2) << (16 * (q & 1) + 4 * r + 2 * pp + (q >> 1));
+    }
+    word |= __shfl_xor(word, 16);
+    word |= __shfl_xor(word, 32);
+    const int p = 2 * pw + pp;
+    const size_t o = tile + ((((hb >> 1) * 4 + (p >> 1)) * 16 + (t & 15)) * 4) + (hb & 1) * 2 + (p & 1);
+    if (q == 0 && head < v.Hkv) v.kc[o] = word;
+    if constexpr (HI) {
+      upper |= __shfl_xor(upper, 16);
+      upper |= __shfl_xor(upper, 32);
+      if (q == 0 && head < v.Hkv) v.kh[o] = upper;
+    }
+    if constexpr (H1) {
+      if (pp == 1) {
+        third |= __shfl_xor(third, 16);
+        third |= __shfl_xor(third, 32);
+        if (q == 0 && head < v.Hkv) v.kh[o >> 1] = third;
+      }
+    }
+  }
+}
+template <int G, int HB>
+__global__ void __launch_bounds__(1024) k_append_row_few(RkvView v, const __half* __restrict__ kin, int n_new, RkvCounts counts) {
+  __shared__ RkvRowFewLds lds;
+  if ((int)blockIdx.x < rkv_count(v, counts, blockIdx.y, n_new)) append_row_few<G, HB>(v, kin, n_new, blockIdx.x, blockIdx.y, lds);
+}
+static int row_few_threads(const RkvView& v) { return 256 * ((v.Hkv + 15) / 16); }
+
 // One decode step's write half and query preparation in one launch: the first 3 * n_slabs
 // workgroups of a (rotation group, sequence) append the step's token as k_append_mfma does, the
 // rest prepare that rotation group's query heads (two heads per workgroup) for the decode kernel,
@@ -888,7 +1020,26 @@ __global__ void __launch_bounds__(256, 4) k_step_mfma(RkvView v, const __half* _
   rkv_prep_q_one(v, q, q_pos, 1, qr, share, 1, h, blockIdx.z, threadIdx.x & 127);
 }
 
-// The same for a reorder over the whole row, whose keys have a kernel of their own: the first workgroup of a
+// The same for a reorder over the whole row: of a sequence's workgroups with x = 0 the first takes the token's keys, those with
+// x = 1 the values of a rotation group each, the rest prepare its query heads (the last two in their first 256 threads).
+template <int G, int HB = 0, int SUB = 0>
+__global__ void __launch_bounds__(1024) k_step_row(RkvView v, const __half* __restrict__ kin, const __half* __restrict__ vin, int slab0,
+                                                  const __half* __restrict__ q, const int* __restrict__ q_pos, float* __restrict__ qr, int share) {
+  __shared__ RkvRowFewLds lds;
+  if (blockIdx.x == 0) {
+    if (blockIdx.y == 0) append_row_few<G, HB>(v, kin, 1, 0, blockIdx.z, lds);
+    return;
+  }
+  if (threadIdx.x >= 256) return;
+  if (blockIdx.x == 1) {
+    append_mfma_body<G, HB, false, SUB>(v, nullptr, vin, 1, 1, slab0, 2, blockIdx.y, blockIdx.z);
+    return;
+  }
+  const int rep = v.Hq / v.Hkv;
+  const int h = blockIdx.y * G * rep + 2 * ((int)blockIdx.x - 2) + (threadIdx.x >> 7);
+  rkv_prep_q_one(v, q, q_pos, 1, qr, share, 1, h, blockIdx.z, threadIdx.x & 127);
+}
+// ... with more heads than a workgroup of append_row_few takes: the keys have a launch of their own, the first workgroup of a
 // (rotation group, sequence) appends the step's values, the rest prepare its query heads.
 template <int G, int HB = 0, int SUB = 0>
 __global__ void __launch_bounds__(256, 4) k_step_values(RkvView v, const __half* __restrict__ vin, int slab0, const __half* __restrict__ q,
@@ -937,6 +1088,11 @@ bool rkv_append_mfma_supported(const rkv_cache* c) {
 template <int G, int HB>
 static int launch_row_keys(const rkv_cache* c, const __half* k, int n_new, int max_slabs, int slab0, const RkvCounts& counts, hipStream_t s) {
   const RkvView& v = c->v;
+  // One workgroup per token while they are at most one per compute unit (and one tile's worth per sequence)
+  if (v.Hkv <= RKV_ROW_FEW_HEADS && n_new <= 16 && (size_t)n_new * v.B <= (size_t)c->n_cu) {
+    hipLaunchKernelGGL((k_append_row_few<G, HB>), dim3(n_new, v.B), dim3(row_few_threads(v)), 0, s, v, k, n_new, counts);
+    return RKV_OK;
+  }
   const size_t dyn = row_keys_dynamic_lds(v);
   // Four wave sets per tile as long as there is at most one such workgroup per compute unit and the tables fit
   // beside their images.  One sequence, 32 heads, keys and values together: 2048 tokens 42 us against 53,
@@ -1052,6 +1208,18 @@ int rkv_launch_step_mfma(rkv_cache* c, const __half* k, const __half* vv, const 
   if (!rkv_append_mfma_supported(c)) return RKV_EINVAL;
   int max_slabs = 1;                                        // one token touches one slab of its sequence
   const int n_append = 3 * max_slabs, rep = v.Hq / v.Hkv;
+  if (append_row(c) && v.Hkv <= RKV_ROW_FEW_HEADS) {
+    dim3 grid(2 + v.g * rep / 2, v.NRG, v.B);
+#define RKV_SR(G_, H_, S_) \
+  hipLaunchKernelGGL((k_step_row<G_, H_, S_>), grid, dim3(row_few_threads(v)), 0, s, v, k, vv, v.len >> 5, q, q_pos, qr, share)
+#define RKV_SR_S(G_, H_) do { if (v.qg == 64) RKV_SR(G_, H_, 2); else if (v.qg == 32) RKV_SR(G_, H_, 4); else RKV_SR(G_, H_, 0); } while (0)
+#define RKV_SR_G(H_) do { if (v.g == 4) RKV_SR_S(4, H_); else RKV_SR_S(2, H_); } while (0)
+    if (v.hb == 2) RKV_SR_G(2); else if (v.hb == 1) RKV_SR_G(1); else RKV_SR_G(0);
+#undef RKV_SR_G
+#undef RKV_SR_S
+#undef RKV_SR
+    return rkv_check_launch();
+  }
   if (append_row(c)) {
     const int rc = launch_row_keys_of(c, k, 1, max_slabs, v.len >> 5, RkvCounts(), s);
     if (rc != RKV_OK) return rc;

@@ -2134,3 +2134,31 @@ def test_truncate_of_equal_lengths_drops_sinks_behind_the_end(new_len):
     assert torch.equal(sa["count"], sb["count"])
     for i in range(B):
         assert torch.equal(sa["pos"][i, :int(sa["count"][i])], sb["pos"][i, :int(sa["count"][i])])
+
+
+@pytest.mark.parametrize("hkv,g,bits,group,fmt,ragged", [(12, 4, 2, 128, 0, False), (40, 4, 3, 128, 1, True), (6, 2, 4, 128, 0, True),
+                                                         (10, 2, 2, 32, 0, False), (32, 4, 4, 64, 1, False), (62, 2, 2, 128, 0, False)])
+def test_whole_row_step_equals_the_two_calls(hkv, g, bits, group, fmt, ragged):
+    """One launch for a step's keys, values and queries under a reorder over the whole row: the same codes, metadata and outputs
+    as a bulk append of the same tokens followed by the attention call."""
+    B, T = 3, 70
+    cfg = R.RkvConfig(batch=B, n_q_heads=hkv, n_kv_heads=hkv, max_tokens=T + 3, max_sinks=0, rot_heads=g, bits=bits, quant_group=group,
+                      meta_format=fmt, perm_span=hkv * 128)
+    gen = torch.Generator(device="cuda").manual_seed(hkv)
+    k, v = (torch.randn(B, T + 3, hkv, 128, device="cuda", generator=gen).half() for _ in range(2))
+    perm = torch.from_numpy(np.random.default_rng(hkv).permutation(hkv * 128).astype(np.int32)).cuda()
+    lens = [T, 13, 64] if ragged else [T] * B
+    a, b = R.RkvCache(cfg), R.RkvCache(cfg)
+    for c in (a, b):
+        c.set_perm(perm)
+        c.quantize_append_ragged(k[:, :T].contiguous(), v[:, :T].contiguous(), lens)
+    for i in range(3):
+        q = torch.randn(B, hkv, 128, device="cuda", generator=gen).half()
+        kn, vn = k[:, T + i:T + i + 1].contiguous(), v[:, T + i:T + i + 1].contiguous()
+        out = a.decode_step(kn, vn, q)
+        b.quantize_append(kn, vn)
+        assert torch.equal(out, b.decode_attention(q)), i
+    assert a.lengths == b.lengths == [n + 3 for n in lens]
+    ea, eb = a.export_codes(), b.export_codes()
+    for s in range(B):
+        assert all(torch.equal(ea[name][s, :lens[s] + 3], eb[name][s, :lens[s] + 3]) for name in ea)
