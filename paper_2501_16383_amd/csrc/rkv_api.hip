@@ -631,9 +631,10 @@ RKV_EXPORT int rkv_decode_step(rkv_cache* cache, const void* dev_k, const void* 
   }
   hipStream_t s = (hipStream_t)stream;
   const int share = rkv_prep_form(cache, cache->v.Hq / cache->v.Hkv);
+  bool lens_set = false;
   int rc = rkv_launch_step_mfma(cache, (const __half*)dev_k, (const __half*)dev_v, (const __half*)dev_q, dev_q_pos,
-                                (float*)dev_scratch, share, s);
-  if (rc == RKV_OK && cache->ragged) rc = rkv_launch_lens(cache, -1, 1, RkvCounts(), s);
+                                (float*)dev_scratch, share, &lens_set, s);
+  if (rc == RKV_OK && cache->ragged && !lens_set) rc = rkv_launch_lens(cache, -1, 1, RkvCounts(), s);
   if (rc != RKV_OK) return rc;
   cache->v.len += 1;
   for (int b = 0; b < cache->v.B; ++b) cache->hlens[b] += 1;

@@ -22,88 +22,15 @@
 //   values  wave w: tokens 8w..8w+7.
 #include "rkv_internal.h"
 #include "rkv_quant.h"
+#include "rkv_append_ops.h"
+#include "rkv_append_one.h"
 #include "rkv_prep_q.h"
 #include "rkv_sinks.h"
 
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ v8h as_v8h(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
-  union { uint32_t u[4]; v8h h; } x;
-  x.u[0] = a; x.u[1] = b; x.u[2] = c; x.u[3] = d;
-  return x.h;
-}
-__device__ __forceinline__ uint32_t parity_mask(int x, uint32_t m) { return (__popc(x) & 1) ? m : 0u; }
-
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, u); }
-__device__ __forceinline__ uint32_t as_u32(h2 h) { return __builtin_bit_cast(uint32_t, h); }
-// packed fp16 min / max as single instructions (the builtin forms add a canonicalizing instruction
-// per operand, which costs as much as the operation itself)
-__device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
-  uint32_t r;
-  asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
-  uint32_t r;
-  asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
 // float minimum / maximum into LDS (ds_min_f32, ds_max_f32; nothing is returned)
 typedef __attribute__((address_space(3))) float lds_float;
 __device__ __forceinline__ void lds_fmin(float* p, float x) { __builtin_amdgcn_ds_fminf((lds_float*)p, x, 0, 0, false); }
 __device__ __forceinline__ void lds_fmax(float* p, float x) { __builtin_amdgcn_ds_fmaxf((lds_float*)p, x, 0, 0, false); }
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
-}
-
-// Eq. 8-9 for one block given its min and max, as quant_params but without IEEE divisions: the
-// division by 3 (or 7, or 15) is a multiplication (error below 1.5 ulp of fp32, which can change the fp16 scale
-// only within 2^-23 of a rounding boundary) and the reciprocal of the scale is v_rcp_f32 refined by
-// one Newton step.
-// meta8: FP8 E4M3 scale rounded up, INT8 zero-point.
-// inv_qmax: 1 / (2^bits - 1) rounded to fp32.
-__device__ __forceinline__ void quant_params_nodiv(float mn, float mx, float& s, float& zero, float& inv_s, bool meta8,
-                                                   float inv_qmax = 0.33333334f) {
-  const float raw = (mx - mn) * inv_qmax;
-  if (meta8) {
-    s = rkv_e4m3_round_up(raw);
-    if (s == 0.0f) {
-      s = rkv_e4m3_round_up(fabsf(mn));
-      if (s == 0.0f) s = 1.0f;
-    }
-  } else {
-    s = __half2float(__float2half_rn(raw));
-    if (!(s <= 65504.0f)) s = 65504.0f;
-    if (s == 0.0f) {
-      s = __half2float(__float2half_rn(fabsf(mn)));
-      if (!(s <= 65504.0f)) s = 65504.0f;
-      if (s == 0.0f) s = 1.0f;
-    }
-  }
-  const float r0 = __builtin_amdgcn_rcpf(s);
-  inv_s = fmaf(fmaf(-s, r0, 1.0f), r0, r0);
-  zero = -rintf(mn * inv_s);
-  zero = meta8 ? fminf(fmaxf(zero, -128.0f), 127.0f) : fminf(fmaxf(zero, -2048.0f), 2048.0f);
-}
-
-// value of x in lane `src_lane` (the address operand is the lane number times 4)
-__device__ __forceinline__ float lane_read(float x, int src_lane4) {
-  return __int_as_float(__builtin_amdgcn_ds_bpermute(src_lane4, __float_as_int(x)));
-}
-
-// Eq. 6 with one FMA per element.  Adding 1.5 * 2^23 rounds to an integer, ties to even, as rintf;
-// adding the (integer) zero-point in the same FMA keeps that rounding only if the constant added is
-// even, so an odd zero-point is raised by one and the clamp bounds and the packing bias move with
-// it.  `base` = 1.5 * 2^23 + (zero & 1); `add` = base + zero; codes are float_bits - bits(base).
-__device__ __forceinline__ void fused_round_consts(float zero, float& base, float& add) {
-  const float odd = (float)((int)zero & 1);
-  base = 12582912.0f + odd;
-  add = base + zero;
-}
-
 // bx, rg, b: the workgroup's place in the (3 x slabs, rotation groups, sequences) grid
 // HB = 1: 3-bit codes, 7 steps; the third bits go to their plane, whose dwords take the bits of
 // one matrix operand each (see the layout notes): the four key waves of a tile, and the four
@@ -125,7 +52,7 @@ __device__ __forceinline__ void fused_round_consts(float zero, float& base, floa
 // channels of a head, so the lane-exchange reduction simply stops earlier.
 template <int G, int HB, bool XW = false, int SUB = 0>
 __device__ __forceinline__ void append_mfma_body(const RkvView& v, const __half* __restrict__ kin, const __half* __restrict__ vin,
-                                                 int n_new, int n_b, int slab0, int bx, int rg, int b) {
+                                                 int n_new, int n_b, int len_b, int slab0, int bx, int rg, int b) {
   constexpr int PL = 2 * G;                    // value channels per lane
   constexpr int LPB = 128 / PL;                // lanes per 128-block in the value role
   constexpr int n = 128 * G;
@@ -159,7 +86,6 @@ __device__ __forceinline__ void append_mfma_body(const RkvView& v, const __half*
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // in a scalar register: everything that depends only on it stays scalar
   const int role = bx % 3;                     // 0, 1: the keys of K tile 0 / 1 of a slab; 2: the slab's values
   // n_new: rows per sequence in kin and vin; sequence b holds len_b tokens and appends the first n_b rows
-  const int len_b = rkv_len(v, b);
   const int slab = (v.lens ? (len_b >> 5) : slab0) + bx / 3;
   const int t_lo = len_b, t_hi = len_b + n_b;
   const int ts = slab * 32;
@@ -580,26 +506,29 @@ struct RkvAppendExtra {
   int* staged;
   RkvCounts counts;
 };
+// Lengths from + counts.n[b], and the running count of their chunks: lane = sequence (at most RKV_ARG_COUNTS of them)
+__device__ __forceinline__ void set_lens(int B, int from, const RkvCounts& counts, int* lens, int* cstart, int* staged) {
+  static_assert(RKV_ARG_COUNTS == 64, "a sequence per lane");
+  const int b = threadIdx.x;
+  if (b >= 64) return;
+  const int n_b = counts.n[b], len = b < B ? from + n_b : 0;
+  int run = (len + 255) >> 8;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int below = __shfl_up(run, o);
+    if (b >= o) run += below;
+  }
+  if (b < B) {
+    lens[b] = len;
+    cstart[b + 1] = run;
+    if (b == 0) cstart[0] = 0;
+    if (staged) staged[b] = n_b;
+  }
+}
 __device__ __forceinline__ void append_extra(const RkvView& v, const __half* kin, const __half* vin, int n_new, const RkvAppendExtra& x) {
   __shared__ RkvSinkLds lds;
   const int idx = blockIdx.z * v.NRG + blockIdx.y;
-  if (x.lens && idx == min(v.B, v.B * v.NRG - 1) && threadIdx.x < 64) {
-    // lane = sequence (at most RKV_ARG_COUNTS of them): lengths, and the running count of their chunks
-    static_assert(RKV_ARG_COUNTS == 64, "a sequence per lane");
-    const int b = threadIdx.x, n_b = b < v.B ? x.counts.n[b] : 0, len = b < v.B ? v.len + n_b : 0;
-    int run = (len + 255) >> 8;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int below = __shfl_up(run, o);
-      if (b >= o) run += below;
-    }
-    if (b < v.B) {
-      x.lens[b] = len;
-      x.staged[b] = n_b;
-      x.cstart[b + 1] = run;
-      if (b == 0) x.cstart[0] = 0;
-    }
-  }
+  if (x.lens && idx == min(v.B, v.B * v.NRG - 1)) set_lens(v.B, v.len, x.counts, x.lens, x.cstart, x.staged);
   if (x.mask && idx < v.B) rkv_sinks_of<256>(v, kin, vin, x.mask, n_new, rkv_count(v, x.counts, idx, n_new), idx, lds);
 }
 
@@ -615,7 +544,7 @@ __global__ void __launch_bounds__(256, (XW || SUB || HB == 1) ? 4 : G == 2 ? 8 :
     }
     bx -= RKV_EXTRA_COLS;
   }
-  append_mfma_body<G, HB, XW, SUB>(v, kin, vin, n_new, rkv_count(v, extra.counts, blockIdx.z, n_new), slab0, bx, blockIdx.y, blockIdx.z);
+  append_mfma_body<G, HB, XW, SUB>(v, kin, vin, n_new, rkv_count(v, extra.counts, blockIdx.z, n_new), rkv_len(v, blockIdx.z), slab0, bx, blockIdx.y, blockIdx.z);
 }
 
 // the value role alone (grid x = slabs): the keys of a reorder over the whole row have a kernel of their own
@@ -630,8 +559,8 @@ __global__ void __launch_bounds__(256, (HB || SUB) ? 4 : 6) k_append_values(RkvV
     }
     --bx;
   }
-  append_mfma_body<G, HB, false, SUB>(v, nullptr, vin, n_new, rkv_count(v, extra.counts, blockIdx.z, n_new), slab0, 3 * bx + 2, blockIdx.y,
-                                      blockIdx.z);
+  append_mfma_body<G, HB, false, SUB>(v, nullptr, vin, n_new, rkv_count(v, extra.counts, blockIdx.z, n_new), rkv_len(v, blockIdx.z), slab0,
+                                      3 * bx + 2, blockIdx.y, blockIdx.z);
 }
 
 // Keys under a reorder over the whole token row (perm_span = n_kv_heads * 128, Alg. 1 as printed;
@@ -1002,22 +931,40 @@ __global__ void __launch_bounds__(1024) k_append_row_few(RkvView v, const __half
 }
 static int row_few_threads(const RkvView& v) { return 256 * ((v.Hkv + 15) / 16); }
 
-// One decode step's write half and query preparation in one launch: the first 3 * n_slabs
-// workgroups of a (rotation group, sequence) append the step's token as k_append_mfma does, the
-// rest prepare that rotation group's query heads (two heads per workgroup) for the decode kernel,
-// which saves a launch of its own for a few microseconds of work.  The query's default position
-// is the appended token's: one past the last token the view knows of.
+// One decode step's write half and query preparation in one launch: the first workgroups of a (rotation group, sequence) - one
+// (rkv_append_one), or with blocks of their own three - append the step's token, the rest prepare that rotation group's query heads (two
+// heads per workgroup) for the decode kernel, which saves a launch of its own for a few microseconds of work.  The query's
+// default position is the appended token's: one past the last token the view knows of.
+// at: the lengths before the step by value, where sequences differ and fit; one more workgroup then gives the device the new
+// ones (nobody reads its copy in this launch, which saves the 3.8 us of one behind it).
+struct RkvStepLens {
+  RkvCounts at;
+  int* lens;
+  int* cstart;
+};
 template <int G, int HB, bool XW = false, int SUB = 0>
 __global__ void __launch_bounds__(256, 4) k_step_mfma(RkvView v, const __half* __restrict__ kin, const __half* __restrict__ vin,
-                                                   int slab0, int n_append_blocks, const __half* __restrict__ q,
-                                                   const int* __restrict__ q_pos, float* __restrict__ qr, int share) {
-  if ((int)blockIdx.x < n_append_blocks) {
-    append_mfma_body<G, HB, XW, SUB>(v, kin, vin, 1, 1, slab0, blockIdx.x, blockIdx.y, blockIdx.z);
+                                                   int slab0, const __half* __restrict__ q, const int* __restrict__ q_pos,
+                                                   float* __restrict__ qr, int share, RkvStepLens sl) {
+  constexpr bool ONE = !XW && SUB == 0;
+  constexpr int N_APPEND = ONE ? 1 : 3;
+  const int rg = blockIdx.y, b = blockIdx.z, rep = v.Hq / v.Hkv;
+  if (sl.at.on && (int)blockIdx.x == N_APPEND + G * rep / 2) {
+    if (rg == 0 && b == 0) set_lens(v.B, 1, sl.at, sl.lens, sl.cstart, nullptr);
     return;
   }
-  const int rep = v.Hq / v.Hkv;
-  const int h = blockIdx.y * G * rep + 2 * ((int)blockIdx.x - n_append_blocks) + (threadIdx.x >> 7);
-  rkv_prep_q_one(v, q, q_pos, 1, qr, share, 1, h, blockIdx.z, threadIdx.x & 127);
+  const int len = sl.at.on ? sl.at.n[b % RKV_ARG_COUNTS] : rkv_len(v, b);
+  if ((int)blockIdx.x < N_APPEND) {
+    if constexpr (ONE) {
+      __shared__ RkvOneLds lds;
+      rkv_append_one<G, HB>(v, kin + (size_t)b * v.E, vin + (size_t)b * v.E, len, b, rg, lds);
+    } else {
+      append_mfma_body<G, HB, XW, SUB>(v, kin, vin, 1, 1, len, len >> 5, blockIdx.x, rg, b);
+    }
+    return;
+  }
+  const int h = rg * G * rep + 2 * ((int)blockIdx.x - N_APPEND) + (threadIdx.x >> 7);
+  rkv_prep_q_one(v, q, q_pos, len, qr, share, 1, h, b, threadIdx.x & 127);
 }
 
 // The same for a reorder over the whole row: of a sequence's workgroups with x = 0 the first takes the token's keys, those with
@@ -1032,12 +979,12 @@ __global__ void __launch_bounds__(1024) k_step_row(RkvView v, const __half* __re
   }
   if (threadIdx.x >= 256) return;
   if (blockIdx.x == 1) {
-    append_mfma_body<G, HB, false, SUB>(v, nullptr, vin, 1, 1, slab0, 2, blockIdx.y, blockIdx.z);
+    append_mfma_body<G, HB, false, SUB>(v, nullptr, vin, 1, 1, rkv_len(v, blockIdx.z), slab0, 2, blockIdx.y, blockIdx.z);
     return;
   }
   const int rep = v.Hq / v.Hkv;
   const int h = blockIdx.y * G * rep + 2 * ((int)blockIdx.x - 2) + (threadIdx.x >> 7);
-  rkv_prep_q_one(v, q, q_pos, 1, qr, share, 1, h, blockIdx.z, threadIdx.x & 127);
+  rkv_prep_q_one(v, q, q_pos, rkv_len(v, blockIdx.z), qr, share, 1, h, blockIdx.z, threadIdx.x & 127);
 }
 // ... with more heads than a workgroup of append_row_few takes: the keys have a launch of their own, the first workgroup of a
 // (rotation group, sequence) appends the step's values, the rest prepare its query heads.
@@ -1045,12 +992,12 @@ template <int G, int HB = 0, int SUB = 0>
 __global__ void __launch_bounds__(256, 4) k_step_values(RkvView v, const __half* __restrict__ vin, int slab0, const __half* __restrict__ q,
                                                      const int* __restrict__ q_pos, float* __restrict__ qr, int share) {
   if (blockIdx.x == 0) {
-    append_mfma_body<G, HB, false, SUB>(v, nullptr, vin, 1, 1, slab0, 2, blockIdx.y, blockIdx.z);
+    append_mfma_body<G, HB, false, SUB>(v, nullptr, vin, 1, 1, rkv_len(v, blockIdx.z), slab0, 2, blockIdx.y, blockIdx.z);
     return;
   }
   const int rep = v.Hq / v.Hkv;
   const int h = blockIdx.y * G * rep + 2 * ((int)blockIdx.x - 1) + (threadIdx.x >> 7);
-  rkv_prep_q_one(v, q, q_pos, 1, qr, share, 1, h, blockIdx.z, threadIdx.x & 127);
+  rkv_prep_q_one(v, q, q_pos, rkv_len(v, blockIdx.z), qr, share, 1, h, blockIdx.z, threadIdx.x & 127);
 }
 
 static size_t row_keys_dynamic_lds(const RkvView& v, bool table = true) {
@@ -1202,12 +1149,14 @@ int rkv_launch_append_mfma(rkv_cache* c, const __half* k, const __half* vv, int 
 }
 
 // The fused launch of k_step_mfma: one token per sequence from k, vv [batch][1][...], queries q.
+// lens_set: whether the launch has given the device the new lengths of sequences that differ
 int rkv_launch_step_mfma(rkv_cache* c, const __half* k, const __half* vv, const __half* q, const int* q_pos, float* qr, int share,
-                         hipStream_t s) {
+                         bool* lens_set, hipStream_t s) {
   const RkvView& v = c->v;
   if (!rkv_append_mfma_supported(c)) return RKV_EINVAL;
-  int max_slabs = 1;                                        // one token touches one slab of its sequence
-  const int n_append = 3 * max_slabs, rep = v.Hq / v.Hkv;
+  const int max_slabs = 1;                                  // one token touches one slab of its sequence
+  const int rep = v.Hq / v.Hkv;
+  *lens_set = false;
   if (append_row(c) && v.Hkv <= RKV_ROW_FEW_HEADS) {
     dim3 grid(2 + v.g * rep / 2, v.NRG, v.B);
 #define RKV_SR(G_, H_, S_) \
@@ -1233,9 +1182,17 @@ int rkv_launch_step_mfma(rkv_cache* c, const __half* k, const __half* vv, const 
 #undef RKV_SV
     return rkv_check_launch();
   }
-  dim3 grid(n_append + v.g * rep / 2, v.NRG, v.B);
+  RkvStepLens sl{};
+  if (c->ragged && v.B <= RKV_ARG_COUNTS) {
+    sl.at.on = 1;
+    for (int b = 0; b < v.B; ++b) sl.at.n[b] = c->hlens[b];
+    sl.lens = c->dev_lens;
+    sl.cstart = c->dev_cstart;
+    *lens_set = true;
+  }
+  dim3 grid((v.qg == 128 && c->blocks_aligned ? 1 : 3) + v.g * rep / 2 + (sl.at.on ? 1 : 0), v.NRG, v.B);
 #define RKV_ST(G_, H_, X_, S_) \
-  hipLaunchKernelGGL((k_step_mfma<G_, H_, X_, S_>), grid, dim3(256), 0, s, v, k, vv, v.len >> 5, n_append, q, q_pos, qr, share)
+  hipLaunchKernelGGL((k_step_mfma<G_, H_, X_, S_>), grid, dim3(256), 0, s, v, k, vv, v.len >> 5, q, q_pos, qr, share, sl)
 #define RKV_ST_G(H_, X_, S_) do { if (v.g == 4) RKV_ST(4, H_, X_, S_); else RKV_ST(2, H_, X_, S_); } while (0)
 #define RKV_ST_H(X_, S_) do { if (v.hb == 2) RKV_ST_G(2, X_, S_); else if (v.hb == 1) RKV_ST_G(1, X_, S_); else RKV_ST_G(0, X_, S_); } while (0)
   if (v.qg == 64 && c->blocks_aligned) RKV_ST_H(false, 2);

@@ -37,7 +37,8 @@ __device__ inline void fwht_lanes_d(T (&x)[PL], int lane, int xstages) {
 
 __global__ void __launch_bounds__(128) k_prep_q(RkvView v, const __half* __restrict__ q, const int* __restrict__ q_pos,
                                                 int cur, float* __restrict__ qr, int share, int nq) {
-  rkv_prep_q_one(v, q, q_pos, cur, qr, share, nq, blockIdx.x, blockIdx.y, threadIdx.x);
+  // (default position: the last cached token's, or one past it when the token being decoded is not in the cache yet, cur = 1)
+  rkv_prep_q_one(v, q, q_pos, rkv_len(v, blockIdx.y) - 1 + cur, qr, share, nq, blockIdx.x, blockIdx.y, threadIdx.x);
 }
 
 __device__ inline bool is_sink(const int* sp, int cnt, int t) {

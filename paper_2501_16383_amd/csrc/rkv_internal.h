@@ -331,7 +331,7 @@ int rkv_launch_scores_row(const rkv_cache* c, const RkvView& v, const float* qr,
 bool rkv_scores_multi_ok(const rkv_cache* c, int n_queries);   // several query tokens per step on that route
 size_t rkv_partial_bytes(int batch, int n_q_heads, int Tpad);
 int rkv_launch_step_mfma(rkv_cache* c, const __half* k, const __half* v, const __half* q, const int* q_pos, float* qr, int share,
-                         hipStream_t s);
+                         bool* lens_set, hipStream_t s);
 bool rkv_mfma_supported(const rkv_cache* c);
 int rkv_mfma_variant(const rkv_cache* c);   // RKV_KERNEL_MFMA, _MFMA_CROSS or _MFMA_SUB (if rkv_mfma_supported)
 void rkv_launch_prep_q(const RkvView& v, const __half* q, const int* q_pos, int cur, float* qr, int share, int nq,

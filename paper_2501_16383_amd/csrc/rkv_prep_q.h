@@ -21,11 +21,11 @@ __device__ __forceinline__ float rkv_prep_q_rotate(const RkvView& v, float x, fl
 // q~[b][h][c] = RoPE(q, q_pos)[c] / sqrt(128), angles in double (q_pos may lie beyond the table).
 // share: 0 for k_decode_shared's operands besides, 1 for k_decode_mfma's (Hq == Hkv), -1 for neither.
 __device__ __forceinline__ void rkv_prep_q_one(const RkvView& v, const __half* __restrict__ q, const int* __restrict__ q_pos,
-                                               int cur, float* __restrict__ qr, int share, int nq, int h, int b, int c) {
+                                               int at, float* __restrict__ qr, int share, int nq, int h, int b, int c) {
   // v.Hq counts virtual heads when nq > 1 (several query tokens, each at its own position)
   const RkvVHead vh = rkv_virtual_head(v, h, nq);
-  // default position: the last cached token's, or one past it when the token being decoded is not in the cache yet (cur = 1)
-  const int pos = q_pos ? q_pos[b * nq + vh.qi] : rkv_len(v, b) - 1 + cur;
+  // at: the default position
+  const int pos = q_pos ? q_pos[b * nq + vh.qi] : at;
   const size_t base = ((size_t)b * v.Hq + h) * RKV_D;                       // where the rotated query goes
   const size_t src = (((size_t)b * nq + vh.qi) * (v.Hq / nq) + vh.h) * RKV_D; // where the raw query is
   int j, partner;
