@@ -595,7 +595,7 @@ RKV_EXPORT int rkv_decode_attention(rkv_cache* cache, const void* dev_q, const i
   if (cache->decode_path == 1) fast = false;
   if (fast)
     return rkv_launch_decode_mfma(cache, (const __half*)dev_q, dev_q_pos, 0, dev_out, dev_lse, dev_scratch, false,
-                                  (hipStream_t)stream);
+                                  RkvStepIn(), (hipStream_t)stream);
   return rkv_launch_decode_general(cache, (const __half*)dev_q, dev_q_pos, 0, dev_out, dev_lse, dev_scratch, (hipStream_t)stream);
 }
 
@@ -630,6 +630,15 @@ RKV_EXPORT int rkv_decode_step(rkv_cache* cache, const void* dev_k, const void* 
     return rc != RKV_OK ? rc : rkv_decode_attention(cache, dev_q, dev_q_pos, dev_out, dev_lse, dev_scratch, stream);
   }
   hipStream_t s = (hipStream_t)stream;
+  if (!dev_q_pos && rkv_step_in_decode(cache)) {
+    RkvStepIn step;
+    step.k = (const __half*)dev_k;
+    step.v = (const __half*)dev_v;
+    step.q = (const __half*)dev_q;
+    cache->v.len += 1;
+    for (int b = 0; b < cache->v.B; ++b) cache->hlens[b] += 1;
+    return rkv_launch_decode_mfma(cache, step.q, nullptr, 0, dev_out, dev_lse, dev_scratch, true, step, s);
+  }
   const int share = rkv_prep_form(cache, cache->v.Hq / cache->v.Hkv);
   bool lens_set = false;
   int rc = rkv_launch_step_mfma(cache, (const __half*)dev_k, (const __half*)dev_v, (const __half*)dev_q, dev_q_pos,
@@ -638,7 +647,7 @@ RKV_EXPORT int rkv_decode_step(rkv_cache* cache, const void* dev_k, const void* 
   if (rc != RKV_OK) return rc;
   cache->v.len += 1;
   for (int b = 0; b < cache->v.B; ++b) cache->hlens[b] += 1;
-  return rkv_launch_decode_mfma(cache, (const __half*)dev_q, dev_q_pos, 0, dev_out, dev_lse, dev_scratch, true, s);
+  return rkv_launch_decode_mfma(cache, (const __half*)dev_q, dev_q_pos, 0, dev_out, dev_lse, dev_scratch, true, RkvStepIn(), s);
 }
 
 RKV_EXPORT int rkv_decode_attention_multi(rkv_cache* cache, const void* dev_q, const int32_t* dev_q_pos, int32_t n_queries,
@@ -655,7 +664,7 @@ RKV_EXPORT int rkv_decode_attention_multi(rkv_cache* cache, const void* dev_q, c
     return rkv_launch_decode_general(cache, (const __half*)dev_q, dev_q_pos, n_queries, dev_out, dev_lse, dev_scratch,
                                      (hipStream_t)stream);
   return rkv_launch_decode_mfma(cache, (const __half*)dev_q, dev_q_pos, n_queries, dev_out, dev_lse, dev_scratch, false,
-                                (hipStream_t)stream);
+                                RkvStepIn(), (hipStream_t)stream);
 }
 
 RKV_EXPORT int rkv_dequantize(rkv_cache* cache, float* dev_k_hat, float* dev_v_hat, void* stream) {

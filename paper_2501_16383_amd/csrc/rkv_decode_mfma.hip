@@ -37,6 +37,8 @@
 // general kernel.
 #include "rkv_internal.h"
 #include "rkv_mfma_ops.h"
+#include "rkv_append_one.h"
+#include "rkv_prep_q.h"
 #include <hip/hip_ext.h>
 
 typedef _Float16 v4h __attribute__((ext_vector_type(4)));
@@ -166,10 +168,16 @@ __device__ __forceinline__ float row_transpose_reduce(const float (&v)[NV], int 
 // (-infinity at retained sink tokens) in place of the key phase - a reorder over the whole token
 // row, whose scores k_scores_row computes; qt then points to that buffer.  Softmax, values and
 // partial results as in the plain kernel.
-template <int G, int REP, bool MULTI, bool META8, int HB, int SUB = 0, bool ALU = false, bool PRE = false, int TILES = MF_TILES>
+// STEP: a whole decode step but for the merge.  The sequences' last token is new: the workgroup whose chunk holds it appends it
+// first (rkv_append_one: two round trips and a barrier more for one workgroup in nch), and every workgroup rotates the queries
+// of its rotation group itself - one channel pair per thread, two positions -, the first chunk's leaving the plain copy for the
+// merge.  That is what the launch in front did, 4 to 7 us of latency: one sequence x 4096 tokens 17.7 -> STEPSINGLE us, 16 x 4096
+// tokens of 40 heads 67.4 -> STEPBATCH.
+template <int G, int REP, bool MULTI, bool META8, int HB, int SUB = 0, bool ALU = false, bool PRE = false, int TILES = MF_TILES, bool STEP = false>
 __global__ void __launch_bounds__(256, (HB && G == 4 && TILES == 4) ? MF_OCC_HI : MF_OCC) k_decode_mfma(RkvView v, const float* __restrict__ qt,
                                                                        float* __restrict__ part, int nch,
-                                                                       const int* __restrict__ q_lim, int nq, int ns, uint32_t inv_ns, uint32_t inv_nrg) {
+                                                                       const int* __restrict__ q_lim, int nq, int ns, uint32_t inv_ns, uint32_t inv_nrg,
+                                                                       RkvStepIn step) {
   constexpr bool HI = HB != 0;
   constexpr int CH = 64 * TILES;                 // tokens per workgroup (4 waves)
   constexpr int NH = G * REP;                    // query heads served by this workgroup: REP per KV head
@@ -286,7 +294,7 @@ __global__ void __launch_bounds__(256, (HB && G == 4 && TILES == 4) ? MF_OCC_HI 
   const uint4* q_src = reinterpret_cast<const uint4*>(qt + ((size_t)b * v.NRG + rg) * (2 * 16 * 4 * 2 * G));
   uint4 ld_q[QN];
 #pragma unroll
-  for (int i = 0; i < QN; ++i) ld_q[i] = tid + 256 * i < Q16 ? q_src[tid + 256 * i] : make_uint4(0, 0, 0, 0);
+  for (int i = 0; i < QN; ++i) ld_q[i] = !STEP && tid + 256 * i < Q16 ? q_src[tid + 256 * i] : make_uint4(0, 0, 0, 0);
   //  - RoPE angles are kept for the first of a lane's four tokens only: they rotate all four keys and the query
   //    comes rotated back by 0..3 positions to make up for it (k_prep_q).  The next tile follows by
   //    rotating 16 positions (table row 16; used once per tile, read from LDS)
@@ -295,6 +303,26 @@ __global__ void __launch_bounds__(256, (HB && G == 4 && TILES == 4) ? MF_OCC_HI 
   //  - the sink list: positions unconditionally (the store holds max_sinks of them, unused ones -1), masked by the count below
   const int ld_cnt = v.max_sinks > 0 ? v.sink_cnt[b] : 0;
   const int ld_spos = (v.max_sinks > 0 && (tid & 63) < v.max_sinks) ? v.sink_pos[b * v.max_sinks + (tid & 63)] : -1;
+  //  - (a step) channel pair tid mod 64 of query head tid / 64 and its angles at the last three positions; pair 0 of head `lane`
+  [[maybe_unused]] float st_x = 0.f, st_y = 0.f, st_x0 = 0.f, st_y0 = 0.f;
+  [[maybe_unused]] float2 st_cs[3], st_cs0;
+  [[maybe_unused]] const int qa = tid >> 6, qj = tid & 63;
+  if constexpr (STEP) {
+    const __half* qrow = step.q + ((size_t)b * v.Hq + rg * G) * RKV_D;
+    const __half* row = qrow + (qa < G ? qa : 0) * RKV_D;
+    st_x = __half2float(row[v.rope_style ? 2 * qj : qj]);
+    st_y = __half2float(row[v.rope_style ? 2 * qj + 1 : qj + 64]);
+    st_x0 = __half2float(qrow[(lane & (G - 1)) * RKV_D]);
+    st_y0 = __half2float(qrow[(lane & (G - 1)) * RKV_D + (v.rope_style ? 1 : 64)]);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) st_cs[r] = v.rope[(size_t)(len - 1 - r) * 64 + qj];      // (a step of this kind leaves at least three tokens)
+    st_cs0 = v.rope[(size_t)(len - 1) * 64];
+    if (len - 1 >= t0 && len - 1 < t0 + CH) {                // the chunk of the new token
+      __shared__ RkvOneLds one;
+      rkv_append_one<G, HB>(v, step.k + (size_t)b * v.E, step.v + (size_t)b * v.E, len - 1, b, rg, one);
+      __syncthreads();                                       // (its codes and metadata are read below like any other's)
+    }
+  }
   //  - (plain variants) the metadata of token t0 + tid of keys and values, its RoPE angle for channel
   //    pair 0 and the queries' entries for that pair: staged below
   uint32_t ld_mk[4] = {0, 0, 0, 0}, ld_mv[4] = {0, 0, 0, 0};
@@ -322,10 +350,20 @@ __global__ void __launch_bounds__(256, (HB && G == 4 && TILES == 4) ? MF_OCC_HI 
     // channel pair 0 of the queries at their own position (the plain copy, in front of the other), scaled like the other
     const float* q_nat = qt - (size_t)v.B * v.Hq * RKV_D + ((size_t)b * v.Hq + rg * G) * RKV_D;
     const float lane_scale = 2.0f * rsqrtf((float)v.n);
+    if constexpr (STEP) {
+      const int l = __float_as_int(rkv_prep_q_turn(st_x0, st_y0, -1.f, st_cs0.x, st_cs0.y) * lane_scale);
+      const int h = __float_as_int(rkv_prep_q_turn(st_y0, st_x0, 1.f, st_cs0.x, st_cs0.y) * lane_scale);
 #pragma unroll
-    for (int i = 0; i < G; ++i) {
-      ld_q0[i][0] = q_nat[i * RKV_D] * lane_scale;
-      ld_q0[i][1] = q_nat[i * RKV_D + (v.rope_style ? 1 : 64)] * lane_scale;
+      for (int i = 0; i < G; ++i) {
+        ld_q0[i][0] = __int_as_float(__builtin_amdgcn_readlane(l, i));
+        ld_q0[i][1] = __int_as_float(__builtin_amdgcn_readlane(h, i));
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < G; ++i) {
+        ld_q0[i][0] = q_nat[i * RKV_D] * lane_scale;
+        ld_q0[i][1] = q_nat[i * RKV_D + (v.rope_style ? 1 : 64)] * lane_scale;
+      }
     }
   }
   //  - the RoPE angles of this lane's first token and the first key tile: in the key phase below
@@ -425,9 +463,27 @@ __global__ void __launch_bounds__(256, (HB && G == 4 && TILES == 4) ? MF_OCC_HI 
       // (the requests are all out: what came back goes to LDS)
       (&s_H[0][0])[tid] = ld_h0;
       (&s_H[0][0])[tid + 256] = ld_h1;
-    #pragma unroll
-      for (int i = 0; i < QN; ++i)
-      if (tid + 256 * i < Q16) (&s_q[0][0][0][0])[tid + 256 * i] = ld_q[i];
+      if constexpr (STEP) {
+        if (qa < G) {
+          const float lane_scale = 2.0f * rsqrtf((float)v.n);
+          float* const qf = reinterpret_cast<float*>(&s_q[0][0][0][0]);
+#pragma unroll
+          for (int r = 1; r < 3; ++r) {
+            float* const at = qf + ((((r - 1) * 4 + (qj >> 4)) * (G / 2) + (qa >> 1)) * 16 + (qj & 15)) * 4 + 2 * (qa & 1);
+            at[0] = rkv_prep_q_turn(st_x, st_y, -1.f, st_cs[r].x, st_cs[r].y) * lane_scale;
+            at[1] = rkv_prep_q_turn(st_y, st_x, 1.f, st_cs[r].x, st_cs[r].y) * lane_scale;
+          }
+          if (chunk == 0) {                                  // the plain copy, which the merge reads
+            float* const qn = step.qr + ((size_t)b * v.Hq + rg * G + qa) * RKV_D;
+            qn[v.rope_style ? 2 * qj : qj] = rkv_prep_q_turn(st_x, st_y, -1.f, st_cs[0].x, st_cs[0].y);
+            qn[v.rope_style ? 2 * qj + 1 : qj + 64] = rkv_prep_q_turn(st_y, st_x, 1.f, st_cs[0].x, st_cs[0].y);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < QN; ++i)
+          if (tid + 256 * i < Q16) (&s_q[0][0][0][0])[tid + 256 * i] = ld_q[i];
+      }
       if (tid < 64) {
         s_step[tid] = ld_step;
         s_c2[tid] = ld_c2;
@@ -886,11 +942,11 @@ bool rkv_mfma_supported(const rkv_cache* c) {
   return c->blocks_aligned && v.qg == 128 && (v.g == 2 || v.g == 4);
 }
 
-typedef void (*RkvDecodeFn)(RkvView, const float*, float*, int, const int*, int, int, uint32_t, uint32_t);
+typedef void (*RkvDecodeFn)(RkvView, const float*, float*, int, const int*, int, int, uint32_t, uint32_t, RkvStepIn);
 
 // The variant of the kernel a cache takes.  multi: several query tokens per sequence; share: query
 // heads of a KV head per workgroup (1 or 2); alu: the arithmetic-only measurement.
-static RkvDecodeFn pick_kernel(const rkv_cache* c, bool multi, int share, bool alu, int chunk) {
+static RkvDecodeFn pick_kernel(const rkv_cache* c, bool multi, int share, bool alu, int chunk, bool step = false) {
   const RkvView& v = c->v;
   // precomputed scores (groups of 64 / 32; a reorder over the whole row): softmax and value phases only
 #define RKV_MF_PRE_M(G_, R_, S_, H_, M_) (v.meta8 ? k_decode_mfma<G_, R_, M_, true, H_, S_, false, true> : k_decode_mfma<G_, R_, M_, false, H_, S_, false, true>)
@@ -911,11 +967,13 @@ static RkvDecodeFn pick_kernel(const rkv_cache* c, bool multi, int share, bool a
 #undef RKV_MF_PRE
 #undef RKV_MF_PRE_M
   if (alu) return v.g == 4 ? k_decode_mfma<4, 1, false, false, 0, 0, true> : k_decode_mfma<2, 1, false, false, 0, 0, true>;
-#define RKV_MF_PICK_H(G_, H_, T_) (v.meta8 ? k_decode_mfma<G_, 1, false, true, H_, 0, false, false, T_> : k_decode_mfma<G_, 1, false, false, H_, 0, false, false, T_>)
+#define RKV_MF_PICK_S(G_, M_, H_, T_) (step ? k_decode_mfma<G_, 1, false, M_, H_, 0, false, false, T_, true> : k_decode_mfma<G_, 1, false, M_, H_, 0, false, false, T_>)
+#define RKV_MF_PICK_H(G_, H_, T_) (v.meta8 ? RKV_MF_PICK_S(G_, true, H_, T_) : RKV_MF_PICK_S(G_, false, H_, T_))
 #define RKV_MF_PICK(G_, T_) (v.hb == 2 ? RKV_MF_PICK_H(G_, 2, T_) : v.hb == 1 ? RKV_MF_PICK_H(G_, 1, T_) : RKV_MF_PICK_H(G_, 0, T_))
   if (chunk == MF_CH) return v.g == 4 ? RKV_MF_PICK(4, MF_TILES) : RKV_MF_PICK(2, MF_TILES);
   return v.g == 4 ? RKV_MF_PICK(4, MF_TILES / 2) : RKV_MF_PICK(2, MF_TILES / 2);
 #undef RKV_MF_PICK_H
+#undef RKV_MF_PICK_S
 #undef RKV_MF_PICK
 }
 
@@ -986,13 +1044,22 @@ int rkv_prep_form(const rkv_cache* c, int heads_per_kv_head) {
   return share == 0 ? 0 : heads_per_kv_head == 1 && !rkv_scores_path(c) ? 1 : -1;
 }
 
+// Whether a decode step's token is appended, and its queries prepared, by k_decode_mfma itself (STEP): one query head per KV head,
+// its own key phase, one length for all - with per-sequence lengths the step's launch in front sets the new ones -, and at
+// least two tokens before this one, so that the query's copies lie at positions the angle table has.
+bool rkv_step_in_decode(const rkv_cache* c) {
+  const RkvView& v = c->v;
+  return rkv_mfma_variant(c) == RKV_KERNEL_MFMA && v.Hq == v.Hkv && c->decode_path != 3 && !c->ragged && v.len >= 2;
+}
+
 // nq == 0: the usual step, one query token that attends the whole cache (and, if set, the current
 // token's exact row).  nq >= 1: nq query tokens per sequence, token i at position q_pos[b][i] and
 // blind to cached tokens behind it; q, out and lse are then [batch][nq][heads][...] and the scratch
 // buffer holds nq times the single-query size.
 // q_prepared: the queries are already in the scratch block (rkv_launch_step_mfma put them there)
+// step: the last token's rows and the raw queries, where the launch is the step itself (rkv_step_in_decode)
 int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int nq, float* out, float* lse, void* scratch,
-                           bool q_prepared, hipStream_t s) {
+                           bool q_prepared, const RkvStepIn& step, hipStream_t s) {
   if (!rkv_mfma_supported(c)) return RKV_EINVAL;
   const bool multi = nq > 0;
   if (multi && (c->cur_k || !q_pos)) return RKV_EINVAL;
@@ -1008,7 +1075,7 @@ int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int 
   const bool row = rkv_scores_path(c);
   if (row && multi && !rkv_scores_multi_ok(c, nq)) return RKV_EINVAL;   // (the scores kernel serves 8 rows per KV head)
   const int share = rkv_mfma_share(c, rep);
-  if (!q_prepared) rkv_launch_prep_q(v, q, q_pos, c->cur_k ? 1 : 0, qr, rkv_prep_form(c, rep), nq, s);
+  if (!q_prepared && !step.q) rkv_launch_prep_q(v, q, q_pos, c->cur_k ? 1 : 0, qr, rkv_prep_form(c, rep), nq, s);
   float* qt = qr + (size_t)v.B * v.Hq * RKV_D;              // lane-ordered copy written by k_prep_q
   const int chunk = rkv_mfma_chunk(c, multi ? nq : 0), split = MF_CH / chunk;
   const int nch = (v.len + chunk - 1) / chunk;
@@ -1050,18 +1117,20 @@ int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int 
     if (rc != RKV_OK) return rc;
     if (nch > 0)
       hipLaunchKernelGGL(pick_kernel(c, multi, share, false, MF_CH), grid, dim3(256), 0, s, v, (const float*)sc, part, nch,
-                         multi ? q_pos : (const int*)nullptr, nq, ns, recip(ns), recip(v.NRG));
+                         multi ? q_pos : (const int*)nullptr, nq, ns, recip(ns), recip(v.NRG), RkvStepIn());
     if (timed) RKV_HIP_CHECK(hipEventRecord(c->ev_stop, s));
     rkv_launch_merge(v, qr, part, nch, MF_CH, c->cur_k, c->cur_v, multi ? q_pos : nullptr, nq, out, lse, s);
     return rkv_check_launch();
   }
+  RkvStepIn in = step;
+  in.qr = qr;
   if (nch > 0) {                                            // (an empty cache has only the current token)
     if (timed)
-      hipExtLaunchKernelGGL(pick_kernel(c, multi, share, c->decode_path == 3, chunk), grid, dim3(256), 0, s, c->ev_start, c->ev_stop, 0, v,
-                            qt, part, nch, multi ? q_pos : nullptr, nq, ns, recip(ns), recip(v.NRG));
+      hipExtLaunchKernelGGL(pick_kernel(c, multi, share, c->decode_path == 3, chunk, step.q != nullptr), grid, dim3(256), 0, s, c->ev_start, c->ev_stop, 0, v,
+                            qt, part, nch, multi ? q_pos : nullptr, nq, ns, recip(ns), recip(v.NRG), in);
     else
-      hipLaunchKernelGGL(pick_kernel(c, multi, share, c->decode_path == 3, chunk), grid, dim3(256), 0, s, v, qt, part, nch,
-                         multi ? q_pos : nullptr, nq, ns, recip(ns), recip(v.NRG));
+      hipLaunchKernelGGL(pick_kernel(c, multi, share, c->decode_path == 3, chunk, step.q != nullptr), grid, dim3(256), 0, s, v, qt, part, nch,
+                         multi ? q_pos : nullptr, nq, ns, recip(ns), recip(v.NRG), in);
   } else if (timed) {
     RKV_HIP_CHECK(hipEventRecord(c->ev_start, s));
     RKV_HIP_CHECK(hipEventRecord(c->ev_stop, s));

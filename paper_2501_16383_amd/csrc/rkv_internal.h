@@ -275,6 +275,15 @@ __device__ __forceinline__ uint2 rkv_ld_stream(const uint2* p) {
 }
 __device__ __forceinline__ void rkv_st_stream(uint32_t* p, uint32_t x) { __builtin_nontemporal_store(x, p); }
 
+// A decode step's rows [batch][n_kv_heads][128] and raw queries [batch][n_q_heads][128], where the decode kernel takes them itself, and
+// where it leaves the rotated queries
+struct RkvStepIn {
+  const __half* k = nullptr;
+  const __half* v = nullptr;
+  const __half* q = nullptr;
+  float* qr = nullptr;
+};
+
 // Several query tokens per sequence in one step: the kernels then run on a view whose Hq counts
 // "virtual" query heads, nq per real one.  Virtual head hv of KV head kvh = hv / rep' (rep' = virtual
 // heads per KV head) is query token qi = (hv % rep') / rep of real head kvh * rep + (hv % rep') % rep,
@@ -311,7 +320,8 @@ int rkv_launch_import(rkv_cache* c, int T, const uint8_t* kc, const float* ks, c
 int rkv_launch_decode_general(rkv_cache* c, const __half* q, const int* q_pos, int n_queries, float* out, float* lse, void* scratch,
                               hipStream_t s);
 int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int nq, float* out, float* lse, void* scratch,
-                           bool q_prepared, hipStream_t s);
+                           bool q_prepared, const RkvStepIn& step, hipStream_t s);
+bool rkv_step_in_decode(const rkv_cache* c);
 int rkv_mfma_chunk(const rkv_cache* c, int nq);             // tokens per workgroup of the matrix-core decode kernels (nq: query tokens, 0 for the usual step)
 size_t rkv_mfma_load(const rkv_cache* c, int chunk);
 int rkv_shared_heads(const rkv_cache* c, int heads_per_kv_head, int chunk);

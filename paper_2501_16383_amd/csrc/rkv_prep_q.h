@@ -3,6 +3,10 @@
 #pragma once
 #include "rkv_internal.h"
 
+// One channel of the query times the angle (cs, sn), scaled: x cs + sgn partner sn.  (Rounded once, the same wherever it is inlined.)
+__device__ __forceinline__ float rkv_prep_q_turn(float x, float partner, float sgn, double cs, double sn) {
+  return (float)(fma((double)x, cs, (double)(sgn * partner) * sn) * 0.08838834764831845);
+}
 // one channel of the query, rotated to position pos and scaled.  Angles from the table (computed in
 // double, stored as float) when the position lies inside it - the usual case -, else computed here
 __device__ __forceinline__ float rkv_prep_q_rotate(const RkvView& v, float x, float partner, float sgn, int pos, int j) {
@@ -14,7 +18,7 @@ __device__ __forceinline__ float rkv_prep_q_rotate(const RkvView& v, float x, fl
   } else {
     sincos((double)pos * pow((double)v.theta, -(double)j / 64.0), &sn, &cs);
   }
-  return (float)(((double)x * cs + (double)sgn * (double)partner * sn) * 0.08838834764831845);
+  return rkv_prep_q_turn(x, partner, sgn, cs, sn);
 }
 
 // One output channel c (0..127) of (virtual) query head h of sequence b.
