@@ -171,8 +171,8 @@ __device__ __forceinline__ float row_transpose_reduce(const float (&v)[NV], int 
 // STEP: a whole decode step but for the merge.  The sequences' last token is new: the workgroup whose chunk holds it appends it
 // first (rkv_append_one: two round trips and a barrier more for one workgroup in nch), and every workgroup rotates the queries
 // of its rotation group itself - one channel pair per thread, two positions -, the first chunk's leaving the plain copy for the
-// merge.  That is what the launch in front did, 4 to 7 us of latency: one sequence x 4096 tokens 17.7 -> STEPSINGLE us, 16 x 4096
-// tokens of 40 heads 67.4 -> STEPBATCH.
+// merge.  That is what the launch in front did, 4 to 7 us of latency: one sequence x 4096 tokens 17.7 -> 15.9 us a step
+// (rkv_step_in_decode).
 template <int G, int REP, bool MULTI, bool META8, int HB, int SUB = 0, bool ALU = false, bool PRE = false, int TILES = MF_TILES, bool STEP = false>
 __global__ void __launch_bounds__(256, (HB && G == 4 && TILES == 4) ? MF_OCC_HI : MF_OCC) k_decode_mfma(RkvView v, const float* __restrict__ qt,
                                                                        float* __restrict__ part, int nch,
@@ -994,13 +994,15 @@ size_t rkv_mfma_load(const rkv_cache* c, int chunk) {
 // as fast; up to one and a half (two rounds of whole chunks on some units become three half ones on all) 1.05 to
 // 1.1 times, except where a workgroup has two column tiles (two fit a compute unit, not three) or the query heads
 // have been given to several workgroups already (which half chunks would take back): there they lose.  Above that they
-// lose.  The exception are wider codes on k_decode_mfma with four heads in a rotation group: of whole chunks two fit
-// a compute unit, of half ones three.
-// us, whole / half chunks, at 0.5, 1, 1.5, 1.75, 3 and 10 workgroups per unit:
-//   k_decode_mfma, 2-bit codes             20.6 / 18.2, 20.9 / 19.3, 24.9 / 23.6, 24.8 / 26.9, 34.0 / 36.0, 71.4 / 79.1
-//   ... 3-bit                              22.8 / 19.2, 23.5 / 21.1, 28.1 / 25.9, 29.1 / 29.9, 43.1 / 41.2, 100.7 / 98.5
-//   ... 4-bit                              24.0 / 18.7, 25.2 / 21.7, 29.1 / 26.5, 30.2 / 30.8, 45.8 / 41.5, 110.8 / 104.6
-//   ... 4-bit, two heads per group         20.4 / 16.7, 20.7 / 19.1, 23.5 / 20.6, 23.4 / 24.0, 29.9 / 32.2
+// lose.  Wider codes on k_decode_mfma with four heads in a rotation group, of whose whole chunks two fit a
+// compute unit and of half ones three, take them a quarter of a workgroup further.
+// us a step (k_decode_mfma) or a call, whole / half chunks, at 0.5, 1, 2, 3 and 8 workgroups per unit:
+//   k_decode_mfma, 2-bit codes             17.6 / 14.8, 17.6 / 17.1, 21.7 / 25.4, 28.0 / 32.5, 56.6 / 60.3
+//   ... 3-bit                              19.3 / 16.2, 19.9 / 19.2, 24.4 / 28.4, 37.2 / 36.6, 77.1 / 78.7
+//   ... 4-bit                              19.3 / 16.8, 19.9 / 19.3, 24.9 / 29.5, 38.7 / 39.5, 80.2 / 81.5
+//   ... 2-bit, two heads per group                      15.5 / 15.5, 17.0 / 20.2,              41.3 / 49.0
+//   ... 4-bit, two heads per group                      16.6 / 16.5, 19.1 / 23.0,              51.1 / 58.2
+// and at 0.5, 1, 1.5, 1.75, 3 and 10:
 //   k_decode_shared, 4 heads on each of 8  24.1 / 19.8, 25.2 / 24.9, 34.3 / 32.2, 35.0 / 37.3, 47.8 / 49.9
 //   ... 3-bit                              25.8 / 21.4, 27.3 / 27.3, 38.0 / 37.4, 39.0 / 43.8, 54.4 / 60.6
 //   ... two column tiles, 8 on each of 8   25.0 / 24.6, 33.1 / 34.4, 45.7 / 46.5, 48.0 / 54.1, 69.4 / 76.0
@@ -1012,16 +1014,14 @@ int rkv_mfma_chunk(const rkv_cache* c, int nq) {
   if (c->decode_chunk) return c->decode_chunk;
   const int rep = v.Hq / v.Hkv * (nq > 0 ? nq : 1);
   const bool shared = rkv_shared_decode(c, rep);
-  if (shared || !v.hb || v.g != 4) {
-    size_t load = rkv_mfma_load(c, MF_CH);
-    int halves = 3;                                         // of a workgroup per compute unit
-    if (shared) {
-      const int rs = rkv_shared_heads(c, rep, MF_CH), ns = (rep + rs - 1) / rs;
-      load *= ns;
-      if (ns > 1 || rs * v.g > 16) halves = 1;
-    }
-    if (2 * load > halves * (size_t)c->n_cu) return MF_CH;
+  size_t load = rkv_mfma_load(c, MF_CH);
+  int quarters = v.hb && v.g == 4 ? 7 : 6;                  // of a workgroup per compute unit
+  if (shared) {
+    const int rs = rkv_shared_heads(c, rep, MF_CH), ns = (rep + rs - 1) / rs;
+    load *= ns;
+    quarters = ns > 1 || rs * v.g > 16 ? 2 : 6;
   }
+  if (4 * load > quarters * (size_t)c->n_cu) return MF_CH;
   if (nq > 0) return MF_CH / 2;
   auto fits = [&](int chunk) {
     const size_t nch = ((size_t)v.len + chunk - 1) / chunk;
@@ -1045,11 +1045,15 @@ int rkv_prep_form(const rkv_cache* c, int heads_per_kv_head) {
 }
 
 // Whether a decode step's token is appended, and its queries prepared, by k_decode_mfma itself (STEP): one query head per KV head,
-// its own key phase, one length for all - with per-sequence lengths the step's launch in front sets the new ones -, and at
-// least two tokens before this one, so that the query's copies lie at positions the angle table has.
+// its own key phase, one length for all - with per-sequence lengths the step's launch in front sets the new ones -, at
+// least two tokens before this one, so that the query's copies lie at positions the angle table has, and at most ten workgroups per
+// compute unit: every one of them prepares the queries again.  us per step, with a launch in front and without: 1 workgroup
+// per unit (one sequence x 4096, 32 heads) 17.7 / 15.9, 4 (x 32768) 38.1 / 35.2, 8 (64 x 1024) 59.9 / 57.1, 10 (16 x 4096, 40 heads) 67.4 /
+// 67.6, 16 (16 x 8192) 100.1 / 100.3, 32 (16 x 16384) 190.6 / 192.7, 32 half ones (16 x 8192, 4-bit codes) 148.8 / 152.5.
 bool rkv_step_in_decode(const rkv_cache* c) {
   const RkvView& v = c->v;
-  return rkv_mfma_variant(c) == RKV_KERNEL_MFMA && v.Hq == v.Hkv && c->decode_path != 3 && !c->ragged && v.len >= 2;
+  return rkv_mfma_variant(c) == RKV_KERNEL_MFMA && v.Hq == v.Hkv && c->decode_path != 3 && !c->ragged && v.len >= 2 &&
+         rkv_mfma_load(c, rkv_mfma_chunk(c, 0)) <= 10 * (size_t)c->n_cu;
 }
 
 // nq == 0: the usual step, one query token that attends the whole cache (and, if set, the current
