@@ -639,7 +639,7 @@ RKV_EXPORT int rkv_decode_step(rkv_cache* cache, const void* dev_k, const void* 
     for (int b = 0; b < cache->v.B; ++b) cache->hlens[b] += 1;
     return rkv_launch_decode_mfma(cache, step.q, nullptr, 0, dev_out, dev_lse, dev_scratch, true, step, s);
   }
-  const int share = rkv_prep_form(cache, cache->v.Hq / cache->v.Hkv);
+  const int share = rkv_prep_form(cache, cache->v.Hq / cache->v.Hkv, !dev_q_pos);
   bool lens_set = false;
   int rc = rkv_launch_step_mfma(cache, (const __half*)dev_k, (const __half*)dev_v, (const __half*)dev_q, dev_q_pos,
                                 (float*)dev_scratch, share, &lens_set, s);

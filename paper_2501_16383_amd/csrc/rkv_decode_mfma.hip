@@ -1038,10 +1038,11 @@ int rkv_mfma_share(const rkv_cache* c, int heads_per_kv_head) {
   return heads_per_kv_head % 2 == 0 ? 2 : 1;
 }
 
-// The form of the prepared queries (rkv_prep_q_one): 0 k_decode_shared's, 1 k_decode_mfma's, -1 the plain copy alone.
-int rkv_prep_form(const rkv_cache* c, int heads_per_kv_head) {
+// The form of the prepared queries (rkv_prep_q_one): 0 k_decode_shared's, 2 the same unrotated, 1 k_decode_mfma's, -1 the plain copy alone.
+// at_end: one query token per sequence, at the sequence's last token.
+int rkv_prep_form(const rkv_cache* c, int heads_per_kv_head, bool at_end) {
   const int share = rkv_mfma_share(c, heads_per_kv_head);
-  return share == 0 ? 0 : heads_per_kv_head == 1 && !rkv_scores_path(c) ? 1 : -1;
+  return share == 0 ? (at_end ? 2 : 0) : heads_per_kv_head == 1 && !rkv_scores_path(c) ? 1 : -1;
 }
 
 // Whether a decode step's token is appended, and its queries prepared, by k_decode_mfma itself (STEP): one query head per KV head,
@@ -1079,14 +1080,15 @@ int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int 
   const bool row = rkv_scores_path(c);
   if (row && multi && !rkv_scores_multi_ok(c, nq)) return RKV_EINVAL;   // (the scores kernel serves 8 rows per KV head)
   const int share = rkv_mfma_share(c, rep);
-  if (!q_prepared && !step.q) rkv_launch_prep_q(v, q, q_pos, c->cur_k ? 1 : 0, qr, rkv_prep_form(c, rep), nq, s);
+  const bool at_end = !multi && !q_pos && !c->cur_k;
+  if (!q_prepared && !step.q) rkv_launch_prep_q(v, q, q_pos, c->cur_k ? 1 : 0, qr, rkv_prep_form(c, rep, at_end), nq, s);
   float* qt = qr + (size_t)v.B * v.Hq * RKV_D;              // lane-ordered copy written by k_prep_q
   const int chunk = rkv_mfma_chunk(c, multi ? nq : 0), split = MF_CH / chunk;
   const int nch = (v.len + chunk - 1) / chunk;
   if (share == 0) {
     const bool timed = c->ev_start && c->ev_stop;
     if (nch > 0) {
-      const int rc = rkv_launch_decode_shared(c, v, qr, part, nch, chunk, multi ? q_pos : nullptr, nq, timed ? c->ev_start : nullptr,
+      const int rc = rkv_launch_decode_shared(c, v, qr, part, nch, chunk, multi ? q_pos : nullptr, nq, at_end, timed ? c->ev_start : nullptr,
                                               timed ? c->ev_stop : nullptr, s);
       if (rc != RKV_OK) return rc;
     } else if (timed) {

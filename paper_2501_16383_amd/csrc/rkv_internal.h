@@ -326,10 +326,10 @@ int rkv_mfma_chunk(const rkv_cache* c, int nq);             // tokens per workgr
 size_t rkv_mfma_load(const rkv_cache* c, int chunk);
 int rkv_shared_heads(const rkv_cache* c, int heads_per_kv_head, int chunk);
 int rkv_mfma_share(const rkv_cache* c, int heads_per_kv_head);   // (virtual heads, with several query tokens)
-int rkv_prep_form(const rkv_cache* c, int heads_per_kv_head);
+int rkv_prep_form(const rkv_cache* c, int heads_per_kv_head, bool at_end);
 // several query heads per KV head, or several query tokens per step (rkv_decode_shared.hip)
 bool rkv_shared_decode(const rkv_cache* c, int heads_per_kv_head);
-int rkv_launch_decode_shared(const rkv_cache* c, const RkvView& v, const float* qr, float* part, int nch, int chunk, const int* q_lim, int nq,
+int rkv_launch_decode_shared(const rkv_cache* c, const RkvView& v, const float* qr, float* part, int nch, int chunk, const int* q_lim, int nq, bool exact_q,
                              hipEvent_t ev_start, hipEvent_t ev_stop, hipStream_t s);
 // a reorder over the whole token row (rkv_decode_row.hip): its scores kernel and the buffer it fills
 bool rkv_row_supported(const rkv_cache* c);

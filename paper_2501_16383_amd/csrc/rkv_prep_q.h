@@ -23,7 +23,7 @@ __device__ __forceinline__ float rkv_prep_q_rotate(const RkvView& v, float x, fl
 
 // One output channel c (0..127) of (virtual) query head h of sequence b.
 // q~[b][h][c] = RoPE(q, q_pos)[c] / sqrt(128), angles in double (q_pos may lie beyond the table).
-// share: 0 for k_decode_shared's operands besides, 1 for k_decode_mfma's (Hq == Hkv), -1 for neither.
+// share: 0 for k_decode_shared's operands besides, 2 for the same unrotated, 1 for k_decode_mfma's (Hq == Hkv), -1 for none.
 __device__ __forceinline__ void rkv_prep_q_one(const RkvView& v, const __half* __restrict__ q, const int* __restrict__ q_pos,
                                                int at, float* __restrict__ qr, int share, int nq, int h, int b, int c) {
   // v.Hq counts virtual heads when nq > 1 (several query tokens, each at its own position)
@@ -45,7 +45,7 @@ __device__ __forceinline__ void rkv_prep_q_one(const RkvView& v, const __half* _
   }
   const float x = __half2float(q[src + c]), p = __half2float(q[src + partner]);
   const int nn = v.rope_style ? (c >> 1) & 15 : c & 15, pp = v.rope_style ? (c >> 5) & 3 : (c >> 4) & 3, half = v.rope_style ? c & 1 : c >> 6;
-  if (share == 0) {
+  if (share == 0 || share == 2) {
     // The kernel that serves all query heads of a KV head at once (k_decode_shared) takes the query
     // as fp16 matrix operands, split into a high and a low part (a float to 2^-23): for each head
     //   [p][high, low][lane group nn / 4][half][nn % 4]   fp16,
@@ -60,6 +60,11 @@ __device__ __forceinline__ void rkv_prep_q_one(const RkvView& v, const __half* _
     qr[base + c] = val;
     __half* img = reinterpret_cast<__half*>(qr + (size_t)v.B * v.Hq * RKV_D);
     const size_t o = (((((size_t)b * v.Hq + h) * 4 + pp) * 2) * 4 + (nn >> 2)) * 8 + 4 * half + (nn & 3);
+    if (share == 2) {                                       // (the query as it came, its rotation is on the keys' side: largest component at 2^15 .. 65504, so the power of two never is below one and the product is exact)
+      img[o] = __float2half_rn(ldexpf(x, 16 - ex));
+      if (c == 0) qr[2 * (size_t)v.B * v.Hq * RKV_D + (size_t)b * v.Hq + h] = ldexpf(0.08838834764831845f, ex - 16);
+      return;
+    }
     const float y = ldexpf(val, 14 - ex);
     const __half hi = __float2half_rn(y);
     img[o] = hi;

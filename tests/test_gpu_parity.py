@@ -2162,3 +2162,86 @@ def test_whole_row_step_equals_the_two_calls(hkv, g, bits, group, fmt, ragged):
     ea, eb = a.export_codes(), b.export_codes()
     for s in range(B):
         assert all(torch.equal(ea[name][s, :lens[s] + 3], eb[name][s, :lens[s] + 3]) for name in ea)
+
+
+@pytest.mark.parametrize("B,hkv,g,bits,fmt,style,rotated", [(1, 4, 2, 2, 0, 0, 0), (3, 8, 4, 2, 1, 1, 0), (2, 4, 4, 3, 0, 0, 1), (2, 6, 2, 4, 1, 0, 0),
+                                                            (160, 64, 4, 2, 0, 0, 0), (162, 64, 4, 2, 0, 0, 0)])
+def test_steps_at_tile_and_chunk_edges_equal_the_two_calls(B, hkv, g, bits, fmt, style, rotated):
+    """A step's token at the first positions, the edges of tiles of 16 tokens, of the append's 32 and of both chunk sizes: outputs bit for bit those
+    of an append and an attention call.  2560 workgroups (160 x 16 groups) are the most that take the one launch here, 2592 do not."""
+    T = 260
+    cfg = R.RkvConfig(batch=B, n_q_heads=hkv, n_kv_heads=hkv, max_tokens=T, max_sinks=0, rot_heads=g, bits=bits, meta_format=fmt, rope_style=style,
+                      keys_rotated=rotated)
+    gen = torch.Generator(device="cuda").manual_seed(B + hkv)
+    k, v = (torch.randn(B, T, hkv, 128, device="cuda", generator=gen).half() for _ in range(2))
+    a, b = R.RkvCache(cfg), R.RkvCache(cfg)
+    edges = [1, 2, 3, 15, 16, 31, 32, 33, 64, 127, 128, 255, 256] if B < 100 else [2, 128, 255]
+    for chunk in (256, 128) if B < 100 else (256,):
+        for c in (a, b):
+            c.reset()
+            c.set_decode_chunk(chunk)
+        for n in edges:
+            for c in (a, b):
+                c.truncate(min(c.length, n))
+                if c.length < n:
+                    c.quantize_append(k[:, c.length:n].contiguous(), v[:, c.length:n].contiguous())
+            q = torch.randn(B, hkv, 128, device="cuda", generator=gen).half()
+            kn, vn = k[:, n:n + 1].contiguous(), v[:, n:n + 1].contiguous()
+            out, lse = a.decode_step(kn, vn, q, want_lse=True)
+            b.quantize_append(kn, vn)
+            ref, lse_ref = b.decode_attention(q, want_lse=True)
+            assert torch.equal(out, ref) and torch.equal(lse, lse_ref), (chunk, n)
+    ea, eb = a.export_codes(), b.export_codes()
+    assert all(torch.equal(ea[name], eb[name]) for name in ea)
+
+
+@pytest.mark.parametrize("B,hq", [(64, 4), (65, 4), (65, 8)])
+def test_steps_of_many_sequences_of_different_lengths(B, hq):
+    """The lengths of up to 64 sequences go with the launch, those of more through a launch of their own."""
+    hkv, T = 4, 40
+    cfg = R.RkvConfig(batch=B, n_q_heads=hq, n_kv_heads=hkv, max_tokens=T + 3, max_sinks=2, rot_heads=4)
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    k, v = (torch.randn(B, T, hkv, 128, device="cuda", generator=gen).half() for _ in range(2))
+    mask = torch.zeros(B, T, dtype=torch.uint8, device="cuda")
+    mask[:, 1] = 1
+    lens = [(7 * i) % T for i in range(B)]
+    a, b = R.RkvCache(cfg), R.RkvCache(cfg)
+    for c in (a, b):
+        c.quantize_append_ragged(k, v, lens, mask)
+    for i in range(3):
+        q = torch.randn(B, hq, 128, device="cuda", generator=gen).half()
+        kn, vn = k[:, i:i + 1].contiguous(), v[:, i:i + 1].contiguous()
+        out = a.decode_step(kn, vn, q)
+        b.quantize_append(kn, vn)
+        assert torch.equal(out, b.decode_attention(q)), i
+    assert a.lengths == b.lengths == [n + 3 for n in lens]
+    for s in (0, 1, 6, B - 1):                                  # a cache of the sequence alone, one call
+        one = R.RkvCache(dataclasses.replace(cfg, batch=1))
+        one.quantize_append(torch.cat([k[s:s + 1, :lens[s]], k[s:s + 1, :3]], 1), torch.cat([v[s:s + 1, :lens[s]], v[s:s + 1, :3]], 1),
+                            torch.cat([mask[s:s + 1, :lens[s]], mask[s:s + 1, :3] * 0], 1))
+        ref = one.decode_attention(q[s:s + 1])
+        assert float((out[s] - ref[0]).abs().max()) <= 1e-4 * float(ref.abs().max()), s
+
+
+@pytest.mark.parametrize("hq,hkv,g,bits,lens,style,scale", [
+    (8, 4, 2, 2, [300], 0, 1.0), (32, 8, 4, 2, [1, 130, 513], 1, 1.0), (12, 4, 4, 3, [257, 256], 0, 1.0), (16, 4, 2, 4, [40, 128], 1, 1.0),
+    (20, 4, 4, 2, [261] * 130, 0, 1.0), (8, 4, 4, 2, [300], 0, 2.0 ** -20), (8, 4, 4, 2, [300], 0, 0.0), (8, 4, 4, 2, [130, 20], 0, 60.0)])
+def test_queries_at_the_end_are_not_rotated(hq, hkv, g, bits, lens, style, scale):
+    """A query at its sequence's last token (no position given) against the same position given, which rotates the query in place of the keys:
+    the same attention to the error of both (4e-6 of the norm each at scores of unit size, relative to the scores' size above it), for
+    queries down to fp16's subnormal numbers (exact under the power of two) and zero; a chunk of one token, two column tiles."""
+    B = len(lens)
+    cfg = R.RkvConfig(batch=B, n_q_heads=hq, n_kv_heads=hkv, max_tokens=max(lens), max_sinks=0, rot_heads=g, bits=bits, rope_style=style)
+    gen = torch.Generator(device="cuda").manual_seed(hq)
+    k, v = (torch.randn(B, max(lens), hkv, 128, device="cuda", generator=gen).half() for _ in range(2))
+    cache = R.RkvCache(cfg)
+    cache.quantize_append_ragged(k, v, lens)
+    q = (torch.randn(B, hq, 128, device="cuda", generator=gen) * scale).half()
+    pos = torch.tensor([n - 1 for n in lens], dtype=torch.int32, device="cuda")
+    for chunk in (256, 128):
+        cache.set_decode_chunk(chunk)
+        out, lse = cache.decode_attention(q, want_lse=True)
+        ref, lse_ref = cache.decode_attention(q, pos, want_lse=True)
+        assert torch.isfinite(out).all()
+        bar = 8e-6 * max(1.0, scale)
+        assert float((out - ref).norm() / ref.norm()) <= bar and float((lse - lse_ref).abs().max()) <= 16 * bar, chunk
