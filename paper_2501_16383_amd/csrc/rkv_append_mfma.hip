@@ -804,7 +804,7 @@ __global__ void __launch_bounds__(256 * NP, NP == 1 ? 3 : 1) k_append_row_keys(R
 // token, and the whole row takes 64 products (4096 channels) in place of 2 x 1024.  An output of a product depends on its own
 // row and column alone and the channels are summed in the same order, so the codes are the same bit for bit.  What is left is
 // a chain of latencies (row, extrema through LDS atomics, parameters, codes), three barriers long.  8 sequences x one token, 32
-// heads: 21.9 -> 6.0 us with the values and the query preparation in the same launch, which took 5.4 us of their own.
+// heads: 21.9 -> 5.7 us with the values and the query preparation in the same launch, which took 5.4 us of their own.
 // Wave (hg, pw): heads 16 hg + column, channels 32 pw .. + 31 of them: tiles p = 2 pw and 2 pw + 1; lane (column, q) of a
 // result holds channels 16 p + 4 q + r, which are the four codes at bits 16 (q & 1) + 4 r + 2 (q >> 1) of dword (head, p) of the token.
 // LDS: [NG] minima, [NG] maxima, [NG] parameters.

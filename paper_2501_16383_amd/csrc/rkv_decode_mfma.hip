@@ -295,8 +295,8 @@ __global__ void __launch_bounds__(256, (HB && G == 4 && TILES == 4) ? MF_OCC_HI 
   uint4 ld_q[QN];
 #pragma unroll
   for (int i = 0; i < QN; ++i) ld_q[i] = !STEP && tid + 256 * i < Q16 ? q_src[tid + 256 * i] : make_uint4(0, 0, 0, 0);
-  //  - RoPE angles are kept for the first of a lane's four tokens only: they rotate all four keys and the query
-  //    comes rotated back by 0..3 positions to make up for it (k_prep_q).  The next tile follows by
+  //  - RoPE angles are kept for the first of a lane's four tokens only; the query's copies at positions 1 and 2 back make
+  //    up for it (rkv_prep_q_one).  The next tile follows by
   //    rotating 16 positions (table row 16; used once per tile, read from LDS)
   const float2 ld_step = v.rope[16 * 64 + (tid & 63)];
   const float ld_c2 = 2.0f * v.rope[64 + (tid & 63)].x;

@@ -15,7 +15,7 @@
 //            contraction over the channels:
 //              score(t, a, h) = sum_blk H_g[a][blk] scale_blk(t) * <RoPE_t(H_128 c_blk(t)), q~(a, h)>:
 //            the rotated codes meet the queries of ALL KV heads of the group, sixteen columns per product.
-//            Precision: H_128 c is exact, RoPE runs in fp32; both operands are then split into two
+//            Precision: H_128 c is exact, RoPE runs in fp32; both operands (a query at its sequence's end needs no split: QX) are then split into two
 //            fp16 numbers each (low at most 2^-11 of its number, high + low the number to 2^-23) and the product is high * high +
 //            high * low + low * high, accumulated in fp32; low * low, at most 2^-22 of a term, is left out: with
 //            it outputs were 1 to 3 % closer to 64-bit attention and steps 3 to 6 % slower.  Codes are centred on
@@ -23,15 +23,14 @@
 //            zero-points with them, so that channel 0 is no larger than the others.  Outputs are 0.4 to 2.0e-6 of the norm
 //            away from 64-bit attention on the same codes (2 to 56 rows per KV head, 140 to 25000 tokens), where the same dot
 //            products in fp32 on k_decode_mfma were 0.4 to 8e-6 away; where its workgroups had one query head the two
-//            are equal within 5 % (30 draws), where they had two this one is 2 to 10 times closer.
+//            were equal within 5 % (30 draws; since then that kernel has centred codes, and this one QX), where they had two this one was 2 to 10 times closer.
 //   phase S  wave: softmax statistics and weight digits of four query heads of one KV head; the digits
 //            (six base-16 digits of a 24-bit integer, in FP8, see k_decode_mfma) stay in the wave's own LDS.
 //   phase V  the same wave: rows = 4 query heads x 4 digits, contraction over 128 tokens of ONE KV head:
 //            no part of the operand is zero (k_decode_mfma's is block-diagonal over the heads), the codes
 //            are fetched once for all query heads.
-// 32 sequences x 8192 tokens, 32 query heads on 8: step 153.5 -> 91.3 us against two query heads per workgroup of
-// k_decode_mfma, vector pipe busy 71 % of the kernel, matrix pipe 24 %; four query tokens, 8 x 4096 tokens: 98.4 -> 59.3 us (45 and 20 %:
-// one round of two workgroups per compute unit).  Bound by the vector pipe in phase K (16 instructions of
+// 32 sequences x 8192 tokens, 32 query heads on 8: step 153.5 us with two query heads per workgroup of k_decode_mfma, 85.0 here;
+// four query tokens, 8 x 4096 tokens: 98.4 and 48.3 us (one round of two workgroups per compute unit).  Bound by the vector pipe in phase K (16 instructions of
 // RoPE and 12 of the split for eight channels of a token and block).
 // The variants with 32 columns and 3- or 4-bit codes hold 8 registers in scratch memory.
 #include "rkv_internal.h"
