@@ -270,6 +270,11 @@ __global__ void __launch_bounds__(256, (HB && G == 4 && TILES == 4) ? MF_OCC_HI 
     const int xcd = blockIdx.x & 7, rem = blockIdx.x >> 3;
     chunk = inv_ns ? (int)__umulhi((uint32_t)rem, inv_ns) : rem;
     rrg = rem - chunk * ns;
+    // A step's chunk with the append lives the longest: where a die runs several pairs it goes first, so as not to be behind all
+    // others (us per step: 16 sequences x 4096, 40 heads 67.3 -> 65.7; 8 x 4096, rotation over two heads 39.3 -> 37.4).  With one pair
+    // per die the order stays: one x 32768, 36.1 and in reverse 37.3 to 38.0.
+    if constexpr (STEP)
+      if (gridDim.y > 1) chunk = nch - 1 - chunk;
     const int br = blockIdx.y * 8 + xcd;
     if (br >= v.B * v.NRG) return;
     b = inv_nrg ? (int)__umulhi((uint32_t)br, inv_nrg) : br;
@@ -1047,14 +1052,14 @@ int rkv_prep_form(const rkv_cache* c, int heads_per_kv_head, bool at_end) {
 
 // Whether a decode step's token is appended, and its queries prepared, by k_decode_mfma itself (STEP): one query head per KV head,
 // its own key phase, one length for all - with per-sequence lengths the step's launch in front sets the new ones -, at
-// least two tokens before this one, so that the query's copies lie at positions the angle table has, and at most ten workgroups per
+// least two tokens before this one, so that the query's copies lie at positions the angle table has, and at most sixteen workgroups per
 // compute unit: every one of them prepares the queries again.  us per step, with a launch in front and without: 1 workgroup
-// per unit (one sequence x 4096, 32 heads) 17.7 / 15.9, 4 (x 32768) 38.1 / 35.2, 8 (64 x 1024) 59.9 / 57.1, 10 (16 x 4096, 40 heads) 67.4 /
-// 67.6, 16 (16 x 8192) 100.1 / 100.3, 32 (16 x 16384) 190.6 / 192.7, 32 half ones (16 x 8192, 4-bit codes) 148.8 / 152.5.
+// per unit (one sequence x 4096, 32 heads) 17.7 / 15.9, 4 (x 32768) 38.1 / 35.2, 8 (64 x 1024) 59.9 / 57.1, 12 (16 x 4096, 48 heads) 80.5 /
+// 79.4, 16 (16 x 8192) 101.6 / 99.2, 32 (16 x 16384) 192.4 / 192.3, 64 (32 x 8192, rotation over two heads) 238.2 / 242.2.
 bool rkv_step_in_decode(const rkv_cache* c) {
   const RkvView& v = c->v;
   return rkv_mfma_variant(c) == RKV_KERNEL_MFMA && v.Hq == v.Hkv && c->decode_path != 3 && !c->ragged && v.len >= 2 &&
-         rkv_mfma_load(c, rkv_mfma_chunk(c, 0)) <= 10 * (size_t)c->n_cu;
+         rkv_mfma_load(c, rkv_mfma_chunk(c, 0)) <= 16 * (size_t)c->n_cu;
 }
 
 // nq == 0: the usual step, one query token that attends the whole cache (and, if set, the current

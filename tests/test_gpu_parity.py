@@ -2165,10 +2165,10 @@ def test_whole_row_step_equals_the_two_calls(hkv, g, bits, group, fmt, ragged):
 
 
 @pytest.mark.parametrize("B,hkv,g,bits,fmt,style,rotated", [(1, 4, 2, 2, 0, 0, 0), (3, 8, 4, 2, 1, 1, 0), (2, 4, 4, 3, 0, 0, 1), (2, 6, 2, 4, 1, 0, 0),
-                                                            (160, 64, 4, 2, 0, 0, 0), (162, 64, 4, 2, 0, 0, 0)])
+                                                            (256, 64, 4, 2, 0, 0, 0), (258, 64, 4, 2, 0, 0, 0)])
 def test_steps_at_tile_and_chunk_edges_equal_the_two_calls(B, hkv, g, bits, fmt, style, rotated):
     """A step's token at the first positions, the edges of tiles of 16 tokens, of the append's 32 and of both chunk sizes: outputs bit for bit those
-    of an append and an attention call.  2560 workgroups (160 x 16 groups) are the most that take the one launch here, 2592 do not."""
+    of an append and an attention call.  4096 workgroups (256 x 16 groups) are the most that take the one launch here, 4128 do not."""
     T = 260
     cfg = R.RkvConfig(batch=B, n_q_heads=hkv, n_kv_heads=hkv, max_tokens=T, max_sinks=0, rot_heads=g, bits=bits, meta_format=fmt, rope_style=style,
                       keys_rotated=rotated)
