@@ -1,6 +1,7 @@
 // Host side of the C ABI: argument checks, the cache object, dispatch to the kernels.
 #include "rkv_internal.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -495,7 +496,8 @@ RKV_EXPORT int rkv_quantize_append(rkv_cache* cache, const void* dev_k, const vo
   if ((int64_t)cache->v.len + n_new > cache->cfg.max_tokens) return RKV_ECAPACITY;   // v.len: the longest sequence
   if (cache->ragged && !rkv_append_mfma_supported(cache)) return RKV_EINVAL;
   int rc = rkv_launch_append(cache, (const __half*)dev_k, (const __half*)dev_v, n_new, dev_sink_mask, (hipStream_t)stream);
-  if (dev_sink_mask) cache->sinks_below = cache->v.len + n_new;   // (also after an error: retention may be under way)
+  // (also after an error: retention may be under way; a maximum, since an import may have left a sink behind the end)
+  if (dev_sink_mask) cache->sinks_below = std::max(cache->sinks_below, cache->v.len + n_new);
   if (rc == RKV_OK && cache->ragged) rc = rkv_launch_lens(cache, -1, n_new, RkvCounts(), (hipStream_t)stream);
   if (rc == RKV_OK) {
     cache->v.len += n_new;
@@ -528,7 +530,7 @@ RKV_EXPORT int rkv_quantize_append_ragged(rkv_cache* cache, const void* dev_k, c
   if (!rkv_append_mfma_supported(cache)) return RKV_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   const uint8_t* mask = cache->v.max_sinks > 0 ? dev_sink_mask : nullptr;
-  if (mask) cache->sinks_below = cache->sinks_below > new_max ? cache->sinks_below : new_max;
+  if (mask) cache->sinks_below = std::max(cache->sinks_below, new_max);
   RkvCounts counts;
   int rc = RKV_OK;
   if (counts_by_value(cache, host_n_new, counts)) {

@@ -2245,3 +2245,29 @@ def test_queries_at_the_end_are_not_rotated(hq, hkv, g, bits, lens, style, scale
         assert torch.isfinite(out).all()
         bar = 8e-6 * max(1.0, scale)
         assert float((out - ref).norm() / ref.norm()) <= bar and float((lse - lse_ref).abs().max()) <= 16 * bar, chunk
+
+
+@pytest.mark.parametrize("sinks", [(100,), (5, 100)])
+def test_truncate_after_an_import_drops_sinks_behind_the_end(sinks):
+    """An import shortens a cache and keeps its sinks: one of them then lies behind the end, and behind whatever an append with flags
+    adds.  A cut in front of it drops it all the same."""
+    B, hkv = 2, 4
+    cfg = R.RkvConfig(batch=B, n_q_heads=hkv, n_kv_heads=hkv, max_tokens=128, max_sinks=len(sinks), rot_heads=4)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    k, v = (torch.randn(B, 128, hkv, 128, device="cuda", generator=gen).half() for _ in range(2))
+    mask = torch.zeros(B, 128, dtype=torch.uint8, device="cuda")
+    mask[:, list(sinks)] = 1
+    kept = [s for s in sinks if s < 10]
+    a, b = R.RkvCache(cfg), R.RkvCache(cfg)
+    a.quantize_append(k[:, :120].contiguous(), v[:, :120].contiguous(), mask[:, :120].contiguous())
+    a.import_codes(**{name: t[:, :10].contiguous() for name, t in a.export_codes().items()})
+    b.quantize_append(k[:, :10].contiguous(), v[:, :10].contiguous(), mask[:, :10].contiguous())
+    full = torch.ones(B, 5, dtype=torch.uint8, device="cuda")
+    a.quantize_append(k[:, 10:15].contiguous(), v[:, 10:15].contiguous(), full)        # (no room: all of them are ordinary tokens)
+    b.quantize_append(k[:, 10:15].contiguous(), v[:, 10:15].contiguous())
+    for c in (a, b):
+        c.quantize_append(k[:, 15:115].contiguous(), v[:, 15:115].contiguous())
+        c.truncate(50)
+    assert a.export_sinks()["count"].tolist() == [len(kept)] * B
+    q = torch.randn(B, hkv, 128, device="cuda", generator=gen).half()
+    assert torch.equal(a.decode_attention(q), b.decode_attention(q))
