@@ -597,7 +597,7 @@ RKV_EXPORT int rkv_decode_attention(rkv_cache* cache, const void* dev_q, const i
   if (cache->decode_path == 1) fast = false;
   if (fast)
     return rkv_launch_decode_mfma(cache, (const __half*)dev_q, dev_q_pos, 0, dev_out, dev_lse, dev_scratch, false,
-                                  RkvStepIn(), (hipStream_t)stream);
+                                  RkvStepIn(), nullptr, (hipStream_t)stream);
   return rkv_launch_decode_general(cache, (const __half*)dev_q, dev_q_pos, 0, dev_out, dev_lse, dev_scratch, (hipStream_t)stream);
 }
 
@@ -622,6 +622,12 @@ RKV_EXPORT int rkv_decode_attention_static(rkv_cache* cache, const void* dev_q, 
   return rkv_decode_attention(cache, dev_q, dev_q_pos, dev_out, dev_lse, ptr, stream);
 }
 
+// one token more (n = 1) or less (-1) in every sequence
+static void count_step(rkv_cache* c, int n) {
+  c->v.len += n;
+  for (int b = 0; b < c->v.B; ++b) c->hlens[b] += n;
+}
+
 RKV_EXPORT int rkv_decode_step(rkv_cache* cache, const void* dev_k, const void* dev_v, const void* dev_q, const int32_t* dev_q_pos,
                                float* dev_out, float* dev_lse, void* dev_scratch, void* stream) {
   if (!cache || !dev_k || !dev_v || !dev_q || !dev_out || !dev_scratch) return RKV_EINVAL;
@@ -637,9 +643,12 @@ RKV_EXPORT int rkv_decode_step(rkv_cache* cache, const void* dev_k, const void* 
     step.k = (const __half*)dev_k;
     step.v = (const __half*)dev_v;
     step.q = (const __half*)dev_q;
-    cache->v.len += 1;
-    for (int b = 0; b < cache->v.B; ++b) cache->hlens[b] += 1;
-    return rkv_launch_decode_mfma(cache, step.q, nullptr, 0, dev_out, dev_lse, dev_scratch, true, step, s);
+    // (counted ahead of the launch, whose grid covers the new token; taken back unless the launch that appends it went out)
+    bool appended = false;
+    count_step(cache, 1);
+    const int rc = rkv_launch_decode_mfma(cache, step.q, nullptr, 0, dev_out, dev_lse, dev_scratch, true, step, &appended, s);
+    if (!appended) count_step(cache, -1);
+    return rc;
   }
   const int share = rkv_prep_form(cache, cache->v.Hq / cache->v.Hkv, !dev_q_pos);
   bool lens_set = false;
@@ -647,9 +656,8 @@ RKV_EXPORT int rkv_decode_step(rkv_cache* cache, const void* dev_k, const void* 
                                 (float*)dev_scratch, share, &lens_set, s);
   if (rc == RKV_OK && cache->ragged && !lens_set) rc = rkv_launch_lens(cache, -1, 1, RkvCounts(), s);
   if (rc != RKV_OK) return rc;
-  cache->v.len += 1;
-  for (int b = 0; b < cache->v.B; ++b) cache->hlens[b] += 1;
-  return rkv_launch_decode_mfma(cache, (const __half*)dev_q, dev_q_pos, 0, dev_out, dev_lse, dev_scratch, true, RkvStepIn(), s);
+  count_step(cache, 1);
+  return rkv_launch_decode_mfma(cache, (const __half*)dev_q, dev_q_pos, 0, dev_out, dev_lse, dev_scratch, true, RkvStepIn(), nullptr, s);
 }
 
 RKV_EXPORT int rkv_decode_attention_multi(rkv_cache* cache, const void* dev_q, const int32_t* dev_q_pos, int32_t n_queries,
@@ -666,7 +674,7 @@ RKV_EXPORT int rkv_decode_attention_multi(rkv_cache* cache, const void* dev_q, c
     return rkv_launch_decode_general(cache, (const __half*)dev_q, dev_q_pos, n_queries, dev_out, dev_lse, dev_scratch,
                                      (hipStream_t)stream);
   return rkv_launch_decode_mfma(cache, (const __half*)dev_q, dev_q_pos, n_queries, dev_out, dev_lse, dev_scratch, false,
-                                RkvStepIn(), (hipStream_t)stream);
+                                RkvStepIn(), nullptr, (hipStream_t)stream);
 }
 
 RKV_EXPORT int rkv_dequantize(rkv_cache* cache, float* dev_k_hat, float* dev_v_hat, void* stream) {

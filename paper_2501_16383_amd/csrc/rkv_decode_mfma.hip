@@ -1067,9 +1067,10 @@ bool rkv_step_in_decode(const rkv_cache* c) {
 // blind to cached tokens behind it; q, out and lse are then [batch][nq][heads][...] and the scratch
 // buffer holds nq times the single-query size.
 // q_prepared: the queries are already in the scratch block (rkv_launch_step_mfma put them there)
-// step: the last token's rows and the raw queries, where the launch is the step itself (rkv_step_in_decode)
+// step: the last token's rows and the raw queries, where the launch is the step itself (rkv_step_in_decode); *appended
+// then says whether it went out, whatever becomes of the merge behind it
 int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int nq, float* out, float* lse, void* scratch,
-                           bool q_prepared, const RkvStepIn& step, hipStream_t s) {
+                           bool q_prepared, const RkvStepIn& step, bool* appended, hipStream_t s) {
   if (!rkv_mfma_supported(c)) return RKV_EINVAL;
   const bool multi = nq > 0;
   if (multi && (c->cur_k || !q_pos)) return RKV_EINVAL;
@@ -1145,6 +1146,11 @@ int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int 
   } else if (timed) {
     RKV_HIP_CHECK(hipEventRecord(c->ev_start, s));
     RKV_HIP_CHECK(hipEventRecord(c->ev_stop, s));
+  }
+  if (step.q) {
+    const int rc = rkv_check_launch();
+    if (rc != RKV_OK) return rc;
+    *appended = true;
   }
   rkv_launch_merge(v, qr, part, nch, chunk, c->cur_k, c->cur_v, multi ? q_pos : nullptr, nq, out, lse, s);
   return rkv_check_launch();

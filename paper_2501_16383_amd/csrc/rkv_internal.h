@@ -320,7 +320,7 @@ int rkv_launch_import(rkv_cache* c, int T, const uint8_t* kc, const float* ks, c
 int rkv_launch_decode_general(rkv_cache* c, const __half* q, const int* q_pos, int n_queries, float* out, float* lse, void* scratch,
                               hipStream_t s);
 int rkv_launch_decode_mfma(rkv_cache* c, const __half* q, const int* q_pos, int nq, float* out, float* lse, void* scratch,
-                           bool q_prepared, const RkvStepIn& step, hipStream_t s);
+                           bool q_prepared, const RkvStepIn& step, bool* appended, hipStream_t s);
 bool rkv_step_in_decode(const rkv_cache* c);
 int rkv_mfma_chunk(const rkv_cache* c, int nq);             // tokens per workgroup of the matrix-core decode kernels (nq: query tokens, 0 for the usual step)
 size_t rkv_mfma_load(const rkv_cache* c, int chunk);

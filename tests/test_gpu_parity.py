@@ -2271,3 +2271,36 @@ def test_truncate_after_an_import_drops_sinks_behind_the_end(sinks):
     assert a.export_sinks()["count"].tolist() == [len(kept)] * B
     q = torch.randn(B, hkv, 128, device="cuda", generator=gen).half()
     assert torch.equal(a.decode_attention(q), b.decode_attention(q))
+
+
+@pytest.mark.parametrize("hq,B,kw", [(4, 2, {}), (8, 2, {}), (4, 2, {"perm_span": 512})])
+def test_a_step_that_returns_an_error_is_not_counted(hq, B, kw):
+    """An error that the runtime holds from before - here of a device number that does not exist - is what a failed launch looks like to
+    the library: the step returns it, the cache has the length it had, and the step can be made again."""
+    hkv, T = 4, 40
+    cfg = R.RkvConfig(batch=B, n_q_heads=hq, n_kv_heads=hkv, max_tokens=T + 2, max_sinks=0, rot_heads=4, **kw)
+    gen = torch.Generator(device="cuda").manual_seed(hq)
+    k, v = (torch.randn(B, T + 2, hkv, 128, device="cuda", generator=gen).half() for _ in range(2))
+    a, b = R.RkvCache(cfg), R.RkvCache(cfg)
+    for c in (a, b):
+        if kw:
+            c.set_perm(torch.arange(hkv * 128 - 1, -1, -1, dtype=torch.int32, device="cuda"))
+        c.quantize_append(k[:, :T].contiguous(), v[:, :T].contiguous())
+    hip = R.load_library()                                     # (symbols of the runtime the library is linked with)
+    for n in (T, T + 1):
+        q = torch.randn(B, hq, 128, device="cuda", generator=gen).half()
+        kn, vn = k[:, n:n + 1].contiguous(), v[:, n:n + 1].contiguous()
+        out = torch.empty(B, hq, 128, device="cuda")
+        torch.cuda.synchronize()
+        try:
+            assert hip.hipSetDevice(4095) != 0 and hip.hipPeekAtLastError() != 0
+            with pytest.raises(R.RkvError) as ei:
+                a.decode_step(kn, vn, q, out=out)
+        finally:
+            hip.hipGetLastError()
+        assert ei.value.code == -4 and a.lengths == [n] * B
+        a.decode_step(kn, vn, q, out=out)
+        b.quantize_append(kn, vn)
+        assert a.lengths == b.lengths and torch.equal(out, b.decode_attention(q))
+    ea, eb = a.export_codes(), b.export_codes()
+    assert all(torch.equal(ea[name], eb[name]) for name in ea)
