@@ -74,8 +74,11 @@ __device__ __forceinline__ Split8 split8(const float (&x)[8]) {
 // QX: the one query token of a sequence is the last one.  Keys are then rotated by their distance from it, and the query
 // needs no rotation: its fp16 numbers are the operand as they came (times a power of two), and the product with its low part
 // falls away, a third of the products with the queries.  32 sequences x 8192 tokens, 32 heads on 8: 90.0 -> 85.2 us a step, and outputs 7 % closer to 64-bit attention (100 draws).
+// Three workgroups fit a compute unit with one column tile, but for a second plane of codes of four heads over whole chunks (192 registers); the others
+// are told so, since the wider codes' take 169 to 175 registers, a few too many, where two are asked for.  us a call with two and three, 32 heads on 8: rotation
+// over two heads, 16 sequences x 4096 tokens, 3-bit 42.1 and 39.3, 4-bit 42.4 and 39.7; over four, half chunks, 12 x 4096, 3-bit 34.6 and 32.4, 4-bit 35.5 and 32.8.
 template <int G, int CT, int HB, int TILES, bool QX>
-__global__ void __launch_bounds__(256, (CT == 1 && HB == 0) ? 3 : 2) k_decode_shared(RkvView v, const float* __restrict__ qr,
+__global__ void __launch_bounds__(256, (CT == 1 && (HB == 0 || G == 2 || TILES == 2)) ? 3 : 2) k_decode_shared(RkvView v, const float* __restrict__ qr,
                                                                                      float* __restrict__ part, int nch,
                                                                                      const int* __restrict__ q_lim, int nq, int ns, int rs,
                                                                                      uint32_t inv_ns, uint32_t inv_nrg) {
