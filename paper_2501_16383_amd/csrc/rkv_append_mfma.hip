@@ -499,6 +499,22 @@ __device__ __forceinline__ void append_mfma_body(const RkvView& v, const __half*
 // the view has no per-sequence lengths yet).  4 x 4096 tokens, 40 heads: 119 -> 109 us with selection and reset in front; 8
 // prompts of 37 to 1531 tokens, 8 heads: 54 -> 42 us (retention and two updates of the lengths were launches of 3.8 to 9.9 us).
 #define RKV_EXTRA_COLS 8               // columns in front of k_append_mfma's own, of which the first is used: the others keep their places among the eight dies
+// Where an append's workgroup finds its sequence: tokens before it, tokens of this call.  One round trip for the arguments, and one more
+// where sequences differ: what is asked for together is used together (left to itself the compiler waited for the
+// first of the arguments before it asked for the count, which every workgroup paid for: 200 sequences of 20 to 720 tokens, 8 heads in
+// groups of two, 110.3 -> 109.0 us; 32 x 1024, 32 heads 147.8 -> 146.3).  b is the same for all of a wave.
+struct RkvPlace {
+  int len, n;
+};
+__device__ __forceinline__ RkvPlace rkv_place(const RkvView& v, const RkvCounts& counts, int b, int n_new) {
+  int n = counts.n[b & (RKV_ARG_COUNTS - 1)], on = counts.on, len = v.len;
+  uint64_t nnew = (uint64_t)v.nnew, lens = (uint64_t)v.lens;
+  asm("" : "+s"(n), "+s"(on), "+s"(len), "+s"(n_new), "+s"(nnew), "+s"(lens));
+  if (nnew) n_new = v.nnew[b];
+  if (lens) len = v.lens[b];
+  return {len, on ? n : n_new};
+}
+
 struct RkvAppendExtra {
   const uint8_t* mask;                 // flags of sink tokens [batch][n_new], or null
   int* lens;                           // lengths, chunk table and staged counts to write, or null
@@ -544,7 +560,8 @@ __global__ void __launch_bounds__(256, (XW || SUB || HB == 1) ? 4 : G == 2 ? 8 :
     }
     bx -= RKV_EXTRA_COLS;
   }
-  append_mfma_body<G, HB, XW, SUB>(v, kin, vin, n_new, rkv_count(v, extra.counts, blockIdx.z, n_new), rkv_len(v, blockIdx.z), slab0, bx, blockIdx.y, blockIdx.z);
+  const RkvPlace at = rkv_place(v, extra.counts, blockIdx.z, n_new);
+  append_mfma_body<G, HB, XW, SUB>(v, kin, vin, n_new, at.n, at.len, slab0, bx, blockIdx.y, blockIdx.z);
 }
 
 // the value role alone (grid x = slabs): the keys of a reorder over the whole row have a kernel of their own
@@ -559,8 +576,8 @@ __global__ void __launch_bounds__(256, (HB || SUB) ? 4 : 6) k_append_values(RkvV
     }
     --bx;
   }
-  append_mfma_body<G, HB, false, SUB>(v, nullptr, vin, n_new, rkv_count(v, extra.counts, blockIdx.z, n_new), rkv_len(v, blockIdx.z), slab0,
-                                      3 * bx + 2, blockIdx.y, blockIdx.z);
+  const RkvPlace at = rkv_place(v, extra.counts, blockIdx.z, n_new);
+  append_mfma_body<G, HB, false, SUB>(v, nullptr, vin, n_new, at.n, at.len, slab0, 3 * bx + 2, blockIdx.y, blockIdx.z);
 }
 
 // Keys under a reorder over the whole token row (perm_span = n_kv_heads * 128, Alg. 1 as printed;
@@ -604,7 +621,8 @@ __global__ void __launch_bounds__(256 * NP, NP == 1 ? 3 : 1) k_append_row_keys(R
   uint32_t* img = img_all[set];
   uint32_t* imgh = imgh_all[set];
   const int b = blockIdx.y, ti = blockIdx.x & 1;
-  const int len_b = rkv_len(v, b), n_b = rkv_count(v, counts, b, n_new);
+  const RkvPlace at = rkv_place(v, counts, b, n_new);
+  const int len_b = at.len, n_b = at.n;
   const int slab = (v.lens ? (len_b >> 5) : slab0) + (blockIdx.x >> 1);
   const int t_lo = len_b, t_hi = len_b + n_b;
   const int ts = slab * 32;

@@ -90,13 +90,13 @@ struct RkvView {
 
 // Per-sequence token counts of an append or a truncation.  Up to RKV_ARG_COUNTS sequences they are part of the kernel's
 // arguments: a copy to the device ahead of it is an operation of its own on the stream, and the host has to keep its source.
-#define RKV_ARG_COUNTS 64
+#define RKV_ARG_COUNTS 64              // (a power of two)
 struct RkvCounts {
   int on = 0;                          // 1: n[b] counts; 0: RkvView::nnew, if set
   int n[RKV_ARG_COUNTS] = {};
 };
 __device__ inline int rkv_count(const RkvView& v, const RkvCounts& c, int b, int otherwise) {
-  const int n = c.n[b % RKV_ARG_COUNTS];                    // (asked for together with the rest of the arguments)
+  const int n = c.n[b & (RKV_ARG_COUNTS - 1)];              // (asked for together with the rest of the arguments)
   if (v.nnew) otherwise = v.nnew[b];
   return c.on ? n : otherwise;
 }
