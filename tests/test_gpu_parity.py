@@ -2139,8 +2139,9 @@ def test_truncate_of_equal_lengths_drops_sinks_behind_the_end(new_len):
 @pytest.mark.parametrize("hkv,g,bits,group,fmt,ragged", [(12, 4, 2, 128, 0, False), (40, 4, 3, 128, 1, True), (6, 2, 4, 128, 0, True),
                                                          (10, 2, 2, 32, 0, False), (32, 4, 4, 64, 1, False), (62, 2, 2, 128, 0, False)])
 def test_whole_row_step_equals_the_two_calls(hkv, g, bits, group, fmt, ragged):
-    """One launch for a step's keys, values and queries under a reorder over the whole row: the same codes, metadata and outputs
-    as a bulk append of the same tokens followed by the attention call."""
+    """One launch for a step's keys, values and queries under a reorder over the whole row: the outputs of an append of one token followed
+    by the attention call, and the codes and metadata of a bulk append of all tokens (more than sixteen: tiles of sixteen tokens in the columns
+    of a product in place of sixteen heads)."""
     B, T = 3, 70
     cfg = R.RkvConfig(batch=B, n_q_heads=hkv, n_kv_heads=hkv, max_tokens=T + 3, max_sinks=0, rot_heads=g, bits=bits, quant_group=group,
                       meta_format=fmt, perm_span=hkv * 128)
@@ -2159,9 +2160,51 @@ def test_whole_row_step_equals_the_two_calls(hkv, g, bits, group, fmt, ragged):
         b.quantize_append(kn, vn)
         assert torch.equal(out, b.decode_attention(q)), i
     assert a.lengths == b.lengths == [n + 3 for n in lens]
-    ea, eb = a.export_codes(), b.export_codes()
+    bulk = whole_row_bulk(cfg, perm, k, v, [list(range(n)) + [T, T + 1, T + 2] for n in lens])
+    ea, eb, ec = a.export_codes(), b.export_codes(), bulk.export_codes()
     for s in range(B):
-        assert all(torch.equal(ea[name][s, :lens[s] + 3], eb[name][s, :lens[s] + 3]) for name in ea)
+        for name in ea:
+            assert torch.equal(ea[name][s, :lens[s] + 3], eb[name][s, :lens[s] + 3]), (s, name)
+            assert torch.equal(ea[name][s, :lens[s] + 3], ec[name][s, :lens[s] + 3]), (s, name)
+
+
+def whole_row_bulk(cfg, perm, k, v, tokens):
+    """A cache that holds rows tokens[b] of k and v in sequence b, from one append of more than sixteen tokens."""
+    lens = [len(t) for t in tokens]
+    kb, vb = (torch.zeros(cfg.batch, max(lens + [17]), *x.shape[2:], device="cuda", dtype=x.dtype) for x in (k, v))
+    for b, t in enumerate(tokens):
+        kb[b, :len(t)], vb[b, :len(t)] = k[b, t], v[b, t]
+    cache = R.RkvCache(cfg)
+    cache.set_perm(perm)
+    cache.quantize_append_ragged(kb, vb, lens)
+    return cache
+
+
+@pytest.mark.parametrize("hkv,g,bits,group,fmt", [(12, 4, 2, 128, 1), (40, 4, 3, 128, 0), (6, 2, 4, 128, 1), (10, 2, 2, 32, 1), (32, 4, 4, 64, 0),
+                                                  (12, 4, 3, 32, 1)])
+def test_short_whole_row_appends_with_counts_equal_bulk(hkv, g, bits, group, fmt):
+    """Appends of at most sixteen tokens, a workgroup per token, with counts of their own: over the edges of tiles of 16 tokens and slabs of 32,
+    none, one and all of the rows; codes and metadata of one bulk append."""
+    B, T = 3, 80
+    cfg = R.RkvConfig(batch=B, n_q_heads=hkv, n_kv_heads=hkv, max_tokens=T, max_sinks=0, rot_heads=g, bits=bits, quant_group=group,
+                      meta_format=fmt, perm_span=hkv * 128)
+    gen = torch.Generator(device="cuda").manual_seed(hkv + group)
+    k, v = (torch.randn(B, T, hkv, 128, device="cuda", generator=gen).half() for _ in range(2))
+    perm = torch.from_numpy(np.random.default_rng(hkv).permutation(hkv * 128).astype(np.int32)).cuda()
+    cache = R.RkvCache(cfg)
+    cache.set_perm(perm)
+    lens = [0] * B
+    for n, counts in ((16, [14, 15, 16]), (7, [0, 7, 3]), (16, [16, 11, 1]), (2, [1, 2, 2]), (16, [3, 16, 12]), (5, [5, 5, 5])):
+        kn, vn = (torch.full((B, n, hkv, 128), 7.0, device="cuda", dtype=torch.float16) for _ in range(2))
+        for b, c in enumerate(counts):
+            kn[b, :c], vn[b, :c] = k[b, lens[b]:lens[b] + c], v[b, lens[b]:lens[b] + c]
+        cache.quantize_append_ragged(kn, vn, counts)
+        lens = [a + c for a, c in zip(lens, counts)]
+    assert cache.lengths == lens
+    bulk = whole_row_bulk(cfg, perm, k, v, [list(range(n)) for n in lens])
+    ea, eb = cache.export_codes(), bulk.export_codes()
+    for b in range(B):
+        assert all(torch.equal(ea[name][b, :lens[b]], eb[name][b, :lens[b]]) for name in ea), b
 
 
 @pytest.mark.parametrize("B,hkv,g,bits,fmt,style,rotated", [(1, 4, 2, 2, 0, 0, 0), (3, 8, 4, 2, 1, 1, 0), (2, 4, 4, 3, 0, 0, 1), (2, 6, 2, 4, 1, 0, 0),
