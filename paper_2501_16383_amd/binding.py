@@ -135,7 +135,10 @@ def _ptr(t) -> Optional[int]:
 def _stream() -> int:
     """Raw handle of the current device's current stream (an object per call costs a microsecond of a 12 us step)."""
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:                                     # names torch does not promise to keep
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _dev(t, dtype, what: str):

@@ -126,3 +126,18 @@ def test_whole_row_reorder_is_bounded_by_the_append_kernels_lds(lib, heads, bits
         assert ei.value.code == binding.RKV_EINVAL
     # the same head count is fine when the reorder stays inside the rotation groups
     R.query_sizes(R.RkvConfig(batch=1, n_q_heads=heads, n_kv_heads=heads, max_tokens=128, perm_span=512, bits=bits, quant_group=group))
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_stream_handle_without_torchs_private_names(monkeypatch, missing):
+    """The stream of a call by torch's public names where it has no shortcut to it."""
+    import torch
+
+    class Stream:
+        cuda_stream = 77
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 5, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    assert binding._stream() == 5
+    monkeypatch.delattr(torch._C, missing)
+    assert binding._stream() == 77
