@@ -522,7 +522,9 @@ struct RkvAppendExtra {
   int* staged;
   RkvCounts counts;
 };
-// Lengths from + counts.n[b], and the running count of their chunks: lane = sequence (at most RKV_ARG_COUNTS of them)
+// Lengths from + counts.n[b], and the running count of their chunks: lane = sequence (at most RKV_ARG_COUNTS of them).  The counts go to
+// their place in the cache's block too, where staged ones are copied: no kernel reads them there, but the block is the
+// caller's memory, and has the same bytes whichever way the counts came.
 __device__ __forceinline__ void set_lens(int B, int from, const RkvCounts& counts, int* lens, int* cstart, int* staged) {
   static_assert(RKV_ARG_COUNTS == 64, "a sequence per lane");
   const int b = threadIdx.x;
@@ -962,7 +964,7 @@ struct RkvStepLens {
 };
 template <int G, int HB, bool XW = false, int SUB = 0>
 __global__ void __launch_bounds__(256, 4) k_step_mfma(RkvView v, const __half* __restrict__ kin, const __half* __restrict__ vin,
-                                                   int slab0, const __half* __restrict__ q, const int* __restrict__ q_pos,
+                                                   const __half* __restrict__ q, const int* __restrict__ q_pos,
                                                    float* __restrict__ qr, int share, RkvStepLens sl) {
   constexpr bool ONE = !XW && SUB == 0;
   constexpr int N_APPEND = ONE ? 1 : 3;
@@ -971,7 +973,7 @@ __global__ void __launch_bounds__(256, 4) k_step_mfma(RkvView v, const __half* _
     if (rg == 0 && b == 0) set_lens(v.B, 1, sl.at, sl.lens, sl.cstart, nullptr);
     return;
   }
-  const int len = sl.at.on ? sl.at.n[b % RKV_ARG_COUNTS] : rkv_len(v, b);
+  const int len = sl.at.on ? sl.at.n[b & (RKV_ARG_COUNTS - 1)] : rkv_len(v, b);
   if ((int)blockIdx.x < N_APPEND) {
     if constexpr (ONE) {
       __shared__ RkvOneLds lds;
@@ -1210,7 +1212,7 @@ int rkv_launch_step_mfma(rkv_cache* c, const __half* k, const __half* vv, const 
   }
   dim3 grid((v.qg == 128 && c->blocks_aligned ? 1 : 3) + v.g * rep / 2 + (sl.at.on ? 1 : 0), v.NRG, v.B);
 #define RKV_ST(G_, H_, X_, S_) \
-  hipLaunchKernelGGL((k_step_mfma<G_, H_, X_, S_>), grid, dim3(256), 0, s, v, k, vv, v.len >> 5, q, q_pos, qr, share, sl)
+  hipLaunchKernelGGL((k_step_mfma<G_, H_, X_, S_>), grid, dim3(256), 0, s, v, k, vv, q, q_pos, qr, share, sl)
 #define RKV_ST_G(H_, X_, S_) do { if (v.g == 4) RKV_ST(4, H_, X_, S_); else RKV_ST(2, H_, X_, S_); } while (0)
 #define RKV_ST_H(X_, S_) do { if (v.hb == 2) RKV_ST_G(2, X_, S_); else if (v.hb == 1) RKV_ST_G(1, X_, S_); else RKV_ST_G(0, X_, S_); } while (0)
   if (v.qg == 64 && c->blocks_aligned) RKV_ST_H(false, 2);

@@ -111,8 +111,8 @@ struct rkv_cache {
   int32_t* stage;      // pinned host ring [RKV_STAGE_SLOTS][batch]: per-sequence counts of more than RKV_ARG_COUNTS sequences on their way to dev_nnew
   hipEvent_t stage_ev[RKV_STAGE_SLOTS];   // recorded after the copy that reads a slot
   int stage_used[RKV_STAGE_SLOTS], stage_next;
-  int* dev_lens;       // device copy (kept current once `ragged` is set) and staging for per-sequence token counts
-  int* dev_nnew;
+  int* dev_lens;       // device copy (kept current once `ragged` is set)
+  int* dev_nnew;       // per-sequence token counts of the last call that had them
   int* dev_cstart;     // [batch + 1], see RkvView::cstart
   int ragged;          // 1 once sequences differ in length
   int sinks_below;     // every retained sink token lies before this position

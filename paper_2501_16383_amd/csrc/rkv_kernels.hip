@@ -489,7 +489,7 @@ __global__ void __launch_bounds__(256) k_append_fast(RkvView v, const __half* __
 // plus, while an append with per-sequence counts is in progress, by its count.
 // Also rebuilds cstart (running count of 256-token chunks, see RkvView) - one workgroup; thread i
 // owns a contiguous slice of the sequences.
-// Counts come by value or from the staged array; what came by value is left there.
+// Counts come by value or from the staged array; what came by value is left there, so that the cache's block has the same bytes either way.
 __global__ void __launch_bounds__(256) k_lens(RkvView v, int* lens, int* cstart, int* staged, int set_to, int add, RkvCounts counts) {
   __shared__ int s_sum[256];
   const int tid = threadIdx.x;
