@@ -853,8 +853,39 @@ __device__ __forceinline__ void append_row_few(const RkvView& v, const __half* _
     lds.mn[e] = 3.0e38f;
     lds.mx[e] = -3.0e38f;
   }
+  // A operand: lane (row m, k-group kg) holds H_128[16 p + m][32 ks + 8 kg + j], j = 0..7: the parity of (channel & k)
+  const int m = col, kg = q;
+  uint32_t sg[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    sg[j] = (0x3C003C00u ^ parity_mask(m & (2 * j) & 7, 0x00008000u)) ^ parity_mask(m & (2 * j + 1) & 7, 0x80000000u);
   v4f acc[2];
-  rotate_columns<G>(x, pw, col, q, acc);
+#pragma unroll
+  for (int pp = 0; pp < 2; ++pp) {
+    const int p = 2 * pw + pp;
+    const uint32_t mk = parity_mask(((m >> 3) & 1 & kg) ^ ((p & 1) & (kg >> 1)), 0x80008000u);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const uint32_t mm = mk ^ parity_mask((p >> 1) & ks, 0x80008000u);
+      const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+      acc[pp] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_v8h(sg[0] ^ mm, sg[1] ^ mm, sg[2] ^ mm, sg[3] ^ mm),
+                                                       as_v8h(x[ks].x, x[ks].y, x[ks].z, x[ks].w), ks == 0 ? zero4 : acc[pp], 0, 0, 0);
+    }
+  }
+  // H_g over the heads: neighbouring columns
+#pragma unroll
+  for (int pp = 0; pp < 2; ++pp)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float a = acc[pp][r];
+      const float b1 = __uint_as_float(dpp_u<0xB1>(__float_as_uint(a)));             // quad_perm [1,0,3,2]
+      a = (col & 1) ? b1 - a : a + b1;
+      if constexpr (G == 4) {
+        const float b2 = __uint_as_float(dpp_u<0x4E>(__float_as_uint(a)));           // quad_perm [2,3,0,1]
+        a = (col & 2) ? b2 - a : a + b2;
+      }
+      acc[pp][r] = a;
+    }
   __syncthreads();
   if (head < v.Hkv) {
 #pragma unroll
@@ -877,12 +908,41 @@ __device__ __forceinline__ void append_row_few(const RkvView& v, const __half* _
     rkv_store_meta(v, v.km, rkv_meta_index(v, b, t, e), sc, zero_b);
   }
   __syncthreads();
-  store_column_codes<HB>(v, b, head / G, t, head & (G - 1), pw, q, q == 0 && head < v.Hkv, [&](int pp, int r) __attribute__((always_inline)) {
-    const int4 bk = blk[pp];
-    const float4 pr = lds.par[r == 0 ? bk.x : r == 1 ? bk.y : r == 2 ? bk.z : bk.w];
-    const float c = __builtin_amdgcn_fmed3f(fmaf(acc[pp][r], pr.x, pr.y), pr.z, pr.z + QMAX);
-    return __float_as_uint(c) - __float_as_uint(pr.z);
-  });
+  const int rg = head / G, hb = head & (G - 1);
+  const size_t tile = rkv_k_tilebase(v, b, rg, t >> 4);
+  uint32_t third = 0;
+#pragma unroll
+  for (int pp = 0; pp < 2; ++pp) {
+    const int bk[4] = {blk[pp].x, blk[pp].y, blk[pp].z, blk[pp].w};
+    uint32_t word = 0, upper = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float4 pr = lds.par[bk[r]];
+      const float c = __builtin_amdgcn_fmed3f(fmaf(acc[pp][r], pr.x, pr.y), pr.z, pr.z + QMAX);
+      const uint32_t code = __float_as_uint(c) - __float_as_uint(pr.z);
+      word |= (code & 3u) << (16 * (q & 1) + 4 * r + 2 * (q >> 1));
+      if constexpr (HI) upper |= (code >> 2) << (16 * (q & 1) + 4 * r + 2 * (q >> 1));
+      // (bit position m = 8 (q & 1) + 2 r + (q >> 1) of dword pp of the pair: bit 4 (m >> 1) + 2 pp + (m & 1))
+      if constexpr (H1) third |= (code >> 2) << (16 * (q & 1) + 4 * r + 2 * pp + (q >> 1));
+    }
+    word |= __shfl_xor(word, 16);
+    word |= __shfl_xor(word, 32);
+    const int p = 2 * pw + pp;
+    const size_t o = tile + ((((hb >> 1) * 4 + (p >> 1)) * 16 + (t & 15)) * 4) + (hb & 1) * 2 + (p & 1);
+    if (q == 0 && head < v.Hkv) v.kc[o] = word;
+    if constexpr (HI) {
+      upper |= __shfl_xor(upper, 16);
+      upper |= __shfl_xor(upper, 32);
+      if (q == 0 && head < v.Hkv) v.kh[o] = upper;
+    }
+    if constexpr (H1) {
+      if (pp == 1) {
+        third |= __shfl_xor(third, 16);
+        third |= __shfl_xor(third, 32);
+        if (q == 0 && head < v.Hkv) v.kh[o >> 1] = third;
+      }
+    }
+  }
 }
 template <int G, int HB>
 __global__ void __launch_bounds__(1024) k_append_row_few(RkvView v, const __half* __restrict__ kin, int n_new, RkvCounts counts) {

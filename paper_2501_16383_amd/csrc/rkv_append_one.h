@@ -47,7 +47,37 @@ __device__ __forceinline__ void rkv_append_one(const RkvView& v, const __half* _
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[pp][r] = __half2float(kg[v.pinv[rg * n + head * RKV_D + 16 * (2 * wave + pp) + 4 * q + r] - rg * n]);
   } else {
-    rotate_columns<G>(x, wave, col, q, acc);
+    // A operand: lane (row m, k-group q) holds H_128[16 p + m][32 ks + 8 q + j], j = 0..7: the parity of (channel & k)
+    uint32_t sg[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      sg[j] = (0x3C003C00u ^ parity_mask(col & (2 * j) & 7, 0x00008000u)) ^ parity_mask(col & (2 * j + 1) & 7, 0x80000000u);
+#pragma unroll
+    for (int pp = 0; pp < 2; ++pp) {
+      const int p = 2 * wave + pp;
+      const uint32_t mk = parity_mask(((col >> 3) & 1 & q) ^ ((p & 1) & (q >> 1)), 0x80008000u);
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const uint32_t mm = mk ^ parity_mask((p >> 1) & ks, 0x80008000u);
+        const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
+        acc[pp] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_v8h(sg[0] ^ mm, sg[1] ^ mm, sg[2] ^ mm, sg[3] ^ mm),
+                                                         as_v8h(x[ks].x, x[ks].y, x[ks].z, x[ks].w), ks == 0 ? zero4 : acc[pp], 0, 0, 0);
+      }
+    }
+    // H_g over the heads: neighbouring columns
+#pragma unroll
+    for (int pp = 0; pp < 2; ++pp)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float a = acc[pp][r];
+        const float b1 = __uint_as_float(dpp_u<0xB1>(__float_as_uint(a)));             // quad_perm [1,0,3,2]
+        a = (col & 1) ? b1 - a : a + b1;
+        if constexpr (G == 4) {
+          const float b2 = __uint_as_float(dpp_u<0x4E>(__float_as_uint(a)));           // quad_perm [2,3,0,1]
+          a = (col & 2) ? b2 - a : a + b2;
+        }
+        acc[pp][r] = a;
+      }
   }
   {
     float mn = acc[0][0], mx = mn;
@@ -106,8 +136,35 @@ __device__ __forceinline__ void rkv_append_one(const RkvView& v, const __half* _
   fused_round_consts(zero_h, base, add);
   const float inv2 = inv * rs;
   if (tid < G) rkv_store_meta(v, v.km, rkv_meta_index(v, b, t, rg * G + tid), sc, zero_h);
-  store_column_codes<HB>(v, b, rg, t, head, wave, q, lane < G, [&](int pp, int r) __attribute__((always_inline)) {
-    const float c = __builtin_amdgcn_fmed3f(fmaf(acc[pp][r], inv2, add), base, base + QMAX);
-    return __float_as_uint(c) - __float_as_uint(base);
-  });
+  const size_t tile = rkv_k_tilebase(v, b, rg, t >> 4);
+  uint32_t third = 0;
+#pragma unroll
+  for (int pp = 0; pp < 2; ++pp) {
+    uint32_t word = 0, upper = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float c = __builtin_amdgcn_fmed3f(fmaf(acc[pp][r], inv2, add), base, base + QMAX);
+      const uint32_t code = __float_as_uint(c) - __float_as_uint(base);
+      word |= (code & 3u) << (16 * (q & 1) + 4 * r + 2 * (q >> 1));
+      if constexpr (HI) upper |= (code >> 2) << (16 * (q & 1) + 4 * r + 2 * (q >> 1));
+      if constexpr (H1) third |= (code >> 2) << (16 * (q & 1) + 4 * r + 2 * pp + (q >> 1));
+    }
+    word |= __shfl_xor(word, 16);
+    word |= __shfl_xor(word, 32);
+    const int p = 2 * wave + pp;
+    const size_t o = tile + ((((head >> 1) * 4 + (p >> 1)) * 16 + (t & 15)) * 4) + (head & 1) * 2 + (p & 1);
+    if (lane < G) v.kc[o] = word;
+    if constexpr (HI) {
+      upper |= __shfl_xor(upper, 16);
+      upper |= __shfl_xor(upper, 32);
+      if (lane < G) v.kh[o] = upper;
+    }
+    if constexpr (H1) {
+      if (pp == 1) {
+        third |= __shfl_xor(third, 16);
+        third |= __shfl_xor(third, 32);
+        if (lane < G) v.kh[o >> 1] = third;
+      }
+    }
+  }
 }

@@ -76,79 +76,3 @@ __device__ __forceinline__ void fused_round_consts(float zero, float& base, floa
   base = 12582912.0f + odd;
   add = base + zero;
 }
-
-// ---- one token's keys as columns (rkv_append_one, append_row_few): a product's columns are sixteen heads, its rows
-// channels 16 p + 4 q + r of head `col`, p = 2 w and 2 w + 1 for wave w of four.
-
-// H_128 of the columns' heads, from x[ks] = the head's channels 32 ks + 8 q .. + 7, and H_G over neighbouring columns.
-// A operand: lane (row m = col, k-group q) holds H_128[16 p + m][32 ks + 8 q + j], j = 0..7: the parity of (channel & k)
-template <int G>
-__device__ __forceinline__ void rotate_columns(const uint4 (&x)[4], int w, int col, int q, v4f (&acc)[2]) {
-  uint32_t sg[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    sg[j] = (0x3C003C00u ^ parity_mask(col & (2 * j) & 7, 0x00008000u)) ^ parity_mask(col & (2 * j + 1) & 7, 0x80000000u);
-#pragma unroll
-  for (int pp = 0; pp < 2; ++pp) {
-    const int p = 2 * w + pp;
-    const uint32_t mk = parity_mask(((col >> 3) & 1 & q) ^ ((p & 1) & (q >> 1)), 0x80008000u);
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const uint32_t mm = mk ^ parity_mask((p >> 1) & ks, 0x80008000u);
-      const v4f zero4 = {0.f, 0.f, 0.f, 0.f};
-      acc[pp] = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_v8h(sg[0] ^ mm, sg[1] ^ mm, sg[2] ^ mm, sg[3] ^ mm),
-                                                       as_v8h(x[ks].x, x[ks].y, x[ks].z, x[ks].w), ks == 0 ? zero4 : acc[pp], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int pp = 0; pp < 2; ++pp)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      float a = acc[pp][r];
-      const float b1 = __uint_as_float(dpp_u<0xB1>(__float_as_uint(a)));             // quad_perm [1,0,3,2]
-      a = (col & 1) ? b1 - a : a + b1;
-      if constexpr (G == 4) {
-        const float b2 = __uint_as_float(dpp_u<0x4E>(__float_as_uint(a)));           // quad_perm [2,3,0,1]
-        a = (col & 2) ? b2 - a : a + b2;
-      }
-      acc[pp][r] = a;
-    }
-}
-
-// A lane's eight codes (see above) into the dwords of its head `hb` of the rotation group, token t: four codes of product pp at bits 16 (q & 1) + 4 r + 2 (q >> 1)
-// of dword (hb, p); third bits: code m = 8 (q & 1) + 2 r + (q >> 1) of dword pp of a pair at bit 4 (m >> 1) + 2 pp + (m & 1) of the pair's.
-// code(pp, r): the code; live: the lane that stores (one per column).
-template <int HB, typename Code>
-__device__ __forceinline__ void store_column_codes(const RkvView& v, int b, int rg, int t, int hb, int w, int q, bool live, Code code) {
-  constexpr bool HI = HB == 2, H1 = HB == 1;
-  const size_t tile = rkv_k_tilebase(v, b, rg, t >> 4);
-  uint32_t third = 0;
-#pragma unroll
-  for (int pp = 0; pp < 2; ++pp) {
-    uint32_t word = 0, upper = 0;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const uint32_t c = code(pp, r);
-      word |= (c & 3u) << (16 * (q & 1) + 4 * r + 2 * (q >> 1));
-      if constexpr (HI) upper |= (c >> 2) << (16 * (q & 1) + 4 * r + 2 * (q >> 1));
-      if constexpr (H1) third |= (c >> 2) << (16 * (q & 1) + 4 * r + 2 * pp + (q >> 1));
-    }
-    word |= __shfl_xor(word, 16);
-    word |= __shfl_xor(word, 32);
-    const int p = 2 * w + pp;
-    const size_t o = tile + ((((hb >> 1) * 4 + (p >> 1)) * 16 + (t & 15)) * 4) + (hb & 1) * 2 + (p & 1);
-    if (live) v.kc[o] = word;
-    if constexpr (HI) {
-      upper |= __shfl_xor(upper, 16);
-      upper |= __shfl_xor(upper, 32);
-      if (live) v.kh[o] = upper;
-    }
-    if constexpr (H1) {
-      if (pp == 1) {
-        third |= __shfl_xor(third, 16);
-        third |= __shfl_xor(third, 32);
-        if (live) v.kh[o >> 1] = third;
-      }
-    }
-  }
-}
