@@ -233,8 +233,10 @@ int rkv_decode_attention_with_current(rkv_cache* cache, const void* dev_q, const
  * [batch][1][n_kv_heads][head_dim] fp16, no sink mask) followed by rkv_decode_attention with the
  * same remaining arguments - and the same results, bit for bit.  Where the matrix-core kernels
  * cover the configuration the token's compression and the query's preparation share one kernel
- * launch, which shortens the step by a few microseconds per layer; elsewhere the two calls are
- * made one after the other.  Error codes as for the two calls. */
+ * launch, or are part of the decode kernel (one query head per KV head, the reorder inside blocks of 128, sequences of
+ * one length, dev_q_pos NULL, grids of up to sixteen workgroups per compute unit), which shortens the step by a few
+ * microseconds per layer; elsewhere the two calls are made one after the other.  Error codes as for the two
+ * calls; the token counts (rkv_cache_length) if the launch that appends it went out. */
 int rkv_decode_step(rkv_cache* cache, const void* dev_k, const void* dev_v, const void* dev_q, const int32_t* dev_q_pos,
                     float* dev_out, float* dev_lse, void* dev_scratch, void* stream);
 
@@ -327,7 +329,9 @@ int rkv_export_codes(rkv_cache* cache, uint8_t* dev_k_codes, float* dev_k_scale,
                      uint8_t* dev_v_codes, float* dev_v_scale, float* dev_v_zero, void* stream);
 
 /* Overwrite the cache contents with n_tokens tokens given in the same canonical form (scale and
- * zero must be exactly representable in fp16); sets length = n_tokens, keeps sinks and perm. */
+ * zero must be exactly representable in fp16); sets length = n_tokens, keeps sinks and perm.  A sink
+ * row at or behind n_tokens is attended until a truncation in front of it drops it - provided no
+ * later append has retained a row at a lower position. */
 int rkv_import_codes(rkv_cache* cache, int32_t n_tokens, const uint8_t* dev_k_codes,
                      const float* dev_k_scale, const float* dev_k_zero, const uint8_t* dev_v_codes,
                      const float* dev_v_scale, const float* dev_v_zero, void* stream);

@@ -550,7 +550,12 @@ __device__ __forceinline__ void append_extra(const RkvView& v, const __half* kin
   if (x.mask && idx < v.B) rkv_sinks_of<256>(v, kin, vin, x.mask, n_new, rkv_count(v, x.counts, idx, n_new), idx, lds);
 }
 
-// EXTRA: with the work above (a variant of its own: an append that has none keeps the scalar registers it takes)
+// EXTRA: with the work above (a variant of its own: an append that has none keeps the scalar registers it takes.  Rotation over two heads
+// then holds 25 to 46 scalar registers in vector ones, most of them of the column's own code: 8 x 4096 tokens, 32 heads with flags, us, retention in a
+// launch of its own and here: 2-bit 150.6 and 143.8, 4-bit 170.6 and 162.6.)
+// Waves per SIMD asked for: what LDS and the work leave room for.  Six for four heads brought 4-bit codes from 78 registers to 69 and a seventh wave
+// (8 x 4096 tokens, 32 heads 153.8 -> 147.7 us).  The variants with a table of
+// blocks, and the third bits', ask for the four they were measured with and reach five or six.
 template <int G, int HB, bool XW = false, int SUB = 0, bool EXTRA = false>
 __global__ void __launch_bounds__(256, (XW || SUB || HB == 1) ? 4 : G == 2 ? 8 : 6) k_append_mfma(RkvView v, const __half* __restrict__ kin, const __half* __restrict__ vin,
                                                                       int n_new, int slab0, RkvAppendExtra extra) {

@@ -615,8 +615,8 @@ __global__ void __launch_bounds__(256, (HB && G == 4 && TILES == 4) ? MF_OCC_HI 
         }
         if (ti + 1 < TILES) load_tile(ti + 1);          // prefetch (inside the padded allocation)
 
-        // (One pass.  Without the loop the compiler waits for the value codes before the softmax phase's barrier
-        // instead of behind it: one sequence x 4096 tokens, half chunks, 9.4 -> 10.0 us.)
+        // (One pass.  Without the loop some variants wait for the value codes before the softmax phase's barrier instead of behind
+        // it: one sequence x 8192 tokens, 4-bit codes, half chunks, 21.7 -> 22.3 us a call; 2-bit codes are the same within 1 %.)
 #pragma unroll
         for (int pass = 0; pass < 1; ++pass) {
         const float centre = n == 0 ? -64.0f * MID : 0.f;  // channel 0 of H_128 of the constant MID / 2
@@ -1000,7 +1000,9 @@ size_t rkv_mfma_load(const rkv_cache* c, int chunk) {
 // 1.1 times, except where a workgroup has two column tiles (two fit a compute unit, not three) or the query heads
 // have been given to several workgroups already (which half chunks would take back): there they lose.  Above that they
 // lose.  Wider codes on k_decode_mfma with four heads in a rotation group, of whose whole chunks two fit a
-// compute unit and of half ones three, take them a quarter of a workgroup further.
+// compute unit and of half ones three, take them a quarter of a workgroup further.  (k_decode_shared with one column tile: 1.2 times
+// as fast up to half a workgroup, 1.02 to 1.05 above one and up to one and a half; at one workgroup per unit whole chunks are the
+// faster ones by 1 to 7 %, which the rule does not use.)
 // us a step (k_decode_mfma) or a call, whole / half chunks, at 0.5, 1, 2, 3 and 8 workgroups per unit:
 //   k_decode_mfma, 2-bit codes             17.6 / 14.8, 17.6 / 17.1, 21.7 / 25.4, 28.0 / 32.5, 56.6 / 60.3
 //   ... 3-bit                              19.3 / 16.2, 19.9 / 19.2, 24.4 / 28.4, 37.2 / 36.6, 77.1 / 78.7
@@ -1008,9 +1010,10 @@ size_t rkv_mfma_load(const rkv_cache* c, int chunk) {
 //   ... 2-bit, two heads per group                      15.5 / 15.5, 17.0 / 20.2,              41.3 / 49.0
 //   ... 4-bit, two heads per group                      16.6 / 16.5, 19.1 / 23.0,              51.1 / 58.2
 // and at 0.5, 1, 1.5, 1.75, 3 and 10:
-//   k_decode_shared, 4 heads on each of 8  24.1 / 19.8, 25.2 / 24.9, 34.3 / 32.2, 35.0 / 37.3, 47.8 / 49.9
-//   ... 3-bit                              25.8 / 21.4, 27.3 / 27.3, 38.0 / 37.4, 39.0 / 43.8, 54.4 / 60.6
-//   ... two column tiles, 8 on each of 8   25.0 / 24.6, 33.1 / 34.4, 45.7 / 46.5, 48.0 / 54.1, 69.4 / 76.0
+//   k_decode_shared, 4 heads on each of 8  23.1 / 19.9, 23.6 / 25.2, 30.9 / 30.2, 31.1 / 34.6, 39.7 / 44.6, 97.0 / 114
+//   ... 3-bit                              24.6 / 20.8, 25.8 / 26.7, 33.8 / 32.6, 34.2 / 37.5, 46.9 / 48.2, 124 / 135
+//   ... 4-bit                              25.2 / 21.2, 26.2 / 27.0, 33.9 / 32.4, 35.0 / 38.0, 48.3 / 50.1, 130 / 142
+//   ... two column tiles, 8 on each of 8   23.8 / 23.8, 29.3 / 31.7, 38.6 / 41.0, 40.8 / 49.7, 54.6 / 66.7, 145 / 195
 // (The work space: partial results of half chunks are within what a caller brings.  The one built in for
 // rkv_decode_attention_static, a single query's, may hold those of whole chunks only; the usual step then takes these, with it or without.)
 int rkv_mfma_chunk(const rkv_cache* c, int nq) {

@@ -317,8 +317,10 @@ __global__ void __launch_bounds__(256, 3) k_scores_row(RkvView v, const float* _
 // the bits {0, 3, 4} by accumulation - the eight products of a head's eight steps s onto output
 // tile mt carry the sign (-1)^popc(mt & s), the same for every lane, i.e. A or -A.  The stage of bit 3
 // is done that way, three products for two results of two steps; those of bits 0 and 4 are additions in the lane: 12 products
-// and 64 additions per head, 199 + 150 cycles of a SIMD.  (A product takes 16.6, an addition 2.3 and they do not overlap: 43
-// products and none 714, 22 and 32 440, 8 and 96 354.)  A lane
+// and 64 additions per head.  Against 22 and 32 (bit 0 by accumulation too) the matrix pipe is busy 9 % of the kernel's time in place
+// of 16, the vector pipe 71 in place of 67, and the kernel is 0 to 1.5 % shorter (8 sequences x 4096 tokens, us, 22 and 12: whole rows of 32 heads
+// 57.5 and 57.6, of 40 76.0 and 74.9, groups of 32 58.6 and 58.0): the waves of a SIMD fill much of each other's product
+// time, so that a product costs less than its 16.6 cycles.  (43 and none was 8 % longer than 22 and 32.)  A lane
 // (token, g4) of the result holds, per head, tiles mt = 0..7 x rows r = 0..3: output channel bits
 // 6 = r & 1, 5 = g4 >> 1, 4 3 0 = mt, 2 = g4 & 1, 1 = r >> 1 - both channels of a RoPE pair of either
 // pairing.  H_g over the heads is split: P0 = X0 + X1, P1 = X0 - X1 of a pair of heads go through

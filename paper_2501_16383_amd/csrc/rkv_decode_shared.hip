@@ -27,11 +27,10 @@
 //   phase S  wave: softmax statistics and weight digits of four query heads of one KV head; the digits
 //            (six base-16 digits of a 24-bit integer, in FP8, see k_decode_mfma) stay in the wave's own LDS.
 //   phase V  the same wave: rows = 4 query heads x 4 digits, contraction over 128 tokens of ONE KV head:
-//            no part of the operand is zero (k_decode_mfma's is block-diagonal over the heads), the codes
-//            are fetched once for all query heads.
+//            no part of the operand is zero, the codes are fetched once for all query heads.
 // 32 sequences x 8192 tokens, 32 query heads on 8: step 153.5 us with two query heads per workgroup of k_decode_mfma, 85.0 here;
 // four query tokens, 8 x 4096 tokens: 98.4 and 48.3 us (one round of two workgroups per compute unit).  Bound by the vector pipe in phase K (16 instructions of
-// RoPE and 12 of the split for eight channels of a token and block).
+// RoPE and 16 of the split for eight channels of a token and block).
 // The variants with 32 columns and 3- or 4-bit codes hold 8 registers in scratch memory.
 #include "rkv_internal.h"
 #include "rkv_mfma_ops.h"
